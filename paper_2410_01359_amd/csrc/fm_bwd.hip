@@ -820,7 +820,9 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(FmBwdArgs a)
     settle(b_uts);
     settle(b_ute);
     // lengths of the key's two masked row intervals (0 for an empty one), for the element mask's compare
-    const unsigned len_lt = (unsigned)max(b_lte - b_lts, 0), len_ut = (unsigned)max(b_ute - b_uts, 0);
+    // (any int32 bounds: the difference is formed in unsigned arithmetic, it may not fit an int)
+    const unsigned len_lt = b_lte > b_lts ? (unsigned)b_lte - (unsigned)b_lts : 0u;
+    const unsigned len_ut = b_ute > b_uts ? (unsigned)b_ute - (unsigned)b_uts : 0u;
     async_wait<(C::NSTAGE - 2) * C::NC>();
     barrier_nofence();
     int e_cur = __builtin_amdgcn_readfirstlane(list[0]);
