@@ -71,12 +71,8 @@ int check_strides(const flashmask_strides* s, int B, int heads, int N, int d) {
   return FM_OK;
 }
 
-// The tile loops work at the sequence length rounded up to a multiple of 128; a sequence that is
-// not such a multiple gets padded copies of its bound vectors at the front of the workspace.
+// The tile loops work at the sequence length rounded up to a multiple of 128.
 inline int padded_len(int N) { return (N + 127) / 128 * 128; }
-inline size_t padded_bounds_bytes(int B, int N) {
-  return padded_len(N) == N ? 0 : align_up((size_t)4 * B * padded_len(N) * 4, 256);
-}
 
 // Workspace layout of a pass: tables, work counts and unit queues.
 struct PassSpace {
@@ -159,12 +155,11 @@ int flashmask_tile_shape(int pass, int d, int* block_r, int* block_c) {
 size_t flashmask_workspace_bytes(int pass, int B, int H, int N, int d) {
   if (check_shape(B, H, N, d) != FM_OK) return 0;
   const int Np = padded_len(N);
-  const size_t pad = padded_bounds_bytes(B, N);
-  if (pass == FM_PASS_FWD) return pad + pass_space(B, H, Np, FM_FWD_BR, FM_FWD_BC, true, 0).total;
+  if (pass == FM_PASS_FWD) return pass_space(B, H, Np, FM_FWD_BR, FM_FWD_BC, true, 0).total;
   if (pass == FM_PASS_BWD) {
     const PassSpace dq = pass_space(B, H, Np, FM_DQ_BR, fm_dq_bc(d), true, 0);
     const PassSpace kv = pass_space(B, H, Np, FM_DKDV_BR, FM_DKDV_BC, false, dq.total);
-    return pad + kv.total + 2 * align_up((size_t)B * H * Np * 4, 256);  // + D vector + log2-domain lse
+    return kv.total + 2 * align_up((size_t)B * H * Np * 4, 256);  // + D vector + log2-domain lse
   }
   return 0;
 }
@@ -173,7 +168,7 @@ int flashmask_preprocess(const int32_t* lts, const int32_t* lte, const int32_t* 
                          int block_c, int32_t* minmax, void* hip_stream) {
   if (!lts || !lte || !uts || !ute || !minmax) return FM_ERR_NULL;
   if (B <= 0 || N <= 0 || block_c <= 0 || block_c % 32 != 0) return FM_ERR_SHAPE;
-  hipError_t e = fm_launch_preprocess(lts, lte, uts, ute, B, N, block_c, minmax, (hipStream_t)hip_stream);
+  hipError_t e = fm_launch_preprocess(lts, lte, uts, ute, B, N, N, block_c, minmax, (hipStream_t)hip_stream);
   return e == hipSuccess ? FM_OK : hip_fail(e);
 }
 
@@ -203,22 +198,14 @@ static int fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
   char* ws = (char*)workspace;
   mark(0, stream);
   hipError_t e;
-  if (Np != N) {   // padded bound vectors first
-    int* padded = (int*)ws;
-    e = fm_launch_pad_bounds(lts, lte, uts, ute, B, N, Np, padded, stream);
-    if (e != hipSuccess) return hip_fail(e);
-    const size_t plane = (size_t)B * Np;
-    lts = padded; lte = padded + plane; uts = padded + 2 * plane; ute = padded + 3 * plane;
-    ws += padded_bounds_bytes(B, N);
-  }
   const PassSpace sp = pass_space(B, H, Np, FM_FWD_BR, FM_FWD_BC, true, 0);
   int* minmax = (int*)(ws + sp.minmax);
   int* work = (int*)(ws + sp.work);
   int* range = (int*)(ws + sp.range);
   int* order = (int*)(ws + sp.order);
-  e = fm_launch_preprocess(lts, lte, uts, ute, B, Np, FM_FWD_BC, minmax, stream);
+  e = fm_launch_preprocess(lts, lte, uts, ute, B, N, Np, FM_FWD_BC, minmax, stream);
   if (e != hipSuccess) return hip_fail(e);
-  e = fm_launch_row_order(minmax, B, H, Hk, Np, FM_FWD_BR, FM_FWD_BC, work, range, order, stream);
+  e = fm_launch_row_order(minmax, B, H, Hk, N, Np, FM_FWD_BR, FM_FWD_BC, work, range, order, stream);
   if (e != hipSuccess) return hip_fail(e);
   mark(1, stream);
   FmFwdArgs a;
@@ -256,21 +243,13 @@ int flashmask_unit_queues(int pass, const int32_t* lts, const int32_t* lte, cons
   hipStream_t stream = (hipStream_t)hip_stream;
   char* ws = (char*)workspace;
   hipError_t e;
-  if (Np != N) {
-    int* padded = (int*)ws;
-    e = fm_launch_pad_bounds(lts, lte, uts, ute, B, N, Np, padded, stream);
-    if (e != hipSuccess) return hip_fail(e);
-    const size_t plane = (size_t)B * Np;
-    lts = padded; lte = padded + plane; uts = padded + 2 * plane; ute = padded + 3 * plane;
-    ws += padded_bounds_bytes(B, N);
-  }
   const PassSpace sp = pass_space(B, H, Np, br, bc, rows, 0);
   int* minmax = (int*)(ws + sp.minmax);
-  e = fm_launch_preprocess(lts, lte, uts, ute, B, Np, bc, minmax, stream);
+  e = fm_launch_preprocess(lts, lte, uts, ute, B, N, Np, bc, minmax, stream);
   if (e != hipSuccess) return hip_fail(e);
-  e = rows ? fm_launch_row_order(minmax, B, H, H, Np, br, bc, (int*)(ws + sp.work), (int*)(ws + sp.range),
+  e = rows ? fm_launch_row_order(minmax, B, H, H, N, Np, br, bc, (int*)(ws + sp.work), (int*)(ws + sp.range),
                                  (int*)(ws + sp.order), stream)
-           : fm_launch_col_order(minmax, B, H, Np, br, bc, (int*)(ws + sp.work), (int*)(ws + sp.range),
+           : fm_launch_col_order(minmax, B, H, N, Np, br, bc, (int*)(ws + sp.work), (int*)(ws + sp.range),
                                  (int*)(ws + sp.order), stream);
   if (e != hipSuccess) return hip_fail(e);
   e = hipMemcpyAsync(records, ws + sp.order, (size_t)*slots * 16, hipMemcpyDeviceToDevice, stream);
@@ -333,14 +312,6 @@ static int bwd_impl(const void* q, const void* k, const void* v, const void* out
   char* ws = (char*)workspace;
   mark(0, stream);
   hipError_t e;
-  if (Np != N) {   // padded bound vectors first
-    int* padded = (int*)ws;
-    e = fm_launch_pad_bounds(lts, lte, uts, ute, B, N, Np, padded, stream);
-    if (e != hipSuccess) return hip_fail(e);
-    const size_t plane = (size_t)B * Np;
-    lts = padded; lte = padded + plane; uts = padded + 2 * plane; ute = padded + 3 * plane;
-    ws += padded_bounds_bytes(B, N);
-  }
   const PassSpace sq = pass_space(B, H, Np, FM_DQ_BR, fm_dq_bc(d), true, 0);
   const PassSpace skv = pass_space(B, H, Np, FM_DKDV_BR, FM_DKDV_BC, false, sq.total);   // sized for H >= Hk heads
   FmBwdArgs a;
@@ -366,7 +337,7 @@ static int bwd_impl(const void* q, const void* k, const void* v, const void* out
                      (int*)(ws + sq.order)};
   const FmSetup cols{FM_DKDV_BR, FM_DKDV_BC, (int*)(ws + skv.minmax), (int*)(ws + skv.work), (int*)(ws + skv.range),
                      (int*)(ws + skv.order)};
-  e = fm_launch_bwd_setup(lts, lte, uts, ute, B, H, Hk, Np, rows, cols, stream);
+  e = fm_launch_bwd_setup(lts, lte, uts, ute, B, H, Hk, N, Np, rows, cols, stream);
   if (e != hipSuccess) return hip_fail(e);
   mark(1, stream);
   // the dQ loop first: its prologue is also Algorithm 2's D pre-pass and leaves -D and the log2-domain

@@ -76,8 +76,11 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(FmBwdArgs a) {
     if (which == 1) p = a.lte;
     if (which == 2) p = a.uts;
     if (which == 3) p = a.ute;
-    my_bvec = p + (size_t)b * N + (lane % BND_LPV) * 4;
+    my_bvec = p + (size_t)b * Nr + (lane % BND_LPV) * 4;
   }
+  // RAGGED: rows of the bound vectors are 4-byte aligned only and the last key block reaches past their end:
+  // wave w copies one vector's slice, 4 bytes per lane
+  const int* wave_bvec = (wave == 0 ? a.lts : wave == 1 ? a.lte : wave == 2 ? a.uts : a.ute) + (size_t)b * Nr;
   CopyLanes<D> copy_lanes, copy_lanes_v_;
   copy_lanes.init(lane, 2 * k_rs);
   if (GEN) copy_lanes_v_.init(lane, 2 * v_rs);
@@ -153,14 +156,21 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(FmBwdArgs a) {
         tile_load_async<D>(vp + (size_t)r_ * v_rs, copy_lanes_v, ks_ + C::K_BYTES, wave, 2 * v_rs); \
       }                                                                                        \
     }                                                                                          \
-    if (entry_tile_class(ENTRY) == T_PARTIAL && wave < BND_WAVES)                              \
-      async_copy16(my_bvec + j_ * KT, lds_address(st_ + C::K_BYTES + C::V_BYTES) + wave * 1024); \
+    if (entry_tile_class(ENTRY) == T_PARTIAL) {                                                \
+      const unsigned bnd_ = lds_address(st_ + C::K_BYTES + C::V_BYTES);                        \
+      if (RAGGED) {                                                                            \
+        _Pragma("unroll") for (int sub = 0; sub < KT / 64; ++sub)                              \
+          async_copy4(bound_or_pad(wave_bvec, wave, j_ * KT + sub * 64 + lane, Nr), bnd_ + wave * (KT * 4) + sub * 256); \
+      } else if (wave < BND_WAVES) {                                                           \
+        async_copy16(my_bvec + j_ * KT, bnd_ + wave * 1024);                                   \
+      }                                                                                        \
+    }                                                                                          \
   }
 
   // only the key blocks [j_lo, j_hi) can be live for this row block (found by the work pre-pass)
   for (int chunk = j_lo; chunk < j_hi; chunk += C::LIST_CAP) {
-    const int n_live = build_live_key_blocks(table, t_c, chunk, min(chunk + C::LIST_CAP, j_hi), q0, min(q0 + C::BR, N),
-                                             C::BR / 4, list, wave_cnt);
+    const int n_live = build_live_key_blocks<T_FULLY>(table, t_c, chunk, min(chunk + C::LIST_CAP, j_hi), q0,
+                                                      min(q0 + C::BR, Nr), C::BR / 4, list, wave_cnt);
     if (n_live == 0) continue;
     // the entries of tiles t and t + 1 travel in scalar registers; the one that joins them at the next tile is
     // read from the list at the top of a tile and picked up behind the tile's barrier, so that no tile starts by
@@ -759,8 +769,15 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(FmBwdArgs a)
     kreg[kk] = *(const bf16x8*)(kp + (size_t)key_ld * k_rs + kk * 16 + 8 * g);
     vreg[kk] = *(const bf16x8*)(vp + (size_t)key_ld * v_rs + kk * 16 + 8 * g);
   }
-  int b_lts = a.lts[(size_t)b * N + key], b_lte = a.lte[(size_t)b * N + key];
-  int b_uts = a.uts[(size_t)b * N + key], b_ute = a.ute[(size_t)b * N + key];
+  const size_t bnd_row = (size_t)b * Nr;
+  int b_lts, b_lte, b_uts, b_ute;
+  if (RAGGED) {
+    b_lts = *bound_or_pad(a.lts + bnd_row, 0, key, Nr), b_lte = *bound_or_pad(a.lte + bnd_row, 1, key, Nr);
+    b_uts = *bound_or_pad(a.uts + bnd_row, 2, key, Nr), b_ute = *bound_or_pad(a.ute + bnd_row, 3, key, Nr);
+  } else {
+    b_lts = a.lts[bnd_row + key], b_lte = a.lte[bnd_row + key];
+    b_uts = a.uts[bnd_row + key], b_ute = a.ute[bnd_row + key];
+  }
 
   f32x16 dkacc[NDB], dvacc[NDB];
 #pragma unroll
@@ -775,7 +792,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(FmBwdArgs a)
   // only the row blocks [i_lo, i_hi) can be live for this key block (found by the work pre-pass)
   for (int chunk = i_lo; chunk < i_hi; chunk += C::LIST_CAP) {
     int n_plain = 0;
-    const int n_live = build_live_row_blocks(gmm, N, QT, chunk, min(chunk + C::LIST_CAP, i_hi), list, wave_cnt, n_plain);
+    const int n_live = build_live_row_blocks(gmm, Nr, QT, chunk, min(chunk + C::LIST_CAP, i_hi), list, wave_cnt, n_plain);
     if (n_live == 0) continue;
     // the query heads that share this K/V head, one after the other (one pass if there is no sharing)
     for (int hq = 0; hq < (GEN ? G : 1); ++hq) {

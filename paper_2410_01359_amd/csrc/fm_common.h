@@ -30,6 +30,15 @@ enum { LTS_MAX = 0, LTS_MIN, LTE_MAX, LTE_MIN, UTS_MAX, UTS_MIN, UTE_MAX, UTE_MI
 // Tile classes (Equation 4); same encoding as FM_TILE_* in flashmask.h.
 enum { T_UNMASKED = 0, T_PARTIAL = 1, T_FULLY = 2, T_NEED_LT = 16, T_NEED_UT = 32 };
 
+// What the key columns past the end of a sequence carry (LTS, LTE, UTS, UTE): one interval that masks every
+// row.  A sequence whose length is not a multiple of 128 runs at the padded length; its extra columns exist
+// nowhere in memory, every reader of the bound vectors substitutes these four values instead.
+static __device__ const int pad_column[4] = {INT32_MIN, INT32_MAX, 0, 0};
+// Bound `which` (0..3 = LTS, LTE, UTS, UTE) of key column `key` of a batch row's vector.
+__device__ __forceinline__ const int* bound_or_pad(const int* vec, int which, int key, int n) {
+  return key < n ? vec + key : pad_column + which;
+}
+
 struct MinMax8 {
   int v[8];
 };
@@ -184,6 +193,14 @@ struct CopyLanes {
 // memory operations only ever makes the compiler's own vmcnt waits stricter.)
 __device__ __forceinline__ void async_copy16(const void* gsrc, unsigned lds_addr) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
+               :
+               : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(gsrc)
+               : "memory", "m0");
+}
+// The same with 4 bytes per lane (lane l lands at lds_addr + 4 l): for sources that are only 4-byte aligned
+// or differ from lane to lane.
+__device__ __forceinline__ void async_copy4(const void* gsrc, unsigned lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off"
                :
                : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(gsrc)
                : "memory", "m0");
@@ -445,7 +462,9 @@ __device__ __forceinline__ void append_live(bool live, int entry, int* list, int
 //                "row >= LTS" alone decides the LT pair;  bit 29: every UT interval starts at or above the first
 //                row (max UTS <= r0), so "row < UTE" alone decides the UT pair.  (Causal, window, document and
 //                prefix masks are all of this kind: their intervals run to row N resp. from row 0.)
+// Rows end at r1 (the sequence's end for the last row block); a wave that owns none of them gets class EMPTY.
 // Returns the number of entries (uniform over the workgroup).
+template <int EMPTY>
 __device__ __forceinline__ int build_live_key_blocks(const int* __restrict__ table, int t_c, int j_begin, int j_end,
                                                      int r0, int r1, int rows_per_wave, int* list, int* wave_cnt) {
   int running = 0;
@@ -460,7 +479,7 @@ __device__ __forceinline__ int build_live_key_blocks(const int* __restrict__ tab
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
         const int w0 = min(r0 + w * rows_per_wave, r1), w1 = min(w0 + rows_per_wave, r1);
-        entry |= (classify_tile(w0, w1, mm) & 3) << (18 + 2 * w);
+        entry |= (w0 < w1 ? classify_tile(w0, w1, mm) & 3 : EMPTY) << (18 + 2 * w);
       }
     }
     append_live(cls != T_FULLY, entry, list, wave_cnt, running);

@@ -228,8 +228,7 @@ __device__ __forceinline__ void fwd_step(f32x16 (&cur)[2], f32x16 (&nxt)[2], f32
 }
 
 // RAGGED: the sequence length is not a multiple of 128.  The loops then run at the padded length
-// Np (tables, lists and the padded bound vectors are built for it; the padding columns are masked
-// for every row), tile copies that reach past row N clamp their source rows, and rows >= N are
+// Np (tables and lists are built for it; the padding columns are masked for every row), tile copies that reach past row N clamp their source rows, and rows >= N are
 // computed but not stored.
 // GEN: tensors with caller-given strides and fewer K/V heads than query heads (see FmFwdArgs).
 template <int D, bool RAGGED, bool GEN>
@@ -266,8 +265,11 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void fwd_kernel(FmFwdArgs a) 
     if (which == 1) p = a.lte;
     if (which == 2) p = a.uts;
     if (which == 3) p = a.ute;
-    my_bvec = p + (size_t)b * N + (lane & 15) * 4;
+    my_bvec = p + (size_t)b * Nr + (lane & 15) * 4;
   }
+  // RAGGED: rows of the bound vectors are 4-byte aligned only and the last key block reaches past their end:
+  // wave w copies one vector's slice, 4 bytes per lane
+  const int* wave_bvec = (wave == 0 ? a.lts : wave == 1 ? a.lte : wave == 2 ? a.uts : a.ute) + (size_t)b * Nr;
   CopyLanes<D> copy_lanes, copy_lanes_v_;
   copy_lanes.init(lane, 2 * k_rs);
   if (GEN) copy_lanes_v_.init(lane, 2 * v_rs);
@@ -320,8 +322,13 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void fwd_kernel(FmFwdArgs a) 
       tile_load_async_clamped<D>(vp, j_ * KT, Nr, st_, wave, lane, 2 * v_rs);                    \
     else                                                                                         \
       tile_load_async<D>(vp + (size_t)j_ * KT * v_rs, copy_lanes_v, st_, wave, 2 * v_rs);        \
-    if (entry_tile_class(ENTRY) == T_PARTIAL && wave == 0)                                       \
-      async_copy16(my_bvec + j_ * KT, lds_address(st_ + C::V_BYTES));                            \
+    if (entry_tile_class(ENTRY) == T_PARTIAL) {                                                  \
+      if (RAGGED)                                                                                \
+        async_copy4(bound_or_pad(wave_bvec, wave, j_ * KT + lane, Nr),                           \
+                    lds_address(st_ + C::V_BYTES) + wave * (KT * 4));                            \
+      else if (wave == 0)                                                                        \
+        async_copy16(my_bvec + j_ * KT, lds_address(st_ + C::V_BYTES));                          \
+    }                                                                                            \
   }
   // One iteration: tile T with scores in CUR, scores of tile T + 1 into NXT.  Entries past the
   // end of the list are clamped to the last one: nothing is copied for them, and the scores the last
@@ -347,8 +354,8 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void fwd_kernel(FmFwdArgs a) 
 
   // only the key blocks [j_lo, j_hi) can be live for this row block (found by the work pre-pass)
   for (int chunk = j_lo; chunk < j_hi; chunk += C::LIST_CAP) {
-    const int n_live = build_live_key_blocks(table, t_c, chunk, min(chunk + C::LIST_CAP, j_hi), q0, min(q0 + C::BR, N),
-                                             C::BR / 4, list, wave_cnt);
+    const int n_live = build_live_key_blocks<T_UNMASKED>(table, t_c, chunk, min(chunk + C::LIST_CAP, j_hi), q0,
+                                                         min(q0 + C::BR, Nr), C::BR / 4, list, wave_cnt);
     if (n_live == 0) continue;
     // the entries of tiles T, T + 1, T + 2 of the step about to run (clamped to the last one)
     int e_t = __builtin_amdgcn_readfirstlane(list[0]);

@@ -73,20 +73,19 @@ struct FmSetup {
 // The backward's whole setup (tables, work pre-passes and unit queues of the dQ pass `rows` and of the
 // dK/dV pass `cols`, whose units count K/V heads) in three launches.
 hipError_t fm_launch_bwd_setup(const int* lts, const int* lte, const int* uts, const int* ute, int B, int H, int Hk,
-                               int N, const FmSetup& rows, const FmSetup& cols, hipStream_t stream);
-hipError_t fm_launch_preprocess(const int* lts, const int* lte, const int* uts, const int* ute, int B, int N,
+                               int N, int Np, const FmSetup& rows, const FmSetup& cols, hipStream_t stream);
+// Tables of ceil(Np / block_c) key blocks per batch row.  Np == N: a ragged last block covers the columns that
+// exist.  Np > N: the columns [N, Np) count as masked for every row (pad_column).
+hipError_t fm_launch_preprocess(const int* lts, const int* lte, const int* uts, const int* ute, int B, int N, int Np,
                                 int block_c, int* minmax, hipStream_t stream);
-// Padded copies of the four bound vectors: [4][B][Np], columns >= N masked for every row.
-hipError_t fm_launch_pad_bounds(const int* lts, const int* lte, const int* uts, const int* ute, int B, int N, int Np,
-                                int* padded, hipStream_t stream);
 hipError_t fm_launch_classify(const int* minmax, int B, int N, int block_r, int block_c, uint8_t* cls,
                               hipStream_t stream);
 // work: int[B * T_r] (resp. B * T_c); range: int[2 * B * T] = first live block and one past the
 // last live block of every unit (0, 0 if none); order: fm_order_bytes(B*H*T) bytes = the slot
 // records {unit, first, last, 0} followed by the queue counters (zeroed here).
-hipError_t fm_launch_row_order(const int* minmax, int B, int H, int Hk, int N, int block_r, int block_c, int* work,
+hipError_t fm_launch_row_order(const int* minmax, int B, int H, int Hk, int N, int Np, int block_r, int block_c, int* work,
                                int* range, int* order, hipStream_t stream);
-hipError_t fm_launch_col_order(const int* minmax, int B, int H, int N, int block_r, int block_c, int* work,
+hipError_t fm_launch_col_order(const int* minmax, int B, int H, int N, int Np, int block_r, int block_c, int* work,
                                int* range, int* order, hipStream_t stream);
 
 // Measurement aid (fm_probe.hip): `workgroups` x 4 waves each issue iters x fm_mfma_ceiling_ops_per_iter()
@@ -108,12 +107,12 @@ struct FmStride {
 // `general` selects the kernel instantiations that honour the stride fields and Hk (number of
 // K/V heads, H % Hk == 0: query head h reads K/V head h / (H / Hk)); otherwise every tensor is
 // contiguous [B,H,N,d], Hk == H, and the strides are compile-time constants of the kernels.
-// N is the true sequence length (stride of the tensors), Np = N rounded up to a multiple of 128: the
-// length the tile loops and the tables work at.  When Np > N the bound vectors are the library's
-// padded copies [B][Np] whose extra columns are masked for every row.
+// N is the true sequence length (stride of the tensors and of the bound vectors), Np = N rounded up to a
+// multiple of 128: the length the tile loops and the tables work at.  When Np > N the extra key columns are
+// masked for every row (pad_column); rows are classified up to N only.
 struct FmFwdArgs {
   const void *q, *k, *v;
-  const int *lts, *lte, *uts, *ute;   // [B][Np]
+  const int *lts, *lte, *uts, *ute;   // [B][N]
   const int* minmax;  // [B][8][T_c] at FM_FWD_BC
   int* order;         // queue slots {unit (b*H + h)*T_r + i or -1, first live key block, last + 1, 0}, then the
                       // queue counters; a row block is fully masked outside [first, last)

@@ -12,7 +12,7 @@ namespace fm {
 // then a butterfly over the 64 lanes leaves the 8 results in every lane.
 __device__ __forceinline__ void preprocess_body(const int* __restrict__ lts, const int* __restrict__ lte,
                                                 const int* __restrict__ uts, const int* __restrict__ ute, int n,
-                                                int block_c, int t_c, int total_blocks, int* __restrict__ minmax,
+                                                int np, int block_c, int t_c, int total_blocks, int* __restrict__ minmax,
                                                 int block) {
   const int lane = threadIdx.x & 63;
   const int blk = block * 4 + (threadIdx.x >> 6);
@@ -26,6 +26,10 @@ __device__ __forceinline__ void preprocess_body(const int* __restrict__ lts, con
   for (int a = 0; a < 4; ++a) {
     mx[a] = INT32_MIN;
     mn[a] = INT32_MAX;
+  }
+  if (np > n && c0 + block_c > n) {   // the block's columns past the end of the sequence
+#pragma unroll
+    for (int a = 0; a < 4; ++a) mx[a] = mn[a] = pad_column[a];
   }
   for (int c = c0 + lane; c < c1; c += 64) {
 #pragma unroll
@@ -55,21 +59,21 @@ __device__ __forceinline__ void preprocess_body(const int* __restrict__ lts, con
 
 __global__ __launch_bounds__(256) void preprocess_kernel(const int* __restrict__ lts, const int* __restrict__ lte,
                                                          const int* __restrict__ uts, const int* __restrict__ ute,
-                                                         int n, int block_c, int t_c, int total_blocks,
+                                                         int n, int np, int block_c, int t_c, int total_blocks,
                                                          int* __restrict__ minmax) {
-  preprocess_body(lts, lte, uts, ute, n, block_c, t_c, total_blocks, minmax, blockIdx.x);
+  preprocess_body(lts, lte, uts, ute, n, np, block_c, t_c, total_blocks, minmax, blockIdx.x);
 }
 
 // The tables of two block widths in one launch (the backward's two loops tile the keys differently):
 // workgroups [0, blocks_a) build table a, the rest table b.
 __global__ __launch_bounds__(256) void preprocess2_kernel(const int* __restrict__ lts, const int* __restrict__ lte,
                                                           const int* __restrict__ uts, const int* __restrict__ ute,
-                                                          int n, int batch, int block_c_a, int* __restrict__ minmax_a,
+                                                          int n, int np, int batch, int block_c_a, int* __restrict__ minmax_a,
                                                           int blocks_a, int block_c_b, int* __restrict__ minmax_b) {
   const bool first = (int)blockIdx.x < blocks_a;
   const int block_c = first ? block_c_a : block_c_b;
-  const int t_c = (n + block_c - 1) / block_c;
-  preprocess_body(lts, lte, uts, ute, n, block_c, t_c, batch * t_c, first ? minmax_a : minmax_b,
+  const int t_c = (np + block_c - 1) / block_c;
+  preprocess_body(lts, lte, uts, ute, n, np, block_c, t_c, batch * t_c, first ? minmax_a : minmax_b,
                   first ? blockIdx.x : blockIdx.x - blocks_a);
 }
 
@@ -82,23 +86,6 @@ __global__ __launch_bounds__(256) void classify_kernel(const int* __restrict__ m
   const int r0 = i * block_r;
   const int r1 = min(r0 + block_r, n);
   cls[((size_t)b * t_r + i) * t_c + j] = (uint8_t)classify_tile(r0, r1, t);
-}
-
-// Padded copies of the bound vectors for a sequence length that is not a multiple of 128: the
-// columns past the end get an interval that masks every row (LTS = INT_MIN, LTE = INT_MAX), so
-// the tile loops treat them like any other masked key and every vector read stays in bounds.
-__global__ __launch_bounds__(256) void pad_bounds_kernel(const int* __restrict__ lts, const int* __restrict__ lte,
-                                                         const int* __restrict__ uts, const int* __restrict__ ute,
-                                                         int batch, int n, int np, int* __restrict__ padded) {
-  const long long gid = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (gid >= (long long)batch * np) return;
-  const int b = (int)(gid / np), j = (int)(gid % np);
-  const size_t plane = (size_t)batch * np, src = (size_t)b * n + j;
-  const bool in = j < n;
-  padded[0 * plane + gid] = in ? lts[src] : INT_MIN;
-  padded[1 * plane + gid] = in ? lte[src] : INT_MAX;
-  padded[2 * plane + gid] = in ? uts[src] : 0;
-  padded[3 * plane + gid] = in ? ute[src] : 0;
 }
 
 // Work of one row block = number of key blocks that are not fully masked, and
@@ -352,20 +339,12 @@ __global__ __launch_bounds__(1024) void order2_kernel(OrderJob a, int blocks_a, 
 
 using namespace fm;
 
-hipError_t fm_launch_preprocess(const int* lts, const int* lte, const int* uts, const int* ute, int B, int N,
+hipError_t fm_launch_preprocess(const int* lts, const int* lte, const int* uts, const int* ute, int B, int N, int Np,
                                 int block_c, int* minmax, hipStream_t stream) {
-  const int t_c = (N + block_c - 1) / block_c;
+  const int t_c = (Np + block_c - 1) / block_c;
   const int total = B * t_c;
-  hipLaunchKernelGGL(preprocess_kernel, dim3((total + 3) / 4), dim3(256), 0, stream, lts, lte, uts, ute, N, block_c,
-                     t_c, total, minmax);
-  return hipGetLastError();
-}
-
-hipError_t fm_launch_pad_bounds(const int* lts, const int* lte, const int* uts, const int* ute, int B, int N, int Np,
-                                int* padded, hipStream_t stream) {
-  const long long total = (long long)B * Np;
-  hipLaunchKernelGGL(pad_bounds_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, lts, lte, uts, ute,
-                     B, N, Np, padded);
+  hipLaunchKernelGGL(preprocess_kernel, dim3((total + 3) / 4), dim3(256), 0, stream, lts, lte, uts, ute, N, Np,
+                     block_c, t_c, total, minmax);
   return hipGetLastError();
 }
 
@@ -386,9 +365,9 @@ static OrderJob order_job(int* work, int* range, int B, int H, int group, int bl
                   order + 4 * (size_t)slots};
 }
 
-hipError_t fm_launch_row_order(const int* minmax, int B, int H, int Hk, int N, int block_r, int block_c, int* work,
-                               int* range, int* order, hipStream_t stream) {
-  const int t_c = (N + block_c - 1) / block_c;
+hipError_t fm_launch_row_order(const int* minmax, int B, int H, int Hk, int N, int Np, int block_r, int block_c,
+                               int* work, int* range, int* order, hipStream_t stream) {
+  const int t_c = (Np + block_c - 1) / block_c;
   const int t_r = (N + block_r - 1) / block_r;
   const int total = B * t_r;
   hipLaunchKernelGGL(row_work_kernel, dim3((total + 3) / 4), dim3(256), 0, stream, minmax, N, block_r, t_r, t_c, total,
@@ -398,9 +377,9 @@ hipError_t fm_launch_row_order(const int* minmax, int B, int H, int Hk, int N, i
   return hipGetLastError();
 }
 
-hipError_t fm_launch_col_order(const int* minmax, int B, int H, int N, int block_r, int block_c, int* work,
+hipError_t fm_launch_col_order(const int* minmax, int B, int H, int N, int Np, int block_r, int block_c, int* work,
                                int* range, int* order, hipStream_t stream) {
-  const int t_c = (N + block_c - 1) / block_c;
+  const int t_c = (Np + block_c - 1) / block_c;
   const int t_r = (N + block_r - 1) / block_r;
   const int total = B * t_c;
   hipLaunchKernelGGL(col_work_kernel, dim3((total + 3) / 4), dim3(256), 0, stream, minmax, N, block_r, t_r, t_c, total,
@@ -412,11 +391,11 @@ hipError_t fm_launch_col_order(const int* minmax, int B, int H, int N, int block
 
 // The backward's setup in three launches: both min/max tables, both work pre-passes, both passes' queues.
 hipError_t fm_launch_bwd_setup(const int* lts, const int* lte, const int* uts, const int* ute, int B, int H, int Hk,
-                               int N, const FmSetup& rows, const FmSetup& cols, hipStream_t stream) {
-  const int tc_r = (N + rows.block_c - 1) / rows.block_c, tr_r = (N + rows.block_r - 1) / rows.block_r;
-  const int tc_c = (N + cols.block_c - 1) / cols.block_c, tr_c = (N + cols.block_r - 1) / cols.block_r;
+                               int N, int Np, const FmSetup& rows, const FmSetup& cols, hipStream_t stream) {
+  const int tc_r = (Np + rows.block_c - 1) / rows.block_c, tr_r = (N + rows.block_r - 1) / rows.block_r;
+  const int tc_c = (Np + cols.block_c - 1) / cols.block_c, tr_c = (N + cols.block_r - 1) / cols.block_r;
   const int pre_a = (B * tc_r + 3) / 4, pre_b = (B * tc_c + 3) / 4;
-  hipLaunchKernelGGL(preprocess2_kernel, dim3(pre_a + pre_b), dim3(256), 0, stream, lts, lte, uts, ute, N, B,
+  hipLaunchKernelGGL(preprocess2_kernel, dim3(pre_a + pre_b), dim3(256), 0, stream, lts, lte, uts, ute, N, Np, B,
                      rows.block_c, rows.minmax, pre_a, cols.block_c, cols.minmax);
   const WorkJob wr{rows.minmax, rows.block_r, tr_r, tc_r, B * tr_r, rows.work, rows.range};
   const WorkJob wc{cols.minmax, cols.block_r, tr_c, tc_c, B * tc_c, cols.work, cols.range};
