@@ -203,12 +203,15 @@ static int fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
   int* work = (int*)(ws + sp.work);
   int* range = (int*)(ws + sp.range);
   int* order = (int*)(ws + sp.order);
-  e = fm_launch_preprocess(lts, lte, uts, ute, B, N, Np, FM_FWD_BC, minmax, stream);
-  if (e != hipSuccess) return hip_fail(e);
-  e = fm_launch_row_order(minmax, B, H, Hk, N, Np, FM_FWD_BR, FM_FWD_BC, work, range, order, stream);
-  if (e != hipSuccess) return hip_fail(e);
-  mark(1, stream);
   FmFwdArgs a;
+  a.direct = fm_direct((long long)B * H * (Np / FM_FWD_BR));
+  if (!a.direct) {
+    e = fm_launch_preprocess(lts, lte, uts, ute, B, N, Np, FM_FWD_BC, minmax, stream);
+    if (e != hipSuccess) return hip_fail(e);
+    e = fm_launch_row_order(minmax, B, H, Hk, N, Np, FM_FWD_BR, FM_FWD_BC, work, range, order, stream);
+    if (e != hipSuccess) return hip_fail(e);
+  }
+  mark(1, stream);
   a.q = q; a.k = k; a.v = v;
   a.lts = lts; a.lte = lte; a.uts = uts; a.ute = ute;
   a.minmax = minmax; a.order = order;

@@ -500,6 +500,95 @@ __device__ __forceinline__ int entry_mask_mode(int entry) {
   return need;
 }
 
+// --- direct units -----------------------------------------------------------------------------------------
+// A problem with at most one 128-row unit per compute unit (fm_direct in fm_kernels.h) runs without the setup
+// launches: workgroup x takes unit direct_unit(), every workgroup derives the min/max values it needs from the
+// bound vectors themselves, and the unit is halved (S = 2: half the rows or keys per workgroup, the tiles of its
+// list dealt alternately to two pairs of waves whose partial results meet in LDS at the end), which doubles the
+// workgroups and halves the longest chain of tiles.
+//
+// Units are numbered slice-major and dealt to the XCDs (workgroup x runs on XCD x % 8) in eight contiguous runs, so
+// that a slice's K/V stays in as few L2s as the count allows; within a slice the last block goes first, because in
+// masks with a causal side it is the longest.  -1: nothing to do.
+__device__ __forceinline__ int direct_unit(int units, int blocks) {
+  const int per = (units + FM_QUEUES - 1) / FM_QUEUES;
+  const int p = (int)(blockIdx.x % FM_QUEUES) * per + (int)(blockIdx.x / FM_QUEUES);
+  if ((int)(blockIdx.x / FM_QUEUES) >= per || p >= units) return -1;
+  const int slice = p / blocks, i = p - slice * blocks;
+  return slice * blocks + blocks - 1 - i;
+}
+// x combined with the value CTRL (a DPP row rotation) brings from another lane of the same 16.
+template <int CTRL>
+__device__ __forceinline__ int dpp_max(int x) {
+  return max(x, __builtin_amdgcn_update_dpp(x, x, CTRL, 0xf, 0xf, false));
+}
+template <int CTRL>
+__device__ __forceinline__ int dpp_min(int x) {
+  return min(x, __builtin_amdgcn_update_dpp(x, x, CTRL, 0xf, 0xf, false));
+}
+// max / min over the 16 lanes of a DPP row, left in all of them
+__device__ __forceinline__ int row16_max(int x) { return dpp_max<0x121>(dpp_max<0x122>(dpp_max<0x124>(dpp_max<0x128>(x)))); }
+__device__ __forceinline__ int row16_min(int x) { return dpp_min<0x121>(dpp_min<0x122>(dpp_min<0x124>(dpp_min<0x128>(x)))); }
+
+// build_live_key_blocks for key blocks of 64 columns straight from the bound vectors (vec: a batch row's LTS, LTE,
+// UTS, UTE; n columns).  Sixteen lanes take a block, four columns each, so a pass of the workgroup covers 1024
+// columns; PASSES passes have their loads in flight together.  The raw entries go to list[] in place (-1: fully
+// masked) and are compacted from there.  NW: waves that own rows (32 each) of the unit.
+template <bool RAGGED, int EMPTY, int NW>
+__device__ __forceinline__ int build_live_key_blocks_direct(const int* const (&vec)[4], int n, int j_begin, int j_end,
+                                                            int r0, int r1, int* list, int* wave_cnt) {
+  constexpr int KT = 64, BLOCKS = 256 * 4 / KT, PASSES = 2;
+  const int tid = threadIdx.x;
+  for (int base = j_begin; base < j_end; base += BLOCKS * PASSES) {
+    i32x4 x[PASSES][4];
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+      const int j = base + p * BLOCKS + tid / 16, key = j * KT + (tid % 16) * 4;
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        if (RAGGED) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[p][a][e] = vec[a][min(key + e, n - 1)];
+        } else {
+          x[p][a] = *(const i32x4*)(vec[a] + min(key, n - 4));
+        }
+      }
+    }
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+      const int j = base + p * BLOCKS + tid / 16, key = j * KT + (tid % 16) * 4;
+      MinMax8 mm;
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        if (RAGGED) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (key + e >= n) x[p][a][e] = a == 0 ? INT32_MIN : a == 1 ? INT32_MAX : 0;   // pad_column
+        }
+        const i32x4 v = x[p][a];
+        mm.v[2 * a] = row16_max(max(max(v[0], v[1]), max(v[2], v[3])));
+        mm.v[2 * a + 1] = row16_min(min(min(v[0], v[1]), min(v[2], v[3])));
+      }
+      const int cls = classify_tile(r0, r1, mm);
+      int entry = (j - j_begin) | ((cls & 3) << 16) | (((cls >> 4) & 3) << 26) | ((mm.v[LTE_MIN] >= r1 ? 1 : 0) << 28) |
+                  ((mm.v[UTS_MAX] <= r0 ? 1 : 0) << 29);
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const int w0 = min(r0 + w * 32, r1), w1 = min(w0 + 32, r1);
+        entry |= (w0 < w1 ? classify_tile(w0, w1, mm) & 3 : EMPTY) << (18 + 2 * w);
+      }
+      if (tid % 16 == 0 && j < j_end) list[j - j_begin] = cls == T_FULLY ? -1 : entry;
+    }
+  }
+  barrier_nofence();
+  int running = 0;
+  for (int base = j_begin; base < j_end; base += 256) {
+    const int e = base + tid < j_end ? list[base + tid - j_begin] : -1;
+    append_live(e != -1, e, list, wave_cnt, running);   // writes behind what this and earlier passes have read
+  }
+  return running;
+}
+
 // Column-parallel loop: classify row blocks [i_begin, i_end) of block_r rows
 // against one key block's min/max values; entries are i | class << 24.  The
 // blocks that need no element mask come first (n_plain of them), the partially

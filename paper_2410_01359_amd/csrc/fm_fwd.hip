@@ -25,10 +25,12 @@ namespace fm {
 #define FM_FWD_EXP_A 20
 #endif
 
-template <int D>
+// S: groups of waves that share a unit's key tiles (1: queued units of 128 rows; 2: direct units of 64 rows, each
+// tile of the list belongs to one pair of waves)
+template <int D, int S = 1>
 struct FwdCfg {
   static constexpr int KT = FM_FWD_BC;          // keys per tile
-  static constexpr int BR = FM_FWD_BR;          // query rows per workgroup
+  static constexpr int BR = FM_FWD_BR / S;      // query rows per workgroup
   using L = TileLayout<D>;
   static constexpr int K_BYTES = KT * L::RS;
   static constexpr int V_BYTES = KT * L::RS;
@@ -38,8 +40,8 @@ struct FwdCfg {
   static constexpr int LIST_OFF = 0;
   static constexpr int CNT_OFF = LIST_CAP * 4;
   static constexpr int K_OFF = CNT_OFF + 64;
-  static constexpr int V_OFF = K_OFF + 2 * K_BYTES;
-  static constexpr int LDS_BYTES = V_OFF + 2 * VSTAGE;
+  static constexpr int V_OFF = K_OFF + 2 * S * K_BYTES;   // two stages of S tiles each
+  static constexpr int LDS_BYTES = V_OFF + 2 * S * VSTAGE;
 };
 
 // Per-wave constants of the tile loop.
@@ -231,24 +233,29 @@ __device__ __forceinline__ void fwd_step(f32x16 (&cur)[2], f32x16 (&nxt)[2], f32
 // Np (tables and lists are built for it; the padding columns are masked for every row), tile copies that reach past row N clamp their source rows, and rows >= N are
 // computed but not stored.
 // GEN: tensors with caller-given strides and fewer K/V heads than query heads (see FmFwdArgs).
-template <int D, bool RAGGED, bool GEN>
-__global__ __launch_bounds__(256, D == 64 ? 3 : 2) void fwd_kernel(FmFwdArgs a) {
-  using C = FwdCfg<D>;
+template <int D, bool RAGGED, bool GEN, int S>
+__global__ __launch_bounds__(256, S == 2 ? (D == 64 ? 2 : 1) : D == 64 ? 3 : 2) void fwd_kernel(FmFwdArgs a) {
+  using C = FwdCfg<D, S>;
   constexpr int KT = C::KT, NKB = KT / 32, NDB = D / 32, NKK = D / 16;
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
-  const i32x4 rec = queue_take(a.order, a.slots, (int*)(smem + C::CNT_OFF) + 8);
-  const int unit = rec[0], j_lo = rec[1], j_hi = rec[2];
+  i32x4 rec = {-1, 0, 0, 0};
+  if (S == 1) rec = queue_take(a.order, a.slots, (int*)(smem + C::CNT_OFF) + 8);
+  else rec[0] = direct_unit(a.B * a.H * ((a.N + C::BR - 1) / C::BR), (a.N + C::BR - 1) / C::BR);
+  const int unit = rec[0];
   if (unit < 0) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 5, c = lane & 31;
   const int N = a.Np, H = a.H;            // padded length: what the loops and tables see
   const int Nr = RAGGED ? a.N : a.Np;     // rows the tensors really have
-  const int t_r = N / C::BR, t_c = N / KT;
+  const int t_r = (Nr + C::BR - 1) / C::BR, t_c = N / KT;
+  const int j_lo = S == 1 ? rec[1] : 0, j_hi = S == 1 ? rec[2] : t_c;
   const int bh = unit / t_r, i_blk = unit - bh * t_r, b = bh / H;
   const int q0 = i_blk * C::BR;
-  const int qw0 = q0 + wave * 32;
+  constexpr int WR = 4 / S;               // waves that share the unit's rows, 32 each
+  const int wrow = S == 1 ? wave : wave % WR, grp = S == 1 ? 0 : wave / WR;
+  const int qw0 = q0 + wrow * 32;
 
   const int h = bh - b * H, hk = GEN ? h / (H / a.Hk) : h, Hk = GEN ? a.Hk : H;
   const __bf16* qp = slice_ptr<D, GEN>(a.q, a.sq, b, h, H, Nr);
@@ -305,19 +312,19 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void fwd_kernel(FmFwdArgs a) 
 
   // Asynchronous copies of list entry ENTRY: its K tile into K stage KBUF / its V tile (and, if the
   // workgroup's tile is partially masked, its bound slices) into V stage VBUF.
-#define FM_LOAD_K(ENTRY, KBUF)                                                                   \
+#define FM_LOAD_K(ENTRY, KBUF, SUB)                                                              \
   {                                                                                              \
     const int j_ = entry_block(ENTRY, chunk);                                                    \
-    char* st_ = smem + C::K_OFF + (KBUF) * C::K_BYTES;                                           \
+    char* st_ = smem + C::K_OFF + ((KBUF) * S + (SUB)) * C::K_BYTES;                             \
     if (RAGGED && (j_ + 1) * KT > Nr)                                                            \
       tile_load_async_clamped<D>(kp, j_ * KT, Nr, st_, wave, lane, 2 * k_rs);                    \
     else                                                                                         \
       tile_load_async<D>(kp + (size_t)j_ * KT * k_rs, copy_lanes, st_, wave, 2 * k_rs);          \
   }
-#define FM_LOAD_V(ENTRY, VBUF)                                                                   \
+#define FM_LOAD_V(ENTRY, VBUF, SUB)                                                              \
   {                                                                                              \
     const int j_ = entry_block(ENTRY, chunk);                                                    \
-    char* st_ = smem + C::V_OFF + (VBUF) * C::VSTAGE;                                            \
+    char* st_ = smem + C::V_OFF + ((VBUF) * S + (SUB)) * C::VSTAGE;                              \
     if (RAGGED && (j_ + 1) * KT > Nr)                                                            \
       tile_load_async_clamped<D>(vp, j_ * KT, Nr, st_, wave, lane, 2 * v_rs);                    \
     else                                                                                         \
@@ -330,48 +337,67 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void fwd_kernel(FmFwdArgs a) 
         async_copy16(my_bvec + j_ * KT, lds_address(st_ + C::V_BYTES));                          \
     }                                                                                            \
   }
-  // One iteration: tile T with scores in CUR, scores of tile T + 1 into NXT.  Entries past the
-  // end of the list are clamped to the last one: nothing is copied for them, and the scores the last
-  // step computes from the stale K stage are never used.
+  // One iteration: step T (tiles S T .. S T + S - 1 of the list, one per group of waves) with scores in CUR, scores
+  // of step T + 1 into NXT.  Entries past the end of the list are clamped to the last one: nothing is copied for
+  // them, and the scores the last step computes from the stale K stage are never used.  A group without a tile in
+  // the last step only takes part in the copies and the barrier.
 #define FM_STEP(T, CUR, NXT)                                                                     \
   {                                                                                              \
-    /* the list entry that joins the window at the next step: read now, picked up behind the  */ \
+    /* the list entries that join the window at the next step: read now, picked up behind the */ \
     /* step's barrier, so that no step starts by waiting for LDS                               */ \
-    const int v_3 = list[min((T) + 3, n_live - 1)];                                              \
+    int v_3[S];                                                                                  \
+    _Pragma("unroll") for (int s_ = 0; s_ < S; ++s_) v_3[s_] = list[min(S * ((T) + 3) + s_, n_live - 1)]; \
     __builtin_amdgcn_sched_barrier(0);                                                           \
-    if ((T) + 2 < n_live) FM_LOAD_K(e_2, (T) & 1);                                               \
-    if ((T) + 1 < n_live) FM_LOAD_V(e_1, ((T) + 1) & 1);                                         \
-    const char* vs_ = smem + C::V_OFF + ((T) & 1) * C::VSTAGE;                                   \
-    fwd_step<D>(CUR, NXT, oacc, qreg, m_run, l_run, smem + C::K_OFF + (((T) + 1) & 1) * C::K_BYTES, vs_, \
-                (const int*)(vs_ + C::V_BYTES),                                                  \
-                entry_wave_class(e_t, wave) != T_UNMASKED ? entry_mask_mode(e_t) : 0, w);        \
+    _Pragma("unroll") for (int s_ = 0; s_ < S; ++s_) {                                           \
+      if (S * ((T) + 2) + s_ < n_live) FM_LOAD_K(e_2[s_], (T) & 1, s_);                          \
+      if (S * ((T) + 1) + s_ < n_live) FM_LOAD_V(e_1[s_], ((T) + 1) & 1, s_);                    \
+    }                                                                                            \
+    const char* vs_ = smem + C::V_OFF + (((T) & 1) * S + grp) * C::VSTAGE;                       \
+    const int e_own = S == 1 || grp == 0 ? e_t[0] : e_t[S - 1];                                  \
+    if (S == 1 || S * (T) + grp < n_live)                                                        \
+      fwd_step<D>(CUR, NXT, oacc, qreg, m_run, l_run,                                            \
+                  smem + C::K_OFF + ((((T) + 1) & 1) * S + grp) * C::K_BYTES, vs_,               \
+                  (const int*)(vs_ + C::V_BYTES),                                                \
+                  entry_wave_class(e_own, wrow) != T_UNMASKED ? entry_mask_mode(e_own) : 0, w);  \
     async_wait<0>();   /* K(T+2) and V(T+1) have landed ... */                                   \
     barrier_nofence(); /* ... for every wave, and every wave is done with K(T+1) and V(T) */     \
-    e_t = e_1;                                                                                   \
-    e_1 = e_2;                                                                                   \
-    e_2 = __builtin_amdgcn_readfirstlane(v_3);                                                   \
+    _Pragma("unroll") for (int s_ = 0; s_ < S; ++s_) {                                           \
+      e_t[s_] = e_1[s_];                                                                         \
+      e_1[s_] = e_2[s_];                                                                         \
+      e_2[s_] = __builtin_amdgcn_readfirstlane(v_3[s_]);                                         \
+    }                                                                                            \
   }
 
+  const int* bnd_rows[4] = {a.lts + (size_t)b * Nr, a.lte + (size_t)b * Nr, a.uts + (size_t)b * Nr, a.ute + (size_t)b * Nr};
   // only the key blocks [j_lo, j_hi) can be live for this row block (found by the work pre-pass)
   for (int chunk = j_lo; chunk < j_hi; chunk += C::LIST_CAP) {
-    const int n_live = build_live_key_blocks<T_UNMASKED>(table, t_c, chunk, min(chunk + C::LIST_CAP, j_hi), q0,
-                                                         min(q0 + C::BR, Nr), C::BR / 4, list, wave_cnt);
+    const int chunk_end = min(chunk + C::LIST_CAP, j_hi), r1 = min(q0 + C::BR, Nr);
+    const int n_live =
+        S == 1 ? build_live_key_blocks<T_UNMASKED>(table, t_c, chunk, chunk_end, q0, r1, C::BR / 4, list, wave_cnt)
+               : build_live_key_blocks_direct<RAGGED, T_UNMASKED, WR>(bnd_rows, Nr, chunk, chunk_end, q0, r1, list, wave_cnt);
     if (n_live == 0) continue;
-    // the entries of tiles T, T + 1, T + 2 of the step about to run (clamped to the last one)
-    int e_t = __builtin_amdgcn_readfirstlane(list[0]);
-    int e_1 = __builtin_amdgcn_readfirstlane(list[min(1, n_live - 1)]);
-    int e_2 = __builtin_amdgcn_readfirstlane(list[min(2, n_live - 1)]);
+    // the entries of steps T, T + 1, T + 2 of the step about to run (clamped to the last one)
+    int e_t[S], e_1[S], e_2[S];
+#pragma unroll
+    for (int s_ = 0; s_ < S; ++s_) {
+      e_t[s_] = __builtin_amdgcn_readfirstlane(list[min(s_, n_live - 1)]);
+      e_1[s_] = __builtin_amdgcn_readfirstlane(list[min(S + s_, n_live - 1)]);
+      e_2[s_] = __builtin_amdgcn_readfirstlane(list[min(2 * S + s_, n_live - 1)]);
+    }
     {
-      FM_LOAD_K(e_t, 0);
-      FM_LOAD_V(e_t, 0);
-      FM_LOAD_K(e_1, 1);
+#pragma unroll
+      for (int s_ = 0; s_ < S; ++s_) {
+        FM_LOAD_K(e_t[s_], 0, s_);
+        FM_LOAD_V(e_t[s_], 0, s_);
+        FM_LOAD_K(e_1[s_], 1, s_);
+      }
       async_wait<0>();
       barrier_nofence();
     }
     // scores of the first tile
     f32x16 s0[NKB], s1[NKB];
     {
-      const char* ks = smem + C::K_OFF;
+      const char* ks = smem + C::K_OFF + grp * C::K_BYTES;
 #pragma unroll
       for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
@@ -383,9 +409,10 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void fwd_kernel(FmFwdArgs a) 
           s0[kb] = mfma32(*(const bf16x8*)(ks + kb * 32 * C::L::RS + C::L::add_col(w.a_off, kk * 32)), qreg[kk], s0[kb]);
       barrier_nofence();   // the first iteration refills this K stage: every wave must have read it
     }
-    for (int t = 0; t < n_live; t += 2) {
+    const int n_steps = (n_live + S - 1) / S;
+    for (int t = 0; t < n_steps; t += 2) {
       FM_STEP(t, s0, s1)
-      if (t + 1 < n_live) FM_STEP(t + 1, s1, s0)
+      if (t + 1 < n_steps) FM_STEP(t + 1, s1, s0)
     }
     __syncthreads();     // the list is rebuilt by the next pass
   }
@@ -398,6 +425,39 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void fwd_kernel(FmFwdArgs a) 
   const int o_rs = row_stride<D, GEN>(a.so);
   float* lp = a.lse + (size_t)bh * Nr;
   {
+    if (S == 2) {
+      // The two groups' softmax states of the same rows meet in LDS (nothing is in flight into the stages, every
+      // wave is past its last tile): the second group leaves m, l and O of its rows, the first one brings both to
+      // the larger reference maximum and adds.
+      static_assert(S == 1 || WR * 64 * (16 * NDB + 2) * 4 + 4 * RowStage<D>::BYTES <= C::LDS_BYTES - C::K_OFF, "exchange fits the stages");
+      float* const part = (float*)(smem + C::K_OFF + 4 * RowStage<D>::BYTES) + wrow * 64 * (16 * NDB + 2) + lane * 4;
+      float* const part_ml = (float*)(smem + C::K_OFF + 4 * RowStage<D>::BYTES) + wrow * 64 * (16 * NDB + 2) + 64 * 16 * NDB + lane;
+      if (grp == 1) {
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+          for (int rq = 0; rq < 4; ++rq)
+            *(f32x4*)(part + (db * 4 + rq) * 256) =
+                f32x4{oacc[db][rq * 4], oacc[db][rq * 4 + 1], oacc[db][rq * 4 + 2], oacc[db][rq * 4 + 3]};
+        part_ml[0] = m_run;
+        part_ml[64] = l_run;
+      }
+      barrier_nofence();
+      if (grp == 1) return;
+      const float m_1 = part_ml[0], m_new = fmaxf(m_run, m_1);
+      const float a_0 = m_run == -INFINITY ? 0.f : fast_exp2(m_run - m_new);
+      const float a_1 = m_1 == -INFINITY ? 0.f : fast_exp2(m_1 - m_new);
+      l_run = l_run * a_0 + part_ml[64] * a_1;
+      m_run = m_new;
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int rq = 0; rq < 4; ++rq) {
+          const f32x4 o = *(const f32x4*)(part + (db * 4 + rq) * 256);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) oacc[db][rq * 4 + e] = oacc[db][rq * 4 + e] * a_0 + o[e] * a_1;
+        }
+    }
     const float lt = l_run + partner32(l_run);
     const float inv = lt > 0.f ? 1.f / lt : 0.f;
     const int row = qw0 + c;
@@ -424,13 +484,19 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void fwd_kernel(FmFwdArgs a) 
 
 using namespace fm;
 
+template <int D, bool RAGGED, bool GEN, int S>
+static hipError_t launch_fwd_s(const FmFwdArgs& a, hipStream_t stream) {
+  using C = FwdCfg<D, S>;
+  static bool allowed[FM_MAX_DEVICES] = {};
+  if (hipError_t e = fm_allow_lds((const void*)fwd_kernel<D, RAGGED, GEN, S>, C::LDS_BYTES, allowed); e != hipSuccess) return e;
+  const int grid = S == 1 ? fm_launch_grid(a.slots) : fm_direct_grid(a.B * a.H * ((a.N + C::BR - 1) / C::BR));
+  hipLaunchKernelGGL((fwd_kernel<D, RAGGED, GEN, S>), dim3(grid), dim3(256), C::LDS_BYTES, stream, a);
+  return hipGetLastError();
+}
+
 template <int D, bool RAGGED, bool GEN>
 static hipError_t launch_fwd_t(const FmFwdArgs& a, hipStream_t stream) {
-  using C = FwdCfg<D>;
-  static bool allowed[FM_MAX_DEVICES] = {};
-  if (hipError_t e = fm_allow_lds((const void*)fwd_kernel<D, RAGGED, GEN>, C::LDS_BYTES, allowed); e != hipSuccess) return e;
-  hipLaunchKernelGGL((fwd_kernel<D, RAGGED, GEN>), dim3(fm_launch_grid(a.slots)), dim3(256), C::LDS_BYTES, stream, a);
-  return hipGetLastError();
+  return a.direct ? launch_fwd_s<D, RAGGED, GEN, 2>(a, stream) : launch_fwd_s<D, RAGGED, GEN, 1>(a, stream);
 }
 
 template <int D>

@@ -54,6 +54,12 @@ inline int fm_persistent_grid(int slots, int per_cu) {
   const int g = (cus * per_cu + FM_QUEUES - 1) / FM_QUEUES * FM_QUEUES;
   return g < fm_launch_grid(slots) ? g : fm_launch_grid(slots);
 }
+// Whether a tile loop over `units` units of 128 rows (or keys) runs on direct units (see fm_common.h): no setup
+// launches, halved units.  The line is where the chip has at most one 128-row unit per compute unit.  Beyond it a
+// workgroup per 128 rows fills the chip, and its tiles cost less (two workgroups share a compute unit).
+inline bool fm_direct(long long units) { return units <= fm_compute_units(); }
+// Workgroups of a launch over direct units: every XCD's run of units, rounded up (see direct_unit).
+inline int fm_direct_grid(int units) { return (units + FM_QUEUES - 1) / FM_QUEUES * FM_QUEUES; }
 // Tile shapes (rows x key columns) each pass classifies at.
 constexpr int FM_FWD_BR = 128, FM_FWD_BC = 64;
 constexpr int FM_DQ_BR = 128;
@@ -121,6 +127,7 @@ struct FmFwdArgs {
   float scale;
   int B, H, N, Np, d;
   int slots;
+  bool direct;        // direct units: minmax, order and slots are not used
   bool general;
   int Hk;
   FmStride sq, sk, sv, so;
@@ -142,6 +149,7 @@ struct FmBwdArgs {
   float scale;
   int B, H, N, Np, d;
   int slots_dq, slots_dkdv;
+  bool direct_dq, direct_dkdv;   // direct units: the pass's minmax, order and slots are not used
   bool general;
   int Hk;
   FmStride sq, sk, sv, so, sdo, sdq, sdk, sdv;
