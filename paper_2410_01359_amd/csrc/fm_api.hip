@@ -340,8 +340,17 @@ static int bwd_impl(const void* q, const void* k, const void* v, const void* out
                      (int*)(ws + sq.order)};
   const FmSetup cols{FM_DKDV_BR, FM_DKDV_BC, (int*)(ws + skv.minmax), (int*)(ws + skv.work), (int*)(ws + skv.range),
                      (int*)(ws + skv.order)};
-  e = fm_launch_bwd_setup(lts, lte, uts, ute, B, H, Hk, N, Np, rows, cols, stream);
-  if (e != hipSuccess) return hip_fail(e);
+  a.direct_dq = fm_direct((long long)B * H * (Np / FM_DQ_BR));
+  a.direct_dkdv = fm_direct((long long)B * Hk * (Np / FM_DKDV_BC));   // Hk <= H: direct where dQ is
+  if (!a.direct_dkdv) {
+    e = fm_launch_bwd_setup(lts, lte, uts, ute, B, H, Hk, N, Np, rows, cols, stream);
+    if (e != hipSuccess) return hip_fail(e);
+  } else if (!a.direct_dq) {   // few K/V heads: only the dQ pass has queues
+    e = fm_launch_preprocess(lts, lte, uts, ute, B, N, Np, rows.block_c, rows.minmax, stream);
+    if (e != hipSuccess) return hip_fail(e);
+    e = fm_launch_row_order(rows.minmax, B, H, Hk, N, Np, rows.block_r, rows.block_c, rows.work, rows.range, rows.order, stream);
+    if (e != hipSuccess) return hip_fail(e);
+  }
   mark(1, stream);
   // the dQ loop first: its prologue is also Algorithm 2's D pre-pass and leaves -D and the log2-domain
   // lse of every row in the workspace for the dK/dV loop

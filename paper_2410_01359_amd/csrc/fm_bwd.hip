@@ -20,10 +20,12 @@ namespace fm {
 // ---------------------------------------------------------------------------
 // dQ: row-parallel, same transposed-score layout as the forward kernel.
 // ---------------------------------------------------------------------------
-template <int D>
+// S: groups of waves that share a unit's key tiles (1: queued units of 128 rows; 2: direct units of 64 rows, each
+// tile of the list belongs to one pair of waves, and tiles have 64 keys at either d: the lists are short)
+template <int D, int S = 1>
 struct DqCfg {
-  static constexpr int KT = fm_dq_bc(D);
-  static constexpr int BR = FM_DQ_BR;
+  static constexpr int KT = S == 1 ? fm_dq_bc(D) : 64;
+  static constexpr int BR = FM_DQ_BR / S;
   using L = TileLayout<D>;
   static constexpr int K_BYTES = KT * L::RS;
   static constexpr int V_BYTES = KT * L::RS;
@@ -32,29 +34,34 @@ struct DqCfg {
   static constexpr int LIST_CAP = 1024;
   static constexpr int CNT_OFF = LIST_CAP * 4;
   static constexpr int STAGE_OFF = CNT_OFF + 256;   // stages start at multiples of 256 bytes (see the operand reads)
-  static constexpr int LDS_BYTES = STAGE_OFF + 2 * STAGE;
+  static constexpr int LDS_BYTES = STAGE_OFF + 2 * S * STAGE;   // two stages of S tiles each
   static_assert(STAGE % 256 == 0 && STAGE_OFF % 256 == 0 && K_BYTES % 256 == 0, "XOR after add");
 };
 
 // RAGGED: see the forward kernel -- loops at the padded length, clamped tile copies, guarded stores.
-template <int D, bool RAGGED, bool GEN>
-__global__ __launch_bounds__(256, 2) void dq_kernel(FmBwdArgs a) {
-  using C = DqCfg<D>;
+template <int D, bool RAGGED, bool GEN, int S>
+__device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
+  using C = DqCfg<D, S>;
   constexpr int KT = C::KT, NKB = KT / 32, NDB = D / 32, NKK = D / 16;
   extern __shared__ __attribute__((aligned(256))) char smem[];   // the operand reads rely on the alignment
 
-  const i32x4 rec = queue_take(a.order_dq, a.slots_dq, (int*)(smem + C::CNT_OFF) + 8);
-  const int unit = rec[0], j_lo = rec[1], j_hi = rec[2];
+  i32x4 rec = {-1, 0, 0, 0};
+  if (S == 1) rec = queue_take(a.order_dq, a.slots_dq, (int*)(smem + C::CNT_OFF) + 8);
+  else rec[0] = direct_unit(a.B * a.H * ((a.N + C::BR - 1) / C::BR), (a.N + C::BR - 1) / C::BR);
+  const int unit = rec[0];
   if (unit < 0) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 5, c = lane & 31;
   const int N = a.Np, H = a.H;            // padded length: what the loops and tables see
   const int Nr = RAGGED ? a.N : a.Np;     // rows the tensors really have
-  const int t_r = N / C::BR, t_c = N / KT;
+  const int t_r = (Nr + C::BR - 1) / C::BR, t_c = N / KT;
+  const int j_lo = S == 1 ? rec[1] : 0, j_hi = S == 1 ? rec[2] : t_c;
   const int bh = unit / t_r, i_blk = unit - bh * t_r, b = bh / H;
   const int q0 = i_blk * C::BR;
-  const int qw0 = q0 + wave * 32;
+  constexpr int WR = 4 / S;               // waves that share the unit's rows, 32 each
+  const int wrow = S == 1 ? wave : wave % WR, grp = S == 1 ? 0 : wave / WR;
+  const int qw0 = q0 + wrow * 32;
   const int row = qw0 + c;  // this lane's query row
   const int row_ld = RAGGED ? min(row, Nr - 1) : row;
 
@@ -114,7 +121,7 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(FmBwdArgs a) {
     if (!real_row) dneg = 0.f;
   }
   lse2 = (lse2 == -INFINITY) ? INFINITY : lse2 * kLog2e;
-  if (g == 0) {
+  if (g == 0 && grp == 0) {
     a.dvec[(size_t)bh * N + row] = dneg;
     a.lse2[(size_t)bh * N + row] = lse2;
   }
@@ -141,10 +148,10 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(FmBwdArgs a) {
   const int t_base0 = C::L::off(4 * g + (i16 >> 2), (16 * half + 4 * (i16 & 3)) * 2);
   const int t_base1 = C::L::off(4 * g + (i16 >> 2) + 8, (16 * half + 4 * (i16 & 3)) * 2);
 
-#define FM_LOAD_TILE(ENTRY, BUF)                                                               \
+#define FM_LOAD_TILE(ENTRY, BUF, SUB)                                                          \
   {                                                                                            \
     const int j_ = entry_block(ENTRY, chunk);                                                  \
-    char* st_ = smem + C::STAGE_OFF + (BUF) * C::STAGE;                                        \
+    char* st_ = smem + C::STAGE_OFF + ((BUF) * S + (SUB)) * C::STAGE;                          \
     _Pragma("unroll") for (int sub = 0; sub < KT / 64; ++sub) {   /* 64 keys per copy call */  \
       const int r_ = j_ * KT + sub * 64;                                                       \
       char* ks_ = st_ + sub * 64 * C::L::RS;                                                   \
@@ -169,27 +176,45 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(FmBwdArgs a) {
 
   // only the key blocks [j_lo, j_hi) can be live for this row block (found by the work pre-pass)
   for (int chunk = j_lo; chunk < j_hi; chunk += C::LIST_CAP) {
-    const int n_live = build_live_key_blocks<T_FULLY>(table, t_c, chunk, min(chunk + C::LIST_CAP, j_hi), q0,
-                                                      min(q0 + C::BR, Nr), C::BR / 4, list, wave_cnt);
+    const int chunk_end = min(chunk + C::LIST_CAP, j_hi), r1 = min(q0 + C::BR, Nr);
+    int n_live;
+    if constexpr (S == 1) {
+      n_live = build_live_key_blocks<T_FULLY>(table, t_c, chunk, chunk_end, q0, r1, C::BR / 4, list, wave_cnt);
+    } else {
+      const int* bnd_rows[4] = {a.lts + (size_t)b * Nr, a.lte + (size_t)b * Nr, a.uts + (size_t)b * Nr,
+                                a.ute + (size_t)b * Nr};
+      n_live = build_live_key_blocks_direct<RAGGED, T_FULLY, WR>(bnd_rows, Nr, chunk, chunk_end, q0, r1, list, wave_cnt);
+    }
     if (n_live == 0) continue;
     // the entries of tiles t and t + 1 travel in scalar registers; the one that joins them at the next tile is
     // read from the list at the top of a tile and picked up behind the tile's barrier, so that no tile starts by
     // waiting for LDS
-    int entry = __builtin_amdgcn_readfirstlane(list[0]);
-    int next_entry = __builtin_amdgcn_readfirstlane(list[min(1, n_live - 1)]);
-    FM_LOAD_TILE(entry, 0);
+    int entry_s[S], next_entry_s[S];   // one per group of waves
+#pragma unroll
+    for (int s_ = 0; s_ < S; ++s_) {
+      entry_s[s_] = __builtin_amdgcn_readfirstlane(list[min(s_, n_live - 1)]);
+      next_entry_s[s_] = __builtin_amdgcn_readfirstlane(list[min(S + s_, n_live - 1)]);
+      if (S == 1 || s_ < n_live) FM_LOAD_TILE(entry_s[s_], 0, s_);
+    }
     async_wait<0>();
     barrier_nofence();
 
-    for (int t = 0; t < n_live; ++t) {
-      const int v_after = list[min(t + 2, n_live - 1)];
+    const int n_steps = (n_live + S - 1) / S;
+    for (int t = 0; t < n_steps; ++t) {
+      int v_after[S];
+#pragma unroll
+      for (int s_ = 0; s_ < S; ++s_) v_after[s_] = list[min(S * (t + 2) + s_, n_live - 1)];
       __builtin_amdgcn_sched_barrier(0);
-      if (t + 1 < n_live) FM_LOAD_TILE(next_entry, (t + 1) & 1);
+#pragma unroll
+      for (int s_ = 0; s_ < S; ++s_)
+        if (S * (t + 1) + s_ < n_live) FM_LOAD_TILE(next_entry_s[s_], (t + 1) & 1, s_);
 
-      const char* st = smem + C::STAGE_OFF + (t & 1) * C::STAGE;
+      const char* st = smem + C::STAGE_OFF + ((t & 1) * S + grp) * C::STAGE;
       const int* bnd = (const int*)(st + C::K_BYTES + C::V_BYTES);
 
-      const int wcls = entry_wave_class(entry, wave);   // Equation 4 on this wave's own rows
+      const int entry = S == 1 || grp == 0 ? entry_s[0] : entry_s[S - 1];
+      // Equation 4 on this wave's own rows; a group without a tile in the last step has nothing to do
+      const int wcls = S == 1 || S * t + grp < n_live ? entry_wave_class(entry, wrow) : T_FULLY;
       if (wcls != T_FULLY) {
         // Operand addresses: (stage address + lane part) XOR column offset, + constants.  The stage
         // address is a multiple of 256 bytes, so the sum keeps the lane part's low byte and the XOR
@@ -306,8 +331,11 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(FmBwdArgs a) {
 
       async_wait<0>();   // the next tile has landed ...
       barrier_nofence(); // ... for every wave, and every wave is done reading this one
-      entry = next_entry;
-      next_entry = __builtin_amdgcn_readfirstlane(v_after);
+#pragma unroll
+      for (int s_ = 0; s_ < S; ++s_) {
+        entry_s[s_] = next_entry_s[s_];
+        next_entry_s[s_] = __builtin_amdgcn_readfirstlane(v_after[s_]);
+      }
     }
     __syncthreads();     // the list is rebuilt by the next pass
   }
@@ -318,7 +346,30 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(FmBwdArgs a) {
   // every wave is past its last tile and nothing is in flight into the stages (the barrier that ends a
   // pass over the list): their first bytes serve as the waves' store staging
   using RSt = RowStage<D>;
-  static_assert(4 * RSt::BYTES <= 2 * C::STAGE, "store staging fits the stages");
+  static_assert(4 * RSt::BYTES <= 2 * S * C::STAGE, "store staging fits the stages");
+  if (S == 2) {
+    // the second group hands its sums to the first through LDS
+    static_assert(S == 1 || 4 * RSt::BYTES + WR * 64 * 16 * NDB * 4 <= 2 * S * C::STAGE, "exchange fits the stages");
+    float* const part = (float*)(smem + C::STAGE_OFF + 4 * RSt::BYTES) + wrow * (64 * 16 * NDB) + lane * 4;
+    if (grp == 1) {
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int rq = 0; rq < 4; ++rq)
+          *(f32x4*)(part + (db * 4 + rq) * 256) =
+              f32x4{dqacc[db][rq * 4], dqacc[db][rq * 4 + 1], dqacc[db][rq * 4 + 2], dqacc[db][rq * 4 + 3]};
+    }
+    barrier_nofence();
+    if (grp == 1) return;
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+      for (int rq = 0; rq < 4; ++rq) {
+        const f32x4 o = *(const f32x4*)(part + (db * 4 + rq) * 256);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dqacc[db][rq * 4 + e] += o[e];
+      }
+  }
   char* stage = smem + C::STAGE_OFF + wave * RSt::BYTES;
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
@@ -348,10 +399,12 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(FmBwdArgs a) {
 // with every LDS operand fetched a fixed number of steps ahead of its MFMA.
 // Scheduling fences pin that order.
 // ---------------------------------------------------------------------------
-template <int D>
+// S: groups of waves that share a unit's row tiles (1: queued units of 128 keys; 2: direct units of 64 keys, each tile
+// of the list belongs to one pair of waves)
+template <int D, int S = 1>
 struct DkdvCfg {
   static constexpr int QT = FM_DKDV_BR;    // query rows per step
-  static constexpr int BC = FM_DKDV_BC;    // keys per workgroup
+  static constexpr int BC = FM_DKDV_BC / S;   // keys per workgroup
   using L = TileLayout<D>;
   static constexpr int Q_BYTES = QT * L::RS;
   static constexpr int DO_BYTES = QT * L::RS;
@@ -361,7 +414,8 @@ struct DkdvCfg {
   static constexpr int CNT_OFF = LIST_CAP * 4;
   static constexpr int STAGE_OFF = CNT_OFF + 256;   // stages start at multiples of 256 bytes (dkdv_operand)
   // One workgroup per CU: a tile's math takes about a microsecond, less than a
-  // trip to L2/HBM, so tiles are copied three steps ahead into a ring of four.
+  // trip to L2/HBM, so tiles are copied three steps ahead into a ring of four.  S = 2 has the four stages as two
+  // pairs: a step's two tiles are copied while the step before them runs.
   static constexpr int NSTAGE = 4;
   static constexpr int LDS_BYTES = STAGE_OFF + NSTAGE * STAGE;
   // async copy instructions one wave issues per tile: COPIES for its quarter of Q and dO plus
@@ -416,15 +470,17 @@ __device__ __forceinline__ void dkdv_stage_a(const f32x16& s, const f32x16& dp, 
 }
 
 // What the tail of a tile's stream does for the tiles that follow it.
+template <int S>
 struct DkdvAhead {
   const char* nqs;        // LDS: stage of the next list entry (its Q tile; dO follows), for the operand prefetch
-  int v_copy;             // list entry (still in a vector register) of the tile NSTAGE - 1 ahead, to be copied
+  int v_copy[S];          // list entry (still in a vector register) of the tile NSTAGE - 1 ahead, to be copied
+                          // (S = 2: of the next step's two tiles)
   const char* q_base;     // global Q / dO of this (batch, head), already advanced to this wave's 16-row block
   const char* do_base;    // of a tile, and this lane's lse2 / D source
   const float* vec_src;
   int q_rs2, do_rs2;      // bytes between consecutive rows of Q / dO in global memory
   unsigned lds_ring;      // LDS address of stage 0
-  unsigned stage_copy;    // index of the stage that receives the copy
+  unsigned stage_copy;    // index of the stage that receives the (first) copy
   int n_real, lane;       // ragged sequences: rows the tensors really have, and this thread's lane
   CopyLanes<128> lanes;   // per-lane source offsets of the copy instructions of Q (the first D/32 entries are used)
   CopyLanes<128> lanes_do;   // ... and of dO
@@ -433,20 +489,20 @@ struct DkdvAhead {
 
 // Copy number K (of NC) of the tile whose 64-row base offsets are given.  RAGGED: a tile that
 // reaches past the last real row (i_copy is its index) clamps every lane's source row instead.
-template <int D, int K, bool RAGGED>
-__device__ __forceinline__ void dkdv_issue_copy(const DkdvAhead& ah, const char* q_src, const char* do_src,
+template <int D, int K, bool RAGGED, int S>
+__device__ __forceinline__ void dkdv_issue_copy(const DkdvAhead<S>& ah, const char* q_src, const char* do_src,
                                                 const float* vec_src, unsigned lds_stage, int i_copy) {
   using C = DkdvCfg<D>;
   constexpr int HALF = C::COPIES / 2;
   constexpr int WB = 16 * C::L::RS;   // bytes of a wave's 16-row block
   if (RAGGED && K < C::COPIES && (i_copy + 1) * C::QT > ah.n_real) {
-    constexpr int RPI = 64 / C::L::CPR, S = K % HALF;
-    const int row = ah.wave * 16 + S * RPI + ah.lane / C::L::CPR;
+    constexpr int RPI = 64 / C::L::CPR, I = K % HALF;
+    const int row = ah.wave * 16 + I * RPI + ah.lane / C::L::CPR;
     const int grow = min(i_copy * C::QT + row, ah.n_real - 1);
     const char* base = K < HALF ? ah.q_base : ah.do_base;
     const long long rel = (long long)(grow - ah.wave * 16) * (K < HALF ? ah.q_rs2 : ah.do_rs2);   // the bases are this wave's
     const char* src = base + rel + (((ah.lane % C::L::CPR) ^ C::L::swz(row)) << 4);
-    async_copy16(src, lds_stage + (K < HALF ? 0 : C::Q_BYTES) + ah.wave * WB + S * 1024);
+    async_copy16(src, lds_stage + (K < HALF ? 0 : C::Q_BYTES) + ah.wave * WB + I * 1024);
     return;
   }
   if (K < HALF) {
@@ -532,8 +588,12 @@ __device__ __forceinline__ void dkdv_sync() {
 // step, and its last RD operand fetches already read the next entry's tile, so
 // the MFMA pipe does not drain between tiles.  On entry `op` holds the operands
 // of steps 0..RD-1 of this tile, on exit those of the next one.
-template <int D, bool MASK, bool RAGGED>
-__device__ __forceinline__ void dkdv_tile(const char* qs, const float* vec_s, const DkdvAhead& ah,
+//
+// S = 2 (two stages per group of waves instead of four): the stage that the next step's tiles are copied into is the
+// previous step's, so the copies go out at the start of the stream, behind a barrier that every wave reaches with its
+// previous tile used up, and a second barrier, in front of the first operand fetch from the next tile, publishes them.
+template <int D, bool MASK, bool RAGGED, int S>
+__device__ __forceinline__ void dkdv_tile(const char* qs, const float* vec_s, const DkdvAhead<S>& ah,
                                           bf16x8 (&op)[DkdvCfg<D>::RD], const bf16x8 (&kreg)[D / 16],
                                           const bf16x8 (&vreg)[D / 16], f32x16 (&dkacc)[D / 32],
                                           f32x16 (&dvacc)[D / 32], int a_base, int t_base0, int t_base1, int r0,
@@ -544,8 +604,9 @@ __device__ __forceinline__ void dkdv_tile(const char* qs, const float* vec_s, co
   constexpr int EPS = 16 / NST;    // elements handled next to one MFMA (D = 128: 1, D = 64: 2)
   constexpr int NX = 4 * NST;      // MFMAs per tile
   constexpr int RD = C::RD;
-  constexpr int XS = NX - (C::NC > RD ? C::NC : RD);   // step of the workgroup sync; the copies follow one per step
-  static_assert(NX % RD == 0 && XS > 0, "ring layout");
+  constexpr int XS = S == 2 ? NX - RD : NX - (C::NC > RD ? C::NC : RD);   // step of the workgroup sync
+  constexpr int XC = S == 2 ? 0 : XS;                  // first of the steps that issue the copies, one each
+  static_assert(NX % RD == 0 && XS > 0 && (S == 1 || S * C::NC <= XS), "ring layout");
   const f32x16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
   const DkdvBases bs_cur = dkdv_bases(qs, a_base, t_base0, t_base1);
   const DkdvBases bs_next = dkdv_bases(ah.nqs, a_base, t_base0, t_base1);
@@ -598,17 +659,26 @@ __device__ __forceinline__ void dkdv_tile(const char* qs, const float* vec_s, co
         mfma32_acc(dvacc[db], op[x % RD], pa[qb][h], false);
       }
     }
-    // --- the workgroup step and the copies behind it
+    // --- the workgroup step(s) and the copies behind it
+    if (S == 2 && x == 0) barrier_reads_in_flight();   // the operands in flight are this tile's
     if (x == XS) {
-      dkdv_sync<D>();
-      i_copy = __builtin_amdgcn_readfirstlane(ah.v_copy) & 0xFFFFFF;
-      q_src = ah.q_base + (size_t)i_copy * C::QT * ah.q_rs2;
-      do_src = ah.do_base + (size_t)i_copy * C::QT * ah.do_rs2;
-      vec_src = ah.vec_src + i_copy * C::QT;
-      lds_stage = ah.lds_ring + ah.stage_copy * C::STAGE;
+      if (S == 2) {
+        async_wait<0>();
+        barrier_reads_in_flight();
+      } else {
+        dkdv_sync<D>();
+      }
     }
-    if (x >= XS && x < XS + C::NC) {
-      switch (x - XS) {
+    if (x >= XC && x < XC + S * C::NC) {
+      const int sub = (x - XC) / C::NC;
+      if ((x - XC) % C::NC == 0) {
+        i_copy = __builtin_amdgcn_readfirstlane(ah.v_copy[sub]) & 0xFFFFFF;
+        q_src = ah.q_base + (size_t)i_copy * C::QT * ah.q_rs2;
+        do_src = ah.do_base + (size_t)i_copy * C::QT * ah.do_rs2;
+        vec_src = ah.vec_src + i_copy * C::QT;
+        lds_stage = ah.lds_ring + (ah.stage_copy + sub) * C::STAGE;
+      }
+      switch ((x - XC) % C::NC) {
         case 0: dkdv_issue_copy<D, 0, RAGGED>(ah, q_src, do_src, vec_src, lds_stage, i_copy); break;
         case 1: dkdv_issue_copy<D, 1, RAGGED>(ah, q_src, do_src, vec_src, lds_stage, i_copy); break;
         case 2: dkdv_issue_copy<D, 2, RAGGED>(ah, q_src, do_src, vec_src, lds_stage, i_copy); break;
@@ -665,16 +735,23 @@ __device__ __forceinline__ void dkdv_tile(const char* qs, const float* vec_s, co
 // GEN: tensors with caller-given strides; a workgroup then owns 128 keys of one K/V head and
 // walks the query heads that share it one after the other (same list of live row blocks: the
 // mask does not depend on the head), accumulating dK and dV over all of them.
-template <int D, bool RAGGED, bool GEN>
-__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(FmBwdArgs a) {
-  using C = DkdvCfg<D>;
+template <int D, bool RAGGED, bool GEN, int S>
+__device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
+  using C = DkdvCfg<D, S>;
   constexpr int QT = C::QT, NDB = D / 32, NKK = D / 16;
   static_assert(QT == 64, "the tile loop is written for two 32-row blocks per tile");
   extern __shared__ __attribute__((aligned(256))) char smem[];   // dkdv_operand relies on the alignment
 
   // hand-off words of the unit queue: int 8 = slot of the first take, ints 12..15 = record of the next unit
   int* qwords = (int*)(smem + C::CNT_OFF);
-  i32x4 rec = queue_take(a.order_dkdv, a.slots_dkdv, qwords + 8);
+  i32x4 rec = {-1, 0, 0, 0};
+  if (S == 1) {
+    rec = queue_take(a.order_dkdv, a.slots_dkdv, qwords + 8);
+  } else {
+    const int blocks = (a.N + C::BC - 1) / C::BC;
+    rec[0] = direct_unit(a.B * (GEN ? a.Hk : a.H) * blocks, blocks);
+    rec[2] = (a.N + QT - 1) / QT;   // every row block may be live
+  }
   if (rec[0] < 0) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -682,7 +759,9 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(FmBwdArgs a)
   const int N = a.Np, H = a.H;            // padded length: what the loops and tables see
   const int Hk = GEN ? a.Hk : H, G = GEN ? H / Hk : 1;   // K/V heads, query heads per K/V head
   const int Nr = RAGGED ? a.N : a.Np;     // rows the tensors really have
-  const int t_r = N / QT, t_c = N / C::BC;
+  const int t_c = (Nr + C::BC - 1) / C::BC;
+  constexpr int WK = 4 / S;               // waves that share the unit's keys, 32 each
+  const int wkey = S == 1 ? wave : wave % WK, grp = S == 1 ? 0 : wave / WK;
   const int q_rs = row_stride<D, GEN>(a.sq), k_rs = row_stride<D, GEN>(a.sk), v_rs = row_stride<D, GEN>(a.sv);
   const int do_rs = row_stride<D, GEN>(a.sdo);
   int* list = (int*)smem;
@@ -699,7 +778,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(FmBwdArgs a)
   const CopyLanes<D>& copy_lanes_do = GEN ? copy_lanes_do_ : copy_lanes;
   const unsigned lds_ring = lds_address(smem + C::STAGE_OFF);
 
-  DkdvAhead ah;
+  DkdvAhead<S> ah;
   ah.q_rs2 = 2 * q_rs;
   ah.do_rs2 = 2 * do_rs;
   ah.lds_ring = lds_ring;
@@ -721,22 +800,24 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(FmBwdArgs a)
   // tiles that need only one of the two intervals made it spill inside the mask-free one).
   // Entries past the end of the list are clamped to the last one: the copies and operand
   // fetches made for them are never used, and every entry costs the same number of copies.
+  // S = 2: t counts steps of two tiles, of which this wave's group takes one.
 #define FM_TILE_LOOP(T0, T1, MASK)                                                                     \
   for (int t = (T0); t < (T1); ++t) {                                                                  \
-    const int v_next = list[min(t + 1, n_live - 1)];                                                   \
-    ah.v_copy = list[min(t + C::NSTAGE - 1, n_live - 1)];                                              \
-    ah.nqs = smem + C::STAGE_OFF + ((t + 1) % C::NSTAGE) * C::STAGE;                                   \
-    ah.stage_copy = (t + C::NSTAGE - 1) % C::NSTAGE;                                                   \
-    const char* st = smem + C::STAGE_OFF + (t % C::NSTAGE) * C::STAGE;                                 \
+    const int v_next = list[min(S * (t + 1) + grp, n_live - 1)];                                       \
+    constexpr int AHEAD = C::NSTAGE / S - 1;   /* steps between a tile and the one copied beside it */ \
+    _Pragma("unroll") for (int s_ = 0; s_ < S; ++s_) ah.v_copy[s_] = list[min(S * (t + AHEAD) + s_, n_live - 1)]; \
+    ah.nqs = smem + C::STAGE_OFF + ((S * (t + 1)) % C::NSTAGE + grp) * C::STAGE;                       \
+    ah.stage_copy = (S * (t + AHEAD)) % C::NSTAGE;                                                     \
+    const char* st = smem + C::STAGE_OFF + ((S * t) % C::NSTAGE + grp) * C::STAGE;                     \
     const int r0 = (e_cur & 0xFFFFFF) * QT;                                                            \
-    dkdv_tile<D, MASK, RAGGED>(st, (const float*)(st + C::Q_BYTES + C::DO_BYTES), ah, op, kreg, vreg, dkacc, dvacc, \
+    dkdv_tile<D, MASK, RAGGED, S>(st, (const float*)(st + C::Q_BYTES + C::DO_BYTES), ah, op, kreg, vreg, dkacc, dvacc, \
                          a_base, t_base0, t_base1, r0, g, sc, b_lts, len_lt, b_uts, len_ut);           \
     e_cur = __builtin_amdgcn_readfirstlane(v_next);                                                    \
   }
 
   // the first unit's min/max values (Section 4.2's table); the later units' arrive with their records
   MinMax8 gmm;
-  {
+  if (S == 1) {
     const int bh0 = rec[0] / t_c;
     gmm = load_minmax(a.minmax_dkdv + (size_t)(bh0 / Hk) * 8 * t_c, t_c, rec[0] - bh0 * t_c);
     // into scalar registers here, once: left in vector registers, every unit's list build would wait for
@@ -753,7 +834,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(FmBwdArgs a)
   const int unit = rec[0], i_lo = rec[1], i_hi = rec[2];
   const int bh = unit / t_c, j_blk = unit - bh * t_c, b = bh / Hk, hk = bh - b * Hk;   // bh counts K/V heads
   const int k0 = j_blk * C::BC;
-  const int kw0 = k0 + wave * 32;
+  const int kw0 = k0 + wkey * 32;
   const int key = kw0 + c;  // this lane's key column
   const int key_ld = RAGGED ? min(key, Nr - 1) : key;
 
@@ -777,6 +858,26 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(FmBwdArgs a)
   } else {
     b_lts = a.lts[bnd_row + key], b_lte = a.lte[bnd_row + key];
     b_uts = a.uts[bnd_row + key], b_ute = a.ute[bnd_row + key];
+  }
+
+  if (S == 2) {   // the unit's min/max values from its own keys' bounds: over the wave's 32 keys, then over the waves
+    const int own[4] = {b_lts, b_lte, b_uts, b_ute};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int mx = row16_max(own[e]), mn = row16_min(own[e]);
+      gmm.v[2 * e] = max(mx, __shfl_xor(mx, 16, 64));
+      gmm.v[2 * e + 1] = min(mn, __shfl_xor(mn, 16, 64));
+    }
+    if (lane == 0 && grp == 0) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) qwords[32 + 8 * wkey + e] = gmm.v[e];
+    }
+    barrier_nofence();
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int x = qwords[32 + e], y = qwords[40 + e];
+      gmm.v[e] = __builtin_amdgcn_readfirstlane(e & 1 ? min(x, y) : max(x, y));
+    }
   }
 
   f32x16 dkacc[NDB], dvacc[NDB];
@@ -805,9 +906,11 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(FmBwdArgs a)
     ah.q_base = (const char*)qp + (size_t)(wave * 16) * ah.q_rs2;
     ah.do_base = (const char*)dop + (size_t)(wave * 16) * ah.do_rs2;
     ah.vec_src = my_vec;
-    // prologue: copies of the first NSTAGE - 1 tiles, then the first tile's first operands
+    // prologue: copies of the first NSTAGE - 1 tiles (S = 2: of the first step's two), then the first tile's first
+    // operands
+    constexpr int FIRST = S == 2 ? 2 : C::NSTAGE - 1;
 #pragma unroll
-    for (int p = 0; p < C::NSTAGE - 1; ++p) {
+    for (int p = 0; p < FIRST; ++p) {
       const int i_p = __builtin_amdgcn_readfirstlane(list[min(p, n_live - 1)]) & 0xFFFFFF;
       char* st_ = smem + C::STAGE_OFF + p * C::STAGE;
       if (RAGGED && (i_p + 1) * QT > Nr) {
@@ -820,7 +923,7 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(FmBwdArgs a)
       async_copy16_lanes8(my_vec + i_p * QT, lds_address(st_ + C::Q_BYTES + C::DO_BYTES) + wave * 128);
     }
     // the next unit's ticket and record, while these copies are in flight
-    if (!drawn) {
+    if (S == 1 && !drawn) {
       if (tid == 0) queue_prefetch_key_block(a.order_dkdv, a.slots_dkdv, qwords + 12, a.minmax_dkdv, t_c, Hk);
       drawn = true;
     }
@@ -840,20 +943,27 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(FmBwdArgs a)
     // (any int32 bounds: the difference is formed in unsigned arithmetic, it may not fit an int)
     const unsigned len_lt = b_lte > b_lts ? (unsigned)b_lte - (unsigned)b_lts : 0u;
     const unsigned len_ut = b_ute > b_uts ? (unsigned)b_ute - (unsigned)b_uts : 0u;
-    async_wait<(C::NSTAGE - 2) * C::NC>();
+    async_wait<S == 2 ? 0 : (C::NSTAGE - 2) * C::NC>();
     barrier_nofence();
-    int e_cur = __builtin_amdgcn_readfirstlane(list[0]);
+    int e_cur = __builtin_amdgcn_readfirstlane(list[min(grp, n_live - 1)]);
 #pragma unroll
     for (int x = 0; x < C::RD; ++x)
-      op[x] = dkdv_operand<D>(dkdv_bases(smem + C::STAGE_OFF, a_base, t_base0, t_base1), x);
-    FM_TILE_LOOP(0, n_plain, false)
-    FM_TILE_LOOP(n_plain, n_live, true)
+      op[x] = dkdv_operand<D>(dkdv_bases(smem + C::STAGE_OFF + grp * C::STAGE, a_base, t_base0, t_base1), x);
+    // this group's tiles: entries grp, grp + S, ... (the clamp is for a group without any)
+    const int own_plain = (max(n_plain - grp, 0) + S - 1) / S, own_live = (max(n_live - grp, 0) + S - 1) / S;
+    FM_TILE_LOOP(0, own_plain, false)
+    FM_TILE_LOOP(own_plain, own_live, true)
+    if (S == 2 && own_live < (n_live + S - 1) / S) {   // the last step has no tile for this group: its barriers
+      barrier_reads_in_flight();
+      async_wait<0>();
+      barrier_reads_in_flight();
+    }
     mfma_acc_drain();  // dkacc / dvacc are read by ordinary code after the loops over heads and chunks
     async_wait<0>();   // the copies made for entries past the end must not outlive the list / the workgroup
     __syncthreads();   // the ring is refilled by the next head, the list rebuilt by the next chunk
     }  // query heads
   }
-  if (!drawn) {   // a unit without a live tile: nothing was in flight to hide the draw behind
+  if (S == 1 && !drawn) {   // a unit without a live tile: nothing was in flight to hide the draw behind
     if (tid == 0) queue_prefetch_key_block(a.order_dkdv, a.slots_dkdv, qwords + 12, a.minmax_dkdv, t_c, Hk);
   }
 
@@ -863,7 +973,41 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(FmBwdArgs a)
   __bf16* dkp = (__bf16*)slice_ptr<D, GEN>(a.dk, a.sdk, b, hk, Hk, Nr);
   __bf16* dvp_out = (__bf16*)slice_ptr<D, GEN>(a.dv, a.sdv, b, hk, Hk, Nr);
   const int dk_rs = row_stride<D, GEN>(a.sdk), dv_rs = row_stride<D, GEN>(a.sdv);
-  {
+  if constexpr (S == 2) {
+    // The two groups' sums of the same keys meet in LDS: the first group finishes dK, the second dV.
+    using RSt = RowStage<D>;
+    static_assert(4 * RSt::BYTES + 4 * 64 * 16 * NDB * 4 <= C::NSTAGE * C::STAGE, "exchange fits the ring");
+    char* stage = smem + C::STAGE_OFF + wave * RSt::BYTES;
+    float* const exchange = (float*)(smem + C::STAGE_OFF + 4 * RSt::BYTES) + lane * 4;
+    constexpr int PER_WAVE = 64 * 16 * NDB;
+    auto give = [&](const f32x16(&acc)[NDB]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *(f32x4*)(exchange + wave * PER_WAVE + (db * 4 + q) * 256) =
+              f32x4{acc[db][4 * q], acc[db][4 * q + 1], acc[db][4 * q + 2], acc[db][4 * q + 3]};
+    };
+    auto finish = [&](const f32x16(&acc)[NDB], float factor, __bf16* rows, int rs) __attribute__((always_inline)) {
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x4 o = *(const f32x4*)(exchange + (wave ^ WK) * PER_WAVE + (db * 4 + q) * 256);
+          bf16x4 x4;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x4[e] = (__bf16)((acc[db][4 * q + e] + o[e]) * factor);
+          RSt::put(stage, c, g, db, q, x4);
+        }
+      RSt::flush(stage, rows + (size_t)kw0 * rs, rs, lane, RAGGED ? min(32, Nr - kw0) : 32);
+    };
+    if (grp == 0) give(dvacc);
+    else give(dkacc);
+    barrier_nofence();
+    if (grp == 0) finish(dkacc, a.scale, dkp, dk_rs);
+    else finish(dvacc, 1.f, dvp_out, dv_rs);
+    return;   // one unit per workgroup
+  } else {
     using RSt = RowStage<D>;
     static_assert(8 * RSt::BYTES <= C::NSTAGE * C::STAGE, "store staging fits the ring");
     char* stage_k = smem + C::STAGE_OFF + (2 * wave) * RSt::BYTES;
@@ -895,17 +1039,42 @@ __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(FmBwdArgs a)
 #undef FM_TILE_LOOP
 }
 
+template <int D, bool RAGGED, bool GEN>
+__global__ __launch_bounds__(256, 2) void dq_kernel(FmBwdArgs a) {
+  dq_body<D, RAGGED, GEN, 1>(a);
+}
+template <int D, bool RAGGED, bool GEN>
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(FmBwdArgs a) {
+  dkdv_body<D, RAGGED, GEN, 1>(a);
+}
+// direct units: LDS for two tiles per step leaves one workgroup per compute unit at d = 128, two at d = 64
+template <int D, bool RAGGED, bool GEN>
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void direct_dq_kernel(FmBwdArgs a) {
+  dq_body<D, RAGGED, GEN, 2>(a);
+}
+template <int D, bool RAGGED, bool GEN>
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void direct_dkdv_kernel(FmBwdArgs a) {
+  dkdv_body<D, RAGGED, GEN, 2>(a);
+}
+
 }  // namespace fm
 
 using namespace fm;
 
+template <int D, bool RAGGED, bool GEN, int S>
+static hipError_t launch_dq_s(const FmBwdArgs& a, hipStream_t stream) {
+  using C = DqCfg<D, S>;
+  constexpr auto kernel = S == 1 ? dq_kernel<D, RAGGED, GEN> : direct_dq_kernel<D, RAGGED, GEN>;
+  static bool allowed[FM_MAX_DEVICES] = {};
+  if (hipError_t e = fm_allow_lds((const void*)kernel, C::LDS_BYTES, allowed); e != hipSuccess) return e;
+  const int grid = S == 1 ? fm_launch_grid(a.slots_dq) : fm_direct_grid(a.B * a.H * ((a.N + C::BR - 1) / C::BR));
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), C::LDS_BYTES, stream, a);
+  return hipGetLastError();
+}
+
 template <int D, bool RAGGED, bool GEN>
 static hipError_t launch_dq_t(const FmBwdArgs& a, hipStream_t stream) {
-  using C = DqCfg<D>;
-  static bool allowed[FM_MAX_DEVICES] = {};
-  if (hipError_t e = fm_allow_lds((const void*)dq_kernel<D, RAGGED, GEN>, C::LDS_BYTES, allowed); e != hipSuccess) return e;
-  hipLaunchKernelGGL((dq_kernel<D, RAGGED, GEN>), dim3(fm_launch_grid(a.slots_dq)), dim3(256), C::LDS_BYTES, stream, a);
-  return hipGetLastError();
+  return a.direct_dq ? launch_dq_s<D, RAGGED, GEN, 2>(a, stream) : launch_dq_s<D, RAGGED, GEN, 1>(a, stream);
 }
 
 template <int D>
@@ -919,15 +1088,22 @@ hipError_t fm_launch_bwd_dq(const FmBwdArgs& a, hipStream_t stream) {
   return a.d == 128 ? launch_dq_d<128>(a, stream) : launch_dq_d<64>(a, stream);
 }
 
+template <int D, bool RAGGED, bool GEN, int S>
+static hipError_t launch_dkdv_s(const FmBwdArgs& a, hipStream_t stream) {
+  using C = DkdvCfg<D, S>;
+  constexpr auto kernel = S == 1 ? dkdv_kernel<D, RAGGED, GEN> : direct_dkdv_kernel<D, RAGGED, GEN>;
+  static bool allowed[FM_MAX_DEVICES] = {};
+  if (hipError_t e = fm_allow_lds((const void*)kernel, C::LDS_BYTES, allowed); e != hipSuccess) return e;
+  // queued units: persistent, as many workgroups as the chip holds at once (one per CU at d = 128, two at d = 64)
+  const int grid = S == 1 ? fm_persistent_grid(a.slots_dkdv, D == 64 ? 2 : 1)
+                          : fm_direct_grid(a.B * (GEN ? a.Hk : a.H) * ((a.N + C::BC - 1) / C::BC));
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), C::LDS_BYTES, stream, a);
+  return hipGetLastError();
+}
+
 template <int D, bool RAGGED, bool GEN>
 static hipError_t launch_dkdv_t(const FmBwdArgs& a, hipStream_t stream) {
-  using C = DkdvCfg<D>;
-  static bool allowed[FM_MAX_DEVICES] = {};
-  if (hipError_t e = fm_allow_lds((const void*)dkdv_kernel<D, RAGGED, GEN>, C::LDS_BYTES, allowed); e != hipSuccess) return e;
-  // persistent: as many workgroups as the chip holds at once (one per CU at d = 128, two at d = 64)
-  const int grid = fm_persistent_grid(a.slots_dkdv, D == 64 ? 2 : 1);
-  hipLaunchKernelGGL((dkdv_kernel<D, RAGGED, GEN>), dim3(grid), dim3(256), C::LDS_BYTES, stream, a);
-  return hipGetLastError();
+  return a.direct_dkdv ? launch_dkdv_s<D, RAGGED, GEN, 2>(a, stream) : launch_dkdv_s<D, RAGGED, GEN, 1>(a, stream);
 }
 
 template <int D>

@@ -234,7 +234,7 @@ __device__ __forceinline__ void fwd_step(f32x16 (&cur)[2], f32x16 (&nxt)[2], f32
 // computed but not stored.
 // GEN: tensors with caller-given strides and fewer K/V heads than query heads (see FmFwdArgs).
 template <int D, bool RAGGED, bool GEN, int S>
-__global__ __launch_bounds__(256, S == 2 ? (D == 64 ? 2 : 1) : D == 64 ? 3 : 2) void fwd_kernel(FmFwdArgs a) {
+__device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
   using C = FwdCfg<D, S>;
   constexpr int KT = C::KT, NKB = KT / 32, NDB = D / 32, NKK = D / 16;
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -480,6 +480,16 @@ __global__ __launch_bounds__(256, S == 2 ? (D == 64 ? 2 : 1) : D == 64 ? 3 : 2) 
   }
 }
 
+template <int D, bool RAGGED, bool GEN>
+__global__ __launch_bounds__(256, D == 64 ? 3 : 2) void fwd_kernel(FmFwdArgs a) {
+  fwd_body<D, RAGGED, GEN, 1>(a);
+}
+// direct units: LDS for two tiles per step leaves one workgroup per compute unit at d = 128, two at d = 64
+template <int D, bool RAGGED, bool GEN>
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void direct_fwd_kernel(FmFwdArgs a) {
+  fwd_body<D, RAGGED, GEN, 2>(a);
+}
+
 }  // namespace fm
 
 using namespace fm;
@@ -487,10 +497,11 @@ using namespace fm;
 template <int D, bool RAGGED, bool GEN, int S>
 static hipError_t launch_fwd_s(const FmFwdArgs& a, hipStream_t stream) {
   using C = FwdCfg<D, S>;
+  constexpr auto kernel = S == 1 ? fwd_kernel<D, RAGGED, GEN> : direct_fwd_kernel<D, RAGGED, GEN>;
   static bool allowed[FM_MAX_DEVICES] = {};
-  if (hipError_t e = fm_allow_lds((const void*)fwd_kernel<D, RAGGED, GEN, S>, C::LDS_BYTES, allowed); e != hipSuccess) return e;
+  if (hipError_t e = fm_allow_lds((const void*)kernel, C::LDS_BYTES, allowed); e != hipSuccess) return e;
   const int grid = S == 1 ? fm_launch_grid(a.slots) : fm_direct_grid(a.B * a.H * ((a.N + C::BR - 1) / C::BR));
-  hipLaunchKernelGGL((fwd_kernel<D, RAGGED, GEN, S>), dim3(grid), dim3(256), C::LDS_BYTES, stream, a);
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), C::LDS_BYTES, stream, a);
   return hipGetLastError();
 }
 
