@@ -214,10 +214,10 @@ static int fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
   mark(1, stream);
   a.q = q; a.k = k; a.v = v;
   a.lts = lts; a.lte = lte; a.uts = uts; a.ute = ute;
-  a.minmax = minmax; a.order = order;
+  a.minmax = minmax;
   a.out = out; a.lse = lse; a.scale = scale;
   a.B = B; a.H = H; a.N = N; a.Np = Np; a.d = d;
-  a.slots = fm_order_slots(B * H * (Np / FM_FWD_BR));
+  a.queue = fm_queue(order, B * Hk, H / Hk * (Np / FM_FWD_BR));
   a.general = st != nullptr;
   a.Hk = Hk;
   if (st) { a.sq = st[0]; a.sk = st[1]; a.sv = st[2]; a.so = st[3]; }
@@ -320,14 +320,14 @@ static int bwd_impl(const void* q, const void* k, const void* v, const void* out
   FmBwdArgs a;
   a.q = q; a.k = k; a.v = v; a.out = out; a.dout = dout; a.lse = lse;
   a.lts = lts; a.lte = lte; a.uts = uts; a.ute = ute;
-  a.minmax_dq = (int*)(ws + sq.minmax); a.order_dq = (int*)(ws + sq.order);
-  a.minmax_dkdv = (int*)(ws + skv.minmax); a.order_dkdv = (int*)(ws + skv.order);
+  a.minmax_dq = (int*)(ws + sq.minmax);
+  a.minmax_dkdv = (int*)(ws + skv.minmax);
   a.dvec = (float*)(ws + skv.total);
   a.lse2 = (float*)(ws + skv.total + align_up((size_t)B * H * Np * 4, 256));
   a.dq = dq; a.dk = dk; a.dv = dv; a.scale = scale;
   a.B = B; a.H = H; a.N = N; a.Np = Np; a.d = d;
-  a.slots_dq = fm_order_slots(B * H * (Np / FM_DQ_BR));
-  a.slots_dkdv = fm_order_slots(B * Hk * (Np / FM_DKDV_BC));   // a dK/dV unit is (batch row, K/V head, key block)
+  a.queue_dq = fm_queue((int*)(ws + sq.order), B * Hk, H / Hk * (Np / FM_DQ_BR));
+  a.queue_dkdv = fm_queue((int*)(ws + skv.order), B * Hk, Np / FM_DKDV_BC);   // a dK/dV unit is (batch row, K/V head, key block)
   a.general = st != nullptr;
   a.Hk = Hk;
   if (st) {

@@ -46,7 +46,7 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
   extern __shared__ __attribute__((aligned(256))) char smem[];   // the operand reads rely on the alignment
 
   i32x4 rec = {-1, 0, 0, 0};
-  if (S == 1) rec = queue_take(a.order_dq, a.slots_dq, (int*)(smem + C::CNT_OFF) + 8);
+  if (S == 1) rec = queue_take(a.queue_dq, (int*)(smem + C::CNT_OFF) + 8);
   else rec[0] = direct_unit(a.B * a.H * ((a.N + C::BR - 1) / C::BR), (a.N + C::BR - 1) / C::BR);
   const int unit = rec[0];
   if (unit < 0) return;
@@ -425,6 +425,11 @@ struct DkdvCfg {
   static constexpr int NC = COPIES + 1;
   // MFMA operand fetch distance in steps; divides the steps per tile, so ring slots line up across tiles
   static constexpr int RD = 8;
+  // One workgroup per CU: nothing else hides the start of a unit, so workgroups go on from unit to unit and fetch the
+  // next record early (d = 128, two rows of 8192 tokens in 11 documents: whole step 2 % faster than a workgroup per
+  // unit).  With two on a CU the early draws of all workgroups only meet on the queue counters: a workgroup per unit
+  // is faster from 1024 units of 3 to 8 tiles (65.9 -> 42.9 us) to 4096 units of 64 (557 -> 549 us).
+  static constexpr bool PERSISTENT = D == 128;
 };
 
 // lse / D slice of a tile in LDS: wave w copies rows 16w..16w+15 as 128 contiguous bytes,
@@ -746,7 +751,7 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
   int* qwords = (int*)(smem + C::CNT_OFF);
   i32x4 rec = {-1, 0, 0, 0};
   if (S == 1) {
-    rec = queue_take(a.order_dkdv, a.slots_dkdv, qwords + 8);
+    rec = queue_take(a.queue_dkdv, qwords + 8);
   } else {
     const int blocks = (a.N + C::BC - 1) / C::BC;
     rec[0] = direct_unit(a.B * (GEN ? a.Hk : a.H) * blocks, blocks);
@@ -827,6 +832,7 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
     for (int e = 0; e < 8; ++e) gmm.v[e] = __builtin_amdgcn_readfirstlane(gmm.v[e]);
   }
 
+  const bool one_round = !C::PERSISTENT || a.queue_dkdv.first == a.queue_dkdv.tickets;   // a workgroup per unit
   // A workgroup works units off until the queues are empty: the launch holds as many workgroups as the
   // chip runs at once, and the next unit's ticket, record and min/max values are fetched while the first
   // tile copies of the current unit are in flight.
@@ -888,7 +894,7 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
       dkacc[db][r] = 0.f;
       dvacc[db][r] = 0.f;
     }
-  bool drawn = false;   // the next unit's ticket has been drawn (uniform over the workgroup)
+  bool drawn = one_round;   // the next unit's ticket has been drawn (uniform over the workgroup), or there is none
 
   // only the row blocks [i_lo, i_hi) can be live for this key block (found by the work pre-pass)
   for (int chunk = i_lo; chunk < i_hi; chunk += C::LIST_CAP) {
@@ -924,7 +930,7 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
     }
     // the next unit's ticket and record, while these copies are in flight
     if (S == 1 && !drawn) {
-      if (tid == 0) queue_prefetch_key_block(a.order_dkdv, a.slots_dkdv, qwords + 12, a.minmax_dkdv, t_c, Hk);
+      if (wave == 0) queue_prefetch_key_block(a.queue_dkdv, qwords + 12, a.minmax_dkdv, t_c, Hk);
       drawn = true;
     }
     // The fragment and bound loads must be complete, and known complete to the compiler, before
@@ -964,7 +970,7 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
     }  // query heads
   }
   if (S == 1 && !drawn) {   // a unit without a live tile: nothing was in flight to hide the draw behind
-    if (tid == 0) queue_prefetch_key_block(a.order_dkdv, a.slots_dkdv, qwords + 12, a.minmax_dkdv, t_c, Hk);
+    if (wave == 0) queue_prefetch_key_block(a.queue_dkdv, qwords + 12, a.minmax_dkdv, t_c, Hk);
   }
 
   // accumulators (dK^T, dV^T): register r of block db holds [d = db*32 + 8*(r/4) + 4*g + r%4][key kw0 + c].
@@ -1029,6 +1035,7 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
     RSt::flush(stage_k, dkp + (size_t)kw0 * dk_rs, dk_rs, lane, n_rows);
     RSt::flush(stage_v, dvp_out + (size_t)kw0 * dv_rs, dv_rs, lane, n_rows);
   }
+  if (one_round) break;
   __syncthreads();                       // the next record is in LDS (written before the tile loops, or just above)
   rec = queue_next_record(qwords + 12);
   if (rec[0] < 0) break;
@@ -1067,8 +1074,10 @@ static hipError_t launch_dq_s(const FmBwdArgs& a, hipStream_t stream) {
   constexpr auto kernel = S == 1 ? dq_kernel<D, RAGGED, GEN> : direct_dq_kernel<D, RAGGED, GEN>;
   static bool allowed[FM_MAX_DEVICES] = {};
   if (hipError_t e = fm_allow_lds((const void*)kernel, C::LDS_BYTES, allowed); e != hipSuccess) return e;
-  const int grid = S == 1 ? fm_launch_grid(a.slots_dq) : fm_direct_grid(a.B * a.H * ((a.N + C::BR - 1) / C::BR));
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), C::LDS_BYTES, stream, a);
+  FmBwdArgs args = a;
+  args.queue_dq = fm_queue_for_launch(a.queue_dq, 2);
+  const int grid = S == 1 ? fm_launch_grid(args.queue_dq) : fm_direct_grid(a.B * a.H * ((a.N + C::BR - 1) / C::BR));
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), C::LDS_BYTES, stream, args);
   return hipGetLastError();
 }
 
@@ -1095,9 +1104,11 @@ static hipError_t launch_dkdv_s(const FmBwdArgs& a, hipStream_t stream) {
   static bool allowed[FM_MAX_DEVICES] = {};
   if (hipError_t e = fm_allow_lds((const void*)kernel, C::LDS_BYTES, allowed); e != hipSuccess) return e;
   // queued units: persistent, as many workgroups as the chip holds at once (one per CU at d = 128, two at d = 64)
-  const int grid = S == 1 ? fm_persistent_grid(a.slots_dkdv, D == 64 ? 2 : 1)
+  FmBwdArgs args = a;
+  args.queue_dkdv = fm_queue_for_launch(a.queue_dkdv, D == 64 ? 2 : 1);
+  const int grid = S == 1 ? (C::PERSISTENT ? fm_persistent_grid(args.queue_dkdv) : fm_launch_grid(args.queue_dkdv))
                           : fm_direct_grid(a.B * (GEN ? a.Hk : a.H) * ((a.N + C::BC - 1) / C::BC));
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), C::LDS_BYTES, stream, a);
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), C::LDS_BYTES, stream, args);
   return hipGetLastError();
 }
 

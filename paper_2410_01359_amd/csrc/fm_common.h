@@ -354,67 +354,87 @@ __device__ __forceinline__ int opaque(int x) {
   return x;
 }
 
-// Unit queues.  Workgroup x draws a ticket from queue x % FM_QUEUES (ticket t of queue g is slot
-// t * FM_QUEUES + g of the slot records); when that queue is used up it draws from the queue that
-// has most left, and when all are used up it gets nothing.  Returns the slot record, wave-uniform,
-// with unit = -1 for "nothing".  One barrier; lds_word is a scratch word in LDS.  The counters sit
-// behind the slot records and are zeroed by the queue-building kernel of every call.
-// The slot drawn by the calling thread (one thread per workgroup calls this), -1 for "nothing left".
-__device__ __forceinline__ int queue_draw(int* order, int slots) {
-  int* counters = order + 4 * (size_t)slots;
-  const int per_queue = slots / FM_QUEUES;
-  int q = blockIdx.x % FM_QUEUES;
-  int t = atomicAdd(counters + q, 1);
-  for (int attempt = 0; t >= per_queue && attempt < FM_QUEUES; ++attempt) {
-    int best = -1, best_left = 0;
-    for (int g = 0; g < FM_QUEUES; ++g) {
-      const int left = per_queue - __hip_atomic_load(counters + g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (left > best_left) {
-        best_left = left;
-        best = g;
-      }
-    }
-    if (best < 0) break;
-    q = best;
-    t = atomicAdd(counters + q, 1);
-  }
-  return t < per_queue ? t * FM_QUEUES + q : -1;
+// x combined with the value CTRL (a DPP row rotation) brings from another lane of the same 16.
+template <int CTRL>
+__device__ __forceinline__ int dpp_max(int x) {
+  return max(x, __builtin_amdgcn_update_dpp(x, x, CTRL, 0xf, 0xf, false));
 }
-__device__ __forceinline__ i32x4 queue_take(int* order, int slots, int* lds_word) {
-  if (threadIdx.x == 0) *lds_word = queue_draw(order, slots);
-  __syncthreads();
-  const int slot = __builtin_amdgcn_readfirstlane(*lds_word);
+template <int CTRL>
+__device__ __forceinline__ int dpp_min(int x) {
+  return min(x, __builtin_amdgcn_update_dpp(x, x, CTRL, 0xf, 0xf, false));
+}
+// max / min over the 16 lanes of a DPP row, left in all of them
+__device__ __forceinline__ int row16_max(int x) { return dpp_max<0x121>(dpp_max<0x122>(dpp_max<0x124>(dpp_max<0x128>(x)))); }
+__device__ __forceinline__ int row16_min(int x) { return dpp_min<0x121>(dpp_min<0x122>(dpp_min<0x124>(dpp_min<0x128>(x)))); }
+
+// Unit queues.  Workgroup x works on queue x % FM_QUEUES (ticket t of queue g is slot t * FM_QUEUES + g of the slot
+// records).  The first `first` workgroups of a launch -- as many as the chip holds at once, fm_first_tickets -- have
+// their ticket in their number: slot x.  Later ones, and a persistent workgroup's later units, draw from the queue's
+// counter; when that queue is used up, from the queue that has most left, and when all are used up they get nothing.
+// The counters sit behind the slot records and are zeroed by the queue-building kernel of every call.
+// The slot drawn by the calling wave (all its lanes call this), -1 for "nothing left".  Lanes 0..7 read the eight
+// counters together: read one after the other by one thread, an empty queue cost its workgroup eight round trips
+// per attempt, and in launches of few rounds those were the longest chain of all.  (Before this scan, the given first
+// tickets and the exact ticket count -- after them, one-round launches do not draw at all: N = 512, 64 slices, d = 64,
+// 512 units of 3 to 8 tiles: forward 28.7 -> 20.5 us, dQ 28.0 -> 23.0, dK/dV 59.8 -> 24.2.)
+__device__ __forceinline__ int queue_draw(const FmQueue& queue) {
+  int* counters = queue.order + 4 * (size_t)queue.slots;
+  // tickets of a queue that have a workgroup from the start, and that are drawn
+  const int given = queue.first / FM_QUEUES, per_queue = queue.tickets / FM_QUEUES - given;
+  const int lane = threadIdx.x & 63;
+  int q = blockIdx.x % FM_QUEUES, t = 0;
+  if (lane == 0) t = atomicAdd(counters + q, 1);
+  t = __builtin_amdgcn_readfirstlane(t);
+  for (int attempt = 0; t >= per_queue && attempt < FM_QUEUES; ++attempt) {
+    int fullest = -1;
+    if (lane < FM_QUEUES) {
+      const int left = per_queue - __hip_atomic_load(counters + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (left > 0) fullest = left * FM_QUEUES + lane;
+    }
+    fullest = __builtin_amdgcn_readfirstlane(row16_max(fullest));
+    if (fullest < 0) break;
+    q = fullest % FM_QUEUES;
+    if (lane == 0) t = atomicAdd(counters + q, 1);
+    t = __builtin_amdgcn_readfirstlane(t);
+  }
+  return t < per_queue ? (given + t) * FM_QUEUES + q : -1;
+}
+// The slot record of the workgroup's first unit, wave-uniform, with unit = -1 for "nothing".  lds_word is a scratch
+// word in LDS.
+__device__ __forceinline__ i32x4 queue_take(const FmQueue& queue, int* lds_word) {
+  int slot = blockIdx.x;
+  if (slot >= queue.first) {
+    if (threadIdx.x < 64) {
+      const int s = queue_draw(queue);
+      if (threadIdx.x == 0) *lds_word = s;
+    }
+    __syncthreads();
+    slot = __builtin_amdgcn_readfirstlane(*lds_word);
+  }
   i32x4 rec = {-1, 0, 0, 0};
   if (slot >= 0) {
-    const i32x4 r = *(const i32x4*)(order + 4 * (size_t)slot);
+    const i32x4 r = *(const i32x4*)(queue.order + 4 * (size_t)slot);
 #pragma unroll
     for (int e = 0; e < 4; ++e) rec[e] = __builtin_amdgcn_readfirstlane(r[e]);
   }
   return rec;
 }
 // A workgroup that goes on to another unit after this one draws that unit's ticket ahead of time: one
-// thread calls this while the tile copies of the current unit are in flight (the atomic and the record
-// load that depends on it then cost nothing), and every thread picks the record up with
-// queue_next_record() after a barrier at the end of the unit.  lds_rec: four words of LDS.
-__device__ __forceinline__ void queue_prefetch(int* order, int slots, int* lds_rec) {
-  const int slot = queue_draw(order, slots);
-  i32x4 r = {-1, 0, 0, 0};
-  if (slot >= 0) r = *(const i32x4*)(order + 4 * (size_t)slot);
-  *(i32x4*)lds_rec = r;
-}
-// The same for a pass whose units are key blocks: the unit's eight min/max values (Section 4.2's table,
-// row stride t_c, `kv_heads` units per batch row and key block) go into lds_rec[4..11] as well.
-__device__ __forceinline__ void queue_prefetch_key_block(int* order, int slots, int* lds_rec, const int* table, int t_c,
+// wave calls this while the tile copies of the current unit are in flight (the atomic and the loads
+// that depend on it then cost nothing), and every thread picks the record up with
+// queue_next_record() after a barrier at the end of the unit.  lds_rec: four words of LDS for the record, then
+// eight for the unit's min/max values (Section 4.2's table, row stride t_c, `kv_heads` units per batch row and
+// key block).
+__device__ __forceinline__ void queue_prefetch_key_block(const FmQueue& queue, int* lds_rec, const int* table, int t_c,
                                                          int kv_heads) {
-  const int slot = queue_draw(order, slots);
+  const int slot = queue_draw(queue), lane = threadIdx.x & 63;
   i32x4 r = {-1, 0, 0, 0};
-  if (slot >= 0) r = *(const i32x4*)(order + 4 * (size_t)slot);
-  *(i32x4*)lds_rec = r;
-  if (r[0] >= 0) {
-    const int bh = r[0] / t_c, j = r[0] - bh * t_c, b = bh / kv_heads;
-    const MinMax8 mm = load_minmax(table + (size_t)b * 8 * t_c, t_c, j);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) lds_rec[4 + e] = mm.v[e];
+  if (slot >= 0) r = *(const i32x4*)(queue.order + 4 * (size_t)slot);
+  const int unit = __builtin_amdgcn_readfirstlane(r[0]);
+  if (lane == 0) *(i32x4*)lds_rec = r;
+  if (unit >= 0) {
+    const int bh = unit / t_c, j = unit - bh * t_c, b = bh / kv_heads;
+    if (lane < 8) lds_rec[4 + lane] = table[(size_t)b * 8 * t_c + (size_t)lane * t_c + j];
   }
 }
 __device__ __forceinline__ i32x4 queue_next_record(const int* lds_rec) {
@@ -517,19 +537,6 @@ __device__ __forceinline__ int direct_unit(int units, int blocks) {
   const int slice = p / blocks, i = p - slice * blocks;
   return slice * blocks + blocks - 1 - i;
 }
-// x combined with the value CTRL (a DPP row rotation) brings from another lane of the same 16.
-template <int CTRL>
-__device__ __forceinline__ int dpp_max(int x) {
-  return max(x, __builtin_amdgcn_update_dpp(x, x, CTRL, 0xf, 0xf, false));
-}
-template <int CTRL>
-__device__ __forceinline__ int dpp_min(int x) {
-  return min(x, __builtin_amdgcn_update_dpp(x, x, CTRL, 0xf, 0xf, false));
-}
-// max / min over the 16 lanes of a DPP row, left in all of them
-__device__ __forceinline__ int row16_max(int x) { return dpp_max<0x121>(dpp_max<0x122>(dpp_max<0x124>(dpp_max<0x128>(x)))); }
-__device__ __forceinline__ int row16_min(int x) { return dpp_min<0x121>(dpp_min<0x122>(dpp_min<0x124>(dpp_min<0x128>(x)))); }
-
 // build_live_key_blocks for key blocks of 64 columns straight from the bound vectors (vec: a batch row's LTS, LTE,
 // UTS, UTE; n columns).  Sixteen lanes take a block, four columns each, so a pass of the workgroup covers 1024
 // columns; PASSES passes have their loads in flight together.  The raw entries go to list[] in place (-1: fully

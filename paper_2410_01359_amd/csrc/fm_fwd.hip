@@ -42,6 +42,7 @@ struct FwdCfg {
   static constexpr int K_OFF = CNT_OFF + 64;
   static constexpr int V_OFF = K_OFF + 2 * S * K_BYTES;   // two stages of S tiles each
   static constexpr int LDS_BYTES = V_OFF + 2 * S * VSTAGE;
+  static constexpr int PER_CU = D == 64 ? 3 : 2;          // workgroups of queued units on a compute unit
 };
 
 // Per-wave constants of the tile loop.
@@ -240,7 +241,7 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
   i32x4 rec = {-1, 0, 0, 0};
-  if (S == 1) rec = queue_take(a.order, a.slots, (int*)(smem + C::CNT_OFF) + 8);
+  if (S == 1) rec = queue_take(a.queue, (int*)(smem + C::CNT_OFF) + 8);
   else rec[0] = direct_unit(a.B * a.H * ((a.N + C::BR - 1) / C::BR), (a.N + C::BR - 1) / C::BR);
   const int unit = rec[0];
   if (unit < 0) return;
@@ -481,7 +482,7 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
 }
 
 template <int D, bool RAGGED, bool GEN>
-__global__ __launch_bounds__(256, D == 64 ? 3 : 2) void fwd_kernel(FmFwdArgs a) {
+__global__ __launch_bounds__(256, FwdCfg<D>::PER_CU) void fwd_kernel(FmFwdArgs a) {
   fwd_body<D, RAGGED, GEN, 1>(a);
 }
 // direct units: LDS for two tiles per step leaves one workgroup per compute unit at d = 128, two at d = 64
@@ -500,8 +501,10 @@ static hipError_t launch_fwd_s(const FmFwdArgs& a, hipStream_t stream) {
   constexpr auto kernel = S == 1 ? fwd_kernel<D, RAGGED, GEN> : direct_fwd_kernel<D, RAGGED, GEN>;
   static bool allowed[FM_MAX_DEVICES] = {};
   if (hipError_t e = fm_allow_lds((const void*)kernel, C::LDS_BYTES, allowed); e != hipSuccess) return e;
-  const int grid = S == 1 ? fm_launch_grid(a.slots) : fm_direct_grid(a.B * a.H * ((a.N + C::BR - 1) / C::BR));
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), C::LDS_BYTES, stream, a);
+  FmFwdArgs args = a;
+  args.queue = fm_queue_for_launch(a.queue, FwdCfg<D>::PER_CU);
+  const int grid = S == 1 ? fm_launch_grid(args.queue) : fm_direct_grid(a.B * a.H * ((a.N + C::BR - 1) / C::BR));
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), C::LDS_BYTES, stream, args);
   return hipGetLastError();
 }
 

@@ -29,10 +29,6 @@ inline hipError_t fm_allow_lds(const void* kernel, int bytes, bool (&done)[FM_MA
   if (e == hipSuccess && dev >= 0 && dev < FM_MAX_DEVICES) __atomic_store_n(&done[dev], true, __ATOMIC_RELEASE);
   return e;
 }
-// Workgroups of a tile-loop launch: one per slot plus a reserve of one eighth, through which the
-// XCDs that finish their own queue early take units from the others (a workgroup that finds
-// every queue empty ends at once).
-inline int fm_launch_grid(int slots) { return slots + fm_order_slots(slots / 8); }
 // Compute units of the current device (looked up once per device), 0 on failure.
 inline int fm_compute_units() {
   static int cached[FM_MAX_DEVICES] = {};
@@ -45,15 +41,35 @@ inline int fm_compute_units() {
   }
   return n;
 }
-// Workgroups of a persistent tile-loop launch (every workgroup works units off until the queues are
-// empty): what the chip holds at once, `per_cu` workgroups on each compute unit, rounded up to whole
-// rounds of the FM_QUEUES queues; never more than the one-unit-per-workgroup launch would have.
-inline int fm_persistent_grid(int slots, int per_cu) {
-  const int cus = fm_compute_units();
-  if (cus <= 0) return fm_launch_grid(slots);
-  const int g = (cus * per_cu + FM_QUEUES - 1) / FM_QUEUES * FM_QUEUES;
-  return g < fm_launch_grid(slots) ? g : fm_launch_grid(slots);
+// A pass's unit queues as its tile loop sees them.
+struct FmQueue {
+  int* order;    // slot records {unit, first live block, one past the last, 0}, unit = -1: none; then the counters
+  int slots;     // records (fm_order_slots)
+  int tickets;   // records that can hold a unit: FM_QUEUES x the longest queue
+  int first;     // tickets that are the number of the workgroup that takes them: those of the workgroups that run
+                 // from the start.  The order in which the others start decides theirs.
+};
+// Queues of `slices` slices (batch row, K/V head) of `units` units each.  How the slices that do not fill a round
+// of 8 queues are shared (fm_queue_of): queue 0 has a half, a quarter and an eighth of them, rounded up.
+inline FmQueue fm_queue(int* order, int slices, int units) {
+  const int r = slices % FM_QUEUES;
+  const int longest = slices / FM_QUEUES * units + ((r & 4) ? (units + 1) / 2 : 0) + ((r & 2) ? (units + 3) / 4 : 0) +
+                      ((r & 1) ? (units + 7) / 8 : 0);
+  return FmQueue{order, fm_order_slots(slices * units), longest * FM_QUEUES, 0};
 }
+// The queues for a launch that runs `per_cu` workgroups on each compute unit.
+inline FmQueue fm_queue_for_launch(FmQueue q, int per_cu) {
+  const int g = fm_compute_units() * per_cu / FM_QUEUES * FM_QUEUES;
+  q.first = g < q.tickets ? g : q.tickets;
+  return q;
+}
+// Workgroups of a tile-loop launch: one per ticket, and where not all of them run from the start a reserve of one
+// eighth, through which the XCDs that finish their own queue early take units from the others (a workgroup that
+// finds every queue empty ends at once).
+inline int fm_launch_grid(const FmQueue& q) { return q.first == q.tickets ? q.tickets : q.tickets + fm_order_slots(q.tickets / 8); }
+// Workgroups of a persistent launch (every workgroup works units off until the queues are empty): those that run
+// from the start (one per ticket if the number of compute units is not known).
+inline int fm_persistent_grid(const FmQueue& q) { return q.first > 0 ? q.first : q.tickets; }
 // Whether a tile loop over `units` units of 128 rows (or keys) runs on direct units (see fm_common.h): no setup
 // launches, halved units.  The line is where the chip has at most one 128-row unit per compute unit.  Beyond it a
 // workgroup per 128 rows fills the chip, and its tiles cost less (two workgroups share a compute unit).
@@ -120,14 +136,12 @@ struct FmFwdArgs {
   const void *q, *k, *v;
   const int *lts, *lte, *uts, *ute;   // [B][N]
   const int* minmax;  // [B][8][T_c] at FM_FWD_BC
-  int* order;         // queue slots {unit (b*H + h)*T_r + i or -1, first live key block, last + 1, 0}, then the
-                      // queue counters; a row block is fully masked outside [first, last)
+  FmQueue queue;      // units (b*H + h)*T_r + i; a row block is fully masked outside its key blocks [first, last)
   void* out;
   float* lse;
   float scale;
   int B, H, N, Np, d;
-  int slots;
-  bool direct;        // direct units: minmax, order and slots are not used
+  bool direct;        // direct units: minmax and queue are not used
   bool general;
   int Hk;
   FmStride sq, sk, sv, so;
@@ -139,17 +153,16 @@ struct FmBwdArgs {
   const float* lse;
   const int *lts, *lte, *uts, *ute;
   const int* minmax_dq;    // [B][8][T_c] at fm_dq_bc(d)
-  int* order_dq;           // queue slots and counters of the dQ pass (live key-block range per row block)
+  FmQueue queue_dq;        // of the dQ pass (live key-block range per row block)
   const int* minmax_dkdv;  // [B][8][T_c] at FM_DKDV_BC
-  int* order_dkdv;         // queue slots and counters of the dK/dV pass (live row-block range per key block)
+  FmQueue queue_dkdv;      // of the dK/dV pass (live row-block range per key block)
   float* dvec;             // -D = -rowsum(dO o O), [B,H,Np] (stored negated; 0 in the padding): written by the
                            // dQ loop's prologue, read by the dK/dV loop
   float* lse2;             // lse * log2(e), +inf where lse = -inf and in the padding, [B,H,Np]: likewise
   void *dq, *dk, *dv;
   float scale;
   int B, H, N, Np, d;
-  int slots_dq, slots_dkdv;
-  bool direct_dq, direct_dkdv;   // direct units: the pass's minmax, order and slots are not used
+  bool direct_dq, direct_dkdv;   // direct units: the pass's minmax and queue are not used
   bool general;
   int Hk;
   FmStride sq, sk, sv, so, sdo, sdq, sdk, sdv;

@@ -1,0 +1,48 @@
+"""GPU: launches over the unit queues at the unit counts where the handing out of tickets changes: exactly as many units
+as run at once, a few more, slices (batch row, head) that do not fill a round of eight queues, grouped K/V heads."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2410_01359_amd as fm
+import workloads
+from gpu_util import bf16_to_np, check_bwd, check_fwd, f64, to_device
+from oracle import flashmask_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,N", [(64, 1024), (65, 1024), (43, 1536), (103, 640), (129, 700), (7, 16384 - 64)])
+def test_every_head_alike(H, N, d):
+    """The same tensors in every head: one head against the oracle, all others bit for bit."""
+    w = workloads.small_workload("causal_document", N, seed=H + N, B=1, H=1, d=d)
+    bits, dev, vecs = to_device(w)
+    x = {n: dev[n].expand(1, H, N, d).contiguous() for n in ("q", "k", "v", "dout")}
+    out, lse = fm.flashmask_fwd(x["q"], x["k"], x["v"], *vecs, w.scale)
+    dq, dk, dv = fm.flashmask_bwd(x["q"], x["k"], x["v"], out, lse, x["dout"], *vecs, w.scale)
+    torch.cuda.synchronize()
+    for name, t in (("out", out), ("lse", lse), ("dq", dq), ("dk", dk), ("dv", dv)):
+        assert torch.equal(t, t[:, :1].expand_as(t)), f"{name}: heads differ"
+    if N > 4096:
+        return
+    q, k, v, do = (f64(bits[n][0, 0]) for n in ("q", "k", "v", "dout"))
+    rdq, rdk, rdv, ro, rl = orc.backward(q, k, v, do, *w.vectors[0], w.scale)
+    check_fwd(bf16_to_np(out[0, 0]), lse[0, 0].cpu().numpy(), ro, rl, f"H={H} N={N} d={d}")
+    for name, got, ref in (("dq", dq, rdq), ("dk", dk, rdk), ("dv", dv, rdv)):
+        check_bwd(bf16_to_np(got[0, 0]), ref, name, f"H={H} N={N} d={d}")
+
+
+@pytest.mark.parametrize("B,H,N", [(1, 64, 1024), (1, 7, 640), (3, 5, 384), (2, 12, 1152), (1, 1, 128)])
+def test_units_lie_within_the_tickets(B, H, N):
+    """No queue is longer than the launch's ticket count: whole rounds of slices, then a half, a quarter and an eighth
+    (rounded up) of the slices left over."""
+    w = workloads.small_workload("causal", N, seed=1, B=B, H=H, d=64)
+    vecs = [torch.from_numpy(v).cuda() for v in w.stacked_vectors()]
+    for pass_id in (fm.FM_PASS_FWD, fm.FM_PASS_BWD_DQ, fm.FM_PASS_BWD_DKDV):
+        rec = fm.flashmask_unit_queues(pass_id, *vecs, H, 64).cpu().numpy()
+        slices, units = B * H, (N + 127) // 128
+        r = slices % 8
+        longest = slices // 8 * units + (r & 4 and -(-units // 2)) + (r & 2 and -(-units // 4)) + (r & 1 and -(-units // 8))
+        assert (rec[8 * longest:, 0] == -1).all()
+        assert np.array_equal(np.sort(rec[rec[:, 0] >= 0, 0]), np.arange(slices * units))
