@@ -206,9 +206,8 @@ static int fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
   FmFwdArgs a;
   a.direct = fm_direct((long long)B * H * (Np / FM_FWD_BR));
   if (!a.direct) {
-    e = fm_launch_preprocess(lts, lte, uts, ute, B, N, Np, FM_FWD_BC, minmax, stream);
-    if (e != hipSuccess) return hip_fail(e);
-    e = fm_launch_row_order(minmax, B, H, Hk, N, Np, FM_FWD_BR, FM_FWD_BC, work, range, order, stream);
+    e = fm_launch_setup(lts, lte, uts, ute, B, H, Hk, N, Np, FmSetup{FM_FWD_BR, FM_FWD_BC, minmax, work, range, order},
+                        false, stream);
     if (e != hipSuccess) return hip_fail(e);
   }
   mark(1, stream);
@@ -247,13 +246,9 @@ int flashmask_unit_queues(int pass, const int32_t* lts, const int32_t* lte, cons
   char* ws = (char*)workspace;
   hipError_t e;
   const PassSpace sp = pass_space(B, H, Np, br, bc, rows, 0);
-  int* minmax = (int*)(ws + sp.minmax);
-  e = fm_launch_preprocess(lts, lte, uts, ute, B, N, Np, bc, minmax, stream);
-  if (e != hipSuccess) return hip_fail(e);
-  e = rows ? fm_launch_row_order(minmax, B, H, H, N, Np, br, bc, (int*)(ws + sp.work), (int*)(ws + sp.range),
-                                 (int*)(ws + sp.order), stream)
-           : fm_launch_col_order(minmax, B, H, N, Np, br, bc, (int*)(ws + sp.work), (int*)(ws + sp.range),
-                                 (int*)(ws + sp.order), stream);
+  e = fm_launch_setup(lts, lte, uts, ute, B, H, H, N, Np,
+                      FmSetup{br, bc, (int*)(ws + sp.minmax), (int*)(ws + sp.work), (int*)(ws + sp.range), (int*)(ws + sp.order)},
+                      !rows, stream);
   if (e != hipSuccess) return hip_fail(e);
   e = hipMemcpyAsync(records, ws + sp.order, (size_t)*slots * 16, hipMemcpyDeviceToDevice, stream);
   return e == hipSuccess ? FM_OK : hip_fail(e);
@@ -346,9 +341,7 @@ static int bwd_impl(const void* q, const void* k, const void* v, const void* out
     e = fm_launch_bwd_setup(lts, lte, uts, ute, B, H, Hk, N, Np, rows, cols, stream);
     if (e != hipSuccess) return hip_fail(e);
   } else if (!a.direct_dq) {   // few K/V heads: only the dQ pass has queues
-    e = fm_launch_preprocess(lts, lte, uts, ute, B, N, Np, rows.block_c, rows.minmax, stream);
-    if (e != hipSuccess) return hip_fail(e);
-    e = fm_launch_row_order(rows.minmax, B, H, Hk, N, Np, rows.block_r, rows.block_c, rows.work, rows.range, rows.order, stream);
+    e = fm_launch_setup(lts, lte, uts, ute, B, H, Hk, N, Np, rows, false, stream);
     if (e != hipSuccess) return hip_fail(e);
   }
   mark(1, stream);

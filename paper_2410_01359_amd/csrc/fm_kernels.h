@@ -87,13 +87,16 @@ constexpr int FM_DKDV_BR = 64, FM_DKDV_BC = 128;
 // One pass's setup buffers (in the workspace) and tile shape.
 struct FmSetup {
   int block_r, block_c;
-  int* minmax;
-  int* work;
-  int* range;
-  int* order;
+  int* minmax;   // int[B][8][T_c]
+  int* work;     // int[B * T], T = row blocks resp. key blocks
+  int* range;    // int[2 * B * T]: first live block and one past the last live block of every unit (0, 0 if none)
+  int* order;    // fm_order_bytes(B * H * T) bytes: slot records {unit, first, last, 0}, then the counters (zeroed here)
 };
-// The backward's whole setup (tables, work pre-passes and unit queues of the dQ pass `rows` and of the
-// dK/dV pass `cols`, whose units count K/V heads) in three launches.
+// A pass's whole setup: table, work and live range of every unit, unit queues.  cols: the units are key blocks (they
+// count K/V heads), else row blocks.  Short sequences take one launch, which writes minmax and order only.
+hipError_t fm_launch_setup(const int* lts, const int* lte, const int* uts, const int* ute, int B, int H, int Hk, int N,
+                           int Np, const FmSetup& pass, bool cols, hipStream_t stream);
+// The same for the dQ pass `rows` and the dK/dV pass `cols` together.
 hipError_t fm_launch_bwd_setup(const int* lts, const int* lte, const int* uts, const int* ute, int B, int H, int Hk,
                                int N, int Np, const FmSetup& rows, const FmSetup& cols, hipStream_t stream);
 // Tables of ceil(Np / block_c) key blocks per batch row.  Np == N: a ragged last block covers the columns that
@@ -102,13 +105,7 @@ hipError_t fm_launch_preprocess(const int* lts, const int* lte, const int* uts, 
                                 int block_c, int* minmax, hipStream_t stream);
 hipError_t fm_launch_classify(const int* minmax, int B, int N, int block_r, int block_c, uint8_t* cls,
                               hipStream_t stream);
-// work: int[B * T_r] (resp. B * T_c); range: int[2 * B * T] = first live block and one past the
-// last live block of every unit (0, 0 if none); order: fm_order_bytes(B*H*T) bytes = the slot
-// records {unit, first, last, 0} followed by the queue counters (zeroed here).
-hipError_t fm_launch_row_order(const int* minmax, int B, int H, int Hk, int N, int Np, int block_r, int block_c, int* work,
-                               int* range, int* order, hipStream_t stream);
-hipError_t fm_launch_col_order(const int* minmax, int B, int H, int N, int Np, int block_r, int block_c, int* work,
-                               int* range, int* order, hipStream_t stream);
+
 
 // Measurement aid (fm_probe.hip): `workgroups` x 4 waves each issue iters x fm_mfma_ceiling_ops_per_iter()
 // MFMA slots (shape 0: one 32x32x16 bf16 instruction; 1: two of the 16x16x32 shape, the same floating-point

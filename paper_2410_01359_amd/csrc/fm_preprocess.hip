@@ -241,11 +241,10 @@ struct OrderJob {
 // Workgroup `block` of `blocks` = 8 x (groups of whole slices + 1): block % 8 is the queue, block / 8 the
 // group; the last group is the shared slices, whose workgroups also clear their queue's unused slots
 // and counter.
-__device__ __forceinline__ void order_body(const OrderJob& job, int block, int blocks) {
-  const int* __restrict__ work = job.work;
-  const int* __restrict__ range = job.range;
+// `unit_work(u)` is {live blocks, first live block, one past the last} of unit u.
+template <class UnitWork>
+__device__ __forceinline__ void order_body(const OrderJob& job, int block, int blocks, const UnitWork& unit_work) {
   const int heads = job.heads, units_per_bh = job.units_per_bh, max_work = job.max_work;
-  const int blocks_per_head = job.blocks;
   const int slots = job.slots;
   i32x4* __restrict__ order = job.order;
   __shared__ int hist[kLevels];
@@ -275,9 +274,8 @@ __device__ __forceinline__ void order_body(const OrderJob& job, int block, int b
     if (tid == 0) job.counters[g] = 0;
   }
   __syncthreads();
-  auto rank_of = [&](int u) {
-    const int ru = (u / (heads * units_per_bh)) * blocks_per_head + u % blocks_per_head;
-    const int w_u = work[ru], mw = max_work > 0 ? max_work : 1;
+  auto rank_of = [&](const i32x4& uw) {
+    const int w_u = uw[0], mw = max_work > 0 ? max_work : 1;
     // Heavy units (an eighth of the largest possible work or more) are ranked finely by work: their
     // order decides how evenly the queue ends.  Lighter ones are ranked by octave of work and, within
     // an octave, by where their live range starts: units of similar size that stream the same blocks
@@ -285,19 +283,28 @@ __device__ __forceinline__ void order_body(const OrderJob& job, int block, int b
     // share the blocks in L2.
     constexpr int kFine = 384, kOct = 8, kPos = (kLevels - kFine) / kOct;
     int rank;
-    if ((long long)w_u * 8 >= mw) {
-      rank = (int)(((long long)(mw - min(w_u, mw)) * 8 * (kFine - 1)) / ((long long)mw * 7));
-      rank = min(max(rank, 0), kFine - 1);
+    const float share = (float)w_u / (float)mw;   // of the largest possible work
+    if (share >= 0.125f) {
+      rank = min(max((int)((1.f - share) * (8.f / 7.f * (kFine - 1))), 0), kFine - 1);
     } else {
       const int oct = min(max((int)__log2f((float)mw / (8.f * (float)max(w_u, 1))), 0), kOct - 1);
-      const int pos = min((int)(((long long)range[2 * ru] * kPos) / mw), kPos - 1);
+      const int pos = min((int)((float)uw[1] / (float)mw * kPos), kPos - 1);
       rank = kFine + oct * kPos + pos;
     }
     return rank;
   };
-  for (int idx = tid; idx < candidates; idx += 1024) {
+  // a thread's first candidate keeps its rank and record between the two passes
+  const int u_0 = tid < candidates ? unit_at(tid) : -1;
+  i32x4 uw_0 = {0, 0, 0, 0};
+  int rank_0 = 0;
+  if (u_0 >= 0) {
+    uw_0 = unit_work(u_0);
+    rank_0 = rank_of(uw_0);
+    atomicAdd(&hist[rank_0], 1);
+  }
+  for (int idx = tid + 1024; idx < candidates; idx += 1024) {
     const int u = unit_at(idx);
-    if (u >= 0) atomicAdd(&hist[rank_of(u)], 1);
+    if (u >= 0) atomicAdd(&hist[rank_of(unit_work(u))], 1);
   }
   __syncthreads();
   // exclusive scan of hist (512 entries, one per thread of the first 8 waves)
@@ -315,24 +322,158 @@ __device__ __forceinline__ void order_body(const OrderJob& job, int block, int b
   __syncthreads();
   if (tid < kLevels) hist[tid] = base + incl - v;   // first queue position (within the group) of this rank
   __syncthreads();
-  for (int idx = tid; idx < candidates; idx += 1024) {
+  auto place = [&](int u, int rank, const i32x4& uw) {
+    const int slot = (pos_base + atomicAdd(&hist[rank], 1)) * kGroups + g;
+    if (slot < slots) order[slot] = i32x4{u, uw[1], uw[2], 0};
+  };
+  if (u_0 >= 0) place(u_0, rank_0, uw_0);
+  for (int idx = tid + 1024; idx < candidates; idx += 1024) {
     const int u = unit_at(idx);
     if (u < 0) continue;
-    const int pos = pos_base + atomicAdd(&hist[rank_of(u)], 1);
-    const int slot = pos * kGroups + g;
-    const int ru = (u / (heads * units_per_bh)) * blocks_per_head + u % blocks_per_head;
-    if (slot < slots) order[slot] = i32x4{u, range[2 * ru], range[2 * ru + 1], 0};
+    const i32x4 uw = unit_work(u);
+    place(u, rank_of(uw), uw);
   }
 }
+// Work and live range from the arrays of the work pre-pass.
+struct WorkArrays {
+  const int* __restrict__ work;
+  const int* __restrict__ range;
+  int units_per_row, blocks;   // units of a batch row, blocks of a (batch row, query head)
+  __device__ __forceinline__ i32x4 operator()(int u) const {
+    const int ru = (u / units_per_row) * blocks + u % blocks;
+    return i32x4{work[ru], range[2 * ru], range[2 * ru + 1], 0};
+  }
+};
+__device__ __forceinline__ void order_from_arrays(const OrderJob& job, int block, int blocks) {
+  order_body(job, block, blocks, WorkArrays{job.work, job.range, job.heads * job.units_per_bh, job.blocks});
+}
 
-__global__ __launch_bounds__(1024) void order_kernel(OrderJob job) { order_body(job, blockIdx.x, gridDim.x); }
+__global__ __launch_bounds__(1024) void order_kernel(OrderJob job) { order_from_arrays(job, blockIdx.x, gridDim.x); }
 
 // the queues of two passes in one launch: workgroups [0, blocks_a) build job a's, the rest job b's
 __global__ __launch_bounds__(1024) void order2_kernel(OrderJob a, int blocks_a, OrderJob b) {
   if ((int)blockIdx.x < blocks_a)
-    order_body(a, blockIdx.x, blocks_a);
+    order_from_arrays(a, blockIdx.x, blocks_a);
   else
-    order_body(b, blockIdx.x - blocks_a, gridDim.x - blocks_a);
+    order_from_arrays(b, blockIdx.x - blocks_a, gridDim.x - blocks_a);
+}
+
+// The whole setup of a pass (or of the backward's two) in one launch, for sequences of at most kOneLaunchLength: every
+// queue-building workgroup forms the table and the work of its slices' batch rows itself, in LDS, from the bound
+// vectors.  At these lengths that is one 16-byte load per thread and vector and at most 32 x 64 tile classes, while
+// each launch of the three-launch form (tables, work, queues) is bound by its start and one round trip to memory.
+// Training step, three launches -> this one in each direction, d = 64 / 128: N = 512 68 -> 58 / 78 -> 70 us, N = 2048
+// 118 -> 109 / 153 -> 146 us, N = 4096 no difference within 3 us; with more passes over the columns (the work grows
+// with N^2 as well) it lost 4 us at N = 8192 and 10 to 15 us at N = 16384.
+constexpr int kOneLaunchLength = 4096;
+struct SetupJob {
+  OrderJob order;          // work and range are not used
+  int block_r, block_c;
+  int t_r, t_c;
+  int cols;                // units are key blocks (else row blocks)
+  int* minmax;             // [batch][8][t_c], written for the tile loops
+};
+struct SetupArgs {
+  const int* vec[4];       // LTS, LTE, UTS, UTE: [batch][n]
+  int n, np;
+  int blocks_first;        // workgroups of job[0], the rest are job[1]'s
+  SetupJob job[2];
+};
+__global__ __launch_bounds__(1024) void setup_kernel(SetupArgs a) {
+  constexpr int kMaxTiles = kOneLaunchLength / 64, kMaxUnits = kOneLaunchLength / 128, kMaxRows = FM_QUEUES - 1;
+  __shared__ i32x4 block_full[kMaxTiles];    // of a key block: LTS max, LTE min, UTS max, UTE min (what T_FULLY asks for)
+  __shared__ int work[kMaxRows * kMaxUnits], first[kMaxRows * kMaxUnits], last[kMaxRows * kMaxUnits];
+  const bool second = (int)blockIdx.x >= a.blocks_first;
+  const SetupJob& job = a.job[second ? 1 : 0];
+  const int block = second ? blockIdx.x - a.blocks_first : blockIdx.x;
+  const int blocks = second ? gridDim.x - a.blocks_first : a.blocks_first;
+  const int n = a.n, t_r = job.t_r, t_c = job.t_c, block_r = job.block_r, units = job.cols ? t_c : t_r;
+  const int tid = threadIdx.x;
+
+  // The batch rows of this workgroup's slices (see order_body): two slices 8 apart, or the slices left over.
+  const int heads = job.order.heads, slices = job.order.batch * heads;
+  const int whole = slices / kGroups * kGroups, g = block % kGroups, grp = block / kGroups;
+  const bool tail = grp == blocks / kGroups - 1;
+  const int s0 = tail ? whole : grp * FM_QUEUE_CHUNK * kGroups + g;
+  const int s1 = tail ? slices - 1 : min(s0 + (FM_QUEUE_CHUNK - 1) * kGroups, whole - kGroups + g);
+  const int row0 = s0 / heads, row1 = s1 / heads;                 // s1 < s0: no slice
+  const int n_rows = s1 < s0 ? 0 : tail ? row1 - row0 + 1 : (row1 > row0 ? 2 : 1);
+  static_assert(FM_QUEUE_CHUNK == 2, "at most two batch rows besides the slices left over");
+
+  for (int i = tid; i < n_rows * kMaxUnits; i += 1024) {
+    work[i] = last[i] = 0;
+    first[i] = INT32_MAX;
+  }
+  // a unit's blocks are shared by 1024 / units_p2 threads, which lie units_p2 apart
+  int shift = 0;
+  while ((1 << shift) < units) ++shift;
+  const int my_unit = tid & ((1 << shift) - 1), seg = tid >> shift, segs = 1024 >> shift;
+  for (int r = 0; r < n_rows; ++r) {
+    const int b = tail ? row0 + r : (r ? row1 : row0);
+    // the table goes to memory from the workgroup of the batch row's first slice (of queue 0 if it is shared)
+    int* const out = (tail ? g == 0 && b * heads >= whole : b * heads == (r ? s1 : s0)) ? job.minmax + (size_t)b * 8 * t_c
+                                                                                        : nullptr;
+    // block_c / 4 lanes take a key block, four columns each
+    static_assert(kOneLaunchLength == 4 * 1024, "four columns per thread");
+    const int lanes = job.block_c / 4, j = tid / lanes, key = tid * 4;
+    i32x4 x[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int* vec = a.vec[v] + (size_t)b * n;
+      if (n == a.np) {
+        x[v] = *(const i32x4*)(vec + min(key, n - 4));
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int y = vec[min(key + e, n - 1)];
+          x[v][e] = key + e < n ? y : v == 0 ? INT32_MIN : v == 1 ? INT32_MAX : 0;   // pad_column
+        }
+      }
+    }
+    int mm[8];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      mm[2 * v] = row16_max(max(max(x[v][0], x[v][1]), max(x[v][2], x[v][3])));
+      mm[2 * v + 1] = row16_min(min(min(x[v][0], x[v][1]), min(x[v][2], x[v][3])));
+      if (lanes == 32) {
+        mm[2 * v] = max(mm[2 * v], __shfl_xor(mm[2 * v], 16, 64));
+        mm[2 * v + 1] = min(mm[2 * v + 1], __shfl_xor(mm[2 * v + 1], 16, 64));
+      }
+    }
+    if ((tid & (lanes - 1)) == 0 && j < t_c) {
+      block_full[j] = i32x4{mm[LTS_MAX], mm[LTE_MIN], mm[UTS_MAX], mm[UTE_MIN]};
+      if (out) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) out[e * t_c + j] = mm[e];
+      }
+    }
+    __syncthreads();
+    // work and live range of every unit
+    const int others = job.cols ? t_r : t_c;
+    int cnt = 0, lo = INT32_MAX, hi = 0;
+    if (my_unit < units) {
+      for (int o = seg; o < others; o += segs) {
+        const i32x4 f = block_full[job.cols ? my_unit : o];
+        const int r0 = (job.cols ? o : my_unit) * block_r, r1 = min(r0 + block_r, n);
+        if (!((r0 >= f[0] && r1 <= f[1]) || (r0 >= f[2] && r1 <= f[3]))) {
+          ++cnt;
+          lo = min(lo, o);
+          hi = o + 1;
+        }
+      }
+      if (cnt) {
+        atomicAdd(&work[r * kMaxUnits + my_unit], cnt);
+        atomicMin(&first[r * kMaxUnits + my_unit], lo);
+        atomicMax(&last[r * kMaxUnits + my_unit], hi);
+      }
+    }
+    __syncthreads();   // the blocks are rebuilt for the next batch row
+  }
+  const int units_per_row = heads * job.order.units_per_bh, blocks_per_head = job.order.blocks;
+  order_body(job.order, block, blocks, [&](int u) {
+    const int b = u / units_per_row, i = (tail ? b - row0 : (b > row0 ? 1 : 0)) * kMaxUnits + u % blocks_per_head;
+    return i32x4{work[i], work[i] ? first[i] : 0, last[i], 0};
+  });
 }
 
 }  // namespace fm
@@ -365,45 +506,58 @@ static OrderJob order_job(int* work, int* range, int B, int H, int group, int bl
                   order + 4 * (size_t)slots};
 }
 
-hipError_t fm_launch_row_order(const int* minmax, int B, int H, int Hk, int N, int Np, int block_r, int block_c,
-                               int* work, int* range, int* order, hipStream_t stream) {
-  const int t_c = (Np + block_c - 1) / block_c;
-  const int t_r = (N + block_r - 1) / block_r;
-  const int total = B * t_r;
-  hipLaunchKernelGGL(row_work_kernel, dim3((total + 3) / 4), dim3(256), 0, stream, minmax, N, block_r, t_r, t_c, total,
-                     work, range);
-  hipLaunchKernelGGL(order_kernel, dim3(fm_order_grid(B, Hk)), dim3(1024), 0, stream,
-                     order_job(work, range, B, H, H / Hk, t_r, t_c, order));
+static WorkJob work_job(const FmSetup& p, int B, int N, int Np, bool cols) {
+  const int t_r = (N + p.block_r - 1) / p.block_r, t_c = (Np + p.block_c - 1) / p.block_c;
+  return WorkJob{p.minmax, p.block_r, t_r, t_c, B * (cols ? t_c : t_r), p.work, p.range};
+}
+static OrderJob pass_order_job(const FmSetup& p, const WorkJob& w, int B, int H, int Hk, bool cols) {
+  return cols ? order_job(p.work, p.range, B, Hk, 1, w.t_c, w.t_r, p.order)
+              : order_job(p.work, p.range, B, H, H / Hk, w.t_r, w.t_c, p.order);
+}
+static SetupJob setup_job(const FmSetup& p, int B, int H, int Hk, int N, int Np, bool cols) {
+  const WorkJob w = work_job(p, B, N, Np, cols);
+  return SetupJob{pass_order_job(p, w, B, H, Hk, cols), p.block_r, p.block_c, w.t_r, w.t_c, cols, p.minmax};
+}
+
+hipError_t fm_launch_setup(const int* lts, const int* lte, const int* uts, const int* ute, int B, int H, int Hk, int N,
+                           int Np, const FmSetup& pass, bool cols, hipStream_t stream) {
+  const int grid = fm_order_grid(B, Hk);
+  if (Np <= kOneLaunchLength) {
+    SetupArgs a{{lts, lte, uts, ute}, N, Np, grid, {setup_job(pass, B, H, Hk, N, Np, cols), {}}};
+    hipLaunchKernelGGL(setup_kernel, dim3(grid), dim3(1024), 0, stream, a);
+    return hipGetLastError();
+  }
+  if (hipError_t e = fm_launch_preprocess(lts, lte, uts, ute, B, N, Np, pass.block_c, pass.minmax, stream); e != hipSuccess)
+    return e;
+  const WorkJob w = work_job(pass, B, N, Np, cols);
+  const int work_grid = (w.total_units + 3) / 4;
+  if (cols)
+    hipLaunchKernelGGL(col_work_kernel, dim3(work_grid), dim3(256), 0, stream, w.minmax, N, w.block_r, w.t_r, w.t_c,
+                       w.total_units, w.work, w.range);
+  else
+    hipLaunchKernelGGL(row_work_kernel, dim3(work_grid), dim3(256), 0, stream, w.minmax, N, w.block_r, w.t_r, w.t_c,
+                       w.total_units, w.work, w.range);
+  hipLaunchKernelGGL(order_kernel, dim3(grid), dim3(1024), 0, stream, pass_order_job(pass, w, B, H, Hk, cols));
   return hipGetLastError();
 }
 
-hipError_t fm_launch_col_order(const int* minmax, int B, int H, int N, int Np, int block_r, int block_c, int* work,
-                               int* range, int* order, hipStream_t stream) {
-  const int t_c = (Np + block_c - 1) / block_c;
-  const int t_r = (N + block_r - 1) / block_r;
-  const int total = B * t_c;
-  hipLaunchKernelGGL(col_work_kernel, dim3((total + 3) / 4), dim3(256), 0, stream, minmax, N, block_r, t_r, t_c, total,
-                     work, range);
-  hipLaunchKernelGGL(order_kernel, dim3(fm_order_grid(B, H)), dim3(1024), 0, stream,
-                     order_job(work, range, B, H, 1, t_c, t_r, order));
-  return hipGetLastError();
-}
-
-// The backward's setup in three launches: both min/max tables, both work pre-passes, both passes' queues.
+// The backward's setup: one launch, or three (both min/max tables, both work pre-passes, both passes' queues).
 hipError_t fm_launch_bwd_setup(const int* lts, const int* lte, const int* uts, const int* ute, int B, int H, int Hk,
                                int N, int Np, const FmSetup& rows, const FmSetup& cols, hipStream_t stream) {
-  const int tc_r = (Np + rows.block_c - 1) / rows.block_c, tr_r = (N + rows.block_r - 1) / rows.block_r;
-  const int tc_c = (Np + cols.block_c - 1) / cols.block_c, tr_c = (N + cols.block_r - 1) / cols.block_r;
-  const int pre_a = (B * tc_r + 3) / 4, pre_b = (B * tc_c + 3) / 4;
+  const int grid = fm_order_grid(B, Hk);
+  if (Np <= kOneLaunchLength) {
+    SetupArgs a{{lts, lte, uts, ute}, N, Np, grid,
+                {setup_job(rows, B, H, Hk, N, Np, false), setup_job(cols, B, H, Hk, N, Np, true)}};
+    hipLaunchKernelGGL(setup_kernel, dim3(2 * grid), dim3(1024), 0, stream, a);
+    return hipGetLastError();
+  }
+  const WorkJob wr = work_job(rows, B, N, Np, false), wc = work_job(cols, B, N, Np, true);
+  const int pre_a = (B * wr.t_c + 3) / 4, pre_b = (B * wc.t_c + 3) / 4;
   hipLaunchKernelGGL(preprocess2_kernel, dim3(pre_a + pre_b), dim3(256), 0, stream, lts, lte, uts, ute, N, Np, B,
                      rows.block_c, rows.minmax, pre_a, cols.block_c, cols.minmax);
-  const WorkJob wr{rows.minmax, rows.block_r, tr_r, tc_r, B * tr_r, rows.work, rows.range};
-  const WorkJob wc{cols.minmax, cols.block_r, tr_c, tc_c, B * tc_c, cols.work, cols.range};
   const int work_a = (wr.total_units + 3) / 4, work_b = (wc.total_units + 3) / 4;
   hipLaunchKernelGGL(work2_kernel, dim3(work_a + work_b), dim3(256), 0, stream, wr, work_a, wc, N);
-  const int grid_a = fm_order_grid(B, Hk), grid_b = fm_order_grid(B, Hk);
-  hipLaunchKernelGGL(order2_kernel, dim3(grid_a + grid_b), dim3(1024), 0, stream,
-                     order_job(rows.work, rows.range, B, H, H / Hk, tr_r, tc_r, rows.order), grid_a,
-                     order_job(cols.work, cols.range, B, Hk, 1, tc_c, tr_c, cols.order));
+  hipLaunchKernelGGL(order2_kernel, dim3(2 * grid), dim3(1024), 0, stream, pass_order_job(rows, wr, B, H, Hk, false), grid,
+                     pass_order_job(cols, wc, B, H, Hk, true));
   return hipGetLastError();
 }

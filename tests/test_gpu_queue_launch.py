@@ -46,3 +46,34 @@ def test_units_lie_within_the_tickets(B, H, N):
         longest = slices // 8 * units + (r & 4 and -(-units // 2)) + (r & 2 and -(-units // 4)) + (r & 1 and -(-units // 8))
         assert (rec[8 * longest:, 0] == -1).all()
         assert np.array_equal(np.sort(rec[rec[:, 0] >= 0, 0]), np.arange(slices * units))
+
+
+@pytest.mark.parametrize("B,H,N", [(1, 3, 64), (2, 1, 2049), (9, 1, 700), (7, 3, 1153), (3, 16, 2048), (2, 8, 4096), (1, 2, 4097),
+                                   (2, 9, 4224)])
+@pytest.mark.parametrize("kind", ["document", "random_intervals", "sliding_window"])
+def test_records_on_both_sides_of_the_one_launch_setup(kind, B, H, N):
+    """Every unit's live range is what Equation 4 gives, in the one-launch setup (N <= 4096) and beyond it."""
+    w = workloads.small_workload(kind, N, seed=B + H + N, B=B, H=H, d=64)
+    vecs = [torch.from_numpy(v).cuda() for v in w.stacked_vectors()]
+    n_pad = -(-N // 128) * 128
+    for pass_id in (fm.FM_PASS_FWD, fm.FM_PASS_BWD_DQ, fm.FM_PASS_BWD_DKDV):
+        br, bc = fm.flashmask_tile_shape(pass_id, 64)
+        rec = fm.flashmask_unit_queues(pass_id, *vecs, H, 64).cpu().numpy()
+        rec = rec[rec[:, 0] >= 0]
+        rec = rec[np.argsort(rec[:, 0])]
+        units = n_pad // 128
+        assert len(rec) == B * H * units
+        for b in range(B):
+            # the columns past the end carry one interval that masks every row
+            pads = (np.iinfo(np.int32).min, np.iinfo(np.int32).max, 0, 0)
+            mm = [np.pad(v[b].astype(np.int64), (0, n_pad - N), constant_values=p).reshape(-1, bc)
+                  for v, p in zip(w.stacked_vectors(), pads)]
+            r0 = np.arange(0, N, br)[:, None]
+            r1 = np.minimum(r0 + br, N)
+            full = ((r0 >= mm[0].max(1)) & (r1 <= mm[1].min(1))) | ((r0 >= mm[2].max(1)) & (r1 <= mm[3].min(1)))
+            live = ~full if pass_id != fm.FM_PASS_BWD_DKDV else ~full.T
+            lo = np.where(live.any(1), live.argmax(1), 0)
+            hi = np.where(live.any(1), live.shape[1] - live[:, ::-1].argmax(1), 0)
+            for h in range(H):
+                got = rec[(b * H + h) * units:(b * H + h + 1) * units]
+                assert np.array_equal(got[:, 1], lo) and np.array_equal(got[:, 2], hi), (pass_id, b, h)
