@@ -204,8 +204,8 @@ static int fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
   int* range = (int*)(ws + sp.range);
   int* order = (int*)(ws + sp.order);
   FmFwdArgs a;
-  a.direct = fm_direct((long long)B * H * (Np / FM_FWD_BR));
-  if (!a.direct) {
+  a.units = fm_row_units((long long)B * H * (Np / FM_FWD_BR), fm_fwd_per_cu(d), d, Np);
+  if (a.units == FM_QUEUED) {
     e = fm_launch_setup(lts, lte, uts, ute, B, H, Hk, N, Np, FmSetup{FM_FWD_BR, FM_FWD_BC, minmax, work, range, order},
                         false, stream);
     if (e != hipSuccess) return hip_fail(e);
@@ -335,13 +335,16 @@ static int bwd_impl(const void* q, const void* k, const void* v, const void* out
                      (int*)(ws + sq.order)};
   const FmSetup cols{FM_DKDV_BR, FM_DKDV_BC, (int*)(ws + skv.minmax), (int*)(ws + skv.work), (int*)(ws + skv.range),
                      (int*)(ws + skv.order)};
-  a.direct_dq = fm_direct((long long)B * H * (Np / FM_DQ_BR));
-  a.direct_dkdv = fm_direct((long long)B * Hk * (Np / FM_DKDV_BC));   // Hk <= H: direct where dQ is
-  if (!a.direct_dkdv) {
+  a.units_dq = fm_row_units((long long)B * H * (Np / FM_DQ_BR), FM_DQ_PER_CU, d, Np);
+  a.units_dkdv = fm_key_units((long long)B * Hk * (Np / FM_DKDV_BC), H / Hk, d, Np);
+  // queues for dK/dV come with queues for dQ in the same launch
+  if (a.units_dkdv == FM_QUEUED && a.units_dq == FM_DIRECT) a.units_dq = FM_QUEUED;
+  const bool queue_dq = a.units_dq == FM_QUEUED, queue_dkdv = a.units_dkdv == FM_QUEUED;
+  if (queue_dq && queue_dkdv) {
     e = fm_launch_bwd_setup(lts, lte, uts, ute, B, H, Hk, N, Np, rows, cols, stream);
     if (e != hipSuccess) return hip_fail(e);
-  } else if (!a.direct_dq) {   // few K/V heads: only the dQ pass has queues
-    e = fm_launch_setup(lts, lte, uts, ute, B, H, Hk, N, Np, rows, false, stream);
+  } else if (queue_dq || queue_dkdv) {
+    e = fm_launch_setup(lts, lte, uts, ute, B, H, Hk, N, Np, queue_dq ? rows : cols, queue_dkdv, stream);
     if (e != hipSuccess) return hip_fail(e);
   }
   mark(1, stream);

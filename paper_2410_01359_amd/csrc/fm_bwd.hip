@@ -20,12 +20,13 @@ namespace fm {
 // ---------------------------------------------------------------------------
 // dQ: row-parallel, same transposed-score layout as the forward kernel.
 // ---------------------------------------------------------------------------
-// S: groups of waves that share a unit's key tiles (1: queued units of 128 rows; 2: direct units of 64 rows, each
-// tile of the list belongs to one pair of waves, and tiles have 64 keys at either d: the lists are short)
-template <int D, int S = 1>
+// S: groups of waves that share a unit's key tiles, each tile of the list belongs to one group (2: direct units only).
+// WR: waves of a group, 32 rows each.  DIRECT: direct units, whose tiles have 64 keys at either d (short lists).
+template <int D, int S = 1, int WR = 4, bool DIRECT = false>
 struct DqCfg {
-  static constexpr int KT = S == 1 ? fm_dq_bc(D) : 64;
-  static constexpr int BR = FM_DQ_BR / S;
+  static constexpr int KT = DIRECT ? 64 : fm_dq_bc(D);
+  static constexpr int BR = 32 * WR;
+  static constexpr int THREADS = 64 * S * WR;
   using L = TileLayout<D>;
   static constexpr int K_BYTES = KT * L::RS;
   static constexpr int V_BYTES = KT * L::RS;
@@ -39,14 +40,15 @@ struct DqCfg {
 };
 
 // RAGGED: see the forward kernel -- loops at the padded length, clamped tile copies, guarded stores.
-template <int D, bool RAGGED, bool GEN, int S>
+template <int D, bool RAGGED, bool GEN, int S, int WR, bool DIRECT>
 __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
-  using C = DqCfg<D, S>;
+  using C = DqCfg<D, S, WR, DIRECT>;
+  constexpr int NTC = WR == 4 ? 1 : S;    // tiles per step that a wave takes part in copying (see the forward)
   constexpr int KT = C::KT, NKB = KT / 32, NDB = D / 32, NKK = D / 16;
   extern __shared__ __attribute__((aligned(256))) char smem[];   // the operand reads rely on the alignment
 
   i32x4 rec = {-1, 0, 0, 0};
-  if (S == 1) rec = queue_take(a.queue_dq, (int*)(smem + C::CNT_OFF) + 8);
+  if (!DIRECT) rec = queue_take(a.queue_dq, (int*)(smem + C::CNT_OFF) + 8);
   else rec[0] = direct_unit(a.B * a.H * ((a.N + C::BR - 1) / C::BR), (a.N + C::BR - 1) / C::BR);
   const int unit = rec[0];
   if (unit < 0) return;
@@ -56,11 +58,11 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
   const int N = a.Np, H = a.H;            // padded length: what the loops and tables see
   const int Nr = RAGGED ? a.N : a.Np;     // rows the tensors really have
   const int t_r = (Nr + C::BR - 1) / C::BR, t_c = N / KT;
-  const int j_lo = S == 1 ? rec[1] : 0, j_hi = S == 1 ? rec[2] : t_c;
+  const int j_lo = DIRECT ? 0 : rec[1], j_hi = DIRECT ? t_c : rec[2];
   const int bh = unit / t_r, i_blk = unit - bh * t_r, b = bh / H;
   const int q0 = i_blk * C::BR;
-  constexpr int WR = 4 / S;               // waves that share the unit's rows, 32 each
   const int wrow = S == 1 ? wave : wave % WR, grp = S == 1 ? 0 : wave / WR;
+  const int cwave = S * WR == 4 ? wave : wave % 4, sub0 = WR == 4 ? grp : 0;
   const int qw0 = q0 + wrow * 32;
   const int row = qw0 + c;  // this lane's query row
   const int row_ld = RAGGED ? min(row, Nr - 1) : row;
@@ -74,11 +76,11 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
   const int do_rs = row_stride<D, GEN>(a.sdo);
   const int* table = a.minmax_dq + (size_t)b * 8 * t_c;
   // The four bound slices of a partially masked tile (KT ints each, one after the other in LDS) are copied by the
-  // first BND_WAVES waves, 1 KB each: a lane moves 16 bytes of vector (64 * wave + lane) / (KT / 4).
+  // first BND_WAVES waves, 1 KB each: a lane moves 16 bytes of vector (64 * cwave + lane) / (KT / 4).
   constexpr int BND_LPV = KT / 4, BND_WAVES = 4 * BND_LPV / 64;
   const int* my_bvec;
   {
-    const int which = (64 * wave + lane) / BND_LPV;
+    const int which = (64 * cwave + lane) / BND_LPV;
     const int* p = a.lts;
     if (which == 1) p = a.lte;
     if (which == 2) p = a.uts;
@@ -87,7 +89,7 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
   }
   // RAGGED: rows of the bound vectors are 4-byte aligned only and the last key block reaches past their end:
   // wave w copies one vector's slice, 4 bytes per lane
-  const int* wave_bvec = (wave == 0 ? a.lts : wave == 1 ? a.lte : wave == 2 ? a.uts : a.ute) + (size_t)b * Nr;
+  const int* wave_bvec = (cwave == 0 ? a.lts : cwave == 1 ? a.lte : cwave == 2 ? a.uts : a.ute) + (size_t)b * Nr;
   CopyLanes<D> copy_lanes, copy_lanes_v_;
   copy_lanes.init(lane, 2 * k_rs);
   if (GEN) copy_lanes_v_.init(lane, 2 * v_rs);
@@ -156,20 +158,20 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
       const int r_ = j_ * KT + sub * 64;                                                       \
       char* ks_ = st_ + sub * 64 * C::L::RS;                                                   \
       if (RAGGED && r_ + 64 > Nr) {                                                            \
-        tile_load_async_clamped<D>(kp, r_, Nr, ks_, wave, lane, 2 * k_rs);                     \
-        tile_load_async_clamped<D>(vp, r_, Nr, ks_ + C::K_BYTES, wave, lane, 2 * v_rs);        \
+        tile_load_async_clamped<D>(kp, r_, Nr, ks_, cwave, lane, 2 * k_rs);                     \
+        tile_load_async_clamped<D>(vp, r_, Nr, ks_ + C::K_BYTES, cwave, lane, 2 * v_rs);        \
       } else {                                                                                 \
-        tile_load_async<D>(kp + (size_t)r_ * k_rs, copy_lanes, ks_, wave, 2 * k_rs);           \
-        tile_load_async<D>(vp + (size_t)r_ * v_rs, copy_lanes_v, ks_ + C::K_BYTES, wave, 2 * v_rs); \
+        tile_load_async<D>(kp + (size_t)r_ * k_rs, copy_lanes, ks_, cwave, 2 * k_rs);           \
+        tile_load_async<D>(vp + (size_t)r_ * v_rs, copy_lanes_v, ks_ + C::K_BYTES, cwave, 2 * v_rs); \
       }                                                                                        \
     }                                                                                          \
     if (entry_tile_class(ENTRY) == T_PARTIAL) {                                                \
       const unsigned bnd_ = lds_address(st_ + C::K_BYTES + C::V_BYTES);                        \
       if (RAGGED) {                                                                            \
         _Pragma("unroll") for (int sub = 0; sub < KT / 64; ++sub)                              \
-          async_copy4(bound_or_pad(wave_bvec, wave, j_ * KT + sub * 64 + lane, Nr), bnd_ + wave * (KT * 4) + sub * 256); \
-      } else if (wave < BND_WAVES) {                                                           \
-        async_copy16(my_bvec + j_ * KT, bnd_ + wave * 1024);                                   \
+          async_copy4(bound_or_pad(wave_bvec, cwave, j_ * KT + sub * 64 + lane, Nr), bnd_ + cwave * (KT * 4) + sub * 256); \
+      } else if (cwave < BND_WAVES) {                                                           \
+        async_copy16(my_bvec + j_ * KT, bnd_ + cwave * 1024);                                   \
       }                                                                                        \
     }                                                                                          \
   }
@@ -178,41 +180,41 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
   for (int chunk = j_lo; chunk < j_hi; chunk += C::LIST_CAP) {
     const int chunk_end = min(chunk + C::LIST_CAP, j_hi), r1 = min(q0 + C::BR, Nr);
     int n_live;
-    if constexpr (S == 1) {
+    if constexpr (!DIRECT) {
       n_live = build_live_key_blocks<T_FULLY>(table, t_c, chunk, chunk_end, q0, r1, C::BR / 4, list, wave_cnt);
     } else {
       const int* bnd_rows[4] = {a.lts + (size_t)b * Nr, a.lte + (size_t)b * Nr, a.uts + (size_t)b * Nr,
                                 a.ute + (size_t)b * Nr};
-      n_live = build_live_key_blocks_direct<RAGGED, T_FULLY, WR>(bnd_rows, Nr, chunk, chunk_end, q0, r1, list, wave_cnt);
+      n_live = build_live_key_blocks_direct<RAGGED, T_FULLY, WR, S * WR>(bnd_rows, Nr, chunk, chunk_end, q0, r1, list, wave_cnt);
     }
     if (n_live == 0) continue;
     // the entries of tiles t and t + 1 travel in scalar registers; the one that joins them at the next tile is
     // read from the list at the top of a tile and picked up behind the tile's barrier, so that no tile starts by
     // waiting for LDS
-    int entry_s[S], next_entry_s[S];   // one per group of waves
+    int entry_s[NTC], next_entry_s[NTC];   // one per group of waves
 #pragma unroll
-    for (int s_ = 0; s_ < S; ++s_) {
-      entry_s[s_] = __builtin_amdgcn_readfirstlane(list[min(s_, n_live - 1)]);
-      next_entry_s[s_] = __builtin_amdgcn_readfirstlane(list[min(S + s_, n_live - 1)]);
-      if (S == 1 || s_ < n_live) FM_LOAD_TILE(entry_s[s_], 0, s_);
+    for (int s_ = 0; s_ < NTC; ++s_) {
+      entry_s[s_] = __builtin_amdgcn_readfirstlane(list[min(sub0 + s_, n_live - 1)]);
+      next_entry_s[s_] = __builtin_amdgcn_readfirstlane(list[min(S + sub0 + s_, n_live - 1)]);
+      if (S == 1 || sub0 + s_ < n_live) FM_LOAD_TILE(entry_s[s_], 0, sub0 + s_);
     }
     async_wait<0>();
     barrier_nofence();
 
     const int n_steps = (n_live + S - 1) / S;
     for (int t = 0; t < n_steps; ++t) {
-      int v_after[S];
+      int v_after[NTC];
 #pragma unroll
-      for (int s_ = 0; s_ < S; ++s_) v_after[s_] = list[min(S * (t + 2) + s_, n_live - 1)];
+      for (int s_ = 0; s_ < NTC; ++s_) v_after[s_] = list[min(S * (t + 2) + sub0 + s_, n_live - 1)];
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int s_ = 0; s_ < S; ++s_)
-        if (S * (t + 1) + s_ < n_live) FM_LOAD_TILE(next_entry_s[s_], (t + 1) & 1, s_);
+      for (int s_ = 0; s_ < NTC; ++s_)
+        if (S * (t + 1) + sub0 + s_ < n_live) FM_LOAD_TILE(next_entry_s[s_], (t + 1) & 1, sub0 + s_);
 
       const char* st = smem + C::STAGE_OFF + ((t & 1) * S + grp) * C::STAGE;
       const int* bnd = (const int*)(st + C::K_BYTES + C::V_BYTES);
 
-      const int entry = S == 1 || grp == 0 ? entry_s[0] : entry_s[S - 1];
+      const int entry = NTC == 1 || grp == 0 ? entry_s[0] : entry_s[NTC - 1];
       // Equation 4 on this wave's own rows; a group without a tile in the last step has nothing to do
       const int wcls = S == 1 || S * t + grp < n_live ? entry_wave_class(entry, wrow) : T_FULLY;
       if (wcls != T_FULLY) {
@@ -332,7 +334,7 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
       async_wait<0>();   // the next tile has landed ...
       barrier_nofence(); // ... for every wave, and every wave is done reading this one
 #pragma unroll
-      for (int s_ = 0; s_ < S; ++s_) {
+      for (int s_ = 0; s_ < NTC; ++s_) {
         entry_s[s_] = next_entry_s[s_];
         next_entry_s[s_] = __builtin_amdgcn_readfirstlane(v_after[s_]);
       }
@@ -399,8 +401,8 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
 // with every LDS operand fetched a fixed number of steps ahead of its MFMA.
 // Scheduling fences pin that order.
 // ---------------------------------------------------------------------------
-// S: groups of waves that share a unit's row tiles (1: queued units of 128 keys; 2: direct units of 64 keys, each tile
-// of the list belongs to one pair of waves)
+// S: groups of waves that share a unit's row tiles (1: units of 128 keys; 2: direct units of 64 keys, each tile of the
+// list belongs to one pair of waves)
 template <int D, int S = 1>
 struct DkdvCfg {
   static constexpr int QT = FM_DKDV_BR;    // query rows per step
@@ -430,6 +432,7 @@ struct DkdvCfg {
   // unit).  With two on a CU the early draws of all workgroups only meet on the queue counters: a workgroup per unit
   // is faster from 1024 units of 3 to 8 tiles (65.9 -> 42.9 us) to 4096 units of 64 (557 -> 549 us).
   static constexpr bool PERSISTENT = D == 128;
+  static constexpr int PER_CU = fm_dkdv_per_cu(D);   // workgroups of 128-key units on a compute unit
 };
 
 // lse / D slice of a tile in LDS: wave w copies rows 16w..16w+15 as 128 contiguous bytes,
@@ -740,7 +743,7 @@ __device__ __forceinline__ void dkdv_tile(const char* qs, const float* vec_s, co
 // GEN: tensors with caller-given strides; a workgroup then owns 128 keys of one K/V head and
 // walks the query heads that share it one after the other (same list of live row blocks: the
 // mask does not depend on the head), accumulating dK and dV over all of them.
-template <int D, bool RAGGED, bool GEN, int S>
+template <int D, bool RAGGED, bool GEN, int S, bool DIRECT>
 __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
   using C = DkdvCfg<D, S>;
   constexpr int QT = C::QT, NDB = D / 32, NKK = D / 16;
@@ -750,11 +753,11 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
   // hand-off words of the unit queue: int 8 = slot of the first take, ints 12..15 = record of the next unit
   int* qwords = (int*)(smem + C::CNT_OFF);
   i32x4 rec = {-1, 0, 0, 0};
-  if (S == 1) {
+  if (!DIRECT) {
     rec = queue_take(a.queue_dkdv, qwords + 8);
   } else {
     const int blocks = (a.N + C::BC - 1) / C::BC;
-    rec[0] = direct_unit(a.B * (GEN ? a.Hk : a.H) * blocks, blocks);
+    rec[0] = direct_unit<true>(a.B * (GEN ? a.Hk : a.H) * blocks, blocks);
     rec[2] = (a.N + QT - 1) / QT;   // every row block may be live
   }
   if (rec[0] < 0) return;
@@ -822,7 +825,7 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
 
   // the first unit's min/max values (Section 4.2's table); the later units' arrive with their records
   MinMax8 gmm;
-  if (S == 1) {
+  if (!DIRECT) {
     const int bh0 = rec[0] / t_c;
     gmm = load_minmax(a.minmax_dkdv + (size_t)(bh0 / Hk) * 8 * t_c, t_c, rec[0] - bh0 * t_c);
     // into scalar registers here, once: left in vector registers, every unit's list build would wait for
@@ -832,7 +835,7 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
     for (int e = 0; e < 8; ++e) gmm.v[e] = __builtin_amdgcn_readfirstlane(gmm.v[e]);
   }
 
-  const bool one_round = !C::PERSISTENT || a.queue_dkdv.first == a.queue_dkdv.tickets;   // a workgroup per unit
+  const bool one_round = DIRECT || !C::PERSISTENT || a.queue_dkdv.first == a.queue_dkdv.tickets;   // a workgroup per unit
   // A workgroup works units off until the queues are empty: the launch holds as many workgroups as the
   // chip runs at once, and the next unit's ticket, record and min/max values are fetched while the first
   // tile copies of the current unit are in flight.
@@ -866,7 +869,7 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
     b_uts = a.uts[bnd_row + key], b_ute = a.ute[bnd_row + key];
   }
 
-  if (S == 2) {   // the unit's min/max values from its own keys' bounds: over the wave's 32 keys, then over the waves
+  if (DIRECT) {   // the unit's min/max values from its own keys' bounds: over the wave's 32 keys, then over the waves
     const int own[4] = {b_lts, b_lte, b_uts, b_ute};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -881,8 +884,10 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
     barrier_nofence();
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const int x = qwords[32 + e], y = qwords[40 + e];
-      gmm.v[e] = __builtin_amdgcn_readfirstlane(e & 1 ? min(x, y) : max(x, y));
+      int x = qwords[32 + e];
+#pragma unroll
+      for (int w = 1; w < WK; ++w) x = e & 1 ? min(x, qwords[32 + 8 * w + e]) : max(x, qwords[32 + 8 * w + e]);
+      gmm.v[e] = __builtin_amdgcn_readfirstlane(x);
     }
   }
 
@@ -929,7 +934,7 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
       async_copy16_lanes8(my_vec + i_p * QT, lds_address(st_ + C::Q_BYTES + C::DO_BYTES) + wave * 128);
     }
     // the next unit's ticket and record, while these copies are in flight
-    if (S == 1 && !drawn) {
+    if (!DIRECT && !drawn) {
       if (wave == 0) queue_prefetch_key_block(a.queue_dkdv, qwords + 12, a.minmax_dkdv, t_c, Hk);
       drawn = true;
     }
@@ -969,7 +974,7 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
     __syncthreads();   // the ring is refilled by the next head, the list rebuilt by the next chunk
     }  // query heads
   }
-  if (S == 1 && !drawn) {   // a unit without a live tile: nothing was in flight to hide the draw behind
+  if (!DIRECT && !drawn) {   // a unit without a live tile: nothing was in flight to hide the draw behind
     if (wave == 0) queue_prefetch_key_block(a.queue_dkdv, qwords + 12, a.minmax_dkdv, t_c, Hk);
   }
 
@@ -1047,43 +1052,65 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
 }
 
 template <int D, bool RAGGED, bool GEN>
-__global__ __launch_bounds__(256, 2) void dq_kernel(FmBwdArgs a) {
-  dq_body<D, RAGGED, GEN, 1>(a);
+__global__ __launch_bounds__(256, FM_DQ_PER_CU) void dq_kernel(FmBwdArgs a) {
+  dq_body<D, RAGGED, GEN, 1, 4, false>(a);
 }
 template <int D, bool RAGGED, bool GEN>
-__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void dkdv_kernel(FmBwdArgs a) {
-  dkdv_body<D, RAGGED, GEN, 1>(a);
+__global__ __launch_bounds__(256, fm_dkdv_per_cu(D)) void dkdv_kernel(FmBwdArgs a) {
+  dkdv_body<D, RAGGED, GEN, 1, false>(a);
 }
-// direct units: LDS for two tiles per step leaves one workgroup per compute unit at d = 128, two at d = 64
+// Direct units.  LDS for two tiles per step leaves one workgroup per compute unit at d = 128, two at d = 64.
+template <int D, bool RAGGED, bool GEN>
+__global__ __launch_bounds__(256, FM_DQ_PER_CU) void single_dq_kernel(FmBwdArgs a) {
+  dq_body<D, RAGGED, GEN, 1, 4, true>(a);
+}
 template <int D, bool RAGGED, bool GEN>
 __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void direct_dq_kernel(FmBwdArgs a) {
-  dq_body<D, RAGGED, GEN, 2>(a);
+  dq_body<D, RAGGED, GEN, 2, 2, true>(a);
 }
 template <int D, bool RAGGED, bool GEN>
-__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void direct_dkdv_kernel(FmBwdArgs a) {
-  dkdv_body<D, RAGGED, GEN, 2>(a);
+__global__ __launch_bounds__(512, 1) void wide_dq_kernel(FmBwdArgs a) {
+  dq_body<D, RAGGED, GEN, 2, 4, true>(a);
+}
+template <int D, bool RAGGED, bool GEN>
+__global__ __launch_bounds__(256, fm_dkdv_per_cu(D)) void single_dkdv_kernel(FmBwdArgs a) {
+  dkdv_body<D, RAGGED, GEN, 1, true>(a);
+}
+template <int D, bool RAGGED, bool GEN>
+__global__ __launch_bounds__(256, fm_dkdv_per_cu(D)) void direct_dkdv_kernel(FmBwdArgs a) {
+  dkdv_body<D, RAGGED, GEN, 2, true>(a);
 }
 
 }  // namespace fm
 
 using namespace fm;
 
-template <int D, bool RAGGED, bool GEN, int S>
+template <int D, bool RAGGED, bool GEN, FmUnits U>
 static hipError_t launch_dq_s(const FmBwdArgs& a, hipStream_t stream) {
-  using C = DqCfg<D, S>;
-  constexpr auto kernel = S == 1 ? dq_kernel<D, RAGGED, GEN> : direct_dq_kernel<D, RAGGED, GEN>;
+  using C = DqCfg<D, fm_groups(U), fm_group_waves(U), U != FM_QUEUED>;
+  void (*kernel)(FmBwdArgs);
+  if constexpr (U == FM_QUEUED) kernel = dq_kernel<D, RAGGED, GEN>;
+  else if constexpr (U == FM_DIRECT) kernel = single_dq_kernel<D, RAGGED, GEN>;
+  else if constexpr (U == FM_DIRECT_HALVED) kernel = direct_dq_kernel<D, RAGGED, GEN>;
+  else kernel = wide_dq_kernel<D, RAGGED, GEN>;
   static bool allowed[FM_MAX_DEVICES] = {};
   if (hipError_t e = fm_allow_lds((const void*)kernel, C::LDS_BYTES, allowed); e != hipSuccess) return e;
   FmBwdArgs args = a;
-  args.queue_dq = fm_queue_for_launch(a.queue_dq, 2);
-  const int grid = S == 1 ? fm_launch_grid(args.queue_dq) : fm_direct_grid(a.B * a.H * ((a.N + C::BR - 1) / C::BR));
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), C::LDS_BYTES, stream, args);
+  args.queue_dq = fm_queue_for_launch(a.queue_dq, FM_DQ_PER_CU);
+  const int grid = U == FM_QUEUED ? fm_launch_grid(args.queue_dq) : fm_direct_grid(a.B * a.H * ((a.N + C::BR - 1) / C::BR));
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(C::THREADS), C::LDS_BYTES, stream, args);
   return hipGetLastError();
 }
 
 template <int D, bool RAGGED, bool GEN>
 static hipError_t launch_dq_t(const FmBwdArgs& a, hipStream_t stream) {
-  return a.direct_dq ? launch_dq_s<D, RAGGED, GEN, 2>(a, stream) : launch_dq_s<D, RAGGED, GEN, 1>(a, stream);
+  switch (a.units_dq) {
+    case FM_DIRECT: return launch_dq_s<D, RAGGED, GEN, FM_DIRECT>(a, stream);
+    case FM_DIRECT_HALVED: return launch_dq_s<D, RAGGED, GEN, FM_DIRECT_HALVED>(a, stream);
+    case FM_DIRECT_PAIRED:
+      if constexpr (D == 128) return launch_dq_s<D, RAGGED, GEN, FM_DIRECT_PAIRED>(a, stream);
+    default: return launch_dq_s<D, RAGGED, GEN, FM_QUEUED>(a, stream);
+  }
 }
 
 template <int D>
@@ -1097,24 +1124,32 @@ hipError_t fm_launch_bwd_dq(const FmBwdArgs& a, hipStream_t stream) {
   return a.d == 128 ? launch_dq_d<128>(a, stream) : launch_dq_d<64>(a, stream);
 }
 
-template <int D, bool RAGGED, bool GEN, int S>
+template <int D, bool RAGGED, bool GEN, FmUnits U>
 static hipError_t launch_dkdv_s(const FmBwdArgs& a, hipStream_t stream) {
-  using C = DkdvCfg<D, S>;
-  constexpr auto kernel = S == 1 ? dkdv_kernel<D, RAGGED, GEN> : direct_dkdv_kernel<D, RAGGED, GEN>;
+  using C = DkdvCfg<D, fm_groups(U)>;
+  void (*kernel)(FmBwdArgs);
+  if constexpr (U == FM_QUEUED) kernel = dkdv_kernel<D, RAGGED, GEN>;
+  else if constexpr (U == FM_DIRECT) kernel = single_dkdv_kernel<D, RAGGED, GEN>;
+  else kernel = direct_dkdv_kernel<D, RAGGED, GEN>;
   static bool allowed[FM_MAX_DEVICES] = {};
   if (hipError_t e = fm_allow_lds((const void*)kernel, C::LDS_BYTES, allowed); e != hipSuccess) return e;
-  // queued units: persistent, as many workgroups as the chip holds at once (one per CU at d = 128, two at d = 64)
   FmBwdArgs args = a;
-  args.queue_dkdv = fm_queue_for_launch(a.queue_dkdv, D == 64 ? 2 : 1);
-  const int grid = S == 1 ? (C::PERSISTENT ? fm_persistent_grid(args.queue_dkdv) : fm_launch_grid(args.queue_dkdv))
-                          : fm_direct_grid(a.B * (GEN ? a.Hk : a.H) * ((a.N + C::BC - 1) / C::BC));
+  args.queue_dkdv = fm_queue_for_launch(a.queue_dkdv, C::PER_CU);
+  const int units = a.B * (GEN ? a.Hk : a.H) * ((a.N + C::BC - 1) / C::BC);
+  const int grid = U != FM_QUEUED   ? fm_direct_grid(units)
+                   : C::PERSISTENT ? fm_persistent_grid(args.queue_dkdv)
+                                   : fm_launch_grid(args.queue_dkdv);
   hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), C::LDS_BYTES, stream, args);
   return hipGetLastError();
 }
 
 template <int D, bool RAGGED, bool GEN>
 static hipError_t launch_dkdv_t(const FmBwdArgs& a, hipStream_t stream) {
-  return a.direct_dkdv ? launch_dkdv_s<D, RAGGED, GEN, 2>(a, stream) : launch_dkdv_s<D, RAGGED, GEN, 1>(a, stream);
+  switch (a.units_dkdv) {
+    case FM_DIRECT: return launch_dkdv_s<D, RAGGED, GEN, FM_DIRECT>(a, stream);
+    case FM_DIRECT_HALVED: return launch_dkdv_s<D, RAGGED, GEN, FM_DIRECT_HALVED>(a, stream);
+    default: return launch_dkdv_s<D, RAGGED, GEN, FM_QUEUED>(a, stream);
+  }
 }
 
 template <int D>

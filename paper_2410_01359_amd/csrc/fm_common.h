@@ -445,10 +445,10 @@ __device__ __forceinline__ i32x4 queue_next_record(const int* lds_rec) {
   return rec;
 }
 
-// Ordered compaction shared by the tile loops: every thread of a 256-thread
-// workgroup offers one candidate per pass (live or not, with its list entry);
+// Ordered compaction shared by the tile loops: every thread of a workgroup (WAVES waves) offers one candidate per pass (live or not, with its list entry);
 // live entries are appended to list[] in candidate order.  `running` carries
 // the count across passes.  Contains two barriers (LDS only: no wait for global memory).
+template <int WAVES = 4>
 __device__ __forceinline__ void append_live(bool live, int entry, int* list, int* wave_cnt, int& running) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const unsigned long long ballot = __ballot(live);
@@ -457,7 +457,7 @@ __device__ __forceinline__ void append_live(bool live, int entry, int* list, int
   barrier_nofence();   // only LDS is exchanged: the callers' global loads stay in flight across the list build
   int off = running, tot = 0;
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
+  for (int w = 0; w < WAVES; ++w) {
     const int cw = wave_cnt[w];
     if (w < wave) off += cw;
     tot += cw;
@@ -521,30 +521,32 @@ __device__ __forceinline__ int entry_mask_mode(int entry) {
 }
 
 // --- direct units -----------------------------------------------------------------------------------------
-// A problem with at most one 128-row unit per compute unit (fm_direct in fm_kernels.h) runs without the setup
-// launches: workgroup x takes unit direct_unit(), every workgroup derives the min/max values it needs from the
-// bound vectors themselves, and the unit is halved (S = 2: half the rows or keys per workgroup, the tiles of its
-// list dealt alternately to two pairs of waves whose partial results meet in LDS at the end), which doubles the
-// workgroups and halves the longest chain of tiles.
+// A problem whose units all run at once (fm_row_units, fm_key_units in fm_kernels.h) needs no order and runs without
+// the setup launches: workgroup x takes unit direct_unit() and every workgroup derives the min/max values it needs
+// from the bound vectors themselves.  Where that leaves the chip with idle compute units the unit is halved (half the
+// rows or keys per workgroup), and the tiles of its list are dealt alternately to two groups of waves whose partial
+// results meet in LDS at the end, which halves the longest chain of tiles.
 //
 // Units are numbered slice-major and dealt to the XCDs (workgroup x runs on XCD x % 8) in eight contiguous runs, so
-// that a slice's K/V stays in as few L2s as the count allows; within a slice the last block goes first, because in
-// masks with a causal side it is the longest.  -1: nothing to do.
+// that a slice's K/V stays in as few L2s as the count allows.  Within a slice the block that is longest in masks with a
+// causal side goes first: the last row block, the first key block.  -1: nothing to do.
+template <bool KEY_BLOCKS = false>
 __device__ __forceinline__ int direct_unit(int units, int blocks) {
   const int per = (units + FM_QUEUES - 1) / FM_QUEUES;
   const int p = (int)(blockIdx.x % FM_QUEUES) * per + (int)(blockIdx.x / FM_QUEUES);
   if ((int)(blockIdx.x / FM_QUEUES) >= per || p >= units) return -1;
   const int slice = p / blocks, i = p - slice * blocks;
-  return slice * blocks + blocks - 1 - i;
+  return slice * blocks + (KEY_BLOCKS ? i : blocks - 1 - i);
 }
 // build_live_key_blocks for key blocks of 64 columns straight from the bound vectors (vec: a batch row's LTS, LTE,
-// UTS, UTE; n columns).  Sixteen lanes take a block, four columns each, so a pass of the workgroup covers 1024
+// UTS, UTE; n columns).  Sixteen lanes take a block, four columns each, so a pass of four waves covers 1024
 // columns; PASSES passes have their loads in flight together.  The raw entries go to list[] in place (-1: fully
 // masked) and are compacted from there.  NW: waves that own rows (32 each) of the unit.
-template <bool RAGGED, int EMPTY, int NW>
+// WAVES: waves of the workgroup.
+template <bool RAGGED, int EMPTY, int NW, int WAVES>
 __device__ __forceinline__ int build_live_key_blocks_direct(const int* const (&vec)[4], int n, int j_begin, int j_end,
                                                             int r0, int r1, int* list, int* wave_cnt) {
-  constexpr int KT = 64, BLOCKS = 256 * 4 / KT, PASSES = 2;
+  constexpr int KT = 64, THREADS = 64 * WAVES, BLOCKS = THREADS * 4 / KT, PASSES = 2;
   const int tid = threadIdx.x;
   for (int base = j_begin; base < j_end; base += BLOCKS * PASSES) {
     i32x4 x[PASSES][4];
@@ -589,9 +591,9 @@ __device__ __forceinline__ int build_live_key_blocks_direct(const int* const (&v
   }
   barrier_nofence();
   int running = 0;
-  for (int base = j_begin; base < j_end; base += 256) {
+  for (int base = j_begin; base < j_end; base += THREADS) {
     const int e = base + tid < j_end ? list[base + tid - j_begin] : -1;
-    append_live(e != -1, e, list, wave_cnt, running);   // writes behind what this and earlier passes have read
+    append_live<WAVES>(e != -1, e, list, wave_cnt, running);   // writes behind what this and earlier passes have read
   }
   return running;
 }

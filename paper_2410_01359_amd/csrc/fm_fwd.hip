@@ -25,12 +25,13 @@ namespace fm {
 #define FM_FWD_EXP_A 20
 #endif
 
-// S: groups of waves that share a unit's key tiles (1: queued units of 128 rows; 2: direct units of 64 rows, each
-// tile of the list belongs to one pair of waves)
-template <int D, int S = 1>
+// S: groups of waves that share a unit's key tiles, each tile of the list belongs to one group (2: direct units only).
+// WR: waves of a group, 32 query rows each.
+template <int D, int S = 1, int WR = 4>
 struct FwdCfg {
   static constexpr int KT = FM_FWD_BC;          // keys per tile
-  static constexpr int BR = FM_FWD_BR / S;      // query rows per workgroup
+  static constexpr int BR = 32 * WR;            // query rows per workgroup
+  static constexpr int THREADS = 64 * S * WR;
   using L = TileLayout<D>;
   static constexpr int K_BYTES = KT * L::RS;
   static constexpr int V_BYTES = KT * L::RS;
@@ -42,7 +43,7 @@ struct FwdCfg {
   static constexpr int K_OFF = CNT_OFF + 64;
   static constexpr int V_OFF = K_OFF + 2 * S * K_BYTES;   // two stages of S tiles each
   static constexpr int LDS_BYTES = V_OFF + 2 * S * VSTAGE;
-  static constexpr int PER_CU = D == 64 ? 3 : 2;          // workgroups of queued units on a compute unit
+  static constexpr int PER_CU = fm_fwd_per_cu(D);         // workgroups of 128-row units on a compute unit
 };
 
 // Per-wave constants of the tile loop.
@@ -234,14 +235,18 @@ __device__ __forceinline__ void fwd_step(f32x16 (&cur)[2], f32x16 (&nxt)[2], f32
 // Np (tables and lists are built for it; the padding columns are masked for every row), tile copies that reach past row N clamp their source rows, and rows >= N are
 // computed but not stored.
 // GEN: tensors with caller-given strides and fewer K/V heads than query heads (see FmFwdArgs).
-template <int D, bool RAGGED, bool GEN, int S>
+// DIRECT: direct units (see fm_common.h), else queued ones.
+template <int D, bool RAGGED, bool GEN, int S, int WR, bool DIRECT>
 __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
-  using C = FwdCfg<D, S>;
+  using C = FwdCfg<D, S, WR>;
+  // Four waves copy a tile, 16 of its 64 rows each: a group of four its own tiles, a group of two every tile
+  // together with the other group.
+  constexpr int NT = WR == 4 ? 1 : S;     // tiles per step that a wave takes part in copying
   constexpr int KT = C::KT, NKB = KT / 32, NDB = D / 32, NKK = D / 16;
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
   i32x4 rec = {-1, 0, 0, 0};
-  if (S == 1) rec = queue_take(a.queue, (int*)(smem + C::CNT_OFF) + 8);
+  if (!DIRECT) rec = queue_take(a.queue, (int*)(smem + C::CNT_OFF) + 8);
   else rec[0] = direct_unit(a.B * a.H * ((a.N + C::BR - 1) / C::BR), (a.N + C::BR - 1) / C::BR);
   const int unit = rec[0];
   if (unit < 0) return;
@@ -251,11 +256,12 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
   const int N = a.Np, H = a.H;            // padded length: what the loops and tables see
   const int Nr = RAGGED ? a.N : a.Np;     // rows the tensors really have
   const int t_r = (Nr + C::BR - 1) / C::BR, t_c = N / KT;
-  const int j_lo = S == 1 ? rec[1] : 0, j_hi = S == 1 ? rec[2] : t_c;
+  const int j_lo = DIRECT ? 0 : rec[1], j_hi = DIRECT ? t_c : rec[2];
   const int bh = unit / t_r, i_blk = unit - bh * t_r, b = bh / H;
   const int q0 = i_blk * C::BR;
-  constexpr int WR = 4 / S;               // waves that share the unit's rows, 32 each
   const int wrow = S == 1 ? wave : wave % WR, grp = S == 1 ? 0 : wave / WR;
+  const int cwave = S * WR == 4 ? wave : wave % 4;             // which quarter of a tile it copies
+  const int sub0 = WR == 4 ? grp : 0;     // first of the NT tiles of a step that it copies
   const int qw0 = q0 + wrow * 32;
 
   const int h = bh - b * H, hk = GEN ? h / (H / a.Hk) : h, Hk = GEN ? a.Hk : H;
@@ -277,7 +283,7 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
   }
   // RAGGED: rows of the bound vectors are 4-byte aligned only and the last key block reaches past their end:
   // wave w copies one vector's slice, 4 bytes per lane
-  const int* wave_bvec = (wave == 0 ? a.lts : wave == 1 ? a.lte : wave == 2 ? a.uts : a.ute) + (size_t)b * Nr;
+  const int* wave_bvec = (cwave == 0 ? a.lts : cwave == 1 ? a.lte : cwave == 2 ? a.uts : a.ute) + (size_t)b * Nr;
   CopyLanes<D> copy_lanes, copy_lanes_v_;
   copy_lanes.init(lane, 2 * k_rs);
   if (GEN) copy_lanes_v_.init(lane, 2 * v_rs);
@@ -318,23 +324,23 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
     const int j_ = entry_block(ENTRY, chunk);                                                    \
     char* st_ = smem + C::K_OFF + ((KBUF) * S + (SUB)) * C::K_BYTES;                             \
     if (RAGGED && (j_ + 1) * KT > Nr)                                                            \
-      tile_load_async_clamped<D>(kp, j_ * KT, Nr, st_, wave, lane, 2 * k_rs);                    \
+      tile_load_async_clamped<D>(kp, j_ * KT, Nr, st_, cwave, lane, 2 * k_rs);                    \
     else                                                                                         \
-      tile_load_async<D>(kp + (size_t)j_ * KT * k_rs, copy_lanes, st_, wave, 2 * k_rs);          \
+      tile_load_async<D>(kp + (size_t)j_ * KT * k_rs, copy_lanes, st_, cwave, 2 * k_rs);          \
   }
 #define FM_LOAD_V(ENTRY, VBUF, SUB)                                                              \
   {                                                                                              \
     const int j_ = entry_block(ENTRY, chunk);                                                    \
     char* st_ = smem + C::V_OFF + ((VBUF) * S + (SUB)) * C::VSTAGE;                              \
     if (RAGGED && (j_ + 1) * KT > Nr)                                                            \
-      tile_load_async_clamped<D>(vp, j_ * KT, Nr, st_, wave, lane, 2 * v_rs);                    \
+      tile_load_async_clamped<D>(vp, j_ * KT, Nr, st_, cwave, lane, 2 * v_rs);                    \
     else                                                                                         \
-      tile_load_async<D>(vp + (size_t)j_ * KT * v_rs, copy_lanes_v, st_, wave, 2 * v_rs);        \
+      tile_load_async<D>(vp + (size_t)j_ * KT * v_rs, copy_lanes_v, st_, cwave, 2 * v_rs);        \
     if (entry_tile_class(ENTRY) == T_PARTIAL) {                                                  \
       if (RAGGED)                                                                                \
-        async_copy4(bound_or_pad(wave_bvec, wave, j_ * KT + lane, Nr),                           \
-                    lds_address(st_ + C::V_BYTES) + wave * (KT * 4));                            \
-      else if (wave == 0)                                                                        \
+        async_copy4(bound_or_pad(wave_bvec, cwave, j_ * KT + lane, Nr),                           \
+                    lds_address(st_ + C::V_BYTES) + cwave * (KT * 4));                            \
+      else if (cwave == 0)                                                                        \
         async_copy16(my_bvec + j_ * KT, lds_address(st_ + C::V_BYTES));                          \
     }                                                                                            \
   }
@@ -346,15 +352,15 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
   {                                                                                              \
     /* the list entries that join the window at the next step: read now, picked up behind the */ \
     /* step's barrier, so that no step starts by waiting for LDS                               */ \
-    int v_3[S];                                                                                  \
-    _Pragma("unroll") for (int s_ = 0; s_ < S; ++s_) v_3[s_] = list[min(S * ((T) + 3) + s_, n_live - 1)]; \
+    int v_3[NT];                                                                                 \
+    _Pragma("unroll") for (int s_ = 0; s_ < NT; ++s_) v_3[s_] = list[min(S * ((T) + 3) + sub0 + s_, n_live - 1)]; \
     __builtin_amdgcn_sched_barrier(0);                                                           \
-    _Pragma("unroll") for (int s_ = 0; s_ < S; ++s_) {                                           \
-      if (S * ((T) + 2) + s_ < n_live) FM_LOAD_K(e_2[s_], (T) & 1, s_);                          \
-      if (S * ((T) + 1) + s_ < n_live) FM_LOAD_V(e_1[s_], ((T) + 1) & 1, s_);                    \
+    _Pragma("unroll") for (int s_ = 0; s_ < NT; ++s_) {                                          \
+      if (S * ((T) + 2) + sub0 + s_ < n_live) FM_LOAD_K(e_2[s_], (T) & 1, sub0 + s_);            \
+      if (S * ((T) + 1) + sub0 + s_ < n_live) FM_LOAD_V(e_1[s_], ((T) + 1) & 1, sub0 + s_);      \
     }                                                                                            \
     const char* vs_ = smem + C::V_OFF + (((T) & 1) * S + grp) * C::VSTAGE;                       \
-    const int e_own = S == 1 || grp == 0 ? e_t[0] : e_t[S - 1];                                  \
+    const int e_own = NT == 1 || grp == 0 ? e_t[0] : e_t[NT - 1];                                  \
     if (S == 1 || S * (T) + grp < n_live)                                                        \
       fwd_step<D>(CUR, NXT, oacc, qreg, m_run, l_run,                                            \
                   smem + C::K_OFF + ((((T) + 1) & 1) * S + grp) * C::K_BYTES, vs_,               \
@@ -362,7 +368,7 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
                   entry_wave_class(e_own, wrow) != T_UNMASKED ? entry_mask_mode(e_own) : 0, w);  \
     async_wait<0>();   /* K(T+2) and V(T+1) have landed ... */                                   \
     barrier_nofence(); /* ... for every wave, and every wave is done with K(T+1) and V(T) */     \
-    _Pragma("unroll") for (int s_ = 0; s_ < S; ++s_) {                                           \
+    _Pragma("unroll") for (int s_ = 0; s_ < NT; ++s_) {                                          \
       e_t[s_] = e_1[s_];                                                                         \
       e_1[s_] = e_2[s_];                                                                         \
       e_2[s_] = __builtin_amdgcn_readfirstlane(v_3[s_]);                                         \
@@ -374,23 +380,23 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
   for (int chunk = j_lo; chunk < j_hi; chunk += C::LIST_CAP) {
     const int chunk_end = min(chunk + C::LIST_CAP, j_hi), r1 = min(q0 + C::BR, Nr);
     const int n_live =
-        S == 1 ? build_live_key_blocks<T_UNMASKED>(table, t_c, chunk, chunk_end, q0, r1, C::BR / 4, list, wave_cnt)
-               : build_live_key_blocks_direct<RAGGED, T_UNMASKED, WR>(bnd_rows, Nr, chunk, chunk_end, q0, r1, list, wave_cnt);
+        !DIRECT ? build_live_key_blocks<T_UNMASKED>(table, t_c, chunk, chunk_end, q0, r1, C::BR / 4, list, wave_cnt)
+                : build_live_key_blocks_direct<RAGGED, T_UNMASKED, WR, S * WR>(bnd_rows, Nr, chunk, chunk_end, q0, r1, list, wave_cnt);
     if (n_live == 0) continue;
     // the entries of steps T, T + 1, T + 2 of the step about to run (clamped to the last one)
-    int e_t[S], e_1[S], e_2[S];
+    int e_t[NT], e_1[NT], e_2[NT];
 #pragma unroll
-    for (int s_ = 0; s_ < S; ++s_) {
-      e_t[s_] = __builtin_amdgcn_readfirstlane(list[min(s_, n_live - 1)]);
-      e_1[s_] = __builtin_amdgcn_readfirstlane(list[min(S + s_, n_live - 1)]);
-      e_2[s_] = __builtin_amdgcn_readfirstlane(list[min(2 * S + s_, n_live - 1)]);
+    for (int s_ = 0; s_ < NT; ++s_) {
+      e_t[s_] = __builtin_amdgcn_readfirstlane(list[min(sub0 + s_, n_live - 1)]);
+      e_1[s_] = __builtin_amdgcn_readfirstlane(list[min(S + sub0 + s_, n_live - 1)]);
+      e_2[s_] = __builtin_amdgcn_readfirstlane(list[min(2 * S + sub0 + s_, n_live - 1)]);
     }
     {
 #pragma unroll
-      for (int s_ = 0; s_ < S; ++s_) {
-        FM_LOAD_K(e_t[s_], 0, s_);
-        FM_LOAD_V(e_t[s_], 0, s_);
-        FM_LOAD_K(e_1[s_], 1, s_);
+      for (int s_ = 0; s_ < NT; ++s_) {
+        FM_LOAD_K(e_t[s_], 0, sub0 + s_);
+        FM_LOAD_V(e_t[s_], 0, sub0 + s_);
+        FM_LOAD_K(e_1[s_], 1, sub0 + s_);
       }
       async_wait<0>();
       barrier_nofence();
@@ -483,34 +489,52 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
 
 template <int D, bool RAGGED, bool GEN>
 __global__ __launch_bounds__(256, FwdCfg<D>::PER_CU) void fwd_kernel(FmFwdArgs a) {
-  fwd_body<D, RAGGED, GEN, 1>(a);
+  fwd_body<D, RAGGED, GEN, 1, 4, false>(a);
 }
-// direct units: LDS for two tiles per step leaves one workgroup per compute unit at d = 128, two at d = 64
+// Direct units.  LDS for two tiles per step leaves one workgroup per compute unit at d = 128, two at d = 64.
+template <int D, bool RAGGED, bool GEN>
+__global__ __launch_bounds__(256, FwdCfg<D>::PER_CU) void single_fwd_kernel(FmFwdArgs a) {
+  fwd_body<D, RAGGED, GEN, 1, 4, true>(a);
+}
 template <int D, bool RAGGED, bool GEN>
 __global__ __launch_bounds__(256, D == 64 ? 2 : 1) void direct_fwd_kernel(FmFwdArgs a) {
-  fwd_body<D, RAGGED, GEN, 2>(a);
+  fwd_body<D, RAGGED, GEN, 2, 2, true>(a);
+}
+template <int D, bool RAGGED, bool GEN>
+__global__ __launch_bounds__(512, 1) void wide_fwd_kernel(FmFwdArgs a) {
+  fwd_body<D, RAGGED, GEN, 2, 4, true>(a);
 }
 
 }  // namespace fm
 
 using namespace fm;
 
-template <int D, bool RAGGED, bool GEN, int S>
+template <int D, bool RAGGED, bool GEN, FmUnits U>
 static hipError_t launch_fwd_s(const FmFwdArgs& a, hipStream_t stream) {
-  using C = FwdCfg<D, S>;
-  constexpr auto kernel = S == 1 ? fwd_kernel<D, RAGGED, GEN> : direct_fwd_kernel<D, RAGGED, GEN>;
+  using C = FwdCfg<D, fm_groups(U), fm_group_waves(U)>;
+  void (*kernel)(FmFwdArgs);
+  if constexpr (U == FM_QUEUED) kernel = fwd_kernel<D, RAGGED, GEN>;
+  else if constexpr (U == FM_DIRECT) kernel = single_fwd_kernel<D, RAGGED, GEN>;
+  else if constexpr (U == FM_DIRECT_HALVED) kernel = direct_fwd_kernel<D, RAGGED, GEN>;
+  else kernel = wide_fwd_kernel<D, RAGGED, GEN>;
   static bool allowed[FM_MAX_DEVICES] = {};
   if (hipError_t e = fm_allow_lds((const void*)kernel, C::LDS_BYTES, allowed); e != hipSuccess) return e;
   FmFwdArgs args = a;
   args.queue = fm_queue_for_launch(a.queue, FwdCfg<D>::PER_CU);
-  const int grid = S == 1 ? fm_launch_grid(args.queue) : fm_direct_grid(a.B * a.H * ((a.N + C::BR - 1) / C::BR));
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), C::LDS_BYTES, stream, args);
+  const int grid = U == FM_QUEUED ? fm_launch_grid(args.queue) : fm_direct_grid(a.B * a.H * ((a.N + C::BR - 1) / C::BR));
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(C::THREADS), C::LDS_BYTES, stream, args);
   return hipGetLastError();
 }
 
 template <int D, bool RAGGED, bool GEN>
 static hipError_t launch_fwd_t(const FmFwdArgs& a, hipStream_t stream) {
-  return a.direct ? launch_fwd_s<D, RAGGED, GEN, 2>(a, stream) : launch_fwd_s<D, RAGGED, GEN, 1>(a, stream);
+  switch (a.units) {
+    case FM_DIRECT: return launch_fwd_s<D, RAGGED, GEN, FM_DIRECT>(a, stream);
+    case FM_DIRECT_HALVED: return launch_fwd_s<D, RAGGED, GEN, FM_DIRECT_HALVED>(a, stream);
+    case FM_DIRECT_PAIRED:
+      if constexpr (D == 128) return launch_fwd_s<D, RAGGED, GEN, FM_DIRECT_PAIRED>(a, stream);
+    default: return launch_fwd_s<D, RAGGED, GEN, FM_QUEUED>(a, stream);
+  }
 }
 
 template <int D>
@@ -521,6 +545,6 @@ static hipError_t launch_fwd_d(const FmFwdArgs& a, hipStream_t stream) {
 }
 
 hipError_t fm_launch_fwd(const FmFwdArgs& a, hipStream_t stream) {
-  static_assert(FM_FWD_BR == 128, "forward row block");
+  static_assert(FM_FWD_BR == FwdCfg<128>::BR, "forward row block");
   return a.d == 128 ? launch_fwd_d<128>(a, stream) : launch_fwd_d<64>(a, stream);
 }

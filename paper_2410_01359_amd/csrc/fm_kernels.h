@@ -70,12 +70,67 @@ inline int fm_launch_grid(const FmQueue& q) { return q.first == q.tickets ? q.ti
 // Workgroups of a persistent launch (every workgroup works units off until the queues are empty): those that run
 // from the start (one per ticket if the number of compute units is not known).
 inline int fm_persistent_grid(const FmQueue& q) { return q.first > 0 ? q.first : q.tickets; }
-// Whether a tile loop over `units` units of 128 rows (or keys) runs on direct units (see fm_common.h): no setup
-// launches, halved units.  The line is where the chip has at most one 128-row unit per compute unit.  Beyond it a
-// workgroup per 128 rows fills the chip, and its tiles cost less (two workgroups share a compute unit).
-inline bool fm_direct(long long units) { return units <= fm_compute_units(); }
 // Workgroups of a launch over direct units: every XCD's run of units, rounded up (see direct_unit).
 inline int fm_direct_grid(int units) { return (units + FM_QUEUES - 1) / FM_QUEUES * FM_QUEUES; }
+// How a tile loop's work is cut into workgroups.
+enum FmUnits {
+  FM_QUEUED,          // units of 128 rows (keys) off the unit queues, which the setup launches build
+  FM_DIRECT,          // the same units without setup launches (see fm_common.h)
+  FM_DIRECT_HALVED,   // units of 64 rows (keys), their tiles shared by two pairs of waves
+  FM_DIRECT_PAIRED,   // units of 128 rows, their tiles shared by two groups of four waves (row-parallel loops, d = 128)
+};
+constexpr int fm_groups(FmUnits u) { return u == FM_DIRECT_HALVED || u == FM_DIRECT_PAIRED ? 2 : 1; }
+constexpr int fm_group_waves(FmUnits u) { return u == FM_DIRECT_HALVED ? 2 : 4; }
+// Workgroups of 128-row (128-key) units on a compute unit, four waves each.
+constexpr int fm_fwd_per_cu(int d) { return d == 64 ? 3 : 2; }
+constexpr int FM_DQ_PER_CU = 2;
+constexpr int fm_dkdv_per_cu(int d) { return d == 64 ? 2 : 1; }
+// Sequences so short that what a unit does hardly differs gain nothing from an order, and the setup launch is a good
+// part of their time.  Training step, direct / queued, causal, documents, window: d = 128, N = 512, 1024 units 178 / 183,
+// 187 / 191, 167 / 176 us, 2048 units 368 / 363, 397 / 351, 352 / 353; d = 64, N = 512, 2048 units 191 / 222, 223 / 222,
+// 182 / 221, 4096 units 398 / 435, 451 / 436, 386 / 434; N = 1024, 1024 units 159 / 160, 171 / 160, 105 / 123.
+inline bool fm_short_direct(long long units, int d, int N) {
+  return N <= 512 && units <= (d == 64 ? 8ll : 4ll) * fm_compute_units();
+}
+// The cut of a row-parallel loop over `units` units of 128 rows, `per_cu` workgroups of which a compute unit holds, at
+// sequence length N.  What is weighed: the setup launch (4 us up to N = 4096, 8 us beyond), the longest chain of tiles
+// (halved by two groups), waves per SIMD, and building the list from the bound vectors instead of the table (which
+// grows with N).  Loop times in us, masks causal / causal documents of 700 tokens / both-sided ones / window 256:
+//   d = 128  128 units, N = 2048   halved 30 / 37 / 40 / 14, queued 41 / 56 / 59 / 17; N = 16384 causal 190, queued 261
+//            256 units, N = 512    paired 20 / 22 / 23 / 20, queued 19 / 23 / 23 / 19, halved 26 / 31 / 31 / 25
+//            256 units, N = 8192   paired 125 / 53 / 63 / 22, queued 141 / 64 / 77 / 20, halved 152 / 62 / 74 / 32
+//            512 units, N = 1024   direct 38 / 45 / 49 / 26, queued 38 / 40 / 48 / 26, paired 48 / 56 / 58 / 37
+//            512 units, N = 4096   direct 111 / 87 / 99 / 29, queued 92 / 74 / 91 / 27 (heaviest units first)
+//   d = 64   256 units, N = 4096   halved 39 / 37 / 41 / 15, queued 54 / 60 / 67 / 16
+//            512 units, N = 512    direct 21 / 24 / 25 / 20, halved 24 / 29 / 30 / 24, queued 21 / 23 / 25 / 21
+//            512 units, N = 8192   halved 112 / 47 / 63 / 33, queued 116 / 59 / 73 / 21; N = 16384 causal 267, queued 219
+inline FmUnits fm_row_units(long long units, int per_cu, int d, int N) {
+  const long long cus = fm_compute_units();
+  if (d == 128) {
+    if (2 * units <= cus) return FM_DIRECT_HALVED;
+    if (units <= cus) return FM_DIRECT_PAIRED;
+    return (units <= per_cu * cus && N <= 2048) || fm_short_direct(units, d, N) ? FM_DIRECT : FM_QUEUED;
+  }
+  if (units <= cus) return FM_DIRECT_HALVED;
+  if ((units <= per_cu * cus && N <= 1024) || fm_short_direct(units, d, N)) return FM_DIRECT;
+  return units <= 2 * cus && N <= 8192 ? FM_DIRECT_HALVED : FM_QUEUED;
+}
+// The same for the dK/dV loop over units of 128 keys of `group` query heads each (a chain `group` times as long; lists
+// are built from the unit's own keys' bounds at any N).  Masks as above:
+//   d = 128  128 units, N = 2048   halved 34 / 33 / 46 / 17, queued 49 / 46 / 67 / 20
+//            256 units, N = 1024   direct 34 / 32 / 46 / 24, halved 39 / 38 / 52 / 30, queued 34 / 33 / 44 / 24
+//            256 units, N = 4096   direct 96 / 58 / 90 / 25, halved 77 / 49 / 93 / 31, queued 95 / 58 / 90 / 24
+//            512 units, N = 8192   direct 249 / 78 / 112 / 47, queued 280 / 93 / 129 / 53, halved 273 / 76 / 114 / 59;
+//                                  N = 16384 direct 579 / 100 / 135 / 46, queued 578 / 104 / 128 / 55
+//            256 units of 4 query heads, N = 2048, shared questions: halved 126, direct 163, queued 164
+//   d = 64   512 units, N = 1024   direct 36 / 35 / 48 / 24, halved 36 / 35 / 50 / 28
+//            512 units, N = 4096   halved 85 / 48 / 83 / 28, direct 108 / 63 / 99 / 25, queued 87 / 50 / 86 / 26
+inline FmUnits fm_key_units(long long units, int group, int d, int N) {
+  const long long slots = (long long)fm_dkdv_per_cu(d) * fm_compute_units();
+  if (2 * units <= slots) return FM_DIRECT_HALVED;
+  if (units <= slots) return (long long)N * group <= (d == 128 ? 2048 : 1024) ? FM_DIRECT : FM_DIRECT_HALVED;
+  return (d == 128 && units <= 2 * slots && N <= 8192) || fm_short_direct(units, d, N) ? FM_DIRECT : FM_QUEUED;
+}
 // Tile shapes (rows x key columns) each pass classifies at.
 constexpr int FM_FWD_BR = 128, FM_FWD_BC = 64;
 constexpr int FM_DQ_BR = 128;
@@ -138,7 +193,7 @@ struct FmFwdArgs {
   float* lse;
   float scale;
   int B, H, N, Np, d;
-  bool direct;        // direct units: minmax and queue are not used
+  FmUnits units;      // direct ones: minmax and queue are not used
   bool general;
   int Hk;
   FmStride sq, sk, sv, so;
@@ -159,7 +214,7 @@ struct FmBwdArgs {
   void *dq, *dk, *dv;
   float scale;
   int B, H, N, Np, d;
-  bool direct_dq, direct_dkdv;   // direct units: the pass's minmax and queue are not used
+  FmUnits units_dq, units_dkdv;   // direct ones: the pass's minmax and queue are not used
   bool general;
   int Hk;
   FmStride sq, sk, sv, so, sdo, sdq, sdk, sdv;
