@@ -20,9 +20,9 @@
  *   - lts, lte, uts, ute: int32, contiguous [B, N]; one mask per batch row,
  *     shared by all heads.
  *   - lse, and the library's own D vector: fp32 [B, H, N].
- *   - d must be 64 or 128; N is any positive length (a length that is not a
- *     multiple of 128 costs one small extra launch that pads the bound
- *     vectors inside the workspace); tensor pointers must be 16-byte aligned.
+ *   - d must be 64 or 128; N is any positive length (one that is not a multiple
+ *     of 128 runs at the next multiple, its extra columns masked); tensor
+ *     pointers must be 16-byte aligned.
  *   - Outputs are overwritten in full.
  *   - Return value: FM_OK (0) or a negative FM_ERR_* code.  Only conditions the
  *     host can see are checked; bound VALUES live on the device and are not
@@ -31,7 +31,7 @@
  *   - Calls may be recorded into a HIP graph (no allocation, no host synchronisation, and the only
  *     clears of global memory are kernels).  The first call of a kernel variant on a device raises
  *     that kernel's dynamic-LDS limit (hipFuncSetAttribute): issue one call of the same shape class
- *     (d, aligned or ragged N, contiguous or _ex) outside the capture first.
+ *     (d, aligned or ragged N, contiguous or _ex; any sizes) outside the capture first.
  */
 #ifndef FLASHMASK_H
 #define FLASHMASK_H
@@ -115,8 +115,8 @@ int flashmask_bwd(const void* q, const void* k, const void* v,
 /*
  * flashmask_fwd for callers that cannot allocate device memory or pass a workspace: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, arithmetic,
- * kernels and results as flashmask_fwd, but the scratch (min/max tables, work counts, unit queues,
- * padded bound vectors) lives in a static device array inside the library instead of a caller's
+ * kernels and results as flashmask_fwd, but the scratch (min/max tables, work counts, unit queues)
+ * lives in a static device array inside the library instead of a caller's
  * workspace.  The call allocates and frees nothing.
  *   - Limit: flashmask_workspace_bytes(FM_PASS_FWD, B, H, N, d) must not exceed
  *     FLASHMASK_NOALLOC_SCRATCH_BYTES (4 MiB: about 250 000 row blocks of 128 queries over all batch

@@ -73,6 +73,11 @@ int check_strides(const flashmask_strides* s, int B, int heads, int N, int d) {
 
 // The tile loops work at the sequence length rounded up to a multiple of 128.
 inline int padded_len(int N) { return (N + 127) / 128 * 128; }
+// Room a workspace has beyond what its pass uses where N is no multiple of 128: four bound vectors of the padded length.
+// Part of the interface: the sizes decide which workspaces, and which problems for the static scratch, are refused.
+inline size_t ragged_reserve_bytes(int B, int N) {
+  return padded_len(N) == N ? 0 : align_up((size_t)4 * B * padded_len(N) * 4, 256);
+}
 
 // Workspace layout of a pass: tables, work counts and unit queues.
 struct PassSpace {
@@ -155,11 +160,12 @@ int flashmask_tile_shape(int pass, int d, int* block_r, int* block_c) {
 size_t flashmask_workspace_bytes(int pass, int B, int H, int N, int d) {
   if (check_shape(B, H, N, d) != FM_OK) return 0;
   const int Np = padded_len(N);
-  if (pass == FM_PASS_FWD) return pass_space(B, H, Np, FM_FWD_BR, FM_FWD_BC, true, 0).total;
+  const size_t reserve = ragged_reserve_bytes(B, N);
+  if (pass == FM_PASS_FWD) return reserve + pass_space(B, H, Np, FM_FWD_BR, FM_FWD_BC, true, 0).total;
   if (pass == FM_PASS_BWD) {
     const PassSpace dq = pass_space(B, H, Np, FM_DQ_BR, fm_dq_bc(d), true, 0);
     const PassSpace kv = pass_space(B, H, Np, FM_DKDV_BR, FM_DKDV_BC, false, dq.total);
-    return kv.total + 2 * align_up((size_t)B * H * Np * 4, 256);  // + D vector + log2-domain lse
+    return reserve + kv.total + 2 * align_up((size_t)B * H * Np * 4, 256);  // + D vector + log2-domain lse
   }
   return 0;
 }

@@ -80,3 +80,14 @@ def test_strided_entry_points_check_their_arguments_on_the_host():
                                 None, None, None, 1, 4, 4, 256, 64, arr, None, 0, None) == -3
     assert lib.flashmask_bwd_ex(None, None, None, None, None, None, None, None, None, None, ctypes.c_float(1.0),
                                 None, None, None, 1, 4, 4, 256, 64, None, None, 0, None) == -1
+
+
+@pytest.mark.parametrize("B,H,N,d", [(1, 1, 1, 64), (2, 3, 333, 128), (4, 8, 1000, 64), (1, 16, 4099, 128)])
+def test_workspace_of_a_ragged_length_keeps_its_reserve(B, H, N, d):
+    """A length that is no multiple of 128 is sized as its padded length plus four bound vectors of that length: the
+    sizes decide which workspaces are refused."""
+    import paper_2410_01359_amd as fm
+    padded = -(-N // 128) * 128
+    for which in (fm.FM_PASS_FWD, fm.FM_PASS_BWD):
+        extra = fm.flashmask_workspace_bytes(which, B, H, N, d) - fm.flashmask_workspace_bytes(which, B, H, padded, d)
+        assert extra == -(-16 * B * padded // 256) * 256
