@@ -1086,24 +1086,38 @@ __global__ __launch_bounds__(256, fm_dkdv_per_cu(D)) void direct_dkdv_kernel(FmB
 using namespace fm;
 
 template <int D, bool RAGGED, bool GEN, FmUnits U>
-static hipError_t launch_dq_s(const FmBwdArgs& a, hipStream_t stream) {
+struct DqLaunch {
   using C = DqCfg<D, fm_groups(U), fm_group_waves(U), U != FM_QUEUED>;
-  void (*kernel)(FmBwdArgs);
-  if constexpr (U == FM_QUEUED) kernel = dq_kernel<D, RAGGED, GEN>;
-  else if constexpr (U == FM_DIRECT) kernel = single_dq_kernel<D, RAGGED, GEN>;
-  else if constexpr (U == FM_DIRECT_HALVED) kernel = direct_dq_kernel<D, RAGGED, GEN>;
-  else kernel = wide_dq_kernel<D, RAGGED, GEN>;
-  static bool allowed[FM_MAX_DEVICES] = {};
-  if (hipError_t e = fm_allow_lds((const void*)kernel, C::LDS_BYTES, allowed); e != hipSuccess) return e;
+  static constexpr auto kernel() {
+    if constexpr (U == FM_QUEUED) return dq_kernel<D, RAGGED, GEN>;
+    else if constexpr (U == FM_DIRECT) return single_dq_kernel<D, RAGGED, GEN>;
+    else if constexpr (U == FM_DIRECT_HALVED) return direct_dq_kernel<D, RAGGED, GEN>;
+    else return wide_dq_kernel<D, RAGGED, GEN>;
+  }
+  static FmLdsLimit lds() { return {(const void*)kernel(), C::LDS_BYTES}; }
+};
+
+template <int D, bool RAGGED, bool GEN, FmUnits U>
+static hipError_t launch_dq_s(const FmBwdArgs& a, hipStream_t stream) {
+  using L = DqLaunch<D, RAGGED, GEN, U>;
+  using C = typename L::C;
   FmBwdArgs args = a;
   args.queue_dq = fm_queue_for_launch(a.queue_dq, FM_DQ_PER_CU);
   const int grid = U == FM_QUEUED ? fm_launch_grid(args.queue_dq) : fm_direct_grid(a.B * a.H * ((a.N + C::BR - 1) / C::BR));
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(C::THREADS), C::LDS_BYTES, stream, args);
+  hipLaunchKernelGGL(L::kernel(), dim3(grid), dim3(C::THREADS), C::LDS_BYTES, stream, args);
   return hipGetLastError();
 }
 
 template <int D, bool RAGGED, bool GEN>
 static hipError_t launch_dq_t(const FmBwdArgs& a, hipStream_t stream) {
+  static bool allowed[FM_MAX_DEVICES] = {};
+  if (hipError_t e = fm_allow_lds({DqLaunch<D, RAGGED, GEN, FM_QUEUED>::lds(),
+                                   DqLaunch<D, RAGGED, GEN, FM_DIRECT>::lds(),
+                                   DqLaunch<D, RAGGED, GEN, FM_DIRECT_HALVED>::lds(),
+                                   DqLaunch<D, RAGGED, GEN, D == 128 ? FM_DIRECT_PAIRED : FM_QUEUED>::lds()},
+                                  allowed);
+      e != hipSuccess)
+    return e;
   switch (a.units_dq) {
     case FM_DIRECT: return launch_dq_s<D, RAGGED, GEN, FM_DIRECT>(a, stream);
     case FM_DIRECT_HALVED: return launch_dq_s<D, RAGGED, GEN, FM_DIRECT_HALVED>(a, stream);
@@ -1125,26 +1139,39 @@ hipError_t fm_launch_bwd_dq(const FmBwdArgs& a, hipStream_t stream) {
 }
 
 template <int D, bool RAGGED, bool GEN, FmUnits U>
-static hipError_t launch_dkdv_s(const FmBwdArgs& a, hipStream_t stream) {
+struct DkdvLaunch {
   using C = DkdvCfg<D, fm_groups(U)>;
-  void (*kernel)(FmBwdArgs);
-  if constexpr (U == FM_QUEUED) kernel = dkdv_kernel<D, RAGGED, GEN>;
-  else if constexpr (U == FM_DIRECT) kernel = single_dkdv_kernel<D, RAGGED, GEN>;
-  else kernel = direct_dkdv_kernel<D, RAGGED, GEN>;
-  static bool allowed[FM_MAX_DEVICES] = {};
-  if (hipError_t e = fm_allow_lds((const void*)kernel, C::LDS_BYTES, allowed); e != hipSuccess) return e;
+  static constexpr auto kernel() {
+    if constexpr (U == FM_QUEUED) return dkdv_kernel<D, RAGGED, GEN>;
+    else if constexpr (U == FM_DIRECT) return single_dkdv_kernel<D, RAGGED, GEN>;
+    else return direct_dkdv_kernel<D, RAGGED, GEN>;
+  }
+  static FmLdsLimit lds() { return {(const void*)kernel(), C::LDS_BYTES}; }
+};
+
+template <int D, bool RAGGED, bool GEN, FmUnits U>
+static hipError_t launch_dkdv_s(const FmBwdArgs& a, hipStream_t stream) {
+  using L = DkdvLaunch<D, RAGGED, GEN, U>;
+  using C = typename L::C;
   FmBwdArgs args = a;
   args.queue_dkdv = fm_queue_for_launch(a.queue_dkdv, C::PER_CU);
   const int units = a.B * (GEN ? a.Hk : a.H) * ((a.N + C::BC - 1) / C::BC);
   const int grid = U != FM_QUEUED   ? fm_direct_grid(units)
                    : C::PERSISTENT ? fm_persistent_grid(args.queue_dkdv)
                                    : fm_launch_grid(args.queue_dkdv);
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), C::LDS_BYTES, stream, args);
+  hipLaunchKernelGGL(L::kernel(), dim3(grid), dim3(256), C::LDS_BYTES, stream, args);
   return hipGetLastError();
 }
 
 template <int D, bool RAGGED, bool GEN>
 static hipError_t launch_dkdv_t(const FmBwdArgs& a, hipStream_t stream) {
+  static bool allowed[FM_MAX_DEVICES] = {};
+  if (hipError_t e = fm_allow_lds({DkdvLaunch<D, RAGGED, GEN, FM_QUEUED>::lds(),
+                                   DkdvLaunch<D, RAGGED, GEN, FM_DIRECT>::lds(),
+                                   DkdvLaunch<D, RAGGED, GEN, FM_DIRECT_HALVED>::lds()},
+                                  allowed);
+      e != hipSuccess)
+    return e;
   switch (a.units_dkdv) {
     case FM_DIRECT: return launch_dkdv_s<D, RAGGED, GEN, FM_DIRECT>(a, stream);
     case FM_DIRECT_HALVED: return launch_dkdv_s<D, RAGGED, GEN, FM_DIRECT_HALVED>(a, stream);

@@ -368,7 +368,7 @@ __device__ __forceinline__ int row16_max(int x) { return dpp_max<0x121>(dpp_max<
 __device__ __forceinline__ int row16_min(int x) { return dpp_min<0x121>(dpp_min<0x122>(dpp_min<0x124>(dpp_min<0x128>(x)))); }
 
 // Unit queues.  Workgroup x works on queue x % FM_QUEUES (ticket t of queue g is slot t * FM_QUEUES + g of the slot
-// records).  The first `first` workgroups of a launch -- as many as the chip holds at once, fm_first_tickets -- have
+// records).  The first `first` workgroups of a launch -- as many as the chip holds at once, fm_queue_for_launch -- have
 // their ticket in their number: slot x.  Later ones, and a persistent workgroup's later units, draw from the queue's
 // counter; when that queue is used up, from the queue that has most left, and when all are used up they get nothing.
 // The counters sit behind the slot records and are zeroed by the queue-building kernel of every call.

@@ -510,24 +510,38 @@ __global__ __launch_bounds__(512, 1) void wide_fwd_kernel(FmFwdArgs a) {
 using namespace fm;
 
 template <int D, bool RAGGED, bool GEN, FmUnits U>
-static hipError_t launch_fwd_s(const FmFwdArgs& a, hipStream_t stream) {
+struct FwdLaunch {
   using C = FwdCfg<D, fm_groups(U), fm_group_waves(U)>;
-  void (*kernel)(FmFwdArgs);
-  if constexpr (U == FM_QUEUED) kernel = fwd_kernel<D, RAGGED, GEN>;
-  else if constexpr (U == FM_DIRECT) kernel = single_fwd_kernel<D, RAGGED, GEN>;
-  else if constexpr (U == FM_DIRECT_HALVED) kernel = direct_fwd_kernel<D, RAGGED, GEN>;
-  else kernel = wide_fwd_kernel<D, RAGGED, GEN>;
-  static bool allowed[FM_MAX_DEVICES] = {};
-  if (hipError_t e = fm_allow_lds((const void*)kernel, C::LDS_BYTES, allowed); e != hipSuccess) return e;
+  static constexpr auto kernel() {
+    if constexpr (U == FM_QUEUED) return fwd_kernel<D, RAGGED, GEN>;
+    else if constexpr (U == FM_DIRECT) return single_fwd_kernel<D, RAGGED, GEN>;
+    else if constexpr (U == FM_DIRECT_HALVED) return direct_fwd_kernel<D, RAGGED, GEN>;
+    else return wide_fwd_kernel<D, RAGGED, GEN>;
+  }
+  static FmLdsLimit lds() { return {(const void*)kernel(), C::LDS_BYTES}; }
+};
+
+template <int D, bool RAGGED, bool GEN, FmUnits U>
+static hipError_t launch_fwd_s(const FmFwdArgs& a, hipStream_t stream) {
+  using L = FwdLaunch<D, RAGGED, GEN, U>;
+  using C = typename L::C;
   FmFwdArgs args = a;
   args.queue = fm_queue_for_launch(a.queue, FwdCfg<D>::PER_CU);
   const int grid = U == FM_QUEUED ? fm_launch_grid(args.queue) : fm_direct_grid(a.B * a.H * ((a.N + C::BR - 1) / C::BR));
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(C::THREADS), C::LDS_BYTES, stream, args);
+  hipLaunchKernelGGL(L::kernel(), dim3(grid), dim3(C::THREADS), C::LDS_BYTES, stream, args);
   return hipGetLastError();
 }
 
 template <int D, bool RAGGED, bool GEN>
 static hipError_t launch_fwd_t(const FmFwdArgs& a, hipStream_t stream) {
+  static bool allowed[FM_MAX_DEVICES] = {};
+  if (hipError_t e = fm_allow_lds({FwdLaunch<D, RAGGED, GEN, FM_QUEUED>::lds(),
+                                   FwdLaunch<D, RAGGED, GEN, FM_DIRECT>::lds(),
+                                   FwdLaunch<D, RAGGED, GEN, FM_DIRECT_HALVED>::lds(),
+                                   FwdLaunch<D, RAGGED, GEN, D == 128 ? FM_DIRECT_PAIRED : FM_QUEUED>::lds()},
+                                  allowed);
+      e != hipSuccess)
+    return e;
   switch (a.units) {
     case FM_DIRECT: return launch_fwd_s<D, RAGGED, GEN, FM_DIRECT>(a, stream);
     case FM_DIRECT_HALVED: return launch_fwd_s<D, RAGGED, GEN, FM_DIRECT_HALVED>(a, stream);

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <initializer_list>
+
 // The tile loops draw their work units from FM_QUEUES interleaved queues (one per XCD).
 constexpr int FM_QUEUES = 8;
 // Number of queue slots for `units` work units.
@@ -15,18 +17,27 @@ constexpr int FM_QUEUE_CHUNK = 2;
 inline int fm_order_slots(int units) { return ((units + FM_QUEUES - 1) / FM_QUEUES + 3) * FM_QUEUES; }
 // Bytes of a pass's queue area: one 16-byte record per slot, then the FM_QUEUES queue counters.
 inline size_t fm_order_bytes(int units) { return (size_t)fm_order_slots(units) * 16 + FM_QUEUES * 4; }
-// Raise a tile-loop kernel's dynamic LDS limit once per device (the attribute belongs to the device's
-// copy of the kernel); `done` is the launcher's own flag array, one flag per device.
+// Raise the dynamic LDS limits of a tile loop's kernels of one shape class (head dimension, ragged or not, general
+// layout or not) once per device (the attribute belongs to the device's copy of the kernel).  All cuts of the work
+// together: one call prepares its class for a graph capture, whichever cut the captured sizes take.  `done` is the
+// class's own flag array, one flag per device.
 constexpr int FM_MAX_DEVICES = 64;
-inline hipError_t fm_allow_lds(const void* kernel, int bytes, bool (&done)[FM_MAX_DEVICES]) {
+struct FmLdsLimit {
+  const void* kernel;
+  int bytes;
+};
+inline hipError_t fm_allow_lds(std::initializer_list<FmLdsLimit> limits, bool (&done)[FM_MAX_DEVICES]) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   // The flags are shared by every host thread that calls the library: atomic accesses; two threads
-  // that both find a flag clear both set the attribute, which is harmless (same value).
+  // that both find a flag clear both set the attributes, which is harmless (same values).
   if (dev >= 0 && dev < FM_MAX_DEVICES && __atomic_load_n(&done[dev], __ATOMIC_ACQUIRE)) return hipSuccess;
-  e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-  if (e == hipSuccess && dev >= 0 && dev < FM_MAX_DEVICES) __atomic_store_n(&done[dev], true, __ATOMIC_RELEASE);
+  for (const FmLdsLimit& l : limits) {
+    e = hipFuncSetAttribute(l.kernel, hipFuncAttributeMaxDynamicSharedMemorySize, l.bytes);
+    if (e != hipSuccess) return e;
+  }
+  if (dev >= 0 && dev < FM_MAX_DEVICES) __atomic_store_n(&done[dev], true, __ATOMIC_RELEASE);
   return e;
 }
 // Compute units of the current device (looked up once per device), 0 on failure.
