@@ -94,8 +94,22 @@ def _dev(t: torch.Tensor, dtype, name: str) -> torch.Tensor:
     return t
 
 
+_QKV, _BOUNDS = ("q", "k", "v"), ("lts", "lte", "uts", "ute")
+
+
+def _all_fit(tensors, names, dtype, shape) -> bool:
+    """Every tensor passes _dev (which raises otherwise); whether all have `shape`."""
+    fits = True
+    for t, n in zip(tensors, names):
+        if not (t.is_cuda and t.dtype is dtype and t.is_contiguous()):
+            _dev(t, dtype, n)
+        fits = fits and t.shape == shape
+    return fits
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # the current device's current stream as a number, without the Stream object around it
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def flashmask_tile_shape(pass_id: int, d: int):
@@ -138,15 +152,13 @@ def flashmask_classify(minmax: torch.Tensor, N: int, block_r: int, block_c: int)
 
 def flashmask_fwd(q, k, v, lts, lte, uts, ute, scale: float, workspace: torch.Tensor | None = None):
     """out (bf16 [B,H,N,d]) and lse (fp32 [B,H,N])."""
-    for t, n in zip((q, k, v), "qkv"):
-        _dev(t, torch.bfloat16, n)
-    for t, n in zip((lts, lte, uts, ute), ("lts", "lte", "uts", "ute")):
-        _dev(t, torch.int32, n)
-    B, H, N, d = q.shape
-    if k.shape != q.shape or v.shape != q.shape or any(tuple(x.shape) != (B, N) for x in (lts, lte, uts, ute)):
+    shape = q.shape
+    fits = _all_fit((q, k, v), _QKV, torch.bfloat16, shape)
+    fits &= _all_fit((lts, lte, uts, ute), _BOUNDS, torch.int32, shape[:1] + shape[2:3])
+    B, H, N, d = shape
+    if not fits:
         raise FlashMaskError("shape mismatch: q,k,v [B,H,N,d]; lts,lte,uts,ute [B,N]")
-    need = flashmask_workspace_bytes(FM_PASS_FWD, B, H, N, d)
-    ws = workspace if workspace is not None else _workspace(need, q.device)
+    ws = workspace if workspace is not None else _workspace(flashmask_workspace_bytes(FM_PASS_FWD, B, H, N, d), q.device)
     out = torch.empty_like(q)
     lse = torch.empty((B, H, N), dtype=torch.float32, device=q.device)
     _check(load_library().flashmask_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), lts.data_ptr(), lte.data_ptr(),
@@ -158,14 +170,12 @@ def flashmask_fwd(q, k, v, lts, lte, uts, ute, scale: float, workspace: torch.Te
 def flashmask_fwd_noalloc(q, k, v, lts, lte, uts, ute, scale: float, out: torch.Tensor, lse: torch.Tensor):
     """flashmask_fwd into caller-provided out / lse, with the library's static scratch: this call
     itself allocates nothing (not even through torch)."""
-    for t, n in zip((q, k, v, out), ("q", "k", "v", "out")):
-        _dev(t, torch.bfloat16, n)
-    _dev(lse, torch.float32, "lse")
-    for t, n in zip((lts, lte, uts, ute), ("lts", "lte", "uts", "ute")):
-        _dev(t, torch.int32, n)
-    B, H, N, d = q.shape
-    if any(x.shape != q.shape for x in (k, v, out)) or tuple(lse.shape) != (B, H, N) or \
-            any(tuple(x.shape) != (B, N) for x in (lts, lte, uts, ute)):
+    shape = q.shape
+    fits = _all_fit((q, k, v, out), ("q", "k", "v", "out"), torch.bfloat16, shape)
+    fits &= _all_fit((lse,), ("lse",), torch.float32, shape[:3])
+    fits &= _all_fit((lts, lte, uts, ute), _BOUNDS, torch.int32, shape[:1] + shape[2:3])
+    B, H, N, d = shape
+    if not fits:
         raise FlashMaskError("shape mismatch: q,k,v,out [B,H,N,d]; lse [B,H,N]; lts,lte,uts,ute [B,N]")
     _check(load_library().flashmask_fwd_noalloc(q.data_ptr(), k.data_ptr(), v.data_ptr(), lts.data_ptr(),
                                                 lte.data_ptr(), uts.data_ptr(), ute.data_ptr(), float(scale),
@@ -176,17 +186,14 @@ def flashmask_fwd_noalloc(q, k, v, lts, lte, uts, ute, scale: float, out: torch.
 
 def flashmask_bwd(q, k, v, out, lse, dout, lts, lte, uts, ute, scale: float, workspace: torch.Tensor | None = None):
     """dq, dk, dv (bf16 [B,H,N,d])."""
-    for t, n in zip((q, k, v, out, dout), ("q", "k", "v", "out", "dout")):
-        _dev(t, torch.bfloat16, n)
-    _dev(lse, torch.float32, "lse")
-    for t, n in zip((lts, lte, uts, ute), ("lts", "lte", "uts", "ute")):
-        _dev(t, torch.int32, n)
-    B, H, N, d = q.shape
-    if any(x.shape != q.shape for x in (k, v, out, dout)) or tuple(lse.shape) != (B, H, N) or \
-            any(tuple(x.shape) != (B, N) for x in (lts, lte, uts, ute)):
+    shape = q.shape
+    fits = _all_fit((q, k, v, out, dout), ("q", "k", "v", "out", "dout"), torch.bfloat16, shape)
+    fits &= _all_fit((lse,), ("lse",), torch.float32, shape[:3])
+    fits &= _all_fit((lts, lte, uts, ute), _BOUNDS, torch.int32, shape[:1] + shape[2:3])
+    B, H, N, d = shape
+    if not fits:
         raise FlashMaskError("shape mismatch")
-    need = flashmask_workspace_bytes(FM_PASS_BWD, B, H, N, d)
-    ws = workspace if workspace is not None else _workspace(need, q.device)
+    ws = workspace if workspace is not None else _workspace(flashmask_workspace_bytes(FM_PASS_BWD, B, H, N, d), q.device)
     dq, dk, dv = torch.empty_like(q), torch.empty_like(q), torch.empty_like(q)
     _check(load_library().flashmask_bwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(),
                                         dout.data_ptr(), lts.data_ptr(), lte.data_ptr(), uts.data_ptr(),
