@@ -13,6 +13,7 @@
 // the backward far below the matrix-core rate, so dQ gets its own row-parallel
 // pass instead (two extra products per tile, no atomics, bit-reproducible).
 #include "fm_common.h"
+#include "fm_interval.h"
 #include "fm_kernels.h"
 
 namespace fm {
@@ -458,18 +459,19 @@ __device__ __forceinline__ constexpr int dkdv_vec_off(int r, bool d_part) {
 // (dP - D comes straight out of the MFMA: its accumulator starts from the -D values of the rows)
 // Register r of a block is query row 8*(r/4) + 4*g + r%4.
 // The element mask of a lane's key is two row intervals [s, e): row q is masked by one iff
-// (unsigned)(q - s) < (unsigned)max(e - s, 0), one subtraction and one compare per element with the interval's
-// length formed once per unit (off_a, off_b: first row of the block's registers - s).
+// in_interval(q - s, length), one addition and one compare per element with the interval's length formed once
+// per unit (off_a, off_b: where the first row of the block's registers lies from the intervals' starts).
 template <bool MASK>
 __device__ __forceinline__ void dkdv_stage_a(const f32x16& s, const f32x16& dp, float (&t)[16],
                                              float (&u)[16], const f32x4 (&l4)[4], int e0,
-                                             int cnt, float sc, int off_a, unsigned len_a, int off_b, unsigned len_b) {
+                                             int cnt, float sc, unsigned off_a, unsigned len_a, unsigned off_b,
+                                             unsigned len_b) {
 #pragma unroll
   for (int r = e0; r < e0 + cnt; ++r) {
     float x = s[r];
     if (MASK) {
-      const int dr = 8 * (r >> 2) + (r & 3);   // register r is row 8*(r/4) + 4*g + r%4 of the block; 4*g is in the offsets
-      const bool hit = ((unsigned)(off_a + dr) < len_a) | ((unsigned)(off_b + dr) < len_b);
+      const unsigned dr = 8 * (r >> 2) + (r & 3);   // register r is row 8*(r/4) + 4*g + r%4 of the block; 4*g is in the offsets
+      const bool hit = in_interval(off_a + dr, len_a) | in_interval(off_b + dr, len_b);
       if (hit) x = -INFINITY;
     }
     t[r] = __builtin_fmaf(x, sc, -l4[r >> 2][r & 3]);
@@ -715,8 +717,9 @@ __device__ __forceinline__ void dkdv_tile(const char* qs, const float* vec_s, co
         if (stage == 0) {
           if (e0 % 4 == 0 && e0 / 4 + 1 < 4) vec_group(qb, e0 / 4 + 1);
           if (qb == 0 && e0 + EPS == 16) vec_group(1, 0);
-          dkdv_stage_a<MASK>(sb[qb], pb[qb], tq[qb], uq[qb], l4[qb], e0, EPS, sc, r0 + 32 * qb + 4 * g - s_a, len_a,
-                             r0 + 32 * qb + 4 * g - s_b, len_b);
+          const int row = r0 + 32 * qb + 4 * g;
+          dkdv_stage_a<MASK>(sb[qb], pb[qb], tq[qb], uq[qb], l4[qb], e0, EPS, sc, interval_offset(row, s_a), len_a,
+                             interval_offset(row, s_b), len_b);
         } else if (stage == 1) {
 #pragma unroll
           for (int r = e0; r < e0 + EPS; ++r) tq[qb][r] = fast_exp2(tq[qb][r]);
@@ -950,10 +953,8 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
     settle(b_lte);
     settle(b_uts);
     settle(b_ute);
-    // lengths of the key's two masked row intervals (0 for an empty one), for the element mask's compare
-    // (any int32 bounds: the difference is formed in unsigned arithmetic, it may not fit an int)
-    const unsigned len_lt = b_lte > b_lts ? (unsigned)b_lte - (unsigned)b_lts : 0u;
-    const unsigned len_ut = b_ute > b_uts ? (unsigned)b_ute - (unsigned)b_uts : 0u;
+    // lengths of the key's two masked row intervals, for the element mask's compare
+    const unsigned len_lt = interval_length(b_lts, b_lte), len_ut = interval_length(b_uts, b_ute);
     async_wait<S == 2 ? 0 : (C::NSTAGE - 2) * C::NC>();
     barrier_nofence();
     int e_cur = __builtin_amdgcn_readfirstlane(list[min(grp, n_live - 1)]);
