@@ -231,6 +231,18 @@ int flashmask_unit_queues(int pass, const int32_t* lts, const int32_t* lte, cons
  * tiles.  Host-only. */
 int flashmask_tile_shape(int pass, int d, int* block_r, int* block_c);
 
+/* How a tile loop's work is cut into workgroups. */
+enum {
+  FM_CUT_QUEUED = 0, /* units of 128 rows (dK/dV: 128 keys) off the unit queues */
+  FM_CUT_DIRECT = 1, /* the same units without queues and their setup launches */
+  FM_CUT_HALVED = 2, /* units of 64 rows (keys), their tiles shared by two groups of waves; no queues */
+  FM_CUT_PAIRED = 3  /* units of 128 rows, their tiles shared by two groups of waves; no queues */
+};
+/* The cut that a call of this size takes in the given tile loop (FM_PASS_FWD, FM_PASS_BWD_DQ or
+ * FM_PASS_BWD_DKDV) on a GPU of `compute_units` compute units (0: the current device).  Exported, like
+ * the queues above, so that tests and benchmarks know what they run.  Host-only. */
+int flashmask_work_cut(int pass, int B, int H, int H_kv, int N, int d, int compute_units, int* cut);
+
 /* Static, human-readable text for an FM_* code. */
 const char* flashmask_strerror(int code);
 

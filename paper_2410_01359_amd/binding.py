@@ -11,6 +11,7 @@ import os
 import torch
 
 FM_PASS_FWD, FM_PASS_BWD_DKDV, FM_PASS_BWD_DQ, FM_PASS_BWD = 0, 1, 2, 3
+FM_CUT_QUEUED, FM_CUT_DIRECT, FM_CUT_HALVED, FM_CUT_PAIRED = 0, 1, 2, 3
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB = None
@@ -62,6 +63,8 @@ def load_library() -> ctypes.CDLL:
     lib.flashmask_classify.argtypes = [ip, i, i, i, i, vp, vp]
     lib.flashmask_tile_shape.restype = i
     lib.flashmask_tile_shape.argtypes = [i, i, ctypes.POINTER(i), ctypes.POINTER(i)]
+    lib.flashmask_work_cut.restype = i
+    lib.flashmask_work_cut.argtypes = [i, i, i, i, i, i, i, ctypes.POINTER(i)]
     lib.flashmask_strerror.restype = ctypes.c_char_p
     lib.flashmask_strerror.argtypes = [i]
     lib.flashmask_last_hip_error.restype = ctypes.c_char_p
@@ -116,6 +119,14 @@ def flashmask_tile_shape(pass_id: int, d: int):
     br, bc = ctypes.c_int(0), ctypes.c_int(0)
     _check(load_library().flashmask_tile_shape(pass_id, d, ctypes.byref(br), ctypes.byref(bc)), "flashmask_tile_shape")
     return br.value, bc.value
+
+
+def flashmask_work_cut(pass_id: int, B: int, H: int, H_kv: int, N: int, d: int, compute_units: int = 0) -> int:
+    """FM_CUT_* that a tile loop's work takes for this size (compute_units = 0: on the current device)."""
+    cut = ctypes.c_int(0)
+    _check(load_library().flashmask_work_cut(pass_id, B, H, H_kv, N, d, compute_units, ctypes.byref(cut)),
+           "flashmask_work_cut")
+    return cut.value
 
 
 def flashmask_workspace_bytes(pass_id: int, B: int, H: int, N: int, d: int) -> int:

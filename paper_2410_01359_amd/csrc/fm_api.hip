@@ -95,6 +95,17 @@ PassSpace pass_space(int B, int H, int N, int block_r, int block_c, bool row_uni
   return s;
 }
 
+// How the loops cut their work on `cus` compute units.
+FmUnits fwd_units(int B, int H, int N, int d, int cus) {
+  return fm_row_units((long long)B * H * (padded_len(N) / FM_FWD_BR), fm_fwd_per_cu(d), d, padded_len(N), cus);
+}
+FmUnits dq_units(int B, int H, int N, int d, int cus) {
+  return fm_row_units((long long)B * H * (padded_len(N) / FM_DQ_BR), FM_DQ_PER_CU, d, padded_len(N), cus);
+}
+FmUnits dkdv_units(int B, int H, int Hk, int N, int d, int cus) {
+  return fm_key_units((long long)B * Hk * (padded_len(N) / FM_DKDV_BC), H / Hk, d, padded_len(N), cus);
+}
+
 }  // namespace
 
 extern "C" {
@@ -157,6 +168,19 @@ int flashmask_tile_shape(int pass, int d, int* block_r, int* block_c) {
   }
 }
 
+int flashmask_work_cut(int pass, int B, int H, int H_kv, int N, int d, int compute_units, int* cut) {
+  if (!cut) return FM_ERR_NULL;
+  if (int rc = check_shape(B, H, N, d)) return rc;
+  if (H_kv <= 0 || H % H_kv != 0) return FM_ERR_SHAPE;
+  const int cus = compute_units > 0 ? compute_units : fm_compute_units();
+  switch (pass) {
+    case FM_PASS_FWD: *cut = fwd_units(B, H, N, d, cus); return FM_OK;
+    case FM_PASS_BWD_DQ: *cut = dq_units(B, H, N, d, cus); return FM_OK;
+    case FM_PASS_BWD_DKDV: *cut = dkdv_units(B, H, H_kv, N, d, cus); return FM_OK;
+    default: return FM_ERR_ARG;
+  }
+}
+
 size_t flashmask_workspace_bytes(int pass, int B, int H, int N, int d) {
   if (check_shape(B, H, N, d) != FM_OK) return 0;
   const int Np = padded_len(N);
@@ -210,7 +234,7 @@ static int fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
   int* range = (int*)(ws + sp.range);
   int* order = (int*)(ws + sp.order);
   FmFwdArgs a;
-  a.units = fm_row_units((long long)B * H * (Np / FM_FWD_BR), fm_fwd_per_cu(d), d, Np);
+  a.units = fwd_units(B, H, N, d, fm_compute_units());
   if (a.units == FM_QUEUED) {
     e = fm_launch_setup(lts, lte, uts, ute, B, H, Hk, N, Np, FmSetup{FM_FWD_BR, FM_FWD_BC, minmax, work, range, order},
                         false, stream);
@@ -341,8 +365,8 @@ static int bwd_impl(const void* q, const void* k, const void* v, const void* out
                      (int*)(ws + sq.order)};
   const FmSetup cols{FM_DKDV_BR, FM_DKDV_BC, (int*)(ws + skv.minmax), (int*)(ws + skv.work), (int*)(ws + skv.range),
                      (int*)(ws + skv.order)};
-  a.units_dq = fm_row_units((long long)B * H * (Np / FM_DQ_BR), FM_DQ_PER_CU, d, Np);
-  a.units_dkdv = fm_key_units((long long)B * Hk * (Np / FM_DKDV_BC), H / Hk, d, Np);
+  a.units_dq = dq_units(B, H, N, d, fm_compute_units());
+  a.units_dkdv = dkdv_units(B, H, Hk, N, d, fm_compute_units());
   // queues for dK/dV come with queues for dQ in the same launch
   if (a.units_dkdv == FM_QUEUED && a.units_dq == FM_DIRECT) a.units_dq = FM_QUEUED;
   const bool queue_dq = a.units_dq == FM_QUEUED, queue_dkdv = a.units_dkdv == FM_QUEUED;

@@ -100,11 +100,11 @@ constexpr int fm_dkdv_per_cu(int d) { return d == 64 ? 2 : 1; }
 // part of their time.  Training step, direct / queued, causal, documents, window: d = 128, N = 512, 1024 units 178 / 183,
 // 187 / 191, 167 / 176 us, 2048 units 368 / 363, 397 / 351, 352 / 353; d = 64, N = 512, 2048 units 191 / 222, 223 / 222,
 // 182 / 221, 4096 units 398 / 435, 451 / 436, 386 / 434; N = 1024, 1024 units 159 / 160, 171 / 160, 105 / 123.
-inline bool fm_short_direct(long long units, int d, int N) {
-  return N <= 512 && units <= (d == 64 ? 8ll : 4ll) * fm_compute_units();
+inline bool fm_short_direct(long long units, int d, int N, long long cus) {
+  return N <= 512 && units <= (d == 64 ? 8 : 4) * cus;
 }
-// The cut of a row-parallel loop over `units` units of 128 rows, `per_cu` workgroups of which a compute unit holds, at
-// sequence length N.  What is weighed: the setup launch (4 us up to N = 4096, 8 us beyond), the longest chain of tiles
+// The cut of a row-parallel loop over `units` units of 128 rows, `per_cu` workgroups of which one of `cus` compute units
+// holds, at sequence length N.  What is weighed: the setup launch (4 us up to N = 4096, 8 us beyond), the longest chain of tiles
 // (halved by two groups), waves per SIMD, and building the list from the bound vectors instead of the table (which
 // grows with N).  Loop times in us, masks causal / causal documents of 700 tokens / both-sided ones / window 256:
 //   d = 128  128 units, N = 2048   halved 30 / 37 / 40 / 14, queued 41 / 56 / 59 / 17; N = 16384 causal 190, queued 261
@@ -115,15 +115,14 @@ inline bool fm_short_direct(long long units, int d, int N) {
 //   d = 64   256 units, N = 4096   halved 39 / 37 / 41 / 15, queued 54 / 60 / 67 / 16
 //            512 units, N = 512    direct 21 / 24 / 25 / 20, halved 24 / 29 / 30 / 24, queued 21 / 23 / 25 / 21
 //            512 units, N = 8192   halved 112 / 47 / 63 / 33, queued 116 / 59 / 73 / 21; N = 16384 causal 267, queued 219
-inline FmUnits fm_row_units(long long units, int per_cu, int d, int N) {
-  const long long cus = fm_compute_units();
+inline FmUnits fm_row_units(long long units, int per_cu, int d, int N, long long cus) {
   if (d == 128) {
     if (2 * units <= cus) return FM_DIRECT_HALVED;
     if (units <= cus) return FM_DIRECT_PAIRED;
-    return (units <= per_cu * cus && N <= 2048) || fm_short_direct(units, d, N) ? FM_DIRECT : FM_QUEUED;
+    return (units <= per_cu * cus && N <= 2048) || fm_short_direct(units, d, N, cus) ? FM_DIRECT : FM_QUEUED;
   }
   if (units <= cus) return FM_DIRECT_HALVED;
-  if ((units <= per_cu * cus && N <= 1024) || fm_short_direct(units, d, N)) return FM_DIRECT;
+  if ((units <= per_cu * cus && N <= 1024) || fm_short_direct(units, d, N, cus)) return FM_DIRECT;
   return units <= 2 * cus && N <= 8192 ? FM_DIRECT_HALVED : FM_QUEUED;
 }
 // The same for the dK/dV loop over units of 128 keys of `group` query heads each (a chain `group` times as long; lists
@@ -136,11 +135,11 @@ inline FmUnits fm_row_units(long long units, int per_cu, int d, int N) {
 //            256 units of 4 query heads, N = 2048, shared questions: halved 126, direct 163, queued 164
 //   d = 64   512 units, N = 1024   direct 36 / 35 / 48 / 24, halved 36 / 35 / 50 / 28
 //            512 units, N = 4096   halved 85 / 48 / 83 / 28, direct 108 / 63 / 99 / 25, queued 87 / 50 / 86 / 26
-inline FmUnits fm_key_units(long long units, int group, int d, int N) {
-  const long long slots = (long long)fm_dkdv_per_cu(d) * fm_compute_units();
+inline FmUnits fm_key_units(long long units, int group, int d, int N, long long cus) {
+  const long long slots = fm_dkdv_per_cu(d) * cus;
   if (2 * units <= slots) return FM_DIRECT_HALVED;
   if (units <= slots) return (long long)N * group <= (d == 128 ? 2048 : 1024) ? FM_DIRECT : FM_DIRECT_HALVED;
-  return (d == 128 && units <= 2 * slots && N <= 8192) || fm_short_direct(units, d, N) ? FM_DIRECT : FM_QUEUED;
+  return (d == 128 && units <= 2 * slots && N <= 8192) || fm_short_direct(units, d, N, cus) ? FM_DIRECT : FM_QUEUED;
 }
 // Tile shapes (rows x key columns) each pass classifies at.
 constexpr int FM_FWD_BR = 128, FM_FWD_BC = 64;

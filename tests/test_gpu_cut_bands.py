@@ -1,0 +1,59 @@
+"""GPU: the bands of sizes between the cuts of the work that the small sizes of the other tests do not reach -- queues of
+one round, queues for one of the backward's loops only, long sequences of few units.  Each size names the cuts it is
+there for, so that a line that moves shows here.  The same tensors in every head: one head against the oracle on sampled
+rows and columns, all others bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2410_01359_amd as fm
+import workloads
+from gpu_util import bf16_to_np, check_bwd, check_fwd, f64, to_device
+from oracle import flashmask_oracle as orc
+from test_gpu_configs import sample_cols, sample_rows
+
+Q, D, H2, P2 = fm.FM_CUT_QUEUED, fm.FM_CUT_DIRECT, fm.FM_CUT_HALVED, fm.FM_CUT_PAIRED
+
+# H, N, d and the cuts of forward, dQ and dK/dV on 256 compute units
+BANDS = [
+    (16, 4096, 128, (Q, Q, D)),     # one round of 128-row units off the queues, setup in one launch, for the rows only
+    (15, 4000, 128, (Q, Q, D)),
+    (8, 8192, 128, (Q, Q, D)),      # the same with the setup in three launches
+    (20, 2500, 128, (Q, Q, D)),
+    (3, 16320, 64, (Q, Q, H2)),     # d = 64: queued dQ with halved keys
+    (4, 16384, 64, (Q, Q, H2)),
+    (1, 24576, 128, (P2, P2, H2)),
+    (1, 40960, 64, (Q, Q, H2)),
+]
+IDS = [f"{H}x{N}-d{d}" for H, N, d, _ in BANDS]
+
+
+@pytest.mark.parametrize("H,N,d,cuts", BANDS, ids=IDS)
+def test_band_takes_its_cuts(H, N, d, cuts):
+    passes = (fm.FM_PASS_FWD, fm.FM_PASS_BWD_DQ, fm.FM_PASS_BWD_DKDV)
+    assert tuple(fm.flashmask_work_cut(p, 1, H, H, N, d, compute_units=256) for p in passes) == cuts
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,N,d,cuts", BANDS, ids=IDS)
+def test_band(H, N, d, cuts):
+    w = workloads.small_workload("causal_document", N, seed=H + N, B=1, H=1, d=d)
+    bits, dev, vecs = to_device(w)
+    x = {n: dev[n].expand(1, H, N, d).contiguous() for n in ("q", "k", "v", "dout")}
+    out, lse = fm.flashmask_fwd(x["q"], x["k"], x["v"], *vecs, w.scale)
+    dq, dk, dv = fm.flashmask_bwd(x["q"], x["k"], x["v"], out, lse, x["dout"], *vecs, w.scale)
+    torch.cuda.synchronize()
+    for name, t in (("out", out), ("lse", lse), ("dq", dq), ("dk", dk), ("dv", dv)):
+        assert torch.equal(t, t[:, :1].expand_as(t)), f"{name}: heads differ"
+        assert torch.isfinite(t).all(), f"{name} has non-finite values"
+    rng = np.random.default_rng(H + N)
+    vec = w.vectors[0]
+    rows, cols = sample_rows(w, vec, rng, 48), sample_cols(w, vec, rng, 2048)
+    host = [f64(bits[n][0, 0]) for n in ("q", "k", "v", "dout")]
+    what = f"H={H} N={N} d={d}"
+    ro, rl = orc.forward_rows(*host[:3], *vec, w.scale, rows)
+    check_fwd(bf16_to_np(out[0, 0])[rows], lse[0, 0].cpu().numpy()[rows], ro, rl, what)
+    check_bwd(bf16_to_np(dq[0, 0])[rows], orc.backward_rows(*host, *vec, w.scale, rows), "dq", what)
+    rdk, rdv = orc.backward_cols(*host, *vec, w.scale, cols)
+    check_bwd(bf16_to_np(dk[0, 0])[cols], rdk, "dk", what)
+    check_bwd(bf16_to_np(dv[0, 0])[cols], rdv, "dv", what)

@@ -1,5 +1,6 @@
-"""GPU: launches over the unit queues at the unit counts where the handing out of tickets changes: exactly as many units
-as run at once, a few more, slices (batch row, head) that do not fill a round of eight queues, grouped K/V heads."""
+"""GPU: launches over the unit queues at the unit counts where the handing out of tickets changes: a few more units than
+run at once, slices (batch row, head) that do not fill a round of eight queues.  (Launches of one round, where every
+workgroup has its ticket in its number: test_gpu_cut_bands.py.)"""
 import numpy as np
 import pytest
 import torch

@@ -91,3 +91,13 @@ def test_workspace_of_a_ragged_length_keeps_its_reserve(B, H, N, d):
     for which in (fm.FM_PASS_FWD, fm.FM_PASS_BWD):
         extra = fm.flashmask_workspace_bytes(which, B, H, N, d) - fm.flashmask_workspace_bytes(which, B, H, padded, d)
         assert extra == -(-16 * B * padded // 256) * 256
+
+
+def test_work_cut_checks_its_arguments():
+    import paper_2410_01359_amd as fm
+    ok = (fm.FM_PASS_FWD, 1, 8, 8, 1024, 128, 256)
+    assert fm.flashmask_work_cut(*ok) == fm.FM_CUT_HALVED
+    for at, bad in ((0, fm.FM_PASS_BWD), (1, 0), (2, -1), (3, 3), (4, 0), (5, 96)):
+        with pytest.raises(fm.FlashMaskError):
+            fm.flashmask_work_cut(*ok[:at], bad, *ok[at + 1:])
+    assert fm.load_library().flashmask_work_cut(*ok, None) == -1
