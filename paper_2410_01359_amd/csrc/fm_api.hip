@@ -103,7 +103,7 @@ FmUnits dq_units(int B, int H, int N, int d, int cus) {
   return fm_row_units((long long)B * H * (padded_len(N) / FM_DQ_BR), FM_DQ_PER_CU, d, padded_len(N), cus);
 }
 FmUnits dkdv_units(int B, int H, int Hk, int N, int d, int cus) {
-  return fm_key_units((long long)B * Hk * (padded_len(N) / FM_DKDV_BC), H / Hk, d, padded_len(N), cus);
+  return fm_key_units((long long)B * Hk * (padded_len(N) / FM_DKDV_BC), H / Hk, d, N, cus);
 }
 
 }  // namespace

@@ -135,11 +135,31 @@ inline FmUnits fm_row_units(long long units, int per_cu, int d, int N, long long
 //            256 units of 4 query heads, N = 2048, shared questions: halved 126, direct 163, queued 164
 //   d = 64   512 units, N = 1024   direct 36 / 35 / 48 / 24, halved 36 / 35 / 50 / 28
 //            512 units, N = 4096   halved 85 / 48 / 83 / 28, direct 108 / 63 / 99 / 25, queued 87 / 50 / 86 / 26
+// Halved units of a full round copy each row tile twice as often and run in two rounds.  That pays while the longest
+// chain decides and stops paying where the sum of the work does, which for causal masks is at long sequences.  Backward
+// in us, causal / causal documents / documents / window / shared questions:
+//   d = 128  192 units, N = 12288  halved 464 / 112 / 178 / 52 / 225, queued 452 / 148 / 190 / 54 / 231
+//            256 units, N = 16384  halved 677 / 127 / 170 / 58 / 296, queued 647 / 157 / 180 / 63 / 294
+//            256 units, N = 32768  halved 1460 / 157 / 181 / 65 / 231, queued 1313 / 191 / 225 / 68 / 280
+//   d = 64   512 units, N = 32768  halved 1282 / 137 / 191 / 60 / 190, queued 1077 / 167 / 202 / 58 / 242;
+//                                  N = 65536 halved 2714 / 177 / 222 / 61 / 206, queued 2121 / 190 / 226 / 58 / 253
+// The host does not know the mask.  The line is where causal masks stop gaining; documents would gain beyond it.
+// A ragged length has a key block whose padded columns leave nearly every tile of the sequence partially masked: one
+// chain of full length whatever the mask.  Halving halves it (512 units, d = 64, N = 32707, causal / causal documents:
+// halved 1306 / 550, queued 1379 / 861; d = 128, 256 units 1545 / 697 and 1703 / 1133), the queues start with it, direct
+// units of two rounds end with it (512 units, d = 128: N = 4035 direct 384 / 290, queued 326 / 262, N = 8131 711 / 395
+// and 618 / 371; N = 2887 272 / 201 and 283 / 208).
 inline FmUnits fm_key_units(long long units, int group, int d, int N, long long cus) {
   const long long slots = fm_dkdv_per_cu(d) * cus;
+  const int padded = (N + 127) / 128 * 128;
+  const bool ragged = N != padded;
   if (2 * units <= slots) return FM_DIRECT_HALVED;
-  if (units <= slots) return (long long)N * group <= (d == 128 ? 2048 : 1024) ? FM_DIRECT : FM_DIRECT_HALVED;
-  return (d == 128 && units <= 2 * slots && N <= 8192) || fm_short_direct(units, d, N, cus) ? FM_DIRECT : FM_QUEUED;
+  if (units <= slots) {
+    if ((long long)padded * group <= (d == 128 ? 2048 : 1024)) return FM_DIRECT;
+    return ragged || N <= 12288 ? FM_DIRECT_HALVED : FM_QUEUED;
+  }
+  return (d == 128 && units <= 2 * slots && N <= (ragged ? 3072 : 8192)) || fm_short_direct(units, d, N, cus) ? FM_DIRECT
+                                                                                                              : FM_QUEUED;
 }
 // Tile shapes (rows x key columns) each pass classifies at.
 constexpr int FM_FWD_BR = 128, FM_FWD_BC = 64;
