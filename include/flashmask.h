@@ -242,6 +242,9 @@ enum {
  * FM_PASS_BWD_DKDV) on a GPU of `compute_units` compute units (0: the current device).  Exported, like
  * the queues above, so that tests and benchmarks know what they run.  Host-only. */
 int flashmask_work_cut(int pass, int B, int H, int H_kv, int N, int d, int compute_units, int* cut);
+/* Launches that build the tables and queues of a forward (FM_PASS_FWD) or a whole backward (FM_PASS_BWD)
+ * of this size before its tile loops: 0 where no loop is queued, else 1 or 3.  Host-only. */
+int flashmask_setup_launches(int pass, int B, int H, int H_kv, int N, int d, int compute_units, int* launches);
 
 /* Static, human-readable text for an FM_* code. */
 const char* flashmask_strerror(int code);

@@ -65,6 +65,8 @@ def load_library() -> ctypes.CDLL:
     lib.flashmask_tile_shape.argtypes = [i, i, ctypes.POINTER(i), ctypes.POINTER(i)]
     lib.flashmask_work_cut.restype = i
     lib.flashmask_work_cut.argtypes = [i, i, i, i, i, i, i, ctypes.POINTER(i)]
+    lib.flashmask_setup_launches.restype = i
+    lib.flashmask_setup_launches.argtypes = [i, i, i, i, i, i, i, ctypes.POINTER(i)]
     lib.flashmask_strerror.restype = ctypes.c_char_p
     lib.flashmask_strerror.argtypes = [i]
     lib.flashmask_last_hip_error.restype = ctypes.c_char_p
@@ -127,6 +129,14 @@ def flashmask_work_cut(pass_id: int, B: int, H: int, H_kv: int, N: int, d: int, 
     _check(load_library().flashmask_work_cut(pass_id, B, H, H_kv, N, d, compute_units, ctypes.byref(cut)),
            "flashmask_work_cut")
     return cut.value
+
+
+def flashmask_setup_launches(pass_id: int, B: int, H: int, H_kv: int, N: int, d: int, compute_units: int = 0) -> int:
+    """Launches before the tile loops of a forward (FM_PASS_FWD) or a whole backward (FM_PASS_BWD) of this size."""
+    launches = ctypes.c_int(0)
+    _check(load_library().flashmask_setup_launches(pass_id, B, H, H_kv, N, d, compute_units, ctypes.byref(launches)),
+           "flashmask_setup_launches")
+    return launches.value
 
 
 def flashmask_workspace_bytes(pass_id: int, B: int, H: int, N: int, d: int) -> int:

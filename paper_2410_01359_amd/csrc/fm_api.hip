@@ -181,6 +181,18 @@ int flashmask_work_cut(int pass, int B, int H, int H_kv, int N, int d, int compu
   }
 }
 
+int flashmask_setup_launches(int pass, int B, int H, int H_kv, int N, int d, int compute_units, int* launches) {
+  if (!launches) return FM_ERR_NULL;
+  if (int rc = check_shape(B, H, N, d)) return rc;
+  if (H_kv <= 0 || H % H_kv != 0) return FM_ERR_SHAPE;
+  if (pass != FM_PASS_FWD && pass != FM_PASS_BWD) return FM_ERR_ARG;
+  const int cus = compute_units > 0 ? compute_units : fm_compute_units();
+  const int queued = pass == FM_PASS_FWD ? fwd_units(B, H, N, d, cus) == FM_QUEUED
+                                         : (dq_units(B, H, N, d, cus) == FM_QUEUED) + (dkdv_units(B, H, H_kv, N, d, cus) == FM_QUEUED);
+  *launches = queued ? fm_setup_launches(queued, B, H_kv, padded_len(N), cus) : 0;
+  return FM_OK;
+}
+
 size_t flashmask_workspace_bytes(int pass, int B, int H, int N, int d) {
   if (check_shape(B, H, N, d) != FM_OK) return 0;
   const int Np = padded_len(N);

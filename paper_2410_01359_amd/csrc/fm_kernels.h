@@ -177,8 +177,26 @@ struct FmSetup {
   int* range;    // int[2 * B * T]: first live block and one past the last live block of every unit (0, 0 if none)
   int* order;    // fm_order_bytes(B * H * T) bytes: slot records {unit, first, last, 0}, then the counters (zeroed here)
 };
+// Workgroups of the queue-building launch: per queue, one for every FM_QUEUE_CHUNK whole slices and one
+// for its part of the slices left over, its unused slots and its counter.
+inline int fm_order_grid(int B, int H) {
+  return FM_QUEUES * (((B * H) / FM_QUEUES + FM_QUEUE_CHUNK - 1) / FM_QUEUE_CHUNK + 1);
+}
+
+// Launches of the setup of one pass, or of the backward's two together, with B rows of H slices (K/V heads) at the padded
+// length Np: one launch (setup_kernel) or three (tables, work, queues).  One launch repeats the table in every workgroup.
+// Training step, three -> one in each direction, d = 64 / 128: N = 512 68 -> 58 / 78 -> 70 us, N = 2048 118 -> 109 /
+// 153 -> 146 us, N = 4096 no difference within 3 us; with more passes over the columns (the work grows with N^2 as well)
+// it lost 4 us at N = 8192 and 10 to 15 us at N = 16384.  With more workgroups of 1024 threads than compute units the
+// repetition costs more than the launches: forward / backward, one | three launches, d = 128: 200 | 400 workgroups,
+// N = 512 74 / 203 | 77 / 201 us, N = 1024 178 / 471 | 180 / 467; 264 | 528, N = 256 46 / 120 | 46 / 118; 1032 | 2064,
+// N = 128 89 / 239 | 79 / 219, N = 512 349 / 935 | 340 / 916; 72 | 144, N = 1024 74 / 182 | 76 / 185.
+constexpr int FM_ONE_LAUNCH_LENGTH = 4096;
+inline int fm_setup_launches(int passes, int B, int H, int Np, int cus) {
+  return Np <= FM_ONE_LAUNCH_LENGTH && passes * fm_order_grid(B, H) <= cus ? 1 : 3;
+}
 // A pass's whole setup: table, work and live range of every unit, unit queues.  cols: the units are key blocks (they
-// count K/V heads), else row blocks.  Short sequences take one launch, which writes minmax and order only.
+// count K/V heads), else row blocks.  One launch writes minmax and order only.
 hipError_t fm_launch_setup(const int* lts, const int* lte, const int* uts, const int* ute, int B, int H, int Hk, int N,
                            int Np, const FmSetup& pass, bool cols, hipStream_t stream);
 // The same for the dQ pass `rows` and the dK/dV pass `cols` together.

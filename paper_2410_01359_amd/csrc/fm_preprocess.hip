@@ -215,12 +215,6 @@ __host__ __device__ inline int fm_queue_of(int s, int i, int whole, int r) {
   }
   return i & 7;
 }
-// Workgroups of the queue-building launch: per queue, one for every FM_QUEUE_CHUNK whole slices and one
-// for its part of the slices left over, its unused slots and its counter.
-static inline int fm_order_grid(int B, int H) {
-  return FM_QUEUES * (((B * H) / FM_QUEUES + FM_QUEUE_CHUNK - 1) / FM_QUEUE_CHUNK + 1);
-}
-
 // work and range are indexed [batch row][block]; a unit is (batch row, head, block).
 // A queue holds its whole slices in groups of FM_QUEUE_CHUNK, one group after the other, and the
 // shared slices last: the units that run at the same time then belong to few slices and share their
@@ -358,14 +352,11 @@ __global__ __launch_bounds__(1024) void order2_kernel(OrderJob a, int blocks_a, 
     order_from_arrays(b, blockIdx.x - blocks_a, gridDim.x - blocks_a);
 }
 
-// The whole setup of a pass (or of the backward's two) in one launch, for sequences of at most kOneLaunchLength: every
-// queue-building workgroup forms the table and the work of its slices' batch rows itself, in LDS, from the bound
-// vectors.  At these lengths that is one 16-byte load per thread and vector and at most 32 x 64 tile classes, while
-// each launch of the three-launch form (tables, work, queues) is bound by its start and one round trip to memory.
-// Training step, three launches -> this one in each direction, d = 64 / 128: N = 512 68 -> 58 / 78 -> 70 us, N = 2048
-// 118 -> 109 / 153 -> 146 us, N = 4096 no difference within 3 us; with more passes over the columns (the work grows
-// with N^2 as well) it lost 4 us at N = 8192 and 10 to 15 us at N = 16384.
-constexpr int kOneLaunchLength = 4096;
+// The whole setup of a pass (or of the backward's two) in one launch, for sequences of at most FM_ONE_LAUNCH_LENGTH and
+// few slices (fm_setup_launches): every queue-building workgroup forms the table and the work of its slices' batch rows
+// itself, in LDS, from the bound vectors.  At these lengths that is one 16-byte load per thread and vector and at most
+// 32 x 64 tile classes, while each launch of the three-launch form (tables, work, queues) is bound by its start and one
+// round trip to memory.
 struct SetupJob {
   OrderJob order;          // work and range are not used
   int block_r, block_c;
@@ -380,7 +371,7 @@ struct SetupArgs {
   SetupJob job[2];
 };
 __global__ __launch_bounds__(1024) void setup_kernel(SetupArgs a) {
-  constexpr int kMaxTiles = kOneLaunchLength / 64, kMaxUnits = kOneLaunchLength / 128, kMaxRows = FM_QUEUES - 1;
+  constexpr int kMaxTiles = FM_ONE_LAUNCH_LENGTH / 64, kMaxUnits = FM_ONE_LAUNCH_LENGTH / 128, kMaxRows = FM_QUEUES - 1;
   __shared__ i32x4 block_full[kMaxTiles];    // of a key block: LTS max, LTE min, UTS max, UTE min (what T_FULLY asks for)
   __shared__ int work[kMaxRows * kMaxUnits], first[kMaxRows * kMaxUnits], last[kMaxRows * kMaxUnits];
   const bool second = (int)blockIdx.x >= a.blocks_first;
@@ -414,7 +405,7 @@ __global__ __launch_bounds__(1024) void setup_kernel(SetupArgs a) {
     int* const out = (tail ? g == 0 && b * heads >= whole : b * heads == (r ? s1 : s0)) ? job.minmax + (size_t)b * 8 * t_c
                                                                                         : nullptr;
     // block_c / 4 lanes take a key block, four columns each
-    static_assert(kOneLaunchLength == 4 * 1024, "four columns per thread");
+    static_assert(FM_ONE_LAUNCH_LENGTH == 4 * 1024, "four columns per thread");
     const int lanes = job.block_c / 4, j = tid / lanes, key = tid * 4;
     i32x4 x[4];
 #pragma unroll
@@ -522,7 +513,7 @@ static SetupJob setup_job(const FmSetup& p, int B, int H, int Hk, int N, int Np,
 hipError_t fm_launch_setup(const int* lts, const int* lte, const int* uts, const int* ute, int B, int H, int Hk, int N,
                            int Np, const FmSetup& pass, bool cols, hipStream_t stream) {
   const int grid = fm_order_grid(B, Hk);
-  if (Np <= kOneLaunchLength) {
+  if (fm_setup_launches(1, B, Hk, Np, fm_compute_units()) == 1) {
     SetupArgs a{{lts, lte, uts, ute}, N, Np, grid, {setup_job(pass, B, H, Hk, N, Np, cols), {}}};
     hipLaunchKernelGGL(setup_kernel, dim3(grid), dim3(1024), 0, stream, a);
     return hipGetLastError();
@@ -545,7 +536,7 @@ hipError_t fm_launch_setup(const int* lts, const int* lte, const int* uts, const
 hipError_t fm_launch_bwd_setup(const int* lts, const int* lte, const int* uts, const int* ute, int B, int H, int Hk,
                                int N, int Np, const FmSetup& rows, const FmSetup& cols, hipStream_t stream) {
   const int grid = fm_order_grid(B, Hk);
-  if (Np <= kOneLaunchLength) {
+  if (fm_setup_launches(2, B, Hk, Np, fm_compute_units()) == 1) {
     SetupArgs a{{lts, lte, uts, ute}, N, Np, grid,
                 {setup_job(rows, B, H, Hk, N, Np, false), setup_job(cols, B, H, Hk, N, Np, true)}};
     hipLaunchKernelGGL(setup_kernel, dim3(2 * grid), dim3(1024), 0, stream, a);

@@ -26,6 +26,8 @@ BANDS = [
     (1, 40960, 64, (Q, Q, Q)),
     (2, 12288, 128, (P2, P2, H2)),  # the longest halved keys of a full round
     (1, 24500, 128, (P2, P2, H2)),  # ragged: halved at any length
+    (520, 640, 128, (Q, Q, Q)),     # many slices: setup of short sequences in three launches
+    (1100, 200, 64, (Q, Q, Q)),
 ]
 IDS = [f"{H}x{N}-d{d}" for H, N, d, _ in BANDS]
 
@@ -34,6 +36,18 @@ IDS = [f"{H}x{N}-d{d}" for H, N, d, _ in BANDS]
 def test_band_takes_its_cuts(H, N, d, cuts):
     passes = (fm.FM_PASS_FWD, fm.FM_PASS_BWD_DQ, fm.FM_PASS_BWD_DKDV)
     assert tuple(fm.flashmask_work_cut(p, 1, H, H, N, d, compute_units=256) for p in passes) == cuts
+
+
+# B, H, H_kv, N, d; launches of the forward's and of the backward's setup on 256 compute units
+@pytest.mark.parametrize("B,H,Hk,N,d,launches", [
+    (1, 2, 2, 512, 128, (0, 0)), (16, 4, 4, 2048, 128, (1, 1)), (1, 16, 16, 4096, 128, (1, 1)), (1, 8, 8, 8192, 128, (3, 3)),
+    (1, 24, 24, 4224, 64, (3, 3)),
+    (1, 503, 503, 640, 128, (1, 3)), (1, 504, 504, 640, 128, (3, 3)),       # 256 and 264 workgroups a pass
+    (4, 60, 60, 640, 64, (1, 1)), (4, 62, 62, 640, 64, (1, 3)), (8, 256, 128, 200, 64, (3, 3)), (1, 1500, 1500, 128, 128, (3, 3)),
+])
+def test_setup_launches(B, H, Hk, N, d, launches):
+    assert tuple(fm.flashmask_setup_launches(p, B, H, Hk, N, d, compute_units=256)
+                 for p in (fm.FM_PASS_FWD, fm.FM_PASS_BWD)) == launches
 
 
 @pytest.mark.gpu

@@ -50,10 +50,10 @@ def test_units_lie_within_the_tickets(B, H, N):
 
 
 @pytest.mark.parametrize("B,H,N", [(1, 3, 64), (2, 1, 2049), (9, 1, 700), (7, 3, 1153), (3, 16, 2048), (2, 8, 4096), (1, 2, 4097),
-                                   (2, 9, 4224)])
+                                   (2, 9, 4224), (3, 176, 130), (2, 250, 384)])
 @pytest.mark.parametrize("kind", ["document", "random_intervals", "sliding_window"])
 def test_records_on_both_sides_of_the_one_launch_setup(kind, B, H, N):
-    """Every unit's live range is what Equation 4 gives, in the one-launch setup (N <= 4096) and beyond it."""
+    """Every unit's live range is what Equation 4 gives, in the one-launch setup (N <= 4096, few slices) and beyond it."""
     w = workloads.small_workload(kind, N, seed=B + H + N, B=B, H=H, d=64)
     vecs = [torch.from_numpy(v).cuda() for v in w.stacked_vectors()]
     n_pad = -(-N // 128) * 128
