@@ -379,8 +379,6 @@ static int bwd_impl(const void* q, const void* k, const void* v, const void* out
                      (int*)(ws + skv.order)};
   a.units_dq = dq_units(B, H, N, d, fm_compute_units());
   a.units_dkdv = dkdv_units(B, H, Hk, N, d, fm_compute_units());
-  // queues for dK/dV come with queues for dQ in the same launch
-  if (a.units_dkdv == FM_QUEUED && a.units_dq == FM_DIRECT) a.units_dq = FM_QUEUED;
   const bool queue_dq = a.units_dq == FM_QUEUED, queue_dkdv = a.units_dkdv == FM_QUEUED;
   if (queue_dq && queue_dkdv) {
     e = fm_launch_bwd_setup(lts, lte, uts, ute, B, H, Hk, N, Np, rows, cols, stream);

@@ -38,6 +38,24 @@ def test_band_takes_its_cuts(H, N, d, cuts):
     assert tuple(fm.flashmask_work_cut(p, 1, H, H, N, d, compute_units=256) for p in passes) == cuts
 
 
+def test_queued_keys_never_meet_direct_rows():
+    """The backward's cuts go together as they are: where the keys are queued, the rows are queued, halved or paired."""
+    seen = set()
+    for cus in (32, 104, 256, 304):
+        for d in (64, 128):
+            for N in (1, 128, 500, 512, 513, 1024, 2048, 2176, 3000, 4096, 8192, 8200, 16384, 32768, 131072):
+                for Hk in (1, 2, 7, 16, 64, 255, 600, 2100):
+                    for group in (1, 4):
+                        size = (1, Hk * group, Hk, N, d)
+                        if size[1] * N > 1 << 27:
+                            continue
+                        dq, dkdv = (fm.flashmask_work_cut(p, *size, compute_units=cus)
+                                    for p in (fm.FM_PASS_BWD_DQ, fm.FM_PASS_BWD_DKDV))
+                        seen.add((dq, dkdv))
+                        assert (dq, dkdv) != (D, Q), size
+    assert {(Q, Q), (Q, D), (Q, H2), (P2, Q), (H2, H2), (D, D)} <= seen
+
+
 # B, H, H_kv, N, d; launches of the forward's and of the backward's setup on 256 compute units
 @pytest.mark.parametrize("B,H,Hk,N,d,launches", [
     (1, 2, 2, 512, 128, (0, 0)), (16, 4, 4, 2048, 128, (1, 1)), (1, 16, 16, 4096, 128, (1, 1)), (1, 8, 8, 8192, 128, (3, 3)),
