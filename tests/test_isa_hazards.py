@@ -74,9 +74,18 @@ def _blocks(lines):
     return blocks
 
 
+def _kernels(asm, names):
+    """The functions of the assembly that are instantiations of the named kernel templates."""
+    mangled = "|".join(f"{len(n)}{n}" for n in names)
+    return list(re.finditer(r"^(_ZN2fm(?:%s)I\w+):.*?^\.Lfunc_end\d+:" % mangled, asm, re.S | re.M))
+
+
 def test_dkdv_inline_asm_mfma_wait_states(tmp_path):
-    asm = _assembly(str(tmp_path))
-    kernels = list(re.finditer(r"^(_ZN2fm11dkdv_kernel\w+):.*?^\.Lfunc_end\d+:", asm, re.S | re.M))
+    check_inline_asm_mfma_wait_states(_assembly(str(tmp_path)), "dkdv_kernel")
+
+
+def check_inline_asm_mfma_wait_states(asm, kernel):
+    kernels = _kernels(asm, [kernel])
     assert len(kernels) == 8, "two head dims x ragged x general"
     for m in kernels:
         name = m.group(1)
@@ -150,8 +159,13 @@ def test_lds_window_register_is_written_only_by_the_copy_helpers(tmp_path, sourc
     M0 in a tile-loop kernel: every write of M0, and every global_load_lds, must sit inside an
     inline-assembly block of the generated code."""
     asm = _assembly(str(tmp_path), source)
-    kernels = list(re.finditer(r"^(_ZN2fm\d+(?:fwd|dq|dkdv)_kernel\w+):.*?^\.Lfunc_end\d+:", asm, re.S | re.M))
-    assert len(kernels) == (8 if source == "fm_fwd.hip" else 16)
+    names = ["fwd_kernel"] if source == "fm_fwd.hip" else ["dq_kernel", "dkdv_kernel"]
+    check_lds_window_register(asm, names, 8 * len(names))
+
+
+def check_lds_window_register(asm, names, count):
+    kernels = _kernels(asm, names)
+    assert len(kernels) == count
     for m in kernels:
         inside, copies, windows = False, 0, 0
         for raw in m.group(0).split("\n"):
