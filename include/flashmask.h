@@ -23,7 +23,9 @@
  *   - d must be 64 or 128; N is any positive length (one that is not a multiple
  *     of 128 runs at the next multiple, its extra columns masked); tensor
  *     pointers must be 16-byte aligned.
- *   - Outputs are overwritten in full.
+ *   - Outputs are overwritten in full.  The same call gives the same bits every time.  The order of its fp32 sums
+ *     follows from how the work is cut (flashmask_work_cut), so the results of one (b, h) slice may differ in the
+ *     last places with the B, H and N of the call that computes it and with the GPU's number of compute units.
  *   - Return value: FM_OK (0) or a negative FM_ERR_* code.  Only conditions the
  *     host can see are checked; bound VALUES live on the device and are not
  *     validated (the comparison above is defined for every int32).
@@ -206,7 +208,9 @@ int flashmask_classify(const int32_t* minmax, int B, int N, int block_r, int blo
 
 /*
  * The tile scheduler's output for one pass (not in the paper; it is what balances skewed masks over
- * the chip), exported so that it can be checked like the tables above.  Work units are row blocks
+ * the chip), exported so that it can be checked like the tables above.  It is built here for any size; an
+ * attention call builds and follows it where its loop is queued (flashmask_work_cut), the other cuts have
+ * no queues.  Work units are row blocks
  * (FM_PASS_FWD, FM_PASS_BWD_DQ) or key blocks (FM_PASS_BWD_DKDV) of the pass's tile shape, numbered
  * (b * H + h) * T + block.  They are dealt to 8 queues; slot s belongs to queue s % 8 and holds the
  * (s / 8)-th unit that queue hands out:
@@ -227,8 +231,9 @@ int flashmask_unit_queues(int pass, const int32_t* lts, const int32_t* lte, cons
                           int B, int H, int N, int d, int32_t* records, int* slots,
                           void* workspace, size_t workspace_bytes, void* hip_stream);
 
-/* Tile shape (rows x key columns) at which the given pass classifies and skips
- * tiles.  Host-only. */
+/* Tile shape (rows x key columns) at which the given pass classifies and skips tiles where it is queued
+ * (flashmask_work_cut), and of flashmask_unit_queues.  Of the other cuts, the halved one works on 64 x 64
+ * tiles, and the dQ pass on tiles of 64 keys also at d = 64.  Host-only. */
 int flashmask_tile_shape(int pass, int d, int* block_r, int* block_c);
 
 /* How a tile loop's work is cut into workgroups. */

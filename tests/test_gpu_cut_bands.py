@@ -91,3 +91,26 @@ def test_band(H, N, d, cuts):
     rdk, rdv = orc.backward_cols(*host, *vec, w.scale, cols)
     check_bwd(bf16_to_np(dk[0, 0])[cols], rdk, "dk", what)
     check_bwd(bf16_to_np(dv[0, 0])[cols], rdv, "dv", what)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("H,N,d,cut", [(2, 512, 64, H2), (3, 1500, 128, H2), (24, 1024, 128, P2), (64, 1024, 128, D),
+                                       (160, 1000, 128, Q), (200, 1152, 64, Q)])
+def test_same_call_same_bits(H, N, d, cut):
+    """Every cut repeats itself bit for bit, whatever the workspace holds."""
+    assert fm.flashmask_work_cut(fm.FM_PASS_FWD, 1, H, H, N, d, compute_units=256) == cut
+    w = workloads.small_workload("random_intervals", N, seed=3, B=1, H=H, d=d)
+    _, dev, vecs = to_device(w)
+    x = [dev[n] for n in ("q", "k", "v", "dout")]
+    ws = torch.empty(max(fm.flashmask_workspace_bytes(p, 1, H, N, d) for p in (fm.FM_PASS_FWD, fm.FM_PASS_BWD)),
+                     dtype=torch.uint8, device="cuda")
+    first = None
+    for fill in (0, 255, 127):
+        ws.fill_(fill)
+        out, lse = fm.flashmask_fwd(*x[:3], *vecs, w.scale, workspace=ws)
+        ws.fill_(fill)
+        results = (out, lse, *fm.flashmask_bwd(*x[:3], out, lse, x[3], *vecs, w.scale, workspace=ws))
+        torch.cuda.synchronize()
+        first = first or results
+        for name, a, b in zip(("out", "lse", "dq", "dk", "dv"), first, results):
+            assert torch.equal(a, b), f"{name} differs from the first call"
