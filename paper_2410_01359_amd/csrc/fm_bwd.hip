@@ -862,15 +862,11 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
     kreg[kk] = *(const bf16x8*)(kp + (size_t)key_ld * k_rs + kk * 16 + 8 * g);
     vreg[kk] = *(const bf16x8*)(vp + (size_t)key_ld * v_rs + kk * 16 + 8 * g);
   }
-  const size_t bnd_row = (size_t)b * Nr;
-  int b_lts, b_lte, b_uts, b_ute;
-  if (RAGGED) {
-    b_lts = *bound_or_pad(a.lts + bnd_row, 0, key, Nr), b_lte = *bound_or_pad(a.lte + bnd_row, 1, key, Nr);
-    b_uts = *bound_or_pad(a.uts + bnd_row, 2, key, Nr), b_ute = *bound_or_pad(a.ute + bnd_row, 3, key, Nr);
-  } else {
-    b_lts = a.lts[bnd_row + key], b_lte = a.lte[bnd_row + key];
-    b_uts = a.uts[bnd_row + key], b_ute = a.ute[bnd_row + key];
-  }
+  // Lanes past the last key work on a copy of it, its bounds like its K and V: what they sum is stored nowhere, and
+  // the columns that do not exist keep no tile of a direct unit alive (as columns that mask every row they left every
+  // row block partially masked).
+  const size_t bnd = (size_t)b * Nr + key_ld;
+  int b_lts = a.lts[bnd], b_lte = a.lte[bnd], b_uts = a.uts[bnd], b_ute = a.ute[bnd];
 
   if (DIRECT) {   // the unit's min/max values from its own keys' bounds: over the wave's 32 keys, then over the waves
     const int own[4] = {b_lts, b_lte, b_uts, b_ute};

@@ -2,7 +2,9 @@
 start at addresses that are only 4-byte aligned), and bounds at the ends of the int32 range."""
 import numpy as np
 import pytest
+import torch
 
+import paper_2410_01359_amd as fm
 import workloads
 from test_gpu_backward import compare_all, run_fwd_bwd
 
@@ -30,3 +32,24 @@ def test_bounds_at_the_ends_of_int32(N, d):
     uts[3:50:9] = i32.min                                   # from row 0, as before
     w.vectors = [(lts, lte, uts, ute)]
     compare_all(w, *run_fwd_bwd(w), f"int32 ends N={N} d={d}")
+
+
+@pytest.mark.parametrize("H,N,d", [(1, 24576, 128), (2, 24576, 64)])
+def test_the_columns_that_do_not_exist_add_no_tiles(H, N, d):
+    """dK/dV units that run without queues: a window over one key less takes about as long as over N keys (if the last
+    key block's padded columns counted as masked keys, its chain would be the whole sequence: 2 to 6 times as long)."""
+    times = []
+    for n in (N, N - 1):
+        vecs = [torch.from_numpy(x).cuda()[None] for x in workloads.sliding_window_mask(n, 256)]
+        q, k, v, dout = (torch.randn((1, H, n, d), device="cuda", dtype=torch.bfloat16) for _ in range(4))
+        out, lse = fm.flashmask_fwd(q, k, v, *vecs, d ** -0.5)
+        passes = []
+        for _ in range(8):
+            ends = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            ends[0].record()
+            fm.flashmask_bwd(q, k, v, out, lse, dout, *vecs, d ** -0.5)
+            ends[1].record()
+            ends[1].synchronize()
+            passes.append(ends[0].elapsed_time(ends[1]))
+        times.append(min(passes))
+    assert times[1] < 1.7 * times[0], times
