@@ -136,19 +136,21 @@ inline FmUnits fm_row_units(long long units, int per_cu, int d, int N, long long
 //   d = 64   512 units, N = 1024   direct 36 / 35 / 48 / 24, halved 36 / 35 / 50 / 28
 //            512 units, N = 4096   halved 85 / 48 / 83 / 28, direct 108 / 63 / 99 / 25, queued 87 / 50 / 86 / 26
 // Halved units of a full round copy each row tile twice as often and run in two rounds.  That pays while the longest
-// chain decides and stops paying where the sum of the work does, which for causal masks is at long sequences.  Backward
-// in us, causal / causal documents / documents / window / shared questions:
-//   d = 128  192 units, N = 12288  halved 464 / 112 / 178 / 52 / 225, queued 452 / 148 / 190 / 54 / 231
-//            256 units, N = 16384  halved 677 / 127 / 170 / 58 / 296, queued 647 / 157 / 180 / 63 / 294
-//            256 units, N = 32768  halved 1460 / 157 / 181 / 65 / 231, queued 1313 / 191 / 225 / 68 / 280
-//   d = 64   512 units, N = 32768  halved 1282 / 137 / 191 / 60 / 190, queued 1077 / 167 / 202 / 58 / 242;
-//                                  N = 65536 halved 2714 / 177 / 222 / 61 / 206, queued 2121 / 190 / 226 / 58 / 253
-// The host does not know the mask.  The line is where causal masks stop gaining; documents would gain beyond it.
-// A ragged length has a key block whose padded columns leave nearly every tile of the sequence partially masked: one
-// chain of full length whatever the mask.  Halving halves it (512 units, d = 64, N = 32707, causal / causal documents:
-// halved 1306 / 550, queued 1379 / 861; d = 128, 256 units 1545 / 697 and 1703 / 1133), the queues start with it, direct
-// units of two rounds end with it (512 units, d = 128: N = 4035 direct 384 / 290, queued 326 / 262, N = 8131 711 / 395
-// and 618 / 371; N = 2887 272 / 201 and 283 / 208).
+// chain decides and stops paying where the sum of the work does, which for causal and prefix masks is at long sequences.
+// The host does not know the mask; the line lies where the geometric mean over six masks crosses.  Backward in us,
+// halved / queued, causal, prefix, documents of 700 tokens, eight documents, window 256, shared questions (mean ratio):
+//   d = 128  240 units, N = 10240  402 / 400, 437 / 399, 136 / 166, 225 / 240, 54 / 58, 320 / 319   (0.96)
+//            256 units, N = 16384  680 / 647, 731 / 651, 128 / 157, 362 / 363, 58 / 61, 336 / 330   (0.99)
+//            192 units, N = 24576  955 / 876, 1013 / 886, 126 / 156, 557 / 530, 58 / 58, 462 / 434   (1.02)
+//            256 units, N = 32768  1439 / 1292, 1527 / 1296, 158 / 192, 757 / 691, 64 / 68, 633 / 571   (1.04)
+//            of 2, 4, 8 query heads: N = 8192 0.95, 0.93, 0.92, N = 16384 1.02, 1.00, 0.99, N = 24576 1.06, 1.03, 1.02
+//   d = 64   512 units, N = 16384  566 / 546, 605 / 552, 119 / 141, 326 / 332, 57 / 55, 275 / 290   (0.99)
+//            480 units, N = 20480  735 / 657, 784 / 664, 114 / 119, 427 / 411, 58 / 54, 371 / 347   (1.07)
+//            of 2, 4, 8 query heads: N = 16384 0.97, 0.96, 0.96, N = 20480 1.06, 1.06, 1.05
+// A ragged length stays off the queues as long as its units run at once: the table counts the padded columns of its last
+// key block, which leave nearly every tile of that block partially masked, a chain of full length, while direct units go
+// by the bounds of the keys that exist (391 units of 8 query heads, d = 64, N = 49969, window: queued 10667, halved 322;
+// 384 units, d = 128, N = 4019, window: queued 306, direct 84).
 inline FmUnits fm_key_units(long long units, int group, int d, int N, long long cus) {
   const long long slots = fm_dkdv_per_cu(d) * cus;
   const int padded = (N + 127) / 128 * 128;
@@ -156,10 +158,9 @@ inline FmUnits fm_key_units(long long units, int group, int d, int N, long long 
   if (2 * units <= slots) return FM_DIRECT_HALVED;
   if (units <= slots) {
     if ((long long)padded * group <= (d == 128 ? 2048 : 1024)) return FM_DIRECT;
-    return ragged || N <= 12288 ? FM_DIRECT_HALVED : FM_QUEUED;
+    return ragged || N <= 16384 ? FM_DIRECT_HALVED : FM_QUEUED;
   }
-  return (d == 128 && units <= 2 * slots && N <= (ragged ? 3072 : 8192)) || fm_short_direct(units, d, N, cus) ? FM_DIRECT
-                                                                                                              : FM_QUEUED;
+  return (d == 128 && units <= 2 * slots && N <= 8192) || fm_short_direct(units, d, padded, cus) ? FM_DIRECT : FM_QUEUED;
 }
 // Tile shapes (rows x key columns) each pass classifies at.
 constexpr int FM_FWD_BR = 128, FM_FWD_BC = 64;

@@ -17,14 +17,14 @@ Q, D, H2, P2 = fm.FM_CUT_QUEUED, fm.FM_CUT_DIRECT, fm.FM_CUT_HALVED, fm.FM_CUT_P
 # H, N, d and the cuts of forward, dQ and dK/dV on 256 compute units
 BANDS = [
     (16, 4096, 128, (Q, Q, D)),     # one round of 128-row units off the queues, setup in one launch, for the rows only
-    (15, 4000, 128, (Q, Q, Q)),     # ragged: the last key block's chain is the longest and must not start last
+    (15, 4000, 128, (Q, Q, D)),     # the same, ragged
     (8, 8192, 128, (Q, Q, D)),      # the same with the setup in three launches
     (20, 2500, 128, (Q, Q, D)),
     (3, 16320, 64, (Q, Q, H2)),     # d = 64: queued dQ with halved keys
-    (4, 16384, 64, (Q, Q, Q)),      # one round of keys, long: queued
+    (3, 16512, 64, (Q, Q, Q)),      # one round of keys, long: queued
     (1, 24576, 128, (P2, P2, Q)),   # queues and setup for the keys only
     (1, 40960, 64, (Q, Q, Q)),
-    (2, 12288, 128, (P2, P2, H2)),  # the longest halved keys of a full round
+    (2, 16384, 128, (P2, P2, H2)),  # the longest halved keys of a full round
     (1, 24500, 128, (P2, P2, H2)),  # ragged: halved at any length
     (520, 640, 128, (Q, Q, Q)),     # many slices: setup of short sequences in three launches
     (1100, 200, 64, (Q, Q, Q)),

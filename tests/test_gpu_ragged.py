@@ -34,7 +34,7 @@ def test_bounds_at_the_ends_of_int32(N, d):
     compare_all(w, *run_fwd_bwd(w), f"int32 ends N={N} d={d}")
 
 
-@pytest.mark.parametrize("H,N,d", [(1, 24576, 128), (2, 24576, 64)])
+@pytest.mark.parametrize("H,N,d", [(1, 24576, 128), (12, 4096, 128), (2, 24576, 64)])
 def test_the_columns_that_do_not_exist_add_no_tiles(H, N, d):
     """dK/dV units that run without queues: a window over one key less takes about as long as over N keys (if the last
     key block's padded columns counted as masked keys, its chain would be the whole sequence: 2 to 6 times as long)."""
