@@ -32,7 +32,8 @@ enum { T_UNMASKED = 0, T_PARTIAL = 1, T_FULLY = 2, T_NEED_LT = 16, T_NEED_UT = 3
 
 // What the key columns past the end of a sequence carry (LTS, LTE, UTS, UTE): one interval that masks every
 // row.  A sequence whose length is not a multiple of 128 runs at the padded length; its extra columns exist
-// nowhere in memory, every reader of the bound vectors substitutes these four values instead.
+// nowhere in memory; the readers that see them as keys of a row (the tables, the row-parallel loops) substitute these
+// four values instead.  (A dK/dV lane past the last key works on a copy of that key and stores nothing.)
 static __device__ const int pad_column[4] = {INT32_MIN, INT32_MAX, 0, 0};
 // Bound `which` (0..3 = LTS, LTE, UTS, UTE) of key column `key` of a batch row's vector.
 __device__ __forceinline__ const int* bound_or_pad(const int* vec, int which, int key, int n) {
@@ -521,9 +522,9 @@ __device__ __forceinline__ int entry_mask_mode(int entry) {
 }
 
 // --- direct units -----------------------------------------------------------------------------------------
-// A problem whose units all run at once (fm_row_units, fm_key_units in fm_kernels.h) needs no order and runs without
-// the setup launches: workgroup x takes unit direct_unit() and every workgroup derives the min/max values it needs
-// from the bound vectors themselves.  Where that leaves the chip with idle compute units the unit is halved (half the
+// A problem of few units, or of short ones (the lines are at fm_row_units and fm_key_units in fm_kernels.h), gains nothing
+// from an order and runs without the setup launches: workgroup x takes unit direct_unit() and derives the min/max values
+// it needs from the bound vectors themselves.  Where that leaves the chip with idle compute units the unit is halved (half the
 // rows or keys per workgroup), and the tiles of its list are dealt alternately to two groups of waves whose partial
 // results meet in LDS at the end, which halves the longest chain of tiles.
 //

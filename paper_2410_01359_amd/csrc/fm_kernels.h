@@ -115,6 +115,15 @@ inline bool fm_short_direct(long long units, int d, int N, long long cus) {
 //   d = 64   256 units, N = 4096   halved 39 / 37 / 41 / 15, queued 54 / 60 / 67 / 16
 //            512 units, N = 512    direct 21 / 24 / 25 / 20, halved 24 / 29 / 30 / 24, queued 21 / 23 / 25 / 21
 //            512 units, N = 8192   halved 112 / 47 / 63 / 33, queued 116 / 59 / 73 / 21; N = 16384 causal 267, queued 219
+// At long sequences, forward alone with its setup, direct | queued, causal, prefix, documents of 700 tokens, eight documents,
+// window 256, shared questions (geometric mean of the ratios; ragged: N - 77):
+//   d = 128  256 units, N = 16384  paired 246 245 60 162 23 118 | 276 278 79 225 28 161   (0.80, ragged 0.88)
+//            256 units, N = 32768  paired 495 497 78 314 30 200 | 537 541 97 433 30 270   (0.85, ragged 0.96)
+//   d = 64   256 units, N = 16384  halved 169 167 43 115 21 84 | 197 195 72 196 24 159   (0.70, ragged 0.89)
+//            256 units, N = 32768  halved 344 345 64 218 33 143 | 376 376 100 380 26 246   (0.79, ragged 1.05)
+//            512 units, N = 8192   halved 108 109 44 64 30 77 | 118 120 65 110 27 117   (0.78, ragged 0.98)
+// Only windows lose at that length, and ragged ones most (4-byte loads of the bounds: N = 32691, d = 64 72 | 30); the line
+// carries no N where the mean does not cross.
 inline FmUnits fm_row_units(long long units, int per_cu, int d, int N, long long cus) {
   if (d == 128) {
     if (2 * units <= cus) return FM_DIRECT_HALVED;

@@ -185,12 +185,13 @@ __global__ __launch_bounds__(256) void work2_kernel(WorkJob rows, int blocks_row
 // slice count is a multiple of 8, so that the units sharing one head's K/V also
 // share one L2), each queue is sorted heaviest first within groups of slices (see
 // order_kernel; work quantised to 512 levels), and the queues are interleaved:
-// slot 8*s + g = position s of queue g.  A workgroup draws the next ticket of its
-// XCD's queue when it starts, so every queue is worked off longest-job-first; the
-// launch holds more workgroups than there are slots, and a workgroup that finds its
-// own queue empty draws from the queue that has most left.  (The XCDs do not run
-// at the same speed: with equal shares the slowest one finishes about a tenth
-// later than the fastest.)
+// slot 8*s + g = position s of queue g.  The workgroups that run from the start have
+// their ticket in their number, later ones draw the next of their XCD's queue when they
+// start, so every queue is worked off longest-job-first.  A launch of more units than run
+// at once holds more workgroups than tickets, and a workgroup that finds its own queue
+// empty draws from the queue that has most left.  (The XCDs do not run at the same
+// speed: with equal shares the slowest one finishes about a tenth later than the
+// fastest.)
 // A slot is the record {unit, first live block, one past the last live block, 0},
 // so a workgroup learns all it needs to start from one 16-byte load; slots with
 // no unit hold unit = -1.  The kernel also zeroes the 8 queue counters behind
