@@ -210,7 +210,7 @@ int flashmask_preprocess(const int32_t* lts, const int32_t* lte, const int32_t* 
                          int block_c, int32_t* minmax, void* hip_stream) {
   if (!lts || !lte || !uts || !ute || !minmax) return FM_ERR_NULL;
   if (B <= 0 || N <= 0 || block_c <= 0 || block_c % 32 != 0) return FM_ERR_SHAPE;
-  hipError_t e = fm_launch_preprocess(lts, lte, uts, ute, B, N, N, block_c, minmax, (hipStream_t)hip_stream);
+  hipError_t e = fm_launch_preprocess(lts, lte, uts, ute, B, N, N, block_c, FM_PADS_NONE, minmax, (hipStream_t)hip_stream);
   return e == hipSuccess ? FM_OK : hip_fail(e);
 }
 
@@ -248,7 +248,7 @@ static int fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
   FmFwdArgs a;
   a.units = fwd_units(B, H, N, d, fm_compute_units());
   if (a.units == FM_QUEUED) {
-    e = fm_launch_setup(lts, lte, uts, ute, B, H, Hk, N, Np, FmSetup{FM_FWD_BR, FM_FWD_BC, minmax, work, range, order},
+    e = fm_launch_setup(lts, lte, uts, ute, B, H, Hk, N, Np, FmSetup{FM_FWD_BR, FM_FWD_BC, minmax, work, range, order, FM_PADS_MASKED},
                         false, stream);
     if (e != hipSuccess) return hip_fail(e);
   }
@@ -289,7 +289,8 @@ int flashmask_unit_queues(int pass, const int32_t* lts, const int32_t* lte, cons
   hipError_t e;
   const PassSpace sp = pass_space(B, H, Np, br, bc, rows, 0);
   e = fm_launch_setup(lts, lte, uts, ute, B, H, H, N, Np,
-                      FmSetup{br, bc, (int*)(ws + sp.minmax), (int*)(ws + sp.work), (int*)(ws + sp.range), (int*)(ws + sp.order)},
+                      FmSetup{br, bc, (int*)(ws + sp.minmax), (int*)(ws + sp.work), (int*)(ws + sp.range), (int*)(ws + sp.order),
+                              FM_PADS_LOWER},
                       !rows, stream);
   if (e != hipSuccess) return hip_fail(e);
   e = hipMemcpyAsync(records, ws + sp.order, (size_t)*slots * 16, hipMemcpyDeviceToDevice, stream);
@@ -374,9 +375,9 @@ static int bwd_impl(const void* q, const void* k, const void* v, const void* out
     a.sk = a.sv = a.sdk = a.sdv = dense(Hk, N, d);
   }
   const FmSetup rows{FM_DQ_BR, fm_dq_bc(d), (int*)(ws + sq.minmax), (int*)(ws + sq.work), (int*)(ws + sq.range),
-                     (int*)(ws + sq.order)};
+                     (int*)(ws + sq.order), FM_PADS_MASKED};
   const FmSetup cols{FM_DKDV_BR, FM_DKDV_BC, (int*)(ws + skv.minmax), (int*)(ws + skv.work), (int*)(ws + skv.range),
-                     (int*)(ws + skv.order)};
+                     (int*)(ws + skv.order), FM_PADS_NONE};
   a.units_dq = dq_units(B, H, N, d, fm_compute_units());
   a.units_dkdv = dkdv_units(B, H, Hk, N, d, fm_compute_units());
   const bool queue_dq = a.units_dq == FM_QUEUED, queue_dkdv = a.units_dkdv == FM_QUEUED;

@@ -30,11 +30,20 @@ enum { LTS_MAX = 0, LTS_MIN, LTE_MAX, LTE_MIN, UTS_MAX, UTS_MIN, UTE_MAX, UTE_MI
 // Tile classes (Equation 4); same encoding as FM_TILE_* in flashmask.h.
 enum { T_UNMASKED = 0, T_PARTIAL = 1, T_FULLY = 2, T_NEED_LT = 16, T_NEED_UT = 32 };
 
-// What the key columns past the end of a sequence carry (LTS, LTE, UTS, UTE): one interval that masks every
-// row.  A sequence whose length is not a multiple of 128 runs at the padded length; its extra columns exist
+// What the key columns past the end of a sequence carry (LTS, LTE, UTS, UTE): two intervals that mask every
+// row each.  A sequence whose length is not a multiple of 128 runs at the padded length; its extra columns exist
 // nowhere in memory; the readers that see them as keys of a row (the tables, the row-parallel loops) substitute these
 // four values instead.  (A dK/dV lane past the last key works on a copy of that key and stores nothing.)
-static __device__ const int pad_column[4] = {INT32_MIN, INT32_MAX, 0, 0};
+// Masked by both pairs, they leave the max of the starts and the min of the ends, which the "fully masked" test of
+// Equation 4 compares, as the block's real columns have them; masked by the lower pair alone they kept the last key block
+// partially masked for every row that its real columns mask through the upper pair (every row above a causal diagonal).
+static __device__ const int pad_column[4] = {INT32_MIN, INT32_MAX, INT32_MIN, INT32_MAX};
+// The value of bound `which` that the columns past the end count with in a table (FM_PADS_NONE: `real`, a value of the block).
+__device__ __forceinline__ int pad_value(FmPads pads, int which, int real) {
+  if (pads == FM_PADS_NONE) return real;
+  if (pads == FM_PADS_LOWER && which >= 2) return 0;
+  return which & 1 ? INT32_MAX : INT32_MIN;
+}
 // Bound `which` (0..3 = LTS, LTE, UTS, UTE) of key column `key` of a batch row's vector.
 __device__ __forceinline__ const int* bound_or_pad(const int* vec, int which, int key, int n) {
   return key < n ? vec + key : pad_column + which;
@@ -573,7 +582,7 @@ __device__ __forceinline__ int build_live_key_blocks_direct(const int* const (&v
         if (RAGGED) {
 #pragma unroll
           for (int e = 0; e < 4; ++e)
-            if (key + e >= n) x[p][a][e] = a == 0 ? INT32_MIN : a == 1 ? INT32_MAX : 0;   // pad_column
+            if (key + e >= n) x[p][a][e] = a & 1 ? INT32_MAX : INT32_MIN;   // pad_column
         }
         const i32x4 v = x[p][a];
         mm.v[2 * a] = row16_max(max(max(v[0], v[1]), max(v[2], v[3])));

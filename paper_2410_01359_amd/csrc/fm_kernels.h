@@ -156,10 +156,10 @@ inline FmUnits fm_row_units(long long units, int per_cu, int d, int N, long long
 //   d = 64   512 units, N = 16384  566 / 546, 605 / 552, 119 / 141, 326 / 332, 57 / 55, 275 / 290   (0.99)
 //            480 units, N = 20480  735 / 657, 784 / 664, 114 / 119, 427 / 411, 58 / 54, 371 / 347   (1.07)
 //            of 2, 4, 8 query heads: N = 16384 0.97, 0.96, 0.96, N = 20480 1.06, 1.06, 1.05
-// A ragged length stays off the queues as long as its units run at once: the table counts the padded columns of its last
-// key block, which leave nearly every tile of that block partially masked, a chain of full length, while direct units go
-// by the bounds of the keys that exist (391 units of 8 query heads, d = 64, N = 49969, window: queued 10667, halved 322;
-// 384 units, d = 128, N = 4019, window: queued 306, direct 84).
+// Ragged lengths, queued / halved over the same masks (mean ratio of halved): d = 128 N = 16300 297.9 / 287.0 (0.96), 24500
+// 365.0 / 361.1, 32691 465.6 / 458.0, of 4 query heads 24500 1238 / 1218, of 8 32691 3166 / 3081 (0.97): halved at any
+// length; d = 64 16307 232.7 / 227.3 (0.98), 20400 266.6 / 278.4, 32691 361.6 / 387.2, 65459 531.9 / 576.1 (1.08): the
+// line of the other lengths.
 inline FmUnits fm_key_units(long long units, int group, int d, int N, long long cus) {
   const long long slots = fm_dkdv_per_cu(d) * cus;
   const int padded = (N + 127) / 128 * 128;
@@ -167,7 +167,7 @@ inline FmUnits fm_key_units(long long units, int group, int d, int N, long long 
   if (2 * units <= slots) return FM_DIRECT_HALVED;
   if (units <= slots) {
     if ((long long)padded * group <= (d == 128 ? 2048 : 1024)) return FM_DIRECT;
-    return ragged || N <= 16384 ? FM_DIRECT_HALVED : FM_QUEUED;
+    return (ragged && d == 128) || N <= 16384 ? FM_DIRECT_HALVED : FM_QUEUED;
   }
   return (d == 128 && units <= 2 * slots && N <= 8192) || fm_short_direct(units, d, padded, cus) ? FM_DIRECT : FM_QUEUED;
 }
@@ -179,6 +179,12 @@ constexpr int FM_DQ_BR = 128;
 constexpr int fm_dq_bc(int d) { return d == 64 ? 128 : 64; }
 constexpr int FM_DKDV_BR = 64, FM_DKDV_BC = 128;
 
+// What the columns past the end of a sequence whose length is no multiple of 128 count as in a pass's table.
+enum FmPads {
+  FM_PADS_NONE,     // nothing: a block covers the columns that exist (dK/dV units, whose lanes past the last key copy it)
+  FM_PADS_MASKED,   // masked for every row by both pairs (the row-parallel loops, see pad_column)
+  FM_PADS_LOWER,    // masked for every row by the lower pair, upper pair empty at row 0 (flashmask_unit_queues)
+};
 // One pass's setup buffers (in the workspace) and tile shape.
 struct FmSetup {
   int block_r, block_c;
@@ -186,6 +192,7 @@ struct FmSetup {
   int* work;     // int[B * T], T = row blocks resp. key blocks
   int* range;    // int[2 * B * T]: first live block and one past the last live block of every unit (0, 0 if none)
   int* order;    // fm_order_bytes(B * H * T) bytes: slot records {unit, first, last, 0}, then the counters (zeroed here)
+  FmPads pads;
 };
 // Workgroups of the queue-building launch: per queue, one for every FM_QUEUE_CHUNK whole slices and one
 // for its part of the slices left over, its unused slots and its counter.
@@ -212,10 +219,10 @@ hipError_t fm_launch_setup(const int* lts, const int* lte, const int* uts, const
 // The same for the dQ pass `rows` and the dK/dV pass `cols` together.
 hipError_t fm_launch_bwd_setup(const int* lts, const int* lte, const int* uts, const int* ute, int B, int H, int Hk,
                                int N, int Np, const FmSetup& rows, const FmSetup& cols, hipStream_t stream);
-// Tables of ceil(Np / block_c) key blocks per batch row.  Np == N: a ragged last block covers the columns that
-// exist.  Np > N: the columns [N, Np) count as masked for every row (pad_column).
+// Tables of ceil(Np / block_c) key blocks per batch row; the columns [N, Np), and a ragged last block's beyond N, count
+// as `pads` says.
 hipError_t fm_launch_preprocess(const int* lts, const int* lte, const int* uts, const int* ute, int B, int N, int Np,
-                                int block_c, int* minmax, hipStream_t stream);
+                                int block_c, FmPads pads, int* minmax, hipStream_t stream);
 hipError_t fm_launch_classify(const int* minmax, int B, int N, int block_r, int block_c, uint8_t* cls,
                               hipStream_t stream);
 

@@ -12,8 +12,8 @@ namespace fm {
 // then a butterfly over the 64 lanes leaves the 8 results in every lane.
 __device__ __forceinline__ void preprocess_body(const int* __restrict__ lts, const int* __restrict__ lte,
                                                 const int* __restrict__ uts, const int* __restrict__ ute, int n,
-                                                int np, int block_c, int t_c, int total_blocks, int* __restrict__ minmax,
-                                                int block) {
+                                                FmPads pads, int block_c, int t_c, int total_blocks,
+                                                int* __restrict__ minmax, int block) {
   const int lane = threadIdx.x & 63;
   const int blk = block * 4 + (threadIdx.x >> 6);
   if (blk >= total_blocks) return;
@@ -27,9 +27,9 @@ __device__ __forceinline__ void preprocess_body(const int* __restrict__ lts, con
     mx[a] = INT32_MIN;
     mn[a] = INT32_MAX;
   }
-  if (np > n && c0 + block_c > n) {   // the block's columns past the end of the sequence
+  if (pads != FM_PADS_NONE && c0 + block_c > n) {   // the block's columns past the end of the sequence
 #pragma unroll
-    for (int a = 0; a < 4; ++a) mx[a] = mn[a] = pad_column[a];
+    for (int a = 0; a < 4; ++a) mx[a] = mn[a] = pad_value(pads, a, 0);
   }
   for (int c = c0 + lane; c < c1; c += 64) {
 #pragma unroll
@@ -59,21 +59,22 @@ __device__ __forceinline__ void preprocess_body(const int* __restrict__ lts, con
 
 __global__ __launch_bounds__(256) void preprocess_kernel(const int* __restrict__ lts, const int* __restrict__ lte,
                                                          const int* __restrict__ uts, const int* __restrict__ ute,
-                                                         int n, int np, int block_c, int t_c, int total_blocks,
+                                                         int n, FmPads pads, int block_c, int t_c, int total_blocks,
                                                          int* __restrict__ minmax) {
-  preprocess_body(lts, lte, uts, ute, n, np, block_c, t_c, total_blocks, minmax, blockIdx.x);
+  preprocess_body(lts, lte, uts, ute, n, pads, block_c, t_c, total_blocks, minmax, blockIdx.x);
 }
 
 // The tables of two block widths in one launch (the backward's two loops tile the keys differently):
 // workgroups [0, blocks_a) build table a, the rest table b.
 __global__ __launch_bounds__(256) void preprocess2_kernel(const int* __restrict__ lts, const int* __restrict__ lte,
                                                           const int* __restrict__ uts, const int* __restrict__ ute,
-                                                          int n, int np, int batch, int block_c_a, int* __restrict__ minmax_a,
-                                                          int blocks_a, int block_c_b, int* __restrict__ minmax_b) {
+                                                          int n, int np, int batch, int block_c_a, FmPads pads_a,
+                                                          int* __restrict__ minmax_a, int blocks_a, int block_c_b,
+                                                          FmPads pads_b, int* __restrict__ minmax_b) {
   const bool first = (int)blockIdx.x < blocks_a;
   const int block_c = first ? block_c_a : block_c_b;
   const int t_c = (np + block_c - 1) / block_c;
-  preprocess_body(lts, lte, uts, ute, n, np, block_c, t_c, batch * t_c, first ? minmax_a : minmax_b,
+  preprocess_body(lts, lte, uts, ute, n, first ? pads_a : pads_b, block_c, t_c, batch * t_c, first ? minmax_a : minmax_b,
                   first ? blockIdx.x : blockIdx.x - blocks_a);
 }
 
@@ -363,6 +364,7 @@ struct SetupJob {
   int block_r, block_c;
   int t_r, t_c;
   int cols;                // units are key blocks (else row blocks)
+  FmPads pads;
   int* minmax;             // [batch][8][t_c], written for the tile loops
 };
 struct SetupArgs {
@@ -418,7 +420,7 @@ __global__ __launch_bounds__(1024) void setup_kernel(SetupArgs a) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int y = vec[min(key + e, n - 1)];
-          x[v][e] = key + e < n ? y : v == 0 ? INT32_MIN : v == 1 ? INT32_MAX : 0;   // pad_column
+          x[v][e] = key + e < n ? y : pad_value(job.pads, v, y);
         }
       }
     }
@@ -473,10 +475,10 @@ __global__ __launch_bounds__(1024) void setup_kernel(SetupArgs a) {
 using namespace fm;
 
 hipError_t fm_launch_preprocess(const int* lts, const int* lte, const int* uts, const int* ute, int B, int N, int Np,
-                                int block_c, int* minmax, hipStream_t stream) {
+                                int block_c, FmPads pads, int* minmax, hipStream_t stream) {
   const int t_c = (Np + block_c - 1) / block_c;
   const int total = B * t_c;
-  hipLaunchKernelGGL(preprocess_kernel, dim3((total + 3) / 4), dim3(256), 0, stream, lts, lte, uts, ute, N, Np,
+  hipLaunchKernelGGL(preprocess_kernel, dim3((total + 3) / 4), dim3(256), 0, stream, lts, lte, uts, ute, N, pads,
                      block_c, t_c, total, minmax);
   return hipGetLastError();
 }
@@ -508,7 +510,7 @@ static OrderJob pass_order_job(const FmSetup& p, const WorkJob& w, int B, int H,
 }
 static SetupJob setup_job(const FmSetup& p, int B, int H, int Hk, int N, int Np, bool cols) {
   const WorkJob w = work_job(p, B, N, Np, cols);
-  return SetupJob{pass_order_job(p, w, B, H, Hk, cols), p.block_r, p.block_c, w.t_r, w.t_c, cols, p.minmax};
+  return SetupJob{pass_order_job(p, w, B, H, Hk, cols), p.block_r, p.block_c, w.t_r, w.t_c, cols, p.pads, p.minmax};
 }
 
 hipError_t fm_launch_setup(const int* lts, const int* lte, const int* uts, const int* ute, int B, int H, int Hk, int N,
@@ -519,7 +521,7 @@ hipError_t fm_launch_setup(const int* lts, const int* lte, const int* uts, const
     hipLaunchKernelGGL(setup_kernel, dim3(grid), dim3(1024), 0, stream, a);
     return hipGetLastError();
   }
-  if (hipError_t e = fm_launch_preprocess(lts, lte, uts, ute, B, N, Np, pass.block_c, pass.minmax, stream); e != hipSuccess)
+  if (hipError_t e = fm_launch_preprocess(lts, lte, uts, ute, B, N, Np, pass.block_c, pass.pads, pass.minmax, stream); e != hipSuccess)
     return e;
   const WorkJob w = work_job(pass, B, N, Np, cols);
   const int work_grid = (w.total_units + 3) / 4;
@@ -546,7 +548,7 @@ hipError_t fm_launch_bwd_setup(const int* lts, const int* lte, const int* uts, c
   const WorkJob wr = work_job(rows, B, N, Np, false), wc = work_job(cols, B, N, Np, true);
   const int pre_a = (B * wr.t_c + 3) / 4, pre_b = (B * wc.t_c + 3) / 4;
   hipLaunchKernelGGL(preprocess2_kernel, dim3(pre_a + pre_b), dim3(256), 0, stream, lts, lte, uts, ute, N, Np, B,
-                     rows.block_c, rows.minmax, pre_a, cols.block_c, cols.minmax);
+                     rows.block_c, rows.pads, rows.minmax, pre_a, cols.block_c, cols.pads, cols.minmax);
   const int work_a = (wr.total_units + 3) / 4, work_b = (wc.total_units + 3) / 4;
   hipLaunchKernelGGL(work2_kernel, dim3(work_a + work_b), dim3(256), 0, stream, wr, work_a, wc, N);
   hipLaunchKernelGGL(order2_kernel, dim3(2 * grid), dim3(1024), 0, stream, pass_order_job(rows, wr, B, H, Hk, false), grid,

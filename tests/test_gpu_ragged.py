@@ -53,3 +53,10 @@ def test_the_columns_that_do_not_exist_add_no_tiles(H, N, d):
             passes.append(ends[0].elapsed_time(ends[1]))
         times.append(min(passes))
     assert times[1] < 1.7 * times[0], times
+
+
+@pytest.mark.parametrize("H,N,d", [(40, 8192, 128), (16, 32768, 64), (16, 4224, 64)])
+def test_the_columns_that_do_not_exist_add_no_tiles_to_queued_units(H, N, d):
+    """The same for dK/dV units off the queues."""
+    assert fm.flashmask_work_cut(fm.FM_PASS_BWD_DKDV, 1, H, H, N - 1, d, compute_units=256) == fm.FM_CUT_QUEUED
+    test_the_columns_that_do_not_exist_add_no_tiles(H, N, d)
