@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "fm_kernels.h"
 
 namespace fm {
@@ -550,55 +552,64 @@ __device__ __forceinline__ int direct_unit(int units, int blocks) {
 }
 // build_live_key_blocks for key blocks of 64 columns straight from the bound vectors (vec: a batch row's LTS, LTE,
 // UTS, UTE; n columns).  Sixteen lanes take a block, four columns each, so a pass of four waves covers 1024
-// columns; PASSES passes have their loads in flight together.  The raw entries go to list[] in place (-1: fully
+// columns; where the columns go beyond that, two passes have their loads in flight together (forward over a window of
+// 256, N = 16384, d = 64: 16.5 us, one at a time 17.5), and a second pass over no columns is left out (N = 512, d = 64,
+// training step 29.3 -> 28.5 us; the loads and the classes of the columns that it repeated).  Ragged lengths take one pass
+// at a time: their loads are single words, and two passes' worth of registers spilled (N = 333, d = 128, forward 11.2 ->
+// 10.8 us; N = 32691, window 45.0 -> 42.7).  The raw entries go to list[] in place (-1: fully
 // masked) and are compacted from there.  NW: waves that own rows (32 each) of the unit.
 // WAVES: waves of the workgroup.
 template <bool RAGGED, int EMPTY, int NW, int WAVES>
 __device__ __forceinline__ int build_live_key_blocks_direct(const int* const (&vec)[4], int n, int j_begin, int j_end,
                                                             int r0, int r1, int* list, int* wave_cnt) {
-  constexpr int KT = 64, THREADS = 64 * WAVES, BLOCKS = THREADS * 4 / KT, PASSES = 2;
+  constexpr int KT = 64, THREADS = 64 * WAVES, BLOCKS = THREADS * 4 / KT;
   const int tid = threadIdx.x;
-  for (int base = j_begin; base < j_end; base += BLOCKS * PASSES) {
-    i32x4 x[PASSES][4];
+  auto classify_columns = [&](auto passes) __attribute__((always_inline)) {
+    constexpr int PASSES = decltype(passes)::value;
+    for (int base = j_begin; base < j_end; base += BLOCKS * PASSES) {
+      i32x4 x[PASSES][4];
 #pragma unroll
-    for (int p = 0; p < PASSES; ++p) {
-      const int j = base + p * BLOCKS + tid / 16, key = j * KT + (tid % 16) * 4;
+      for (int p = 0; p < PASSES; ++p) {
+        const int j = base + p * BLOCKS + tid / 16, key = j * KT + (tid % 16) * 4;
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        if (RAGGED) {
+        for (int a = 0; a < 4; ++a) {
+          if (RAGGED) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) x[p][a][e] = vec[a][min(key + e, n - 1)];
-        } else {
-          x[p][a] = *(const i32x4*)(vec[a] + min(key, n - 4));
+            for (int e = 0; e < 4; ++e) x[p][a][e] = vec[a][min(key + e, n - 1)];
+          } else {
+            x[p][a] = *(const i32x4*)(vec[a] + min(key, n - 4));
+          }
         }
       }
-    }
 #pragma unroll
-    for (int p = 0; p < PASSES; ++p) {
-      const int j = base + p * BLOCKS + tid / 16, key = j * KT + (tid % 16) * 4;
-      MinMax8 mm;
+      for (int p = 0; p < PASSES; ++p) {
+        const int j = base + p * BLOCKS + tid / 16, key = j * KT + (tid % 16) * 4;
+        MinMax8 mm;
 #pragma unroll
-      for (int a = 0; a < 4; ++a) {
-        if (RAGGED) {
+        for (int a = 0; a < 4; ++a) {
+          if (RAGGED) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (key + e >= n) x[p][a][e] = a & 1 ? INT32_MAX : INT32_MIN;   // pad_column
+            for (int e = 0; e < 4; ++e)
+              if (key + e >= n) x[p][a][e] = a & 1 ? INT32_MAX : INT32_MIN;   // pad_column
+          }
+          const i32x4 v = x[p][a];
+          mm.v[2 * a] = row16_max(max(max(v[0], v[1]), max(v[2], v[3])));
+          mm.v[2 * a + 1] = row16_min(min(min(v[0], v[1]), min(v[2], v[3])));
         }
-        const i32x4 v = x[p][a];
-        mm.v[2 * a] = row16_max(max(max(v[0], v[1]), max(v[2], v[3])));
-        mm.v[2 * a + 1] = row16_min(min(min(v[0], v[1]), min(v[2], v[3])));
-      }
-      const int cls = classify_tile(r0, r1, mm);
-      int entry = (j - j_begin) | ((cls & 3) << 16) | (((cls >> 4) & 3) << 26) | ((mm.v[LTE_MIN] >= r1 ? 1 : 0) << 28) |
-                  ((mm.v[UTS_MAX] <= r0 ? 1 : 0) << 29);
+        const int cls = classify_tile(r0, r1, mm);
+        int entry = (j - j_begin) | ((cls & 3) << 16) | (((cls >> 4) & 3) << 26) | ((mm.v[LTE_MIN] >= r1 ? 1 : 0) << 28) |
+                    ((mm.v[UTS_MAX] <= r0 ? 1 : 0) << 29);
 #pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        const int w0 = min(r0 + w * 32, r1), w1 = min(w0 + 32, r1);
-        entry |= (w0 < w1 ? classify_tile(w0, w1, mm) & 3 : EMPTY) << (18 + 2 * w);
+        for (int w = 0; w < NW; ++w) {
+          const int w0 = min(r0 + w * 32, r1), w1 = min(w0 + 32, r1);
+          entry |= (w0 < w1 ? classify_tile(w0, w1, mm) & 3 : EMPTY) << (18 + 2 * w);
+        }
+        if (tid % 16 == 0 && j < j_end) list[j - j_begin] = cls == T_FULLY ? -1 : entry;
       }
-      if (tid % 16 == 0 && j < j_end) list[j - j_begin] = cls == T_FULLY ? -1 : entry;
     }
-  }
+  };
+  if (RAGGED || j_end - j_begin <= BLOCKS) classify_columns(std::integral_constant<int, 1>{});
+  else classify_columns(std::integral_constant<int, 2>{});
   barrier_nofence();
   int running = 0;
   for (int base = j_begin; base < j_end; base += THREADS) {
