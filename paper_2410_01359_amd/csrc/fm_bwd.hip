@@ -455,26 +455,20 @@ __device__ __forceinline__ constexpr int dkdv_vec_off(int r, bool d_part) {
 // tile loop issues in three consecutive steps, so that a step never holds two
 // dependent vector instructions of the same element (one wave per SIMD: nothing
 // else hides the latency of v_exp_f32 and of the AGPR reads):
-//   A: t = s*sc - lse2 (with the element mask)     B: p = exp2(t)     C: dS = p * (dP - D)
+//   A: t = s*sc - lse2     B: p = exp2(t)     C: p = 0 where masked, dS = p * (dP - D)
 // (dP - D comes straight out of the MFMA: its accumulator starts from the -D values of the rows)
 // Register r of a block is query row 8*(r/4) + 4*g + r%4.
-// The element mask of a lane's key is two row intervals [s, e): row q is masked by one iff
-// in_interval(q - s, length), one addition and one compare per element with the interval's length formed once
-// per unit (off_a, off_b: where the first row of the block's registers lies from the intervals' starts).
-template <bool MASK>
-__device__ __forceinline__ void dkdv_stage_a(const f32x16& s, const f32x16& dp, float (&t)[16],
-                                             float (&u)[16], const f32x4 (&l4)[4], int e0,
-                                             int cnt, float sc, unsigned off_a, unsigned len_a, unsigned off_b,
-                                             unsigned len_b) {
+// The element mask of a lane's key is two row intervals: a 32-row block's are formed as a word with a bit per row
+// (interval_rows) beside the first block's score MFMAs, which no other vector work rides along with, and an element's bit,
+// spread over a word, is ANDed to its P.  Two instructions per element and 42 per tile, where comparing the row with both
+// intervals and selecting took six: a partially masked tile has 530 instead of 619 instructions (417 instead of 506 at
+// d = 64; 422 and 308 without mask).  Training step, both sides: eleven documents in 8192 tokens, 64 slices, d = 128 1050 ->
+// 1030 us, five in 1000, 32 slices 86.7 -> 81.5; window 1024, N = 32768 1458 -> 1443.
+__device__ __forceinline__ void dkdv_stage_a(const f32x16& s, const f32x16& dp, float (&t)[16], float (&u)[16],
+                                             const f32x4 (&l4)[4], int e0, int cnt, float sc) {
 #pragma unroll
   for (int r = e0; r < e0 + cnt; ++r) {
-    float x = s[r];
-    if (MASK) {
-      const unsigned dr = 8 * (r >> 2) + (r & 3);   // register r is row 8*(r/4) + 4*g + r%4 of the block; 4*g is in the offsets
-      const bool hit = in_interval(off_a + dr, len_a) | in_interval(off_b + dr, len_b);
-      if (hit) x = -INFINITY;
-    }
-    t[r] = __builtin_fmaf(x, sc, -l4[r >> 2][r & 3]);
+    t[r] = __builtin_fmaf(s[r], sc, -l4[r >> 2][r & 3]);
     u[r] = dp[r];   // dP - D: the dP accumulator was started from -D
   }
 }
@@ -625,6 +619,8 @@ __device__ __forceinline__ void dkdv_tile(const char* qs, const float* vec_s, co
   bf16x8 pa[2][2], dsa[2][2];      // bf16 P^T and dS^T, [block][16-row half]
   f32x4 l4[2][4];                  // lse (log2 domain) of the blocks' rows, fetched one group of 4 rows ahead
   float tq[2][16], uq[2][16];      // per element: exponent then P, and dP - D then dS
+  unsigned seen[2], hidden = 0;    // rows of the blocks that this lane's key is seen by, a bit each (see interval_rows)
+  int keep[2];                     // the bit of an element, spread over a word
   auto vec_group = [&](int qb, int grp) __attribute__((always_inline)) {
     const int row = qb * 32 + 8 * grp + 4 * g;
     l4[qb][grp] = *(const f32x4*)(vec_s + dkdv_vec_off(row, false));
@@ -709,6 +705,11 @@ __device__ __forceinline__ void dkdv_tile(const char* qs, const float* vec_s, co
     //     block j / NST: stage A at x, stage B one step later, stage C two steps later
     //     (j = x - NST - FM_DKDV_VSHIFT - stage).
     if (x == NST - 1) vec_group(0, 0);
+    if (MASK && x >= NST - 8 && x < NST && x % 2 == 0) {   // no other vector work here: one interval of one block at a time
+      const int qb = (x - NST + 8) / 4, row = r0 + 32 * qb + 4 * g;
+      if (x % 4 == 0) hidden = interval_rows(interval_offset(row, s_a), len_a);
+      else seen[qb] = ~(hidden | interval_rows(interval_offset(row, s_b), len_b));
+    }
 #pragma unroll
     for (int stage = 2; stage >= 0; --stage) {
       const int j = x - NST - FM_DKDV_VSHIFT - stage;
@@ -717,21 +718,34 @@ __device__ __forceinline__ void dkdv_tile(const char* qs, const float* vec_s, co
         if (stage == 0) {
           if (e0 % 4 == 0 && e0 / 4 + 1 < 4) vec_group(qb, e0 / 4 + 1);
           if (qb == 0 && e0 + EPS == 16) vec_group(1, 0);
-          const int row = r0 + 32 * qb + 4 * g;
-          dkdv_stage_a<MASK>(sb[qb], pb[qb], tq[qb], uq[qb], l4[qb], e0, EPS, sc, interval_offset(row, s_a), len_a,
-                             interval_offset(row, s_b), len_b);
+          dkdv_stage_a(sb[qb], pb[qb], tq[qb], uq[qb], l4[qb], e0, EPS, sc);
         } else if (stage == 1) {
 #pragma unroll
-          for (int r = e0; r < e0 + EPS; ++r) tq[qb][r] = fast_exp2(tq[qb][r]);
+          for (int r = e0; r < e0 + EPS; ++r) {
+            tq[qb][r] = fast_exp2(tq[qb][r]);
+            if (MASK) {
+              keep[r % 2] = __builtin_amdgcn_sbfe((int)seen[qb], 8 * (r / 4) + r % 4, 1);
+              asm("" : "+v"(keep[r % 2]));   // or the compiler turns it and the AND below into bit test, compare, select
+            }
+          }
         } else {
 #pragma unroll
-          for (int r = e0; r < e0 + EPS; ++r) uq[qb][r] *= tq[qb][r];
+          for (int r = e0; r < e0 + EPS; ++r) {
+            if (MASK) tq[qb][r] = __builtin_bit_cast(float, __builtin_bit_cast(int, tq[qb][r]) & keep[r % 2]);
+            uq[qb][r] *= tq[qb][r];
+          }
           if ((e0 + EPS) % 8 == 0) {   // a 16-row half of P^T and dS^T is complete: convert it to bf16 operands
             const int hh = (e0 + EPS) / 8 - 1;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
               pa[qb][hh][e] = (__bf16)tq[qb][8 * hh + e];
               dsa[qb][hh][e] = (__bf16)uq[qb][8 * hh + e];
+            }
+            if (D == 128) {
+              // here and not just in front of the MFMAs that read them, where ragged lengths' branches let the compiler
+              // sink the conversions to: mfma32_acc's idle instruction is left out there
+              settle(pa[qb][hh]);
+              settle(dsa[qb][hh]);
             }
           }
         }

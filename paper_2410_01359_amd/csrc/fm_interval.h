@@ -17,3 +17,12 @@ FM_HOST_DEVICE inline unsigned interval_length(int start, int end) {
 FM_HOST_DEVICE inline unsigned interval_offset(int row, int start) { return (unsigned)row - (unsigned)start; }
 // Whether the row at this offset lies in the interval.
 FM_HOST_DEVICE inline bool in_interval(unsigned offset, unsigned length) { return offset < length; }
+// The next 32 rows at once: bit p tells whether the row p further on than this offset lies in the interval.  (An interval
+// that starts at or before the first row reaches past none of them or `length - offset` of them; one that starts later
+// starts -offset rows on, modulo 2^32.  first_row + 31 and the bounds are int32 values, so neither sum wraps.)
+FM_HOST_DEVICE inline unsigned interval_rows(unsigned offset, unsigned length) {
+  const unsigned first = in_interval(offset, length) ? 0u : 0u - offset, end = length - offset;
+  const unsigned from_first = (unsigned)(0xFFFFFFFFull << (first < 32 ? first : 32));
+  const unsigned from_end = (unsigned)(0xFFFFFFFFull << (end < 32 ? end : 32));
+  return from_first & ~from_end;
+}
