@@ -523,13 +523,11 @@ __device__ __forceinline__ int entry_tile_class(int entry) { return (entry >> 16
 __device__ __forceinline__ int entry_wave_class(int entry, int wave) { return (entry >> (18 + 2 * wave)) & 3; }
 // 1 = LT pair only, 2 = UT pair only, 3 = both (0 only for tiles that are not partially masked)
 __device__ __forceinline__ int entry_need_pairs(int entry) { return (entry >> 26) & 3; }
-// The same with 4 added where the one pair needed is decided by a single comparison per element (bits 28, 29):
-// 5 = "row >= LTS", 6 = "row < UTE".
+// The same with 4 added where the pairs needed are decided by a single comparison each per element (bits 28, 29):
+// 5 = "row >= LTS", 6 = "row < UTE", 7 = either.
 __device__ __forceinline__ int entry_mask_mode(int entry) {
-  const int need = (entry >> 26) & 3;
-  if (need == 1 && ((entry >> 28) & 1)) return 5;
-  if (need == 2 && ((entry >> 29) & 1)) return 6;
-  return need;
+  const int need = (entry >> 26) & 3, single = (entry >> 28) & 3;
+  return need != 0 && (need & ~single) == 0 ? need | 4 : need;
 }
 
 // --- direct units -----------------------------------------------------------------------------------------
