@@ -264,7 +264,42 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
             // which pairs the workgroup's tile needs (1 = LT, 2 = UT, 3 = both): a pair that is not needed masks
             // no element of the tile, and most partially masked tiles need only one
             const int need = entry_need_pairs(entry);
-            if (need == 3) {
+            // Where one comparison per pair decides (5, 6, 7, see entry_mask_mode): half the bounds and compares.  Not in
+            // the queued loops over full blocks at d = 128, whose 256 registers are used up (18 spills, documents in
+            // 8192 tokens 988 -> 1010 us).  Training step: documents, d = 128 N = 4099 343 -> 329 us, N = 1000 79.6 ->
+            // 78.6; d = 64 N = 4099 215.7 -> 205.4, N = 1000 55.4 -> 54.0, N = 8192 614 -> 607.
+            constexpr bool SINGLE = D == 64 || DIRECT || RAGGED;
+            const int mode = SINGLE ? entry_mask_mode(entry) : 0;
+            auto bounds = [&](int which, int rq) __attribute__((always_inline)) {
+              return *(const i32x4*)(bnd + which * KT + kb * 32 + 8 * rq + 4 * g);
+            };
+            if (SINGLE && (mode & 4)) {
+              if (mode == 7) {
+#pragma unroll
+                for (int rq = 0; rq < 4; ++rq) {
+                  const i32x4 bl = bounds(0, rq), bv = bounds(3, rq);
+#pragma unroll
+                  for (int e = 0; e < 4; ++e)
+                    if ((row >= bl[e]) | (row < bv[e])) sacc[rq * 4 + e] = -INFINITY;
+                }
+              } else if (mode == 5) {
+                i32x4 b[4];
+#pragma unroll
+                for (int rq = 0; rq < 4; ++rq) b[rq] = bounds(0, rq);
+                __builtin_amdgcn_sched_barrier(0);   // all four in flight together
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                  if (row >= b[r / 4][r % 4]) sacc[r] = -INFINITY;
+              } else {
+                i32x4 b[4];
+#pragma unroll
+                for (int rq = 0; rq < 4; ++rq) b[rq] = bounds(3, rq);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                  if (row < b[r / 4][r % 4]) sacc[r] = -INFINITY;
+              }
+            } else if (need == 3) {
 #pragma unroll
               for (int rq = 0; rq < 4; ++rq) {
                 const int kx = kb * 32 + 8 * rq + 4 * g;
