@@ -324,8 +324,6 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
 #pragma unroll
   for (int kk = 0; kk < NKK; ++kk)
     qreg[kk] = *(const bf16x8*)(qp + (size_t)(RAGGED ? min(qw0 + c, Nr - 1) : qw0 + c) * q_rs + kk * 16 + 8 * g);
-#pragma unroll
-  for (int kk = 0; kk < NKK; ++kk) settle(qreg[kk]);
 
   f32x16 oacc[NDB];
   float m_run = -INFINITY, l_run = 0.f;   // log2 domain
@@ -413,6 +411,9 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
         !DIRECT ? build_live_key_blocks<T_UNMASKED>(table, t_c, chunk, chunk_end, q0, r1, C::BR / 4, list, wave_cnt)
                 : build_live_key_blocks_direct<RAGGED, T_UNMASKED, WR, S * WR>(bnd_rows, Nr, chunk, chunk_end, q0, r1, list, wave_cnt);
     if (n_live == 0) continue;
+    // The Q rows are waited for here, behind the list that their loads were in flight beside.  (No-op after the first pass.)
+#pragma unroll
+    for (int kk = 0; kk < NKK; ++kk) settle(qreg[kk]);
     // the entries of steps T, T + 1, T + 2 of the step about to run (clamped to the last one)
     int e_t[NT], e_1[NT], e_2[NT];
 #pragma unroll
@@ -423,12 +424,14 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
     }
     {
 #pragma unroll
+      for (int s_ = 0; s_ < NT; ++s_) FM_LOAD_K(e_t[s_], 0, sub0 + s_);
+#pragma unroll
       for (int s_ = 0; s_ < NT; ++s_) {
-        FM_LOAD_K(e_t[s_], 0, sub0 + s_);
         FM_LOAD_V(e_t[s_], 0, sub0 + s_);
         FM_LOAD_K(e_1[s_], 1, sub0 + s_);
       }
-      async_wait<0>();
+      // the first scores need the first K tiles only: V and the K after them (at least as many copies) may be in flight
+      async_wait<2 * NT * CopyLanes<D>::NINST>();
       barrier_nofence();
     }
     // scores of the first tile
@@ -444,6 +447,7 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb)
           s0[kb] = mfma32(*(const bf16x8*)(ks + kb * 32 * C::L::RS + C::L::add_col(w.a_off, kk * 32)), qreg[kk], s0[kb]);
+      async_wait<0>();
       barrier_nofence();   // the first iteration refills this K stage: every wave must have read it
     }
     const int n_steps = (n_live + S - 1) / S;
