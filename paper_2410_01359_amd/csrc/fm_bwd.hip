@@ -902,8 +902,16 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
   const __bf16* kp = slice_ptr<D, GEN>(a.k, a.sk, b, hk, Hk, Nr);
   const __bf16* vp = slice_ptr<D, GEN>(a.v, a.sv, b, hk, Hk, Nr);
 
-  // K and V fragments of this wave's 32 keys (B operands of S = Q K^T, dP = dO V^T) and the four
-  // bounds of this lane's key, which stay in registers (Algorithm 2 loads them once per key
+  // Lanes past the last key work on a copy of it, its bounds like its K and V: what they sum is stored nowhere, and
+  // the columns that do not exist keep no tile of a direct unit alive (as columns that mask every row they left every
+  // row block partially masked).
+  const size_t bnd = (size_t)b * Nr + key_ld;
+  int b_lts = a.lts[bnd], b_lte = a.lte[bnd], b_uts = a.uts[bnd], b_ute = a.ute[bnd];
+  // Requested first: a direct unit's list is built from them, and loads return in order.  Training step, d = 128, N = 512
+  // 35.0 -> 33.9 us, N = 1500 window 200 55.1 -> 54.1, causal 2048, 24 slices 199.2 -> 196.9; d = 64 0.3 to 1.3 %.
+  __builtin_amdgcn_sched_barrier(0);
+  // K and V fragments of this wave's 32 keys (B operands of S = Q K^T, dP = dO V^T), which like the four
+  // bounds of this lane's key stay in registers (Algorithm 2 loads them once per key
   // block).  They are only waited for after the first tile copies have been issued.
   bf16x8 kreg[NKK], vreg[NKK];
 #pragma unroll
@@ -911,11 +919,6 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
     kreg[kk] = *(const bf16x8*)(kp + (size_t)key_ld * k_rs + kk * 16 + 8 * g);
     vreg[kk] = *(const bf16x8*)(vp + (size_t)key_ld * v_rs + kk * 16 + 8 * g);
   }
-  // Lanes past the last key work on a copy of it, its bounds like its K and V: what they sum is stored nowhere, and
-  // the columns that do not exist keep no tile of a direct unit alive (as columns that mask every row they left every
-  // row block partially masked).
-  const size_t bnd = (size_t)b * Nr + key_ld;
-  int b_lts = a.lts[bnd], b_lte = a.lte[bnd], b_uts = a.uts[bnd], b_ute = a.ute[bnd];
 
   if (DIRECT) {   // the unit's min/max values from its own keys' bounds: over the wave's 32 keys, then over the waves
     const int own[4] = {b_lts, b_lte, b_uts, b_ute};
