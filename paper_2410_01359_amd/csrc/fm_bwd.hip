@@ -96,6 +96,15 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
   if (GEN) copy_lanes_v_.init(lane, 2 * v_rs);
   const CopyLanes<D>& copy_lanes_v = GEN ? copy_lanes_v_ : copy_lanes;
 
+  const int* bnd_rows[4] = {a.lts + (size_t)b * Nr, a.lte + (size_t)b * Nr, a.uts + (size_t)b * Nr, a.ute + (size_t)b * Nr};
+  // Where one pass covers all key blocks, their bounds are requested ahead of the rows and classified while those are in
+  // flight.  With more passes it would be one more round trip: two are requested together then.
+  DirectPass<RAGGED, T_FULLY, WR, S * WR> first;
+  const bool one_pass = DIRECT && t_c <= first.BLOCKS;
+  if (one_pass) {
+    first.load(bnd_rows, Nr, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  }
   bf16x8 qreg[NKK], doreg[NKK];
 #pragma unroll
   for (int kk = 0; kk < NKK; ++kk) {
@@ -116,6 +125,10 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
     bf16x8 oreg[NKK];
 #pragma unroll
     for (int kk = 0; kk < NKK; ++kk) oreg[kk] = *(const bf16x8*)(outp + (size_t)row_ld * o_rs + kk * 16 + 8 * g);
+    if (one_pass) {
+      __builtin_amdgcn_sched_barrier(0);   // behind the requests for the rows
+      first.classify(Nr, 0, 0, t_c, q0, min(q0 + C::BR, Nr), (int*)smem);
+    }
 #pragma unroll
     for (int kk = 0; kk < NKK; ++kk)
 #pragma unroll
@@ -184,9 +197,7 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
     if constexpr (!DIRECT) {
       n_live = build_live_key_blocks<T_FULLY>(table, t_c, chunk, chunk_end, q0, r1, C::BR / 4, list, wave_cnt);
     } else {
-      const int* bnd_rows[4] = {a.lts + (size_t)b * Nr, a.lte + (size_t)b * Nr, a.uts + (size_t)b * Nr,
-                                a.ute + (size_t)b * Nr};
-      n_live = build_live_key_blocks_direct<RAGGED, T_FULLY, WR, S * WR>(bnd_rows, Nr, chunk, chunk_end, q0, r1, list, wave_cnt);
+      n_live = build_live_key_blocks_direct<RAGGED, T_FULLY, WR, S * WR>(one_pass, bnd_rows, Nr, chunk, chunk_end, q0, r1, list, wave_cnt);
     }
     if (n_live == 0) continue;
     // the entries of tiles t and t + 1 travel in scalar registers; the one that joins them at the next tile is

@@ -551,63 +551,67 @@ __device__ __forceinline__ int direct_unit(int units, int blocks) {
 // build_live_key_blocks for key blocks of 64 columns straight from the bound vectors (vec: a batch row's LTS, LTE,
 // UTS, UTE; n columns).  Sixteen lanes take a block, four columns each, so a pass of four waves covers 1024
 // columns; where the columns go beyond that, two passes have their loads in flight together (forward over a window of
-// 256, N = 16384, d = 64: 16.5 us, one at a time 17.5), and a second pass over no columns is left out (N = 512, d = 64,
-// training step 29.3 -> 28.5 us; the loads and the classes of the columns that it repeated).  Ragged lengths take one pass
+// 256, N = 16384, d = 64: 16.5 us, one at a time 17.5); where they do not, the caller makes the one pass beside its own
+// loads.  Ragged lengths take one pass
 // at a time: their loads are single words, and two passes' worth of registers spilled (N = 333, d = 128, forward 11.2 ->
 // 10.8 us; N = 32691, window 45.0 -> 42.7).  The raw entries go to list[] in place (-1: fully
 // masked) and are compacted from there.  NW: waves that own rows (32 each) of the unit.
 // WAVES: waves of the workgroup.
+// A pass's bounds, and the raw entries of its blocks.
 template <bool RAGGED, int EMPTY, int NW, int WAVES>
-__device__ __forceinline__ int build_live_key_blocks_direct(const int* const (&vec)[4], int n, int j_begin, int j_end,
-                                                            int r0, int r1, int* list, int* wave_cnt) {
-  constexpr int KT = 64, THREADS = 64 * WAVES, BLOCKS = THREADS * 4 / KT;
-  const int tid = threadIdx.x;
-  auto classify_columns = [&](auto passes) __attribute__((always_inline)) {
-    constexpr int PASSES = decltype(passes)::value;
-    for (int base = j_begin; base < j_end; base += BLOCKS * PASSES) {
-      i32x4 x[PASSES][4];
+struct DirectPass {
+  static constexpr int KT = 64, BLOCKS = 64 * WAVES * 4 / KT;   // blocks per pass
+  i32x4 x[4];
+  __device__ __forceinline__ void load(const int* const (&vec)[4], int n, int base) {
+    const int key = (base + (int)threadIdx.x / 16) * KT + ((int)threadIdx.x % 16) * 4;
 #pragma unroll
-      for (int p = 0; p < PASSES; ++p) {
-        const int j = base + p * BLOCKS + tid / 16, key = j * KT + (tid % 16) * 4;
+    for (int a = 0; a < 4; ++a) {
+      if (RAGGED) {
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          if (RAGGED) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) x[p][a][e] = vec[a][min(key + e, n - 1)];
-          } else {
-            x[p][a] = *(const i32x4*)(vec[a] + min(key, n - 4));
-          }
-        }
-      }
-#pragma unroll
-      for (int p = 0; p < PASSES; ++p) {
-        const int j = base + p * BLOCKS + tid / 16, key = j * KT + (tid % 16) * 4;
-        MinMax8 mm;
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          if (RAGGED) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (key + e >= n) x[p][a][e] = a & 1 ? INT32_MAX : INT32_MIN;   // pad_column
-          }
-          const i32x4 v = x[p][a];
-          mm.v[2 * a] = row16_max(max(max(v[0], v[1]), max(v[2], v[3])));
-          mm.v[2 * a + 1] = row16_min(min(min(v[0], v[1]), min(v[2], v[3])));
-        }
-        const int cls = classify_tile(r0, r1, mm);
-        int entry = (j - j_begin) | ((cls & 3) << 16) | (((cls >> 4) & 3) << 26) | ((mm.v[LTE_MIN] >= r1 ? 1 : 0) << 28) |
-                    ((mm.v[UTS_MAX] <= r0 ? 1 : 0) << 29);
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-          const int w0 = min(r0 + w * 32, r1), w1 = min(w0 + 32, r1);
-          entry |= (w0 < w1 ? classify_tile(w0, w1, mm) & 3 : EMPTY) << (18 + 2 * w);
-        }
-        if (tid % 16 == 0 && j < j_end) list[j - j_begin] = cls == T_FULLY ? -1 : entry;
+        for (int e = 0; e < 4; ++e) x[a][e] = vec[a][min(key + e, n - 1)];
+      } else {
+        x[a] = *(const i32x4*)(vec[a] + min(key, n - 4));
       }
     }
-  };
-  if (RAGGED || j_end - j_begin <= BLOCKS) classify_columns(std::integral_constant<int, 1>{});
-  else classify_columns(std::integral_constant<int, 2>{});
+  }
+  __device__ __forceinline__ void classify(int n, int base, int j_begin, int j_end, int r0, int r1, int* list) {
+    const int tid = threadIdx.x, j = base + tid / 16, key = j * KT + (tid % 16) * 4;
+    MinMax8 mm;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      if (RAGGED) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (key + e >= n) x[a][e] = a & 1 ? INT32_MAX : INT32_MIN;   // pad_column
+      }
+      mm.v[2 * a] = row16_max(max(max(x[a][0], x[a][1]), max(x[a][2], x[a][3])));
+      mm.v[2 * a + 1] = row16_min(min(min(x[a][0], x[a][1]), min(x[a][2], x[a][3])));
+    }
+    const int cls = classify_tile(r0, r1, mm);
+    int entry = (j - j_begin) | ((cls & 3) << 16) | (((cls >> 4) & 3) << 26) | ((mm.v[LTE_MIN] >= r1 ? 1 : 0) << 28) |
+                ((mm.v[UTS_MAX] <= r0 ? 1 : 0) << 29);
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const int w0 = min(r0 + w * 32, r1), w1 = min(w0 + 32, r1);
+      entry |= (w0 < w1 ? classify_tile(w0, w1, mm) & 3 : EMPTY) << (18 + 2 * w);
+    }
+    if (tid % 16 == 0 && j < j_end) list[j - j_begin] = cls == T_FULLY ? -1 : entry;
+  }
+};
+// done: the raw entries are in list[] (the caller's single pass covers all blocks).
+template <bool RAGGED, int EMPTY, int NW, int WAVES>
+__device__ __forceinline__ int build_live_key_blocks_direct(bool done, const int* const (&vec)[4], int n, int j_begin,
+                                                            int j_end, int r0, int r1, int* list, int* wave_cnt) {
+  using Pass = DirectPass<RAGGED, EMPTY, NW, WAVES>;
+  constexpr int THREADS = 64 * WAVES, PASSES = RAGGED ? 1 : 2;
+  const int tid = threadIdx.x;
+  for (int base = done ? j_end : j_begin; base < j_end; base += Pass::BLOCKS * PASSES) {
+    Pass pass[PASSES];
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) pass[p].load(vec, n, base + p * Pass::BLOCKS);
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) pass[p].classify(n, base + p * Pass::BLOCKS, j_begin, j_end, r0, r1, list);
+  }
   barrier_nofence();
   int running = 0;
   for (int base = j_begin; base < j_end; base += THREADS) {

@@ -319,11 +319,24 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
   if (GEN) copy_lanes_v_.init(lane, 2 * v_rs);
   const CopyLanes<D>& copy_lanes_v = GEN ? copy_lanes_v_ : copy_lanes;
 
+  const int* bnd_rows[4] = {a.lts + (size_t)b * Nr, a.lte + (size_t)b * Nr, a.uts + (size_t)b * Nr, a.ute + (size_t)b * Nr};
+  // Where one pass covers all key blocks, their bounds are requested ahead of the rows and classified while those are in
+  // flight.  With more passes it would be one more round trip: two are requested together then.
+  DirectPass<RAGGED, T_UNMASKED, WR, S * WR> first;
+  const bool one_pass = DIRECT && t_c <= first.BLOCKS;
+  if (one_pass) {
+    first.load(bnd_rows, Nr, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  }
   // Q fragments (B operand of S^T = K Q^T): lane holds Q[row c][16 kk + 8 g ..+7].
   bf16x8 qreg[NKK];
 #pragma unroll
   for (int kk = 0; kk < NKK; ++kk)
     qreg[kk] = *(const bf16x8*)(qp + (size_t)(RAGGED ? min(qw0 + c, Nr - 1) : qw0 + c) * q_rs + kk * 16 + 8 * g);
+  if (one_pass) {
+    __builtin_amdgcn_sched_barrier(0);   // behind the requests for the rows
+    first.classify(Nr, 0, 0, t_c, q0, min(q0 + C::BR, Nr), (int*)smem);
+  }
 
   f32x16 oacc[NDB];
   float m_run = -INFINITY, l_run = 0.f;   // log2 domain
@@ -403,13 +416,15 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
     }                                                                                            \
   }
 
-  const int* bnd_rows[4] = {a.lts + (size_t)b * Nr, a.lte + (size_t)b * Nr, a.uts + (size_t)b * Nr, a.ute + (size_t)b * Nr};
   // only the key blocks [j_lo, j_hi) can be live for this row block (found by the work pre-pass)
   for (int chunk = j_lo; chunk < j_hi; chunk += C::LIST_CAP) {
     const int chunk_end = min(chunk + C::LIST_CAP, j_hi), r1 = min(q0 + C::BR, Nr);
-    const int n_live =
-        !DIRECT ? build_live_key_blocks<T_UNMASKED>(table, t_c, chunk, chunk_end, q0, r1, C::BR / 4, list, wave_cnt)
-                : build_live_key_blocks_direct<RAGGED, T_UNMASKED, WR, S * WR>(bnd_rows, Nr, chunk, chunk_end, q0, r1, list, wave_cnt);
+    int n_live;
+    if constexpr (!DIRECT) {
+      n_live = build_live_key_blocks<T_UNMASKED>(table, t_c, chunk, chunk_end, q0, r1, C::BR / 4, list, wave_cnt);
+    } else {
+      n_live = build_live_key_blocks_direct<RAGGED, T_UNMASKED, WR, S * WR>(one_pass, bnd_rows, Nr, chunk, chunk_end, q0, r1, list, wave_cnt);
+    }
     if (n_live == 0) continue;
     // The Q rows are waited for here, behind the list that their loads were in flight beside.  (No-op after the first pass.)
 #pragma unroll
