@@ -462,10 +462,15 @@ struct DkdvCfg {
   static constexpr int LIST_CAP = 2048;
   static constexpr int CNT_OFF = LIST_CAP * 4;
   static constexpr int STAGE_OFF = CNT_OFF + 256;   // stages start at multiples of 256 bytes (dkdv_operand)
-  // One workgroup per CU: a tile's math takes about a microsecond, less than a
-  // trip to L2/HBM, so tiles are copied three steps ahead into a ring of four.  S = 2 has the four stages as two
+  // A copy's trip to L2 or HBM is longer than a tile's math, so it has two tiles' time.  Two workgroups per CU (d = 64): a
+  // tile is copied three ahead, behind the workgroup step near a tile's end.  One (d = 128): two ahead, in the first steps
+  // of a tile, which carry no vector work; the stage it goes into held the tile two back, which every wave had left when it
+  // took the last workgroup step, so four stages need no barrier in front of the copies.  A unit then starts with two
+  // tiles' copies instead of three and does not end with a wait for copies issued in its last steps: training step, d =
+  // 128, prefix 4096 of 32768 8037 -> 7968 us, documents in 8192 984 -> 976, causal 4096 615 -> 610; at d = 64, where the
+  // other workgroup covers both, 0.5 % slower.  S = 2 has the four stages as two
   // pairs: a step's two tiles are copied while the step before them runs.
-  static constexpr int NSTAGE = 4;
+  static constexpr int NSTAGE = 4, AHEAD = S == 2 ? 1 : D == 128 ? 2 : 3;   // AHEAD in steps
   static constexpr int LDS_BYTES = STAGE_OFF + NSTAGE * STAGE;
   // async copy instructions one wave issues per tile: COPIES for its quarter of Q and dO plus
   // one for its quarter of the lse / D slice.  Every wave issues the same number for every
@@ -523,7 +528,7 @@ __device__ __forceinline__ void dkdv_stage_a(const f32x16& s, const f32x16& dp, 
 template <int S>
 struct DkdvAhead {
   const char* nqs;        // LDS: stage of the next list entry (its Q tile; dO follows), for the operand prefetch
-  int v_copy[S];          // list entry (still in a vector register) of the tile NSTAGE - 1 ahead, to be copied
+  int v_copy[S];          // list entry (still in a vector register) of the tile AHEAD steps ahead, to be copied
                           // (S = 2: of the next step's two tiles)
   const char* q_base;     // global Q / dO of this (batch, head), already advanced to this wave's 16-row block
   const char* do_base;    // of a tile, and this lane's lse2 / D source
@@ -633,9 +638,8 @@ __device__ __forceinline__ void dkdv_sync() {
 // small register ring.  The exp / dS arithmetic of block 0 is spread over the
 // steps of S1 and dP1, that of block 1 over the dV,dK steps of block 0, so the
 // vector work always has matrix work in flight beside it.  The stream runs on
-// into the next list entry: near its end the wave takes the workgroup step
-// (dkdv_sync), issues the copies of the tile NSTAGE - 1 entries ahead one per
-// step, and its last RD operand fetches already read the next entry's tile, so
+// into the next list entry: the copies of the tile AHEAD entries ahead go out one
+// per step, near its end the wave takes the workgroup step (dkdv_sync), and its last RD operand fetches already read the next entry's tile, so
 // the MFMA pipe does not drain between tiles.  On entry `op` holds the operands
 // of steps 0..RD-1 of this tile, on exit those of the next one.
 //
@@ -654,9 +658,10 @@ __device__ __forceinline__ void dkdv_tile(const char* qs, const float* vec_s, co
   constexpr int EPS = 16 / NST;    // elements handled next to one MFMA (D = 128: 1, D = 64: 2)
   constexpr int NX = 4 * NST;      // MFMAs per tile
   constexpr int RD = C::RD;
-  constexpr int XS = S == 2 ? NX - RD : NX - (C::NC > RD ? C::NC : RD);   // step of the workgroup sync
-  constexpr int XC = S == 2 ? 0 : XS;                  // first of the steps that issue the copies, one each
-  static_assert(NX % RD == 0 && XS > 0 && (S == 1 || S * C::NC <= XS), "ring layout");
+  constexpr bool BEHIND = S == 1 && C::AHEAD == 3;       // the copies are issued behind the workgroup sync
+  constexpr int XS = NX - (BEHIND && C::NC > RD ? C::NC : RD);   // step of the workgroup sync
+  constexpr int XC = BEHIND ? XS : S == 2 ? 0 : RD;      // first of the steps that issue the copies, one each
+  static_assert(NX % RD == 0 && XS > 0 && (BEHIND || XC + S * C::NC <= XS), "ring layout");
   const f32x16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
   const DkdvBases bs_cur = dkdv_bases(qs, a_base, t_base0, t_base1);
   const DkdvBases bs_next = dkdv_bases(ah.nqs, a_base, t_base0, t_base1);
@@ -875,7 +880,7 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
 #define FM_TILE_LOOP(T0, T1, MASK)                                                                     \
   for (int t = (T0); t < (T1); ++t) {                                                                  \
     const int v_next = list[min(S * (t + 1) + grp, n_live - 1)];                                       \
-    constexpr int AHEAD = C::NSTAGE / S - 1;   /* steps between a tile and the one copied beside it */ \
+    constexpr int AHEAD = C::AHEAD;   /* steps between a tile and the one copied beside it */            \
     _Pragma("unroll") for (int s_ = 0; s_ < S; ++s_) ah.v_copy[s_] = list[min(S * (t + AHEAD) + s_, n_live - 1)]; \
     ah.nqs = smem + C::STAGE_OFF + ((S * (t + 1)) % C::NSTAGE + grp) * C::STAGE;                       \
     ah.stage_copy = (S * (t + AHEAD)) % C::NSTAGE;                                                     \
@@ -979,9 +984,8 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
     ah.q_base = (const char*)qp + (size_t)(wave * 16) * ah.q_rs2;
     ah.do_base = (const char*)dop + (size_t)(wave * 16) * ah.do_rs2;
     ah.vec_src = my_vec;
-    // prologue: copies of the first NSTAGE - 1 tiles (S = 2: of the first step's two), then the first tile's first
-    // operands
-    constexpr int FIRST = S == 2 ? 2 : C::NSTAGE - 1;
+    // prologue: copies of the tiles of the first AHEAD steps, then the first tile's first operands
+    constexpr int FIRST = S * C::AHEAD;
 #pragma unroll
     for (int p = 0; p < FIRST; ++p) {
       const int i_p = __builtin_amdgcn_readfirstlane(list[min(p, n_live - 1)]) & 0xFFFFFF;
@@ -1014,7 +1018,7 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
     settle(b_ute);
     // lengths of the key's two masked row intervals, for the element mask's compare
     const unsigned len_lt = interval_length(b_lts, b_lte), len_ut = interval_length(b_uts, b_ute);
-    async_wait<S == 2 ? 0 : (C::NSTAGE - 2) * C::NC>();
+    async_wait<S == 2 ? 0 : (C::AHEAD - 1) * C::NC>();
     barrier_nofence();
     int e_cur = __builtin_amdgcn_readfirstlane(list[min(grp, n_live - 1)]);
 #pragma unroll
