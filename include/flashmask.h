@@ -225,10 +225,9 @@ int flashmask_classify(const int32_t* minmax, int B, int N, int block_r, int blo
  * within a group the units holding at least an eighth of the largest possible work come first, by
  * falling work, then the lighter ones by falling octave of work.  workspace as for the pass
  * (FM_PASS_FWD for the forward, FM_PASS_BWD otherwise); the records are copied out of it on the
- * stream.  N here is rounded up to a multiple of 128 (T counts blocks of the padded length), and the
- * columns past the end count as keys that the lower pair masks for every row, so that a ragged last key
- * block is live wherever the lower pair alone decides.  (An attention call's own queues leave those columns
- * out: no live range reaches a key block for their sake.)
+ * stream.  N here is rounded up to a multiple of 128 (T counts blocks of the padded length); the columns
+ * past the end widen no live range (FM_PASS_FWD, FM_PASS_BWD_DQ: keys that both pairs mask for every row;
+ * FM_PASS_BWD_DKDV: a ragged last key block has the keys that exist).
  */
 int flashmask_unit_queues(int pass, const int32_t* lts, const int32_t* lte, const int32_t* uts, const int32_t* ute,
                           int B, int H, int N, int d, int32_t* records, int* slots,

@@ -290,7 +290,7 @@ int flashmask_unit_queues(int pass, const int32_t* lts, const int32_t* lte, cons
   const PassSpace sp = pass_space(B, H, Np, br, bc, rows, 0);
   e = fm_launch_setup(lts, lte, uts, ute, B, H, H, N, Np,
                       FmSetup{br, bc, (int*)(ws + sp.minmax), (int*)(ws + sp.work), (int*)(ws + sp.range), (int*)(ws + sp.order),
-                              FM_PADS_LOWER},
+                              rows ? FM_PADS_MASKED : FM_PADS_NONE},
                       !rows, stream);
   if (e != hipSuccess) return hip_fail(e);
   e = hipMemcpyAsync(records, ws + sp.order, (size_t)*slots * 16, hipMemcpyDeviceToDevice, stream);

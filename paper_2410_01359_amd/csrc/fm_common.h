@@ -43,7 +43,6 @@ static __device__ const int pad_column[4] = {INT32_MIN, INT32_MAX, INT32_MIN, IN
 // The value of bound `which` that the columns past the end count with in a table (FM_PADS_NONE: `real`, a value of the block).
 __device__ __forceinline__ int pad_value(FmPads pads, int which, int real) {
   if (pads == FM_PADS_NONE) return real;
-  if (pads == FM_PADS_LOWER && which >= 2) return 0;
   return which & 1 ? INT32_MAX : INT32_MIN;
 }
 // Bound `which` (0..3 = LTS, LTE, UTS, UTE) of key column `key` of a batch row's vector.

@@ -183,7 +183,6 @@ constexpr int FM_DKDV_BR = 64, FM_DKDV_BC = 128;
 enum FmPads {
   FM_PADS_NONE,     // nothing: a block covers the columns that exist (dK/dV units, whose lanes past the last key copy it)
   FM_PADS_MASKED,   // masked for every row by both pairs (the row-parallel loops, see pad_column)
-  FM_PADS_LOWER,    // masked for every row by the lower pair, upper pair empty at row 0 (flashmask_unit_queues)
 };
 // One pass's setup buffers (in the workspace) and tile shape.
 struct FmSetup {

@@ -65,10 +65,13 @@ def test_records_on_both_sides_of_the_one_launch_setup(kind, B, H, N):
         units = n_pad // 128
         assert len(rec) == B * H * units
         for b in range(B):
-            # the columns past the end carry one interval that masks every row
-            pads = (np.iinfo(np.int32).min, np.iinfo(np.int32).max, 0, 0)
-            mm = [np.pad(v[b].astype(np.int64), (0, n_pad - N), constant_values=p).reshape(-1, bc)
-                  for v, p in zip(w.stacked_vectors(), pads)]
+            # The columns past the end: masked for every row by both pairs where they are keys of a row; a dK/dV block
+            # has the keys that exist (repeating the last one adds nothing to a min or max).
+            i32 = np.iinfo(np.int32)
+            mm = []
+            for v, p in zip(w.stacked_vectors(), (i32.min, i32.max, i32.min, i32.max)):
+                how = {"mode": "edge"} if pass_id == fm.FM_PASS_BWD_DKDV else {"constant_values": p}
+                mm.append(np.pad(v[b].astype(np.int64), (0, n_pad - N), **how).reshape(-1, bc))
             r0 = np.arange(0, N, br)[:, None]
             r1 = np.minimum(r0 + br, N)
             full = ((r0 >= mm[0].max(1)) & (r1 <= mm[1].min(1))) | ((r0 >= mm[2].max(1)) & (r1 <= mm[3].min(1)))
@@ -78,3 +81,39 @@ def test_records_on_both_sides_of_the_one_launch_setup(kind, B, H, N):
             for h in range(H):
                 got = rec[(b * H + h) * units:(b * H + h + 1) * units]
                 assert np.array_equal(got[:, 1], lo) and np.array_equal(got[:, 2], hi), (pass_id, b, h)
+
+
+# every loop queued, ragged and not: setup in one launch, in three, and in three for short sequences in many slices
+@pytest.mark.parametrize("H,N,d,launches", [(160, 1000, 128, 1), (200, 1100, 64, 1), (24, 4099, 64, 3), (24, 4352, 128, 3),
+                                            (520, 600, 128, 3), (1100, 200, 64, 3)])
+@pytest.mark.parametrize("kind", ["document", "random_intervals", "sliding_window"])
+def test_calls_follow_these_records(kind, H, N, d, launches):
+    """What flashmask_unit_queues returns is what an attention call builds: the call's workspace holds the same records in the
+    same queues (the forward's, and both of the backward's, whose tables one launch forms together)."""
+    w = workloads.small_workload(kind, N, seed=H + N, B=1, H=1, d=d)
+    _, dev, vecs = to_device(w)
+    x = {n: dev[n].expand(1, H, N, d).contiguous() for n in ("q", "k", "v", "dout")}
+    for p in (fm.FM_PASS_FWD, fm.FM_PASS_BWD):
+        assert fm.flashmask_setup_launches(p, 1, H, H, N, d) == launches
+    ws = [torch.zeros(fm.flashmask_workspace_bytes(p, 1, H, N, d), dtype=torch.uint8, device="cuda")
+          for p in (fm.FM_PASS_FWD, fm.FM_PASS_BWD)]
+    out, lse = fm.flashmask_fwd(x["q"], x["k"], x["v"], *vecs, w.scale, workspace=ws[0])
+    fm.flashmask_bwd(x["q"], x["k"], x["v"], out, lse, x["dout"], *vecs, w.scale, workspace=ws[1])
+    held = [t.cpu().numpy().view(np.int32).reshape(-1, 4) for t in ws]
+    for pass_id, where in ((fm.FM_PASS_FWD, 0), (fm.FM_PASS_BWD_DQ, 1), (fm.FM_PASS_BWD_DKDV, 1)):
+        assert fm.flashmask_work_cut(pass_id, 1, H, H, N, d) == fm.FM_CUT_QUEUED
+        rec = fm.flashmask_unit_queues(pass_id, *vecs, H, d).cpu().numpy()
+        assert _holds(held[where], rec), f"pass {pass_id}: the call's records are others"
+
+
+def _by_queue(rec):
+    """Records by queue and unit: units of one rank have no fixed order within their queue."""
+    rows = np.column_stack([np.arange(len(rec)) % 8, rec])
+    return rows[np.lexsort(rows.T[::-1])]
+
+
+def _holds(rows, rec):
+    """Whether a stretch of `rows` is `rec` up to the order within a queue; where its columns add up to rec's, it is compared."""
+    sums = np.vstack([np.zeros((1, 4), np.int64), np.cumsum(rows, axis=0, dtype=np.int64)])
+    starts = np.nonzero((sums[len(rec):] - sums[:-len(rec)] == rec.sum(axis=0, dtype=np.int64)).all(axis=1))[0]
+    return any(np.array_equal(_by_queue(rows[i:i + len(rec)]), _by_queue(rec)) for i in starts)
