@@ -96,10 +96,12 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
   if (GEN) copy_lanes_v_.init(lane, 2 * v_rs);
   const CopyLanes<D>& copy_lanes_v = GEN ? copy_lanes_v_ : copy_lanes;
 
+  int* list = (int*)smem;
   const int* bnd_rows[4] = {a.lts + (size_t)b * Nr, a.lte + (size_t)b * Nr, a.uts + (size_t)b * Nr, a.ute + (size_t)b * Nr};
   // Where one pass covers all key blocks, their bounds are requested ahead of the rows and classified while those are in
   // flight.  With more passes it would be one more round trip: two are requested together then.
   DirectPass<RAGGED, T_FULLY, WR, S * WR> first;
+  static_assert(first.BLOCKS <= C::LIST_CAP, "a pass fits the list");
   const bool one_pass = DIRECT && t_c <= first.BLOCKS;
   if (one_pass) {
     first.load(bnd_rows, Nr, 0);
@@ -127,7 +129,7 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
     for (int kk = 0; kk < NKK; ++kk) oreg[kk] = *(const bf16x8*)(outp + (size_t)row_ld * o_rs + kk * 16 + 8 * g);
     if (one_pass) {
       __builtin_amdgcn_sched_barrier(0);   // behind the requests for the rows
-      first.classify(Nr, 0, 0, t_c, q0, min(q0 + C::BR, Nr), (int*)smem);
+      first.classify(Nr, 0, 0, t_c, q0, min(q0 + C::BR, Nr), list);
     }
 #pragma unroll
     for (int kk = 0; kk < NKK; ++kk)
@@ -155,7 +157,6 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) dqacc[db][r] = 0.f;
 
-  int* list = (int*)smem;
   int* wave_cnt = (int*)(smem + C::CNT_OFF);
   const float sc = a.scale * kLog2e;
   // lane-dependent LDS offsets inside a tile (row block 0, first column group)

@@ -319,10 +319,12 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
   if (GEN) copy_lanes_v_.init(lane, 2 * v_rs);
   const CopyLanes<D>& copy_lanes_v = GEN ? copy_lanes_v_ : copy_lanes;
 
+  int* list = (int*)(smem + C::LIST_OFF);
   const int* bnd_rows[4] = {a.lts + (size_t)b * Nr, a.lte + (size_t)b * Nr, a.uts + (size_t)b * Nr, a.ute + (size_t)b * Nr};
   // Where one pass covers all key blocks, their bounds are requested ahead of the rows and classified while those are in
   // flight.  With more passes it would be one more round trip: two are requested together then.
   DirectPass<RAGGED, T_UNMASKED, WR, S * WR> first;
+  static_assert(first.BLOCKS <= C::LIST_CAP, "a pass fits the list");
   const bool one_pass = DIRECT && t_c <= first.BLOCKS;
   if (one_pass) {
     first.load(bnd_rows, Nr, 0);
@@ -335,7 +337,7 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
     qreg[kk] = *(const bf16x8*)(qp + (size_t)(RAGGED ? min(qw0 + c, Nr - 1) : qw0 + c) * q_rs + kk * 16 + 8 * g);
   if (one_pass) {
     __builtin_amdgcn_sched_barrier(0);   // behind the requests for the rows
-    first.classify(Nr, 0, 0, t_c, q0, min(q0 + C::BR, Nr), (int*)smem);
+    first.classify(Nr, 0, 0, t_c, q0, min(q0 + C::BR, Nr), list);
   }
 
   f32x16 oacc[NDB];
@@ -345,7 +347,6 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) oacc[db][r] = 0.f;
 
-  int* list = (int*)(smem + C::LIST_OFF);
   int* wave_cnt = (int*)(smem + C::CNT_OFF);
   FwdWave<D> w;
   w.sc = a.scale * kLog2e;  // > 0 (checked on the host): scores stay raw, exp2(s*sc - m) is one fma + one exp
