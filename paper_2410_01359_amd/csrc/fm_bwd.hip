@@ -279,7 +279,11 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
             // Where one comparison per pair decides (5, 6, 7, see entry_mask_mode): half the bounds and compares.  Not in
             // the queued loops over full blocks at d = 128, whose 256 registers are used up (18 spills, documents in
             // 8192 tokens 988 -> 1010 us).  Training step: documents, d = 128 N = 4099 343 -> 329 us, N = 1000 79.6 ->
-            // 78.6; d = 64 N = 4099 215.7 -> 205.4, N = 1000 55.4 -> 54.0, N = 8192 614 -> 607.
+            // 78.6; d = 64 N = 4099 215.7 -> 205.4, N = 1000 55.4 -> 54.0, N = 8192 614 -> 607.  The ragged queued loops at
+            // d = 128 spill 19 registers with it and 17 without (grouped heads: 20 and 16).  Backward there, two comparisons
+            // / one: documents N = 2001, 4099, 8115, 16307, 32691 201 / 194, 168 / 160, 366 / 352, 1061 / 1016, 259 / 251
+            // us, shared questions 144 / 141, 153 / 148, 340 / 338, 1045 / 1029, 1160 / 1137, causal, prefix and windows
+            // 0.994 to 1.006, grouped heads 0.989 to 0.998.
             constexpr bool SINGLE = D == 64 || DIRECT || RAGGED;
             const int mode = SINGLE ? entry_mask_mode(entry) : 0;
             auto bounds = [&](int which, int rq) __attribute__((always_inline)) {
@@ -467,8 +471,9 @@ struct DkdvCfg {
   // tile is copied three ahead, behind the workgroup step near a tile's end.  One (d = 128): two ahead, in the first steps
   // of a tile, which carry no vector work; the stage it goes into held the tile two back, which every wave had left when it
   // took the last workgroup step, so four stages need no barrier in front of the copies.  A unit then starts with two
-  // tiles' copies instead of three and does not end with a wait for copies issued in its last steps: training step, d =
-  // 128, prefix 4096 of 32768 8037 -> 7968 us, documents in 8192 984 -> 976, causal 4096 615 -> 610; at d = 64, where the
+  // tiles' copies instead of three and does not end with a wait for copies issued in its last steps: backward, d =
+  // 128, three / two ahead: prefix 4096 of 32768 12325 / 12230 us, documents in 8192 730 / 718, causal 4096 478 / 473,
+  // window 1024 at 32768 1034 / 1028, skewed documents at 131072 7693 / 7630; at d = 64, where the
   // other workgroup covers both, 0.5 % slower.  S = 2 has the four stages as two
   // pairs: a step's two tiles are copied while the step before them runs.
   static constexpr int NSTAGE = 4, AHEAD = S == 2 ? 1 : D == 128 ? 2 : 3;   // AHEAD in steps
@@ -808,7 +813,8 @@ __device__ __forceinline__ void dkdv_tile(const char* qs, const float* vec_s, co
 }
 
 // RAGGED: see the forward kernel -- loops at the padded length, clamped tile copies and fragment
-// loads, guarded stores; the padding rows carry lse = +inf (P = 0), the padding keys are masked.
+// loads, guarded stores; the padding rows carry lse = +inf (P = 0), and a lane past the last key works on a
+// copy of that key and stores nothing.
 // GEN: tensors with caller-given strides; a workgroup then owns 128 keys of one K/V head and
 // walks the query heads that share it one after the other (same list of live row blocks: the
 // mask does not depend on the head), accumulating dK and dV over all of them.

@@ -116,14 +116,21 @@ inline bool fm_short_direct(long long units, int d, int N, long long cus) {
 //            512 units, N = 512    direct 21 / 24 / 25 / 20, halved 24 / 29 / 30 / 24, queued 21 / 23 / 25 / 21
 //            512 units, N = 8192   halved 112 / 47 / 63 / 33, queued 116 / 59 / 73 / 21; N = 16384 causal 267, queued 219
 // At long sequences, forward alone with its setup, direct | queued, causal, prefix, documents of 700 tokens, eight documents,
-// window 256, shared questions (geometric mean of the ratios; ragged: N - 77):
-//   d = 128  256 units, N = 16384  paired 246 245 60 162 23 118 | 276 278 79 225 28 161   (0.80, ragged 0.88)
-//            256 units, N = 32768  paired 495 497 78 314 30 200 | 537 541 97 433 30 270   (0.85, ragged 0.96)
-//   d = 64   256 units, N = 16384  halved 169 167 43 115 21 84 | 197 195 72 196 24 159   (0.70, ragged 0.89)
-//            256 units, N = 32768  halved 344 345 64 218 33 143 | 376 376 100 380 26 246   (0.79, ragged 1.05)
-//            512 units, N = 8192   halved 108 109 44 64 30 77 | 118 120 65 110 27 117   (0.78, ragged 0.98)
-// Only windows lose at that length, and ragged ones most (4-byte loads of the bounds: N = 32691, d = 64 72 | 30); the line
-// carries no N where the mean does not cross.
+// window 256, shared questions (geometric mean of the ratios):
+//   d = 128  256 units, N = 16384  paired 246 245 60 162 23 118 | 276 278 79 225 28 161   (0.80)
+//            256 units, N = 32768  paired 495 497 78 314 30 200 | 537 541 97 433 30 270   (0.85)
+//   d = 64   256 units, N = 16384  halved 169 167 43 115 21 84 | 197 195 72 196 24 159   (0.70)
+//            256 units, N = 32768  halved 344 345 64 218 33 143 | 376 376 100 380 26 246   (0.79)
+//            512 units, N = 8192   halved 108 109 44 64 30 77 | 118 120 65 110 27 117   (0.78)
+// The same at ragged lengths, whose direct lists load bounds 4 bytes at a time and whose queued units have no tile for the
+// columns past the end:
+//   d = 128  256 units, N = 16307  paired 252 248 63 162 28 115 | 279 277 73 206 26 145   (0.88)
+//            256 units, N = 32691  paired 501 501 85 315 42 224 | 542 542 86 399 27 274   (0.97)
+//   d = 64   256 units, N = 16307  halved 179 177 59 126 38 100 | 211 211 63 172 22 121   (0.94)
+//            256 units, N = 32691  halved 371 370 93 243 65 193 | 407 407 73 329 24 226   (1.10)
+//            512 units, N = 8115   halved 125 124 57 74 44 71 | 120 120 54 103 26 71   (1.06)
+// Windows lose at these lengths, ragged ones most, and at d = 64 ragged documents much shorter than the sequence.  The line
+// carries no N and is one for all lengths: windows apart, the ragged mean does not cross either (0.92 and 0.96 in the last two).
 inline FmUnits fm_row_units(long long units, int per_cu, int d, int N, long long cus) {
   if (d == 128) {
     if (2 * units <= cus) return FM_DIRECT_HALVED;
@@ -156,10 +163,20 @@ inline FmUnits fm_row_units(long long units, int per_cu, int d, int N, long long
 //   d = 64   512 units, N = 16384  566 / 546, 605 / 552, 119 / 141, 326 / 332, 57 / 55, 275 / 290   (0.99)
 //            480 units, N = 20480  735 / 657, 784 / 664, 114 / 119, 427 / 411, 58 / 54, 371 / 347   (1.07)
 //            of 2, 4, 8 query heads: N = 16384 0.97, 0.96, 0.96, N = 20480 1.06, 1.06, 1.05
-// Ragged lengths, queued / halved over the same masks (mean ratio of halved): d = 128 N = 16300 297.9 / 287.0 (0.96), 24500
-// 365.0 / 361.1, 32691 465.6 / 458.0, of 4 query heads 24500 1238 / 1218, of 8 32691 3166 / 3081 (0.97): halved at any
-// length; d = 64 16307 232.7 / 227.3 (0.98), 20400 266.6 / 278.4, 32691 361.6 / 387.2, 65459 531.9 / 576.1 (1.08): the
-// line of the other lengths.
+// Ragged lengths, the same masks, halved / queued:
+//   d = 128  256 units, N = 16300  742 / 705, 753 / 704, 130 / 149, 368 / 372, 62 / 68, 342 / 343   (0.98)
+//            192 units, N = 24500  1041 / 927, 1093 / 947, 128 / 149, 566 / 540, 67 / 68, 532 / 492   (1.04)
+//            256 units, N = 32691  1555 / 1404, 1603 / 1429, 159 / 187, 770 / 708, 77 / 82, 748 / 678   (1.03)
+//            of 4 query heads 24500  3742 / 3239, 3980 / 3280, 324 / 391, 1789 / 1661, 144 / 129, 1775 / 1602   (1.08)
+//            of 8 query heads 32691  10630 / 9774, 11263 / 9883, 655 / 834, 4641 / 4096, 283 / 267, 4994 / 4443   (1.05)
+//   d = 64   512 units, N = 16307  589 / 567, 587 / 572, 108 / 124, 307 / 327, 54 / 53, 265 / 299   (0.96)
+//            480 units, N = 20400  775 / 702, 770 / 707, 104 / 104, 410 / 403, 56 / 53, 360 / 364   (1.04)
+//            512 units, N = 32691  1346 / 1139, 1368 / 1147, 123 / 146, 582 / 543, 59 / 57, 633 / 583   (1.06)
+//            512 units, N = 65459  2839 / 2208, 2960 / 2242, 160 / 169, 1525 / 1232, 61 / 56, 1449 / 1110   (1.19)
+//            of 4 query heads 32691  4896 / 4204, 5080 / 4235, 278 / 374, 1854 / 1672, 146 / 148, 2032 / 1813   (1.04)
+// At d = 64 the line of the other lengths: causal and prefix masks and long documents gain 7 to 25 %, documents of 700 tokens
+// lose up to 19 %, with four query heads 35 %.  At d = 128 halved at any length, where the mean has crossed by 3 to 8 % beyond
+// 16384 and documents of 700 tokens are 15 to 27 % faster for it.
 inline FmUnits fm_key_units(long long units, int group, int d, int N, long long cus) {
   const long long slots = fm_dkdv_per_cu(d) * cus;
   const int padded = (N + 127) / 128 * 128;
@@ -246,8 +263,8 @@ struct FmStride {
 // K/V heads, H % Hk == 0: query head h reads K/V head h / (H / Hk)); otherwise every tensor is
 // contiguous [B,H,N,d], Hk == H, and the strides are compile-time constants of the kernels.
 // N is the true sequence length (stride of the tensors and of the bound vectors), Np = N rounded up to a
-// multiple of 128: the length the tile loops and the tables work at.  When Np > N the extra key columns are
-// masked for every row (pad_column); rows are classified up to N only.
+// multiple of 128: the length the tile loops and the tables work at.  When Np > N the extra key columns count as
+// FmPads says (rows' loops: masked for every row); rows are classified up to N only.
 struct FmFwdArgs {
   const void *q, *k, *v;
   const int *lts, *lte, *uts, *ute;   // [B][N]
