@@ -174,8 +174,8 @@ inline FmUnits fm_row_units(long long units, int per_cu, int d, int N, long long
 //            512 units, N = 32691  1346 / 1139, 1368 / 1147, 123 / 146, 582 / 543, 59 / 57, 633 / 583   (1.06)
 //            512 units, N = 65459  2839 / 2208, 2960 / 2242, 160 / 169, 1525 / 1232, 61 / 56, 1449 / 1110   (1.19)
 //            of 4 query heads 32691  4896 / 4204, 5080 / 4235, 278 / 374, 1854 / 1672, 146 / 148, 2032 / 1813   (1.04)
-// At d = 64 the line of the other lengths: causal and prefix masks and long documents gain 7 to 25 %, documents of 700 tokens
-// lose up to 19 %, with four query heads 35 %.  At d = 128 halved at any length, where the mean has crossed by 3 to 8 % beyond
+// At d = 64 the line of the other lengths: causal and prefix masks gain 8 to 24 %, eight documents 2 to 19 %, documents of 700
+// tokens lose up to 19 %, with four query heads 34 %.  At d = 128 halved at any length, where the mean has crossed by 3 to 8 % beyond
 // 16384 and documents of 700 tokens are 15 to 27 % faster for it.
 inline FmUnits fm_key_units(long long units, int group, int d, int N, long long cus) {
   const long long slots = fm_dkdv_per_cu(d) * cus;
