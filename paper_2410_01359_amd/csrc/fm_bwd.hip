@@ -95,6 +95,8 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
   copy_lanes.init(lane, 2 * k_rs);
   if (GEN) copy_lanes_v_.init(lane, 2 * v_rs);
   const CopyLanes<D>& copy_lanes_v = GEN ? copy_lanes_v_ : copy_lanes;
+  const char* const kp_wave = CopyLanes<D>::wave_base(kp, cwave, 2 * k_rs);
+  const char* const vp_wave = CopyLanes<D>::wave_base(vp, cwave, 2 * v_rs);
 
   int* list = (int*)smem;
   const int* bnd_rows[4] = {a.lts + (size_t)b * Nr, a.lte + (size_t)b * Nr, a.uts + (size_t)b * Nr, a.ute + (size_t)b * Nr};
@@ -176,8 +178,8 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
         tile_load_async_clamped<D>(kp, r_, Nr, ks_, cwave, lane, 2 * k_rs);                     \
         tile_load_async_clamped<D>(vp, r_, Nr, ks_ + C::K_BYTES, cwave, lane, 2 * v_rs);        \
       } else {                                                                                 \
-        tile_load_async<D>(kp + (size_t)r_ * k_rs, copy_lanes, ks_, cwave, 2 * k_rs);           \
-        tile_load_async<D>(vp + (size_t)r_ * v_rs, copy_lanes_v, ks_ + C::K_BYTES, cwave, 2 * v_rs); \
+        tile_load_async<D>(kp_wave + (size_t)(2 * r_) * k_rs, copy_lanes, ks_, cwave);          \
+        tile_load_async<D>(vp_wave + (size_t)(2 * r_) * v_rs, copy_lanes_v, ks_ + C::K_BYTES, cwave); \
       }                                                                                        \
     }                                                                                          \
     if (entry_tile_class(ENTRY) == T_PARTIAL) {                                                \
@@ -248,12 +250,12 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
           constexpr int NS = 2 * NKK, RS = 3, NT = 2 * NDB, RT = 3;
           constexpr int EXPS = (16 + NKK - 2) / (NKK - 1);   // exponentials next to each of the last NKK - 1 dP steps
           auto s_operand = [&](int n) __attribute__((always_inline)) {
-            return lds_read_row16((a_s ^ (unsigned)((n % NKK) * 32)) + (n >= NKK ? C::K_BYTES : 0) + kb * 32 * C::L::RS);
+            return lds_read_row16(C::L::add_col(a_s, (n % NKK) * 32) + (n >= NKK ? C::K_BYTES : 0) + kb * 32 * C::L::RS);
           };
           auto t_operand = [&](int n) __attribute__((always_inline)) {
             const unsigned krow = (kb * 32 + 16 * (n / NDB)) * C::L::RS;
-            return cat4(lds_read_tr16_at((t_s0 ^ (unsigned)((n % NDB) * 64)) + krow),
-                        lds_read_tr16_at((t_s1 ^ (unsigned)((n % NDB) * 64)) + krow));
+            return cat4(lds_read_tr16_at(C::L::add_col(t_s0, (n % NDB) * 64) + krow),
+                        lds_read_tr16_at(C::L::add_col(t_s1, (n % NDB) * 64) + krow));
           };
           bf16x8 ring[RS];
 #pragma unroll
@@ -481,7 +483,7 @@ struct DkdvCfg {
   // async copy instructions one wave issues per tile: COPIES for its quarter of Q and dO plus
   // one for its quarter of the lse / D slice.  Every wave issues the same number for every
   // tile, so "tile landed" is a constant outstanding-copy count.
-  static constexpr int COPIES = 2 * (QT / (64 / L::CPR) / 4);
+  static constexpr int COPIES = 2 * CopyLanes<D>::NINST;
   static constexpr int NC = COPIES + 1;
   // MFMA operand fetch distance in steps; divides the steps per tile, so ring slots line up across tiles
   static constexpr int RD = 8;
@@ -557,12 +559,11 @@ __device__ __forceinline__ void dkdv_issue_copy(const DkdvAhead<S>& ah, const ch
   constexpr int HALF = C::COPIES / 2;
   constexpr int WB = 16 * C::L::RS;   // bytes of a wave's 16-row block
   if (RAGGED && K < C::COPIES && (i_copy + 1) * C::QT > ah.n_real) {
-    constexpr int RPI = 64 / C::L::CPR, I = K % HALF;
-    const int row = ah.wave * 16 + I * RPI + ah.lane / C::L::CPR;
-    const int grow = min(i_copy * C::QT + row, ah.n_real - 1);
-    const char* base = K < HALF ? ah.q_base : ah.do_base;
+    constexpr int I = K % HALF;
+    const int grow = min(i_copy * C::QT + ah.wave * 16 + ah.lane / 4, ah.n_real - 1);
+    const char* base = (K < HALF ? ah.q_base : ah.do_base) + CopyLanes<D>::BIAS;
     const long long rel = (long long)(grow - ah.wave * 16) * (K < HALF ? ah.q_rs2 : ah.do_rs2);   // the bases are this wave's
-    const char* src = base + rel + (((ah.lane % C::L::CPR) ^ C::L::swz(row)) << 4);
+    const char* src = base + rel + CopyLanes<D>::source_col(ah.lane, I);
     async_copy16(src, lds_stage + (K < HALF ? 0 : C::Q_BYTES) + ah.wave * WB + I * 1024);
     return;
   }
@@ -616,12 +617,12 @@ __device__ __forceinline__ bf16x8 dkdv_operand(const DkdvBases& bs, int x) {
   if (x < 2 * NST) {             // row reads: Q or dO rows of block x / NST as MFMA A operand
     const int qb = x / NST;
     const unsigned tile = dkdv_is_s<D>(x % NST) ? 0u : DO;
-    return lds_read_row16((bs.a ^ (unsigned)(dkdv_kk<D>(x % NST) * 32)) + tile + qb * 32 * L::RS);
+    return lds_read_row16(L::add_col(bs.a, dkdv_kk<D>(x % NST) * 32) + tile + qb * 32 * L::RS);
   }
   // transpose reads: dO (even step, dV) or Q (odd step, dK) as MFMA B operand
   const int u = x - 2 * NST, qb = u / NST, w = u % NST, h = w / (2 * NDB), db = (w % (2 * NDB)) / 2;
   const unsigned rows = ((u & 1) ? 0u : DO) + (qb * 32 + 16 * h) * L::RS;
-  return cat4(lds_read_tr16_at((bs.t0 ^ (unsigned)(db * 64)) + rows), lds_read_tr16_at((bs.t1 ^ (unsigned)(db * 64)) + rows));
+  return cat4(lds_read_tr16_at(L::add_col(bs.t0, db * 64) + rows), lds_read_tr16_at(L::add_col(bs.t1, db * 64) + rows));
 }
 
 // The workgroup-level step that every wave takes once per list entry, in the middle of the
@@ -988,8 +989,8 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
     // every wave copies its 16 rows of a tile's lse and D slices with lanes 0..7:
     // lanes 0-3 lse, lanes 4-7 D, 16 bytes each
     const float* my_vec = ((lane & 4) ? a.dvec : a.lse2) + (size_t)(b * H + h) * N + wave * 16 + (lane & 3) * 4;
-    ah.q_base = (const char*)qp + (size_t)(wave * 16) * ah.q_rs2;
-    ah.do_base = (const char*)dop + (size_t)(wave * 16) * ah.do_rs2;
+    ah.q_base = CopyLanes<D>::wave_base(qp, wave, ah.q_rs2);
+    ah.do_base = CopyLanes<D>::wave_base(dop, wave, ah.do_rs2);
     ah.vec_src = my_vec;
     // prologue: copies of the tiles of the first AHEAD steps, then the first tile's first operands
     constexpr int FIRST = S * C::AHEAD;
@@ -1001,8 +1002,8 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
         tile_load_async_clamped<D>(qp, i_p * QT, Nr, st_, wave, lane, 2 * q_rs);
         tile_load_async_clamped<D>(dop, i_p * QT, Nr, st_ + C::Q_BYTES, wave, lane, 2 * do_rs);
       } else {
-        tile_load_async<D>(qp + (size_t)i_p * QT * q_rs, copy_lanes, st_, wave, 2 * q_rs);
-        tile_load_async<D>(dop + (size_t)i_p * QT * do_rs, copy_lanes_do, st_ + C::Q_BYTES, wave, 2 * do_rs);
+        tile_load_async<D>(ah.q_base + (size_t)i_p * QT * ah.q_rs2, copy_lanes, st_, wave);
+        tile_load_async<D>(ah.do_base + (size_t)i_p * QT * ah.do_rs2, copy_lanes_do, st_ + C::Q_BYTES, wave);
       }
       async_copy16_lanes8(my_vec + i_p * QT, lds_address(st_ + C::Q_BYTES + C::DO_BYTES) + wave * 128);
     }

@@ -139,37 +139,34 @@ __device__ __forceinline__ u32x4 ldg16(const void* p) { return *reinterpret_cast
 // clock and the 64-bit transpose read 32 lanes per clock.  A tile is read in
 // two ways: as MFMA operand rows (16 consecutive rows, one 16-byte chunk each
 // per clock) and through the transpose read (4 consecutive rows x 64 bytes per
-// clock).  Rows are stored unpadded (the direct global->LDS copy writes 1 KB
-// contiguously per wave) and the 16-byte chunk index of a row is XORed with a
-// bit permutation of the row's low four bits, chosen so that 16 consecutive
-// rows hit 16 different 16-byte slots of the 256-byte bank line (first
-// pattern) and 4 consecutive rows hit 4 different 64-byte groups (second
-// pattern): both reads are conflict-free.
-// off(row + 16*m, col) == off(row, col) + 16*m*RS, so callers precompute the
-// lane-dependent part once.
+// clock).  A tile is groups of 16 rows, a group is panels of 64 bytes of each of its rows (1 KB: what one
+// instruction of the direct global->LDS copy writes), and the four 16-byte chunks of a row's part of a panel are
+// XORed with bits 2 and 3 of the row: 16 consecutive rows hit 16 different 16-byte slots of the 256-byte bank
+// line (first pattern), and 4 consecutive rows of a panel are one bank line (second pattern): both reads are
+// conflict-free.
+// off(row + 16*m, col) == off(row, col) + 16*m*RS, and a panel further on is 1 KB further on, so callers precompute
+// the lane-dependent part once and nearly all of a tile's reads differ from it by an instruction's immediate offset.
 template <int D>
 struct TileLayout {
   static constexpr int RS = D * 2;       // bytes per row
-  static constexpr int CPR = D / 8;      // 16-byte chunks per row
-  static __device__ __forceinline__ int swz(int row) {
-    const int r = row & 15;
-    if (D == 128) return ((r & 3) << 2) | (r >> 2);   // 16 chunks per row, one row per bank line
-    const int a = r >> 1;                               // D == 64: two rows per bank line
-    return ((a & 1) << 2) | (a >> 1);
-  }
+  static constexpr int PANELS = D / 32;  // of 64 bytes per row
+  static __device__ __forceinline__ int swz(int row) { return (row >> 2) & 3; }
   static __device__ __forceinline__ int off(int row, int byte_col) {
-    return row * RS + ((((byte_col >> 4) ^ swz(row)) << 4) | (byte_col & 15));
+    return (row >> 4) * (16 * RS) + (byte_col >> 6) * 1024 + (row & 15) * 64 +
+           (((((byte_col >> 4) & 3) ^ swz(row)) << 4) | (byte_col & 15));
   }
-  // off(row, col0 + colc) from off(row, col0), for a constant colc that is a
-  // multiple of 16 and shares no set bit with col0.
-  static __device__ __forceinline__ int add_col(int base, int colc) { return base ^ colc; }
+  // off(row, col0 + colc) from off(row, col0), for a constant colc that is a multiple of 32 and col0 < 32 (operand
+  // rows) or a multiple of 64 and col0 < 64 (transpose reads).
+  static __device__ __forceinline__ unsigned add_col(unsigned base, unsigned colc) {
+    return (base ^ (colc & 32)) + (colc >> 6) * 1024;
+  }
 };
 
 // Asynchronous global->LDS copy of a [64][D] bf16 tile (global row stride D)
 // into TileLayout<D> order by a 4-wave workgroup.  Wave w copies rows
 // 16w..16w+15, a contiguous block on both sides, with NINST instructions of
-// 64 x 16 B = 1 KB each straight into LDS (no staging registers); the swizzle is
-// applied on the global-address side.  The LDS destination of such an
+// 64 x 16 B = 1 KB each straight into LDS (no staging registers), a panel of 16 rows each; the order of rows and
+// chunks is applied on the global-address side.  The LDS destination of such an
 // instruction is M0 + immediate offset + 16 * lane and the same immediate is
 // added to the global address, so one M0 value (async_window) serves all of a
 // wave's instructions for a tile: rewriting M0 costs the issuing wave about as
@@ -179,18 +176,21 @@ struct TileLayout {
 template <int D>
 struct CopyLanes {
   using L = TileLayout<D>;
-  static constexpr int RPI = 64 / L::CPR;     // rows per instruction
-  static constexpr int NINST = 16 / RPI;      // instructions per wave and tile
+  static constexpr int NINST = L::PANELS;     // instructions per wave and tile
+  // Instruction s carries the immediate s * 1024 on both sides, where its panel is 64 s bytes further on in global memory:
+  // the difference goes into the lane offset, and what keeps that from turning negative into the base (wave_base).
+  static constexpr int BIAS = (NINST - 1) * (1024 - 64);
   unsigned v[NINST];
-  // grs: bytes between consecutive rows of the global tensor (TileLayout::RS when it is
-  // contiguous).  Instruction s carries the immediate s * 1024 on both sides, so what its rows
-  // are really apart in global memory beyond that goes into the lane offset.
+  // grs: bytes between consecutive rows of the global tensor (TileLayout::RS when it is contiguous).
   __device__ __forceinline__ void init(int lane, int grs = L::RS) {
 #pragma unroll
-    for (int s = 0; s < NINST; ++s) {
-      const int row = lane / L::CPR;          // row within the instruction's 1 KB
-      v[s] = (s * RPI + row) * grs - s * 1024 + (((lane % L::CPR) ^ L::swz(s * RPI + row)) << 4);
-    }
+    for (int s = 0; s < NINST; ++s) v[s] = lane / 4 * grs + source_col(lane, s) - s * 1024 + BIAS;
+  }
+  // Byte column of a row that a lane of instruction s copies (row lane / 4 of the wave's 16).
+  static __device__ __forceinline__ int source_col(int lane, int s) { return s * 64 + ((lane % 4 ^ L::swz(lane / 4)) << 4); }
+  // What the lane offsets count from: row 0 of a tensor's slice -> this wave's row 0 of the tile at row 0.
+  static __device__ __forceinline__ const char* wave_base(const void* slice, int wave, int grs) {
+    return (const char*)slice + (size_t)(wave * 16) * grs - BIAS;
   }
 };
 // One wave-wide asynchronous copy: every active lane moves 16 bytes from its own
@@ -275,11 +275,9 @@ template <int D, int S>
 __device__ __forceinline__ void tile_copy_inst(const void* wave_src, const CopyLanes<D>& cl) {
   async_copy16_window<S * 1024>(wave_src, cl.v[S]);
 }
-// A wave's whole part of a [64][D] tile copy: tile_src / lds_tile are the tile's first row.
+// A wave's whole part of a [64][D] tile copy: wave_src is CopyLanes::wave_base advanced to the tile's first row.
 template <int D>
-__device__ __forceinline__ void tile_load_async(const __bf16* tile_src, const CopyLanes<D>& cl, const char* lds_tile,
-                                                int wave, int grs = TileLayout<D>::RS) {
-  const char* wave_src = (const char*)tile_src + (size_t)(wave * 16) * grs;
+__device__ __forceinline__ void tile_load_async(const char* wave_src, const CopyLanes<D>& cl, const char* lds_tile, int wave) {
   async_window(lds_address(lds_tile) + wave * 16 * TileLayout<D>::RS);
   tile_copy_inst<D, 0>(wave_src, cl);
   tile_copy_inst<D, 1>(wave_src, cl);
@@ -297,15 +295,11 @@ template <int D>
 __device__ __forceinline__ void tile_load_async_clamped(const __bf16* tensor_bh, int row0, int n_real,
                                                         const char* lds_tile, int wave, int lane,
                                                         int grs = TileLayout<D>::RS) {
-  using L = TileLayout<D>;
-  constexpr int RPI = 64 / L::CPR, NINST = 16 / RPI;
+  const int grow = min(row0 + wave * 16 + lane / 4, n_real - 1);
 #pragma unroll
-  for (int s = 0; s < NINST; ++s) {
-    const int row = wave * 16 + s * RPI + lane / L::CPR;
-    const int grow = min(row0 + row, n_real - 1);
-    const char* src = (const char*)tensor_bh + (size_t)grow * grs + (((lane % L::CPR) ^ L::swz(row)) << 4);
-    async_copy16(src, lds_address(lds_tile) + wave * 16 * L::RS + s * 1024);
-  }
+  for (int s = 0; s < CopyLanes<D>::NINST; ++s)
+    async_copy16((const char*)tensor_bh + (size_t)grow * grs + CopyLanes<D>::source_col(lane, s),
+                 lds_address(lds_tile) + wave * 16 * TileLayout<D>::RS + s * 1024);
 }
 
 // Result stores.  The tile loops end with a 32-row x D result per wave held rows-on-lanes: lane (c, g)

@@ -318,6 +318,8 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
   copy_lanes.init(lane, 2 * k_rs);
   if (GEN) copy_lanes_v_.init(lane, 2 * v_rs);
   const CopyLanes<D>& copy_lanes_v = GEN ? copy_lanes_v_ : copy_lanes;
+  const char* const kp_wave = CopyLanes<D>::wave_base(kp, cwave, 2 * k_rs);
+  const char* const vp_wave = CopyLanes<D>::wave_base(vp, cwave, 2 * v_rs);
 
   int* list = (int*)(smem + C::LIST_OFF);
   const int* bnd_rows[4] = {a.lts + (size_t)b * Nr, a.lte + (size_t)b * Nr, a.uts + (size_t)b * Nr, a.ute + (size_t)b * Nr};
@@ -368,7 +370,7 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
     if (RAGGED && (j_ + 1) * KT > Nr)                                                            \
       tile_load_async_clamped<D>(kp, j_ * KT, Nr, st_, cwave, lane, 2 * k_rs);                    \
     else                                                                                         \
-      tile_load_async<D>(kp + (size_t)j_ * KT * k_rs, copy_lanes, st_, cwave, 2 * k_rs);          \
+      tile_load_async<D>(kp_wave + (size_t)(2 * j_ * KT) * k_rs, copy_lanes, st_, cwave);         \
   }
 #define FM_LOAD_V(ENTRY, VBUF, SUB)                                                              \
   {                                                                                              \
@@ -377,7 +379,7 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
     if (RAGGED && (j_ + 1) * KT > Nr)                                                            \
       tile_load_async_clamped<D>(vp, j_ * KT, Nr, st_, cwave, lane, 2 * v_rs);                    \
     else                                                                                         \
-      tile_load_async<D>(vp + (size_t)j_ * KT * v_rs, copy_lanes_v, st_, cwave, 2 * v_rs);        \
+      tile_load_async<D>(vp_wave + (size_t)(2 * j_ * KT) * v_rs, copy_lanes_v, st_, cwave);       \
     if (entry_tile_class(ENTRY) == T_PARTIAL) {                                                  \
       if (RAGGED)                                                                                \
         async_copy4(bound_or_pad(wave_bvec, cwave, j_ * KT + lane, Nr),                           \
