@@ -45,7 +45,7 @@ template <int D, bool RAGGED, bool GEN, int S, int WR, bool DIRECT>
 __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
   using C = DqCfg<D, S, WR, DIRECT>;
   constexpr int NTC = WR == 4 ? 1 : S;    // tiles per step that a wave takes part in copying (see the forward)
-  constexpr int KT = C::KT, NKB = KT / 32, NDB = D / 32, NKK = D / 16;
+  constexpr int KT = C::KT, NKB = KT / 32, NDB = D / 16, NKK = D / 32;
   extern __shared__ __attribute__((aligned(256))) char smem[];   // the operand reads rely on the alignment
 
   i32x4 rec = {-1, 0, 0, 0};
@@ -55,7 +55,7 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
   if (unit < 0) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int g = lane >> 5, c = lane & 31;
+  const int quad = lane >> 4, c = lane & 15;   // see mfma16
   const int N = a.Np, H = a.H;            // padded length: what the loops and tables see
   const int Nr = RAGGED ? a.N : a.Np;     // rows the tensors really have
   const int t_r = (Nr + C::BR - 1) / C::BR, t_c = N / KT;
@@ -65,8 +65,7 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
   const int wrow = S == 1 ? wave : wave % WR, grp = S == 1 ? 0 : wave / WR;
   const int cwave = S * WR == 4 ? wave : wave % 4, sub0 = WR == 4 ? grp : 0;
   const int qw0 = q0 + wrow * 32;
-  const int row = qw0 + c;  // this lane's query row
-  const int row_ld = RAGGED ? min(row, Nr - 1) : row;
+  const int row[2] = {qw0 + c, qw0 + 16 + c};  // this lane's query rows
 
   const int h = bh - b * H, hk = GEN ? h / (H / a.Hk) : h, Hk = GEN ? a.Hk : H;
   const __bf16* qp = slice_ptr<D, GEN>(a.q, a.sq, b, h, H, Nr);
@@ -109,63 +108,78 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
     first.load(bnd_rows, Nr, 0);
     __builtin_amdgcn_sched_barrier(0);
   }
-  bf16x8 qreg[NKK], doreg[NKK];
+  // Q and dO fragments (B operands): lane holds elements 32 kk + 8 quad ..+7 of its rows.
+  bf16x8 qreg[2][NKK], doreg[2][NKK];
+  size_t row_ld[2];
 #pragma unroll
-  for (int kk = 0; kk < NKK; ++kk) {
-    qreg[kk] = *(const bf16x8*)(qp + (size_t)row_ld * q_rs + kk * 16 + 8 * g);
-    doreg[kk] = *(const bf16x8*)(dop + (size_t)row_ld * do_rs + kk * 16 + 8 * g);
+  for (int qb = 0; qb < 2; ++qb) {
+    row_ld[qb] = RAGGED ? min(row[qb], Nr - 1) : row[qb];
+#pragma unroll
+    for (int kk = 0; kk < NKK; ++kk) {
+      qreg[qb][kk] = *(const bf16x8*)(qp + row_ld[qb] * q_rs + kk * 32 + 8 * quad);
+      doreg[qb][kk] = *(const bf16x8*)(dop + row_ld[qb] * do_rs + kk * 32 + 8 * quad);
+    }
   }
   // Algorithm 2's D pre-pass, folded into this loop's prologue (the dO fragments are at hand; the O
-  // fragments are loaded in the same layout): D_i = sum_c dO_ic O_ic of this lane's row, a partial sum
-  // per lane and one exchange with the lane that holds the other half of the row.  -D and the log2-domain
+  // fragments are loaded in the same layout): D_i = sum_c dO_ic O_ic of this lane's rows, a partial sum
+  // per lane and the sum over the four lanes that hold a row.  -D and the log2-domain
   // lse (+inf for a row with no visible key and for padding rows, so that P = 0 there) also go to the
   // workspace, where the dK/dV loop, which runs after this one, picks them up per tile.
-  const bool real_row = !RAGGED || row < Nr;
-  float lse2 = real_row ? a.lse[(size_t)bh * Nr + row] : -INFINITY;
-  float dneg = 0.f;
+  float lse2[2], dneg[2] = {0.f, 0.f};
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) lse2[qb] = !RAGGED || row[qb] < Nr ? a.lse[(size_t)bh * Nr + row[qb]] : -INFINITY;
   {
     const __bf16* outp = slice_ptr<D, GEN>(a.out, a.so, b, h, H, Nr);
     const int o_rs = row_stride<D, GEN>(a.so);
-    bf16x8 oreg[NKK];
+    bf16x8 oreg[2][NKK];
 #pragma unroll
-    for (int kk = 0; kk < NKK; ++kk) oreg[kk] = *(const bf16x8*)(outp + (size_t)row_ld * o_rs + kk * 16 + 8 * g);
+    for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+      for (int kk = 0; kk < NKK; ++kk) oreg[qb][kk] = *(const bf16x8*)(outp + row_ld[qb] * o_rs + kk * 32 + 8 * quad);
     if (one_pass) {
       __builtin_amdgcn_sched_barrier(0);   // behind the requests for the rows
       first.classify(Nr, 0, 0, t_c, q0, min(q0 + C::BR, Nr), list);
     }
 #pragma unroll
-    for (int kk = 0; kk < NKK; ++kk)
+    for (int qb = 0; qb < 2; ++qb) {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) dneg -= (float)oreg[kk][e] * (float)doreg[kk][e];
-    dneg += partner32(dneg);
-    if (!real_row) dneg = 0.f;
+      for (int kk = 0; kk < NKK; ++kk)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) dneg[qb] -= (float)oreg[qb][kk][e] * (float)doreg[qb][kk][e];
+      dneg[qb] = quad_sum(dneg[qb]);
+      if (RAGGED && row[qb] >= Nr) dneg[qb] = 0.f;
+      lse2[qb] = (lse2[qb] == -INFINITY) ? INFINITY : lse2[qb] * kLog2e;
+    }
   }
-  lse2 = (lse2 == -INFINITY) ? INFINITY : lse2 * kLog2e;
-  if (g == 0 && grp == 0) {
-    a.dvec[(size_t)bh * N + row] = dneg;
-    a.lse2[(size_t)bh * N + row] = lse2;
+  if (quad < 2 && grp == 0) {
+    a.dvec[(size_t)bh * N + qw0 + lane] = quad ? dneg[1] : dneg[0];
+    a.lse2[(size_t)bh * N + qw0 + lane] = quad ? lse2[1] : lse2[0];
   }
 #pragma unroll
-  for (int kk = 0; kk < NKK; ++kk) {
-    settle(qreg[kk]);
-    settle(doreg[kk]);
+  for (int qb = 0; qb < 2; ++qb) {
+#pragma unroll
+    for (int kk = 0; kk < NKK; ++kk) {
+      settle(qreg[qb][kk]);
+      settle(doreg[qb][kk]);
+    }
+    settle(lse2[qb]);
+    settle(dneg[qb]);
   }
-  settle(lse2);
-  settle(dneg);
 
-  f32x16 dqacc[NDB];
+  f32x4 dqacc[NDB][2];
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) dqacc[db][r] = 0.f;
+    for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) dqacc[db][qb][r] = 0.f;
 
   int* wave_cnt = (int*)(smem + C::CNT_OFF);
   const float sc = a.scale * kLog2e;
-  // lane-dependent LDS offsets inside a tile (row block 0, first column group)
-  const int i16 = lane & 15, half = (lane >> 4) & 1;
-  const int a_base = C::L::off(c, 16 * g);
-  const int t_base0 = C::L::off(4 * g + (i16 >> 2), (16 * half + 4 * (i16 & 3)) * 2);
-  const int t_base1 = C::L::off(4 * g + (i16 >> 2) + 8, (16 * half + 4 * (i16 & 3)) * 2);
+  // lane-dependent LDS offsets inside a tile: operand rows (16 rows, a whole panel) and transpose reads (4 rows and 32
+  // bytes of the panel to every 16 lanes)
+  const int a_base = C::L::off(c, 16 * quad);
+  const int t_base = C::L::off(4 * quad + (c >> 2), 8 * (c & 3));
 
 #define FM_LOAD_TILE(ENTRY, BUF, SUB)                                                          \
   {                                                                                            \
@@ -233,44 +247,41 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
       // Equation 4 on this wave's own rows; a group without a tile in the last step has nothing to do
       const int wcls = S == 1 || S * t + grp < n_live ? entry_wave_class(entry, wrow) : T_FULLY;
       if (wcls != T_FULLY) {
-        // Operand addresses: (stage address + lane part) XOR column offset, + constants.  The stage
-        // address is a multiple of 256 bytes, so the sum keeps the lane part's low byte and the XOR
-        // lands where lane part XOR column offset would put it: one instruction per read, and no
-        // per-(pattern, column) register that lives across tiles.
-        const unsigned st_a = lds_address(st);
-        const unsigned a_s = st_a + (unsigned)a_base, t_s0 = st_a + (unsigned)t_base0, t_s1 = st_a + (unsigned)t_base1;
+        const unsigned a_s = lds_address(st) + (unsigned)a_base, t_s = lds_address(st) + (unsigned)t_base;
 #pragma unroll
         for (int kb = 0; kb < NKB; ++kb) {
-          f32x16 sacc, dpacc;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) sacc[r] = 0.f;
-          // S^T = K Q^T, then dP^T = V dO^T, for 32 keys x 32 queries: 2*NKK MFMA steps; the LDS
-          // operand of a step is fetched RS steps ahead into a small register ring.  The S chain
-          // goes first, so that the exponentials P = exp(S - L) can ride along with the dP chain.
-          constexpr int NS = 2 * NKK, RS = 3, NT = 2 * NDB, RT = 3;
-          constexpr int EXPS = (16 + NKK - 2) / (NKK - 1);   // exponentials next to each of the last NKK - 1 dP steps
+          // S^T = K Q^T, then dP^T = V dO^T, for 32 keys x 32 queries: NS steps of one operand from LDS (16 keys) and two
+          // MFMAs (16 queries each); the operand of a step is fetched RS steps ahead into a small register ring.  The S
+          // chain goes first, so that the exponentials P = exp(S - L) can ride along with the dP chain.  Of either, the
+          // first 16 keys are complete halfway.
+          f32x4 sacc[2][2], dpacc[2][2];   // [16 keys][16 queries]: keys 4 quad + r, query c
+          constexpr int NH = 2 * NKK, NS = 2 * NH, RS = 3, NT = NDB, RT = 3;
+          constexpr int EXPS = (16 + NH - 2) / (NH - 1);   // exponentials next to each of the last NH - 1 dP steps
           auto s_operand = [&](int n) __attribute__((always_inline)) {
-            return lds_read_row16(C::L::add_col(a_s, (n % NKK) * 32) + (n >= NKK ? C::K_BYTES : 0) + kb * 32 * C::L::RS);
+            return lds_read_row16(a_s + (n >= NH ? C::K_BYTES : 0) + (kb * 32 + 16 * (n % NH / NKK)) * C::L::RS + n % NKK * 1024);
           };
           auto t_operand = [&](int n) __attribute__((always_inline)) {
-            const unsigned krow = (kb * 32 + 16 * (n / NDB)) * C::L::RS;
-            return cat4(lds_read_tr16_at(C::L::add_col(t_s0, (n % NDB) * 64) + krow),
-                        lds_read_tr16_at(C::L::add_col(t_s1, (n % NDB) * 64) + krow));
+            const unsigned at = C::L::add_col(t_s, n * 32) + kb * 32 * C::L::RS;
+            return cat4(lds_read_tr16_at(at), lds_read_tr16_at(at + 16 * C::L::RS));
+          };
+          auto s_step = [&](int n, bf16x8 x) __attribute__((always_inline)) {
+            const int ks = n % NH / NKK, kk = n % NKK;
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb) {
+              if (n < NH) sacc[ks][qb] = mfma16(x, qreg[qb][kk], kk == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sacc[ks][qb]);
+              // the dP accumulator starts from -D of the row, so it ends as dP - D
+              else dpacc[ks][qb] = mfma16(x, doreg[qb][kk], kk == 0 ? f32x4{dneg[qb], dneg[qb], dneg[qb], dneg[qb]} : dpacc[ks][qb]);
+            }
           };
           bf16x8 ring[RS];
 #pragma unroll
-          for (int n = 0; n < RS; ++n) ring[n] = s_operand(n);
-          __builtin_amdgcn_sched_barrier(0);
+          for (int n = 0; n < RS; ++n) {
+            ring[n] = s_operand(n);
+            __builtin_amdgcn_sched_barrier(0);
+          }
 #pragma unroll
-          for (int n = 0; n <= NKK; ++n) {   // the S chain and the first dP step
-            if (n < NKK) {
-              sacc = mfma32(ring[n % RS], qreg[n], sacc);
-            } else {
-              // the dP accumulator starts from -D of this lane's row, so it ends as dP - D
-#pragma unroll
-              for (int r = 0; r < 16; ++r) dpacc[r] = dneg;
-              dpacc = mfma32(ring[n % RS], doreg[0], dpacc);
-            }
+          for (int n = 0; n <= NH; ++n) {   // the S chain and the first dP step
+            s_step(n, ring[n % RS]);
             if (n + RS < NS) ring[n % RS] = s_operand(n + RS);
             __builtin_amdgcn_sched_barrier(0);
           }
@@ -288,72 +299,60 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
             // 0.994 to 1.006, grouped heads 0.989 to 0.998.
             constexpr bool SINGLE = D == 64 || DIRECT || RAGGED;
             const int mode = SINGLE ? entry_mask_mode(entry) : 0;
-            auto bounds = [&](int which, int rq) __attribute__((always_inline)) {
-              return *(const i32x4*)(bnd + which * KT + kb * 32 + 8 * rq + 4 * g);
+            auto bounds = [&](int which, int ks) __attribute__((always_inline)) {   // of this lane's keys
+              return *(const i32x4*)(bnd + which * KT + kb * 32 + 16 * ks + 4 * quad);
+            };
+            auto hide = [&](int ks, auto hit) __attribute__((always_inline)) {   // hit(row, key): whether the element is masked
+#pragma unroll
+              for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                  if (hit(row[qb], r)) sacc[ks][qb][r] = -INFINITY;
             };
             if (SINGLE && (mode & 4)) {
               if (mode == 7) {
+                const i32x4 bl[2] = {bounds(0, 0), bounds(0, 1)}, bv[2] = {bounds(3, 0), bounds(3, 1)};
+                __builtin_amdgcn_sched_barrier(0);   // all in flight together
 #pragma unroll
-                for (int rq = 0; rq < 4; ++rq) {
-                  const i32x4 bl = bounds(0, rq), bv = bounds(3, rq);
-#pragma unroll
-                  for (int e = 0; e < 4; ++e)
-                    if ((row >= bl[e]) | (row < bv[e])) sacc[rq * 4 + e] = -INFINITY;
-                }
+                for (int ks = 0; ks < 2; ++ks) hide(ks, [&](int i, int r) { return (i >= bl[ks][r]) | (i < bv[ks][r]); });
               } else if (mode == 5) {
-                i32x4 b[4];
+                const i32x4 bl[2] = {bounds(0, 0), bounds(0, 1)};
 #pragma unroll
-                for (int rq = 0; rq < 4; ++rq) b[rq] = bounds(0, rq);
-                __builtin_amdgcn_sched_barrier(0);   // all four in flight together
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                  if (row >= b[r / 4][r % 4]) sacc[r] = -INFINITY;
+                for (int ks = 0; ks < 2; ++ks) hide(ks, [&](int i, int r) { return i >= bl[ks][r]; });
               } else {
-                i32x4 b[4];
+                const i32x4 bv[2] = {bounds(3, 0), bounds(3, 1)};
 #pragma unroll
-                for (int rq = 0; rq < 4; ++rq) b[rq] = bounds(3, rq);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                  if (row < b[r / 4][r % 4]) sacc[r] = -INFINITY;
+                for (int ks = 0; ks < 2; ++ks) hide(ks, [&](int i, int r) { return i < bv[ks][r]; });
               }
             } else if (need == 3) {
 #pragma unroll
-              for (int rq = 0; rq < 4; ++rq) {
-                const int kx = kb * 32 + 8 * rq + 4 * g;
-                const i32x4 bl = *(const i32x4*)(bnd + 0 * KT + kx);
-                const i32x4 be = *(const i32x4*)(bnd + 1 * KT + kx);
-                const i32x4 bu = *(const i32x4*)(bnd + 2 * KT + kx);
-                const i32x4 bv = *(const i32x4*)(bnd + 3 * KT + kx);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                  const bool masked = ((row >= bl[e]) & (row < be[e])) | ((row >= bu[e]) & (row < bv[e]));
-                  if (masked) sacc[rq * 4 + e] = -INFINITY;
-                }
+              for (int ks = 0; ks < 2; ++ks) {
+                const i32x4 bl = bounds(0, ks), be = bounds(1, ks), bu = bounds(2, ks), bv = bounds(3, ks);
+                hide(ks, [&](int i, int r) { return ((i >= bl[r]) & (i < be[r])) | ((i >= bu[r]) & (i < bv[r])); });
               }
             } else {
-              const int* b_lo = bnd + (need == 2 ? 2 * KT : 0);
+              const int lo = need == 2 ? 2 : 0;   // the one pair that is needed
+              const i32x4 bs[2] = {bounds(lo, 0), bounds(lo, 1)}, be[2] = {bounds(lo + 1, 0), bounds(lo + 1, 1)};
 #pragma unroll
-              for (int rq = 0; rq < 4; ++rq) {
-                const int kx = kb * 32 + 8 * rq + 4 * g;
-                const i32x4 bs = *(const i32x4*)(b_lo + kx);
-                const i32x4 be = *(const i32x4*)(b_lo + KT + kx);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                  const bool masked = (row >= bs[e]) & (row < be[e]);
-                  if (masked) sacc[rq * 4 + e] = -INFINITY;
-                }
-              }
+              for (int ks = 0; ks < 2; ++ks) hide(ks, [&](int i, int r) { return (i >= bs[ks][r]) & (i < be[ks][r]); });
             }
             __builtin_amdgcn_sched_barrier(0);
           }
+          auto ds_elem = [&](int e) __attribute__((always_inline)) { sacc[e / 8][e / 4 % 2][e % 4] *= dpacc[e / 8][e / 4 % 2][e % 4]; };
+          bf16x8 dsb[2];
 #pragma unroll
-          for (int n = NKK + 1; n < NS; ++n) {   // the rest of the dP chain, P = exp(S - L) beside it
-            dpacc = mfma32(ring[n % RS], doreg[n - NKK], dpacc);
+          for (int n = NH + 1; n < NS; ++n) {   // the rest of the dP chain, P = exp(S - L) beside it
+            s_step(n, ring[n % RS]);
             if (n + RS < NS) ring[n % RS] = s_operand(n + RS);
 #pragma unroll
-            for (int r = (n - NKK - 1) * EXPS; r < (n - NKK) * EXPS && r < 16; ++r)
-              sacc[r] = fast_exp2(__builtin_fmaf(sacc[r], sc, -lse2));
+            for (int e = (n - NH - 1) * EXPS; e < (n - NH) * EXPS && e < 16; ++e)
+              sacc[e / 8][e / 4 % 2][e % 4] = fast_exp2(__builtin_fmaf(sacc[e / 8][e / 4 % 2][e % 4], sc, -lse2[e / 4 % 2]));
+            // dS = P o (dP - D) of the first 16 keys beside the last steps
+            constexpr int DS_FROM = NS - 3;
+            if (NKK > 2 && n >= DS_FROM) {
+#pragma unroll
+              for (int e = (n - DS_FROM) * 3; e < (n - DS_FROM + 1) * 3 && e < 8; ++e) ds_elem(e);
+            }
             __builtin_amdgcn_sched_barrier(0);
           }
           // K^T operands of the dQ product do not depend on dS: fetch the first ones now
@@ -361,25 +360,20 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
 #pragma unroll
           for (int n = 0; n < RT; ++n) tring[n] = t_operand(n);
           __builtin_amdgcn_sched_barrier(0);
-          // dS = P o (dP - D): the first 16-key half before the dQ product, the second half spread
-          // over the product's first NDB steps (which only need the first)
-          auto ds_elems = [&](int r0, int r1) __attribute__((always_inline)) {
 #pragma unroll
-            for (int r = r0; r < r1; ++r) sacc[r] *= dpacc[r];
-          };
-          ds_elems(0, 8);
+          for (int e = NKK > 2 ? 8 : 0; e < 16; ++e) ds_elem(e);
+#pragma unroll
+          for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) dsb[qb][e] = (__bf16)sacc[e / 4][qb][e % 4];
           __builtin_amdgcn_sched_barrier(0);
-          // dQ^T += K^T dS^T, step n = (16-key half n / NDB, d block n % NDB)
-          bf16x8 dsb;
+          // dQ^T += K^T dS^T, a step is 16 columns of d: element t of a lane's operands is key 4 quad + t of the first
+          // (t < 4) or second 16 keys
 #pragma unroll
           for (int n = 0; n < NT; ++n) {
-            if (n % NDB == 0) {
 #pragma unroll
-              for (int e = 0; e < 8; ++e) dsb[e] = (__bf16)sacc[8 * (n / NDB) + e];
-            }
-            dqacc[n % NDB] = mfma32(tring[n % RT], dsb, dqacc[n % NDB]);
+            for (int qb = 0; qb < 2; ++qb) dqacc[n][qb] = mfma16(tring[n % RT], dsb[qb], dqacc[n][qb]);
             if (n + RT < NT) tring[n % RT] = t_operand(n + RT);
-            if (n < NDB) ds_elems(8 + n * (8 / NDB), 8 + (n + 1) * (8 / NDB));
             __builtin_amdgcn_sched_barrier(0);
           }
         }
@@ -405,36 +399,34 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
   static_assert(4 * RSt::BYTES <= 2 * S * C::STAGE, "store staging fits the stages");
   if (S == 2) {
     // the second group hands its sums to the first through LDS
-    static_assert(S == 1 || 4 * RSt::BYTES + WR * 64 * 16 * NDB * 4 <= 2 * S * C::STAGE, "exchange fits the stages");
-    float* const part = (float*)(smem + C::STAGE_OFF + 4 * RSt::BYTES) + wrow * (64 * 16 * NDB) + lane * 4;
+    static_assert(S == 1 || 4 * RSt::BYTES + WR * 64 * 8 * NDB * 4 <= 2 * S * C::STAGE, "exchange fits the stages");
+    float* const part = (float*)(smem + C::STAGE_OFF + 4 * RSt::BYTES) + wrow * (64 * 8 * NDB) + lane * 4;
     if (grp == 1) {
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
-        for (int rq = 0; rq < 4; ++rq)
-          *(f32x4*)(part + (db * 4 + rq) * 256) =
-              f32x4{dqacc[db][rq * 4], dqacc[db][rq * 4 + 1], dqacc[db][rq * 4 + 2], dqacc[db][rq * 4 + 3]};
+        for (int qb = 0; qb < 2; ++qb) *(f32x4*)(part + (db * 2 + qb) * 256) = dqacc[db][qb];
     }
     barrier_nofence();
     if (grp == 1) return;
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
-      for (int rq = 0; rq < 4; ++rq) {
-        const f32x4 o = *(const f32x4*)(part + (db * 4 + rq) * 256);
+      for (int qb = 0; qb < 2; ++qb) {
+        const f32x4 o = *(const f32x4*)(part + (db * 2 + qb) * 256);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) dqacc[db][rq * 4 + e] += o[e];
+        for (int r = 0; r < 4; ++r) dqacc[db][qb][r] += o[r];
       }
   }
   char* stage = smem + C::STAGE_OFF + wave * RSt::BYTES;
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
 #pragma unroll
-    for (int rq = 0; rq < 4; ++rq) {
+    for (int qb = 0; qb < 2; ++qb) {
       bf16x4 o4;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(dqacc[db][rq * 4 + e] * a.scale);
-      RSt::put(stage, c, g, db, rq, o4);
+      for (int r = 0; r < 4; ++r) o4[r] = (__bf16)(dqacc[db][qb][r] * a.scale);
+      RSt::put(stage, 16 * qb + c, 16 * db + 4 * quad, o4);
     }
   RSt::flush(stage, dqp + (size_t)qw0 * dq_rs, dq_rs, lane, RAGGED ? min(32, Nr - qw0) : 32);
 }

@@ -78,6 +78,11 @@ __device__ __forceinline__ MinMax8 load_minmax(const int* __restrict__ table, in
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
+// D(16x16) += A(16x32) * B(32x16).  Lane l holds A[m = l%16][k = 8*(l/16) + t], B[k = 8*(l/16) + t][n = l%16],
+// t = 0..7, and D[m = 4*(l/16) + r][n = l%16] in register r = 0..3.
+__device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
 // The same product accumulated in place in accumulation registers (AGPRs).  For accumulators that
 // live through a whole tile loop and are touched by nothing but their own MFMAs: the compiler picks
 // one register file for all of a kernel's MFMA results, and keeping these in the vector file leaves the
@@ -128,6 +133,15 @@ __device__ __forceinline__ float partner32(float x) {
   return __builtin_bit_cast(float, other);
 }
 
+// x summed over the four lanes l, l ^ 16, l ^ 32, l ^ 48; all of them get the same bits.
+__device__ __forceinline__ float quad_sum(float x) {
+  // permlane16_swap(x, x): {row 0, 0, 2, 2} and {row 1, 1, 3, 3} of 16 lanes
+  auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(int, x), __builtin_bit_cast(int, x), false, false);
+  x = __builtin_bit_cast(float, (int)r[0]) + __builtin_bit_cast(float, (int)r[1]);
+  r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(int, x), __builtin_bit_cast(int, x), false, false);
+  return __builtin_bit_cast(float, (int)r[0]) + __builtin_bit_cast(float, (int)r[1]);
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
 
@@ -150,7 +164,7 @@ template <int D>
 struct TileLayout {
   static constexpr int RS = D * 2;       // bytes per row
   static constexpr int PANELS = D / 32;  // of 64 bytes per row
-  static __device__ __forceinline__ int swz(int row) { return (row >> 2) & 3; }
+  static __device__ __forceinline__ int swz(int row) { return ((row >> 1) & 2) | ((row >> 3) & 1); }
   static __device__ __forceinline__ int off(int row, int byte_col) {
     return (row >> 4) * (16 * RS) + (byte_col >> 6) * 1024 + (row & 15) * 64 +
            (((((byte_col >> 4) & 3) ^ swz(row)) << 4) | (byte_col & 15));
@@ -315,7 +329,10 @@ struct RowStage {
   static constexpr int LPR = D / 8;       // lanes per row when every lane moves 16 bytes
   static constexpr int RPI = 64 / LPR;    // rows per store instruction
   static __device__ __forceinline__ void put(char* stage, int c, int g, int db, int q, bf16x4 v) {
-    *(bf16x4*)(stage + c * RS + (32 * db + 8 * q + 4 * g) * 2) = v;
+    put(stage, c, 32 * db + 8 * q + 4 * g, v);
+  }
+  static __device__ __forceinline__ void put(char* stage, int row, int col, bf16x4 v) {
+    *(bf16x4*)(stage + row * RS + col * 2) = v;
   }
   // rows [0, n_rows) of the block go to row0, row0 + row_stride, ... (elements)
   static __device__ __forceinline__ void flush(const char* stage, __bf16* row0, int row_stride, int lane, int n_rows) {
