@@ -174,7 +174,10 @@ __device__ __forceinline__ void fwd_step(f32x16 (&cur)[2], f32x16 (&nxt)[2], f32
 
   // ---- stream A: S^T(next) = K Q^T on the matrix unit, softmax(cur) on the vector unit.
   // MFMA step n: chain kb = n % 2, slice kk = n / 2 (the two accumulation chains alternate);
-  // its K operand is fetched RS steps ahead into a small register ring.
+  // its K operand is fetched about RS steps ahead into a small register ring, two at a time and the later step's first: LDS answers
+  // in order, so one wait covers both (15 instead of 29 waits a tile in both streams at d = 128).  Forward, before / now: prefix 4096 of
+  // 32768 3920 / 3876 us, skewed documents at 131072 2562 / 2510, shared questions 16300 362 / 358, documents 1000 24.1 / 23.8, 4099
+  // at d = 64 59.0 / 59.1.  (In the dQ and dK/dV loops, whose reads fill more of LDS's time, the bursts cost 1 to 4 %.)
   constexpr int NS = NKB * NKK, RS = 4;
   constexpr int NMAX = 4;                          // steps that carry the running max (8 elements each)
   constexpr int NEXP = NS - NMAX - 1;              // steps that carry exponentials
@@ -189,13 +192,20 @@ __device__ __forceinline__ void fwd_step(f32x16 (&cur)[2], f32x16 (&nxt)[2], f32
   };
   const f32x16 zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
-  for (int n = 0; n < RS; ++n) kring[n] = k_operand(n);
+  for (int n = 0; n < RS; ++n) {
+    kring[n ^ 1] = k_operand(n ^ 1);
+    __builtin_amdgcn_sched_barrier(0);
+  }
   __builtin_amdgcn_sched_barrier(0);
   float mx = -INFINITY, neg_m = 0.f, rs = 0.f;
 #pragma unroll
   for (int n = 0; n < NS; ++n) {
     nxt[n % NKB] = mfma32(kring[n % RS], qreg[n / NKB], n < NKB ? zero : nxt[n % NKB]);
-    if (n + RS < NS) kring[n % RS] = k_operand(n + RS);
+    if (n % 2 == 1 && n + RS < NS) {
+      kring[n % RS] = k_operand(n + RS);
+      __builtin_amdgcn_sched_barrier(0);
+      kring[(n - 1) % RS] = k_operand(n - 1 + RS);
+    }
     if (n < NMAX) {
 #pragma unroll
       for (int e = 8 * n; e < 8 * n + 8; ++e) mx = fmaxf(mx, cur[e / 16][e % 16]);
@@ -237,7 +247,10 @@ __device__ __forceinline__ void fwd_step(f32x16 (&cur)[2], f32x16 (&nxt)[2], f32
                 lds_read_tr16(vrow + C::L::add_col(t_b1, (n % NDB) * 64)));
   };
 #pragma unroll
-  for (int n = 0; n < RP; ++n) vring[n] = v_operand(n);
+  for (int n = 0; n < RP; ++n) {
+    vring[n ^ 1] = v_operand(n ^ 1);
+    __builtin_amdgcn_sched_barrier(0);
+  }
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int n = 0; n < NP; ++n) {
@@ -246,7 +259,11 @@ __device__ __forceinline__ void fwd_step(f32x16 (&cur)[2], f32x16 (&nxt)[2], f32
 #pragma unroll
     for (int e = 0; e < 8; ++e) pb[e] = (__bf16)cur[kb][8 * h + e];
     oacc[db] = mfma32(vring[n % RP], pb, oacc[db]);
-    if (n + RP < NP) vring[n % RP] = v_operand(n + RP);
+    if (n % 2 == 1 && n + RP < NP) {
+      vring[n % RP] = v_operand(n + RP);
+      __builtin_amdgcn_sched_barrier(0);
+      vring[(n - 1) % RP] = v_operand(n - 1 + RP);
+    }
     if (n < NP / 2) {   // the remaining exponentials (second 32-key block), beside the first block's MFMAs
       constexpr int EPB = (32 - EXP_A + NP / 2 - 1) / (NP / 2);
 #pragma unroll
