@@ -48,19 +48,29 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
   constexpr int KT = C::KT, NKB = KT / 32, NDB = D / 16, NKK = D / 32;
   extern __shared__ __attribute__((aligned(256))) char smem[];   // the operand reads rely on the alignment
 
+  const int t_r = ((RAGGED ? a.N : a.Np) + C::BR - 1) / C::BR;
   i32x4 rec = {-1, 0, 0, 0};
-  if (!DIRECT) rec = queue_take(a.queue_dq, (int*)(smem + C::CNT_OFF) + 8);
-  else rec[0] = direct_unit(a.B * a.H * ((a.N + C::BR - 1) / C::BR), (a.N + C::BR - 1) / C::BR);
-  const int unit = rec[0];
-  if (unit < 0) return;
+  int bh, i_blk;   // batch row and head, row block
+  if (!DIRECT) {
+    rec = queue_take(a.queue_dq, (int*)(smem + C::CNT_OFF) + 8);
+    if (rec[0] < 0) return;
+    bh = rec[0] / t_r;
+    i_blk = rec[0] - bh * t_r;
+  } else {
+    const int group = GEN ? a.H / a.Hk : 1;
+    const FmDirectUnit u = fm_direct_unit(a.order, (int)blockIdx.x, group, t_r);
+    if (u.block < 0) return;
+    bh = u.slice * group + u.member;
+    i_blk = t_r - 1 - u.block;
+  }
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int quad = lane >> 4, c = lane & 15;   // see mfma16
   const int N = a.Np, H = a.H;            // padded length: what the loops and tables see
   const int Nr = RAGGED ? a.N : a.Np;     // rows the tensors really have
-  const int t_r = (Nr + C::BR - 1) / C::BR, t_c = N / KT;
+  const int t_c = N / KT;
   const int j_lo = DIRECT ? 0 : rec[1], j_hi = DIRECT ? t_c : rec[2];
-  const int bh = unit / t_r, i_blk = unit - bh * t_r, b = bh / H;
+  const int b = bh / H;
   const int q0 = i_blk * C::BR;
   const int wrow = S == 1 ? wave : wave % WR, grp = S == 1 ? 0 : wave / WR;
   const int cwave = S * WR == 4 ? wave : wave % 4, sub0 = WR == 4 ? grp : 0;
@@ -821,11 +831,12 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
   // hand-off words of the unit queue: int 8 = slot of the first take, ints 12..15 = record of the next unit
   int* qwords = (int*)(smem + C::CNT_OFF);
   i32x4 rec = {-1, 0, 0, 0};
+  FmDirectUnit direct = {};
   if (!DIRECT) {
     rec = queue_take(a.queue_dkdv, qwords + 8);
   } else {
-    const int blocks = (a.N + C::BC - 1) / C::BC;
-    rec[0] = direct_unit<true>(a.B * (GEN ? a.Hk : a.H) * blocks, blocks);
+    direct = fm_direct_unit(a.order, (int)blockIdx.x, 1, (a.N + C::BC - 1) / C::BC);
+    rec[0] = direct.block;
     rec[2] = (a.N + QT - 1) / QT;   // every row block may be live
   }
   if (rec[0] < 0) return;
@@ -909,7 +920,8 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
   // tile copies of the current unit are in flight.
   while (true) {
   const int unit = rec[0], i_lo = rec[1], i_hi = rec[2];
-  const int bh = unit / t_c, j_blk = unit - bh * t_c, b = bh / Hk, hk = bh - b * Hk;   // bh counts K/V heads
+  const int bh = DIRECT ? direct.slice : unit / t_c, j_blk = DIRECT ? direct.block : unit - bh * t_c;
+  const int b = bh / Hk, hk = bh - b * Hk;   // bh counts K/V heads
   const int k0 = j_blk * C::BC;
   const int kw0 = k0 + wkey * 32;
   const int key = kw0 + c;  // this lane's key column
@@ -1167,7 +1179,9 @@ static hipError_t launch_dq_s(const FmBwdArgs& a, hipStream_t stream) {
   using C = typename L::C;
   FmBwdArgs args = a;
   args.queue_dq = fm_queue_for_launch(a.queue_dq, FM_DQ_PER_CU);
-  const int grid = U == FM_QUEUED ? fm_launch_grid(args.queue_dq) : fm_direct_grid(a.B * a.H * ((a.N + C::BR - 1) / C::BR));
+  const int blocks = (a.N + C::BR - 1) / C::BR;
+  args.order = fm_direct_order(a.B * a.Hk, blocks);
+  const int grid = U == FM_QUEUED ? fm_launch_grid(args.queue_dq) : fm_direct_grid(args.order, a.H / a.Hk, blocks);
   hipLaunchKernelGGL(L::kernel(), dim3(grid), dim3(C::THREADS), C::LDS_BYTES, stream, args);
   return hipGetLastError();
 }
@@ -1219,8 +1233,9 @@ static hipError_t launch_dkdv_s(const FmBwdArgs& a, hipStream_t stream) {
   using C = typename L::C;
   FmBwdArgs args = a;
   args.queue_dkdv = fm_queue_for_launch(a.queue_dkdv, C::PER_CU);
-  const int units = a.B * (GEN ? a.Hk : a.H) * ((a.N + C::BC - 1) / C::BC);
-  const int grid = U != FM_QUEUED   ? fm_direct_grid(units)
+  const int blocks = (a.N + C::BC - 1) / C::BC;
+  args.order = fm_direct_order(a.B * a.Hk, blocks);
+  const int grid = U != FM_QUEUED   ? fm_direct_grid(args.order, 1, blocks)
                    : C::PERSISTENT ? fm_persistent_grid(args.queue_dkdv)
                                    : fm_launch_grid(args.queue_dkdv);
   hipLaunchKernelGGL(L::kernel(), dim3(grid), dim3(256), C::LDS_BYTES, stream, args);

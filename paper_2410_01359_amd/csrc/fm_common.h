@@ -542,22 +542,13 @@ __device__ __forceinline__ int entry_mask_mode(int entry) {
 
 // --- direct units -----------------------------------------------------------------------------------------
 // A problem of few units, or of short ones (the lines are at fm_row_units and fm_key_units in fm_kernels.h), gains nothing
-// from an order and runs without the setup launches: workgroup x takes unit direct_unit() and derives the min/max values
+// from an order and runs without the setup launches: workgroup x takes fm_direct_unit(x) and derives the min/max values
 // it needs from the bound vectors themselves.  Where that leaves the chip with idle compute units the unit is halved (half the
 // rows or keys per workgroup), and the tiles of its list are dealt alternately to two groups of waves whose partial
 // results meet in LDS at the end, which halves the longest chain of tiles.
 //
-// Units are numbered slice-major and dealt to the XCDs (workgroup x runs on XCD x % 8) in eight contiguous runs, so
-// that a slice's K/V stays in as few L2s as the count allows.  Within a slice the block that is longest in masks with a
-// causal side goes first: the last row block, the first key block.  -1: nothing to do.
-template <bool KEY_BLOCKS = false>
-__device__ __forceinline__ int direct_unit(int units, int blocks) {
-  const int per = (units + FM_QUEUES - 1) / FM_QUEUES;
-  const int p = (int)(blockIdx.x % FM_QUEUES) * per + (int)(blockIdx.x / FM_QUEUES);
-  if ((int)(blockIdx.x / FM_QUEUES) >= per || p >= units) return -1;
-  const int slice = p / blocks, i = p - slice * blocks;
-  return slice * blocks + (KEY_BLOCKS ? i : blocks - 1 - i);
-}
+// The order of the units is fm_direct_order.h's; row blocks count from the last there, key blocks from the first.
+//
 // build_live_key_blocks for key blocks of 64 columns straight from the bound vectors (vec: a batch row's LTS, LTE,
 // UTS, UTE; n columns).  Sixteen lanes take a block, four columns each, so a pass of four waves covers 1024
 // columns; where the columns go beyond that, two passes have their loads in flight together (forward over a window of

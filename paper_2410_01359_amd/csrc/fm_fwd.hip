@@ -292,19 +292,29 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
   constexpr int KT = C::KT, NKB = KT / 32, NDB = D / 32, NKK = D / 16;
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
+  const int t_r = ((RAGGED ? a.N : a.Np) + C::BR - 1) / C::BR;
   i32x4 rec = {-1, 0, 0, 0};
-  if (!DIRECT) rec = queue_take(a.queue, (int*)(smem + C::CNT_OFF) + 8);
-  else rec[0] = direct_unit(a.B * a.H * ((a.N + C::BR - 1) / C::BR), (a.N + C::BR - 1) / C::BR);
-  const int unit = rec[0];
-  if (unit < 0) return;
+  int bh, i_blk;   // batch row and head, row block
+  if (!DIRECT) {
+    rec = queue_take(a.queue, (int*)(smem + C::CNT_OFF) + 8);
+    if (rec[0] < 0) return;
+    bh = rec[0] / t_r;
+    i_blk = rec[0] - bh * t_r;
+  } else {
+    const int group = GEN ? a.H / a.Hk : 1;
+    const FmDirectUnit u = fm_direct_unit(a.order, (int)blockIdx.x, group, t_r);
+    if (u.block < 0) return;
+    bh = u.slice * group + u.member;
+    i_blk = t_r - 1 - u.block;
+  }
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 5, c = lane & 31;
   const int N = a.Np, H = a.H;            // padded length: what the loops and tables see
   const int Nr = RAGGED ? a.N : a.Np;     // rows the tensors really have
-  const int t_r = (Nr + C::BR - 1) / C::BR, t_c = N / KT;
+  const int t_c = N / KT;
   const int j_lo = DIRECT ? 0 : rec[1], j_hi = DIRECT ? t_c : rec[2];
-  const int bh = unit / t_r, i_blk = unit - bh * t_r, b = bh / H;
+  const int b = bh / H;
   const int q0 = i_blk * C::BR;
   const int wrow = S == 1 ? wave : wave % WR, grp = S == 1 ? 0 : wave / WR;
   const int cwave = S * WR == 4 ? wave : wave % 4;             // which quarter of a tile it copies
@@ -596,7 +606,9 @@ static hipError_t launch_fwd_s(const FmFwdArgs& a, hipStream_t stream) {
   using C = typename L::C;
   FmFwdArgs args = a;
   args.queue = fm_queue_for_launch(a.queue, FwdCfg<D>::PER_CU);
-  const int grid = U == FM_QUEUED ? fm_launch_grid(args.queue) : fm_direct_grid(a.B * a.H * ((a.N + C::BR - 1) / C::BR));
+  const int blocks = (a.N + C::BR - 1) / C::BR;
+  args.order = fm_direct_order(a.B * a.Hk, blocks);
+  const int grid = U == FM_QUEUED ? fm_launch_grid(args.queue) : fm_direct_grid(args.order, a.H / a.Hk, blocks);
   hipLaunchKernelGGL(L::kernel(), dim3(grid), dim3(C::THREADS), C::LDS_BYTES, stream, args);
   return hipGetLastError();
 }

@@ -5,6 +5,8 @@
 
 #include <initializer_list>
 
+#include "fm_direct_order.h"
+
 // The tile loops draw their work units from FM_QUEUES interleaved queues (one per XCD).
 constexpr int FM_QUEUES = 8;
 // Number of queue slots for `units` work units.
@@ -81,8 +83,6 @@ inline int fm_launch_grid(const FmQueue& q) { return q.first == q.tickets ? q.ti
 // Workgroups of a persistent launch (every workgroup works units off until the queues are empty): those that run
 // from the start (one per ticket if the number of compute units is not known).
 inline int fm_persistent_grid(const FmQueue& q) { return q.first > 0 ? q.first : q.tickets; }
-// Workgroups of a launch over direct units: every XCD's run of units, rounded up (see direct_unit).
-inline int fm_direct_grid(int units) { return (units + FM_QUEUES - 1) / FM_QUEUES * FM_QUEUES; }
 // How a tile loop's work is cut into workgroups.
 enum FmUnits {
   FM_QUEUED,          // units of 128 rows (keys) off the unit queues, which the setup launches build
@@ -274,7 +274,8 @@ struct FmFwdArgs {
   float* lse;
   float scale;
   int B, H, N, Np, d;
-  FmUnits units;      // direct ones: minmax and queue are not used
+  FmUnits units;      // direct ones: minmax and queue are not used, but
+  FmDirectOrder order;   // (filled in by the launch)
   bool general;
   int Hk;
   FmStride sq, sk, sv, so;
@@ -295,7 +296,8 @@ struct FmBwdArgs {
   void *dq, *dk, *dv;
   float scale;
   int B, H, N, Np, d;
-  FmUnits units_dq, units_dkdv;   // direct ones: the pass's minmax and queue are not used
+  FmUnits units_dq, units_dkdv;   // direct ones: the pass's minmax and queue are not used, but
+  FmDirectOrder order;            // of the pass that is launched (filled in by the launch)
   bool general;
   int Hk;
   FmStride sq, sk, sv, so, sdo, sdq, sdk, sdv;

@@ -1,0 +1,71 @@
+"""The order of direct units: every unit is taken by exactly one workgroup of the launch, the workgroups beyond take none, an
+XCD (workgroup number modulo 8) works on the run of slices of its class, each XCD of a slice gets its share of the blocks, and
+nothing but rounding makes the grid larger than the unit count."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2410_01359_amd", "csrc")
+
+PROGRAM = r"""
+#include <cstdio>
+#include <set>
+#include <vector>
+#include "fm_direct_order.h"
+
+int main() {
+  long long checked = 0;
+  for (int slices : {1, 2, 3, 4, 5, 6, 7, 8, 9, 12, 16, 20, 24, 32, 40, 64, 100})
+    for (int group : {1, 2, 3, 4, 8})
+      for (int blocks : {1, 2, 3, 7, 8, 9, 16, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 1024}) {
+        const FmDirectOrder o = fm_direct_order(slices, blocks);
+        const int grid = fm_direct_grid(o, group, blocks), classes = 1 << o.classes;
+        std::vector<int> taken(slices * group * blocks);
+        std::vector<std::vector<int>> share(8, std::vector<int>(slices));   // blocks of a slice that an XCD works on
+        for (int x = 0; x < grid; ++x, ++checked) {
+          const FmDirectUnit u = fm_direct_unit(o, x, group, blocks);
+          if (u.block < 0) continue;
+          if (u.slice < 0 || u.slice >= slices || u.member < 0 || u.member >= group || u.block >= blocks ||
+              u.slice / o.own != x % 8 % classes) {
+            std::printf("%d %d %d: workgroup %d takes %d %d %d\n", slices, group, blocks, x, u.slice, u.member, u.block);
+            return 1;
+          }
+          ++taken[(u.slice * group + u.member) * blocks + u.block];
+          ++share[x % 8][u.slice];
+        }
+        for (int n : taken)
+          if (n != 1) {
+            std::printf("%d %d %d: a unit is taken %d times\n", slices, group, blocks, n);
+            return 1;
+          }
+        for (int s = 0; s < slices; ++s)
+          for (int a = 0; a < 8; ++a)
+            for (int b = 0; b < 8; ++b)
+              if (a % classes == s / o.own && b % classes == s / o.own &&
+                  share[a][s] - share[b][s] > group << o.chunk) {
+                std::printf("%d %d %d: slice %d is shared %d : %d\n", slices, group, blocks, s, share[a][s], share[b][s]);
+                return 1;
+              }
+        if (grid >= slices * group * (blocks + (1 << (o.sharing + o.chunk)))) {
+          std::printf("%d %d %d: grid %d\n", slices, group, blocks, grid);
+          return 1;
+        }
+      }
+  std::printf("checked %lld\n", checked);
+  return 0;
+}
+"""
+
+
+def test_every_unit_is_taken_once(tmp_path):
+    if not shutil.which("g++"):
+        pytest.skip("g++ not available")
+    source, program = tmp_path / "order.cpp", tmp_path / "order"
+    source.write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fsanitize=undefined", "-fno-sanitize-recover=all", "-I", CSRC, str(source),
+                    "-o", str(program)], check=True, timeout=120)
+    done = subprocess.run([str(program)], capture_output=True, text=True, timeout=120)
+    assert done.returncode == 0, done.stdout + done.stderr
+    assert done.stdout.startswith("checked")
