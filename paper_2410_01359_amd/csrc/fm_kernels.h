@@ -103,6 +103,17 @@ constexpr int fm_dkdv_per_cu(int d) { return d == 64 ? 2 : 1; }
 inline bool fm_short_direct(long long units, int d, int N, long long cus) {
   return N <= 512 && units <= (d == 64 ? 8 : 4) * cus;
 }
+// Where the blocks of all slices go in step (fm_direct_order.h), up to three units a compute unit need no order at short and
+// medium lengths either, rows and keys alike (`units` counts row blocks, so that the backward's loops cross the line together and
+// no setup launch is left for one of them).  Forward / backward with their setup, direct over queued, geometric mean over six
+// masks (causal, prefix, documents of both kinds, window, shared questions):
+//   d = 128  576 units, N = 1000  0.74 / 0.78;   640, N = 600  0.77 / 0.83, N = 1024  0.76 / 0.81, N = 2048  0.82 / 0.84;
+//            768, N = 1500  0.82 / 0.84, N = 2000  0.91 / 0.91;   750 in 150 slices, N = 600  0.92 / 1.03
+//   d = 64   (backward; the forward was direct up to 1024)  640, N = 600  0.79;   768, N = 1000  0.81;   with the forward
+//            640, N = 2048  0.76 / 0.83, N = 4000  0.81 / 0.88;   768, N = 3000  0.94 / 0.91, N = 4096  0.81 / 0.86
+//   grouped heads, 640 units of 40 on 10, N = 2048  d = 128 0.87 / 0.93, d = 64 0.80 / 0.93
+// Single masks: two documents in many short slices lose up to 6 % (150 slices of 600 tokens 30 % of the backward).
+inline bool fm_in_step(long long units, int d, int N, long long cus) { return units <= 3 * cus && N <= (d == 128 ? 2048 : 4096); }
 // The cut of a row-parallel loop over `units` units of 128 rows, `per_cu` workgroups of which one of `cus` compute units
 // holds, at sequence length N.  What is weighed: the setup launch (4 us up to N = 4096, 8 us beyond), the longest chain of tiles
 // (halved by two groups), waves per SIMD, and building the list from the bound vectors instead of the table (which
@@ -115,6 +126,10 @@ inline bool fm_short_direct(long long units, int d, int N, long long cus) {
 //   d = 64   256 units, N = 4096   halved 39 / 37 / 41 / 15, queued 54 / 60 / 67 / 16
 //            512 units, N = 512    direct 21 / 24 / 25 / 20, halved 24 / 29 / 30 / 24, queued 21 / 23 / 25 / 21
 //            512 units, N = 8192   halved 112 / 47 / 63 / 33, queued 116 / 59 / 73 / 21; N = 16384 causal 267, queued 219
+// (all with a contiguous run of units to an XCD; in step the direct ones are faster, see fm_direct_order.h)
+// Forward units at d = 64 that all run at once, three to a compute unit, are direct up to N = 8192: direct / queued over the six masks
+// 768 units, N = 8192 0.82, N = 8115 0.92 (window 1.24), 528 units, N = 4099 0.99.  Below 512 units the halved cut stays ahead (320 units,
+// N = 4096, direct / halved 1.20, 384 units, N = 2048 1.07).
 // At long sequences, forward alone with its setup, direct | queued, causal, prefix, documents of 700 tokens, eight documents,
 // window 256, shared questions (geometric mean of the ratios):
 //   d = 128  256 units, N = 16384  paired 246 245 60 162 23 118 | 276 278 79 225 28 161   (0.80)
@@ -135,11 +150,11 @@ inline FmUnits fm_row_units(long long units, int per_cu, int d, int N, long long
   if (d == 128) {
     if (2 * units <= cus) return FM_DIRECT_HALVED;
     if (units <= cus) return FM_DIRECT_PAIRED;
-    return (units <= per_cu * cus && N <= 2048) || fm_short_direct(units, d, N, cus) ? FM_DIRECT : FM_QUEUED;
+    return fm_in_step(units, d, N, cus) || fm_short_direct(units, d, N, cus) ? FM_DIRECT : FM_QUEUED;
   }
   if (units <= cus) return FM_DIRECT_HALVED;
-  if ((units <= per_cu * cus && N <= 1024) || fm_short_direct(units, d, N, cus)) return FM_DIRECT;
-  return units <= 2 * cus && N <= 8192 ? FM_DIRECT_HALVED : FM_QUEUED;
+  if (units <= 2 * cus && N > 1024) return N <= 8192 ? FM_DIRECT_HALVED : FM_QUEUED;
+  return fm_in_step(units, d, N, cus) || (units <= per_cu * cus && N <= 8192) || fm_short_direct(units, d, N, cus) ? FM_DIRECT : FM_QUEUED;
 }
 // The same for the dK/dV loop over units of 128 keys of `group` query heads each (a chain `group` times as long; lists
 // are built from the unit's own keys' bounds at any N).  Masks as above:
@@ -147,7 +162,7 @@ inline FmUnits fm_row_units(long long units, int per_cu, int d, int N, long long
 //            256 units, N = 1024   direct 34 / 32 / 46 / 24, halved 39 / 38 / 52 / 30, queued 34 / 33 / 44 / 24
 //            256 units, N = 4096   direct 96 / 58 / 90 / 25, halved 77 / 49 / 93 / 31, queued 95 / 58 / 90 / 24
 //            512 units, N = 8192   direct 249 / 78 / 112 / 47, queued 280 / 93 / 129 / 53, halved 273 / 76 / 114 / 59;
-//                                  N = 16384 direct 579 / 100 / 135 / 46, queued 578 / 104 / 128 / 55
+//                                  N = 16384 backward, over six masks, direct / queued 0.95, ragged 0.94 (causal 0.90, documents 1.05)
 //            256 units of 4 query heads, N = 2048, shared questions: halved 126, direct 163, queued 164
 //   d = 64   512 units, N = 1024   direct 36 / 35 / 48 / 24, halved 36 / 35 / 50 / 28
 //            512 units, N = 4096   halved 85 / 48 / 83 / 28, direct 108 / 63 / 99 / 25, queued 87 / 50 / 86 / 26
@@ -186,7 +201,10 @@ inline FmUnits fm_key_units(long long units, int group, int d, int N, long long 
     if ((long long)padded * group <= (d == 128 ? 2048 : 1024)) return FM_DIRECT;
     return (ragged && d == 128) || N <= 16384 ? FM_DIRECT_HALVED : FM_QUEUED;
   }
-  return (d == 128 && units <= 2 * slots && N <= 8192) || fm_short_direct(units, d, padded, cus) ? FM_DIRECT : FM_QUEUED;
+  return (d == 128 && units <= 2 * slots && N <= 16384) || fm_in_step(units * group, d, padded, cus) ||
+                 fm_short_direct(units, d, padded, cus)
+             ? FM_DIRECT
+             : FM_QUEUED;
 }
 // Tile shapes (rows x key columns) each pass classifies at.
 constexpr int FM_FWD_BR = 128, FM_FWD_BC = 64;
