@@ -299,16 +299,11 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
             // which pairs the workgroup's tile needs (1 = LT, 2 = UT, 3 = both): a pair that is not needed masks
             // no element of the tile, and most partially masked tiles need only one
             const int need = entry_need_pairs(entry);
-            // Where one comparison per pair decides (5, 6, 7, see entry_mask_mode): half the bounds and compares.  Not in
-            // the queued loops over full blocks at d = 128, whose 256 registers are used up (18 spills, documents in
-            // 8192 tokens 988 -> 1010 us).  Training step: documents, d = 128 N = 4099 343 -> 329 us, N = 1000 79.6 ->
-            // 78.6; d = 64 N = 4099 215.7 -> 205.4, N = 1000 55.4 -> 54.0, N = 8192 614 -> 607.  The ragged queued loops at
-            // d = 128 spill 19 registers with it and 17 without (grouped heads: 20 and 16).  Backward there, two comparisons
-            // / one: documents N = 2001, 4099, 8115, 16307, 32691 201 / 194, 168 / 160, 366 / 352, 1061 / 1016, 259 / 251
-            // us, shared questions 144 / 141, 153 / 148, 340 / 338, 1045 / 1029, 1160 / 1137, causal, prefix and windows
-            // 0.994 to 1.006, grouped heads 0.989 to 0.998.
-            constexpr bool SINGLE = D == 64 || DIRECT || RAGGED;
-            const int mode = SINGLE ? entry_mask_mode(entry) : 0;
+            // Where one comparison per pair decides (5, 6, 7, see entry_mask_mode): half the bounds and compares.  Training
+            // step: documents, d = 128 N = 4099 343 -> 329 us, N = 1000 79.6 -> 78.6; d = 64 N = 4099 215.7 -> 205.4, N = 1000
+            // 55.4 -> 54.0, N = 8192 614 -> 607.  dQ loop in the queued units over full blocks at d = 128 (which had no register left
+            // for it before the 16x16x32 products): shared questions 2048 83.3 -> 80.1 us, documents 8192 330 -> 323, 16384 918 -> 911.
+            const int mode = entry_mask_mode(entry);
             auto bounds = [&](int which, int ks) __attribute__((always_inline)) {   // of this lane's keys
               return *(const i32x4*)(bnd + which * KT + kb * 32 + 16 * ks + 4 * quad);
             };
@@ -319,7 +314,7 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
                 for (int r = 0; r < 4; ++r)
                   if (hit(row[qb], r)) sacc[ks][qb][r] = -INFINITY;
             };
-            if (SINGLE && (mode & 4)) {
+            if (mode & 4) {
               if (mode == 7) {
                 const i32x4 bl[2] = {bounds(0, 0), bounds(0, 1)}, bv[2] = {bounds(3, 0), bounds(3, 1)};
                 __builtin_amdgcn_sched_barrier(0);   // all in flight together
@@ -328,11 +323,15 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
               } else if (mode == 5) {
                 const i32x4 bl[2] = {bounds(0, 0), bounds(0, 1)};
 #pragma unroll
-                for (int ks = 0; ks < 2; ++ks) hide(ks, [&](int i, int r) { return i >= bl[ks][r]; });
+                for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                  for (int qb = 0; qb < 2; ++qb) hide4(sacc[ks][qb], 0, [&](int r) { return row[qb] >= bl[ks][r]; });
               } else {
                 const i32x4 bv[2] = {bounds(3, 0), bounds(3, 1)};
 #pragma unroll
-                for (int ks = 0; ks < 2; ++ks) hide(ks, [&](int i, int r) { return i < bv[ks][r]; });
+                for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                  for (int qb = 0; qb < 2; ++qb) hide4(sacc[ks][qb], 0, [&](int r) { return row[qb] < bv[ks][r]; });
               }
             } else if (need == 3) {
 #pragma unroll

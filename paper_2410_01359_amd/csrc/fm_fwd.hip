@@ -133,19 +133,13 @@ __device__ __forceinline__ void fwd_step(f32x16 (&cur)[2], f32x16 (&nxt)[2], f32
         for (int q = 0; q < GROUPS; ++q) b[q] = bounds(0, q);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int q = 0; q < GROUPS; ++q)
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (w.row >= b[q][e]) cur[q / 4][q % 4 * 4 + e] = -INFINITY;
+        for (int q = 0; q < GROUPS; ++q) hide4(cur[q / 4], q % 4 * 4, [&](int e) { return w.row >= b[q][e]; });
       } else {
 #pragma unroll
         for (int q = 0; q < GROUPS; ++q) b[q] = bounds(3, q);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int q = 0; q < GROUPS; ++q)
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (w.row < b[q][e]) cur[q / 4][q % 4 * 4 + e] = -INFINITY;
+        for (int q = 0; q < GROUPS; ++q) hide4(cur[q / 4], q % 4 * 4, [&](int e) { return w.row < b[q][e]; });
       }
       __builtin_amdgcn_sched_barrier(0);
     } else {
