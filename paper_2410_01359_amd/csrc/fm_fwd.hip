@@ -56,18 +56,26 @@ struct FwdWave {
   float sc;                // scale * log2(e)
 };
 
+// Softmax state of a lane's query: P = exp2(scale log2(e) S + neg_ref).
+constexpr float kRescaleGap = 8.f;
+struct FwdSoftmax {
+  float neg_ref;   // minus the reference maximum (log2 domain), 0 before the first finite one
+  float limit;     // the reference moves when a tile's maximum exceeds this: reference + gap, -inf before the first finite one
+  float l;         // sum of P over this lane's keys
+  __device__ __forceinline__ float reference() const { return limit == -INFINITY ? -INFINITY : -neg_ref; }
+};
+
 // One pipeline step: exp / row-sum arithmetic and O^T += V^T P^T of the tile whose raw scores
 // are in `cur` (masked first if `masked` != 0), and the raw scores of the NEXT tile (K tile at
 // k_next) into `nxt`.
 template <int D>
 __device__ __forceinline__ void fwd_step(f32x16 (&cur)[2], f32x16 (&nxt)[2], f32x16 (&oacc)[D / 32],
-                                         const bf16x8 (&qreg)[D / 16], float& m_run, float& l_run,
+                                         const bf16x8 (&qreg)[D / 16], FwdSoftmax& sm,
                                          const char* k_next, const char* vs, const int* bnd, int masked,
                                          const FwdWave<D>& w) {
   using C = FwdCfg<D>;
   constexpr int KT = C::KT, NKB = KT / 32, NDB = D / 32, NKK = D / 16;
   static_assert(NKB == 2, "two 32-key blocks per tile");
-  constexpr float kRescaleGap = 8.f;
   // per-lane LDS offsets, made opaque once per tile so that what is derived from them is
   // recomputed (one vector op each) instead of being hoisted out of the tile loop into registers
   const int a_b = opaque(w.a_off), t_b0 = opaque(w.t_off[0]), t_b1 = opaque(w.t_off[1]);
@@ -191,7 +199,7 @@ __device__ __forceinline__ void fwd_step(f32x16 (&cur)[2], f32x16 (&nxt)[2], f32
     __builtin_amdgcn_sched_barrier(0);
   }
   __builtin_amdgcn_sched_barrier(0);
-  float mx = -INFINITY, neg_m = 0.f, rs = 0.f;
+  float mx = -INFINITY, rs = 0.f;
 #pragma unroll
   for (int n = 0; n < NS; ++n) {
     nxt[n % NKB] = mfma32(kring[n % RS], qreg[n / NKB], n < NKB ? zero : nxt[n % NKB]);
@@ -204,27 +212,30 @@ __device__ __forceinline__ void fwd_step(f32x16 (&cur)[2], f32x16 (&nxt)[2], f32
 #pragma unroll
       for (int e = 8 * n; e < 8 * n + 8; ++e) mx = fmaxf(mx, cur[e / 16][e % 16]);
     } else if (n == NMAX) {
-      mx = fmaxf(mx, partner32(mx)) * w.sc;
-      const bool grow = mx > m_run + kRescaleGap;   // also true on the first finite maximum
-      if (__any(grow)) {
+      // A lane has the maximum over its half of the query's keys.  Whether any query's reference moves needs no exchange
+      // between the two halves: it does where one of them asks for it.  (With the exchange and the reference's sign on every
+      // tile's path, ten instructions one behind the other: prefix 32768 at d = 64 4466 -> 4399 us, d = 128 3753 -> 3732.)
+      mx *= w.sc;
+      if (__any(mx > sm.limit)) {   // also on the first finite maximum
         // The reference maximum only moves when a tile's maximum exceeds it by more than the
         // gap (log2 units), so this rescale of O and l is rare; any reference is a valid one,
         // P just grows up to 2^gap.
-        const float m_new = grow ? mx : m_run;
+        mx = fmaxf(mx, partner32(mx));
+        const float m_run = sm.reference(), m_new = mx > sm.limit ? mx : m_run;
         const float alpha = (m_new == -INFINITY) ? 1.f : fast_exp2(m_run - m_new);
-        m_run = m_new;
-        l_run *= alpha;
+        sm.neg_ref = (m_new == -INFINITY) ? 0.f : -m_new;
+        sm.limit = m_new + kRescaleGap;
+        sm.l *= alpha;
 #pragma unroll
         for (int db = 0; db < NDB; ++db)
 #pragma unroll
           for (int r = 0; r < 16; ++r) oacc[db][r] *= alpha;
       }
-      neg_m = (m_run == -INFINITY) ? 0.f : -m_run;
     } else {
       const int j = n - NMAX - 1;
 #pragma unroll
       for (int e = j * EPS; e < (j + 1) * EPS && e < EXP_A; ++e) {
-        const float p = fast_exp2(__builtin_fmaf(cur[e / 16][e % 16], w.sc, neg_m));
+        const float p = fast_exp2(__builtin_fmaf(cur[e / 16][e % 16], w.sc, sm.neg_ref));
         cur[e / 16][e % 16] = p;
         rs += p;
       }
@@ -262,14 +273,14 @@ __device__ __forceinline__ void fwd_step(f32x16 (&cur)[2], f32x16 (&nxt)[2], f32
       constexpr int EPB = (32 - EXP_A + NP / 2 - 1) / (NP / 2);
 #pragma unroll
       for (int e = EXP_A + n * EPB; e < EXP_A + (n + 1) * EPB && e < 32; ++e) {
-        const float p = fast_exp2(__builtin_fmaf(cur[e / 16][e % 16], w.sc, neg_m));
+        const float p = fast_exp2(__builtin_fmaf(cur[e / 16][e % 16], w.sc, sm.neg_ref));
         cur[e / 16][e % 16] = p;
         rs += p;
       }
     }
     __builtin_amdgcn_sched_barrier(0);
   }
-  l_run += rs;
+  sm.l += rs;
 }
 
 // RAGGED: the sequence length is not a multiple of 128.  The loops then run at the padded length
@@ -364,7 +375,7 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
   }
 
   f32x16 oacc[NDB];
-  float m_run = -INFINITY, l_run = 0.f;   // log2 domain
+  FwdSoftmax sm = {0.f, -INFINITY, 0.f};
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -427,7 +438,7 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
     const char* vs_ = smem + C::V_OFF + (((T) & 1) * S + grp) * C::VSTAGE;                       \
     const int e_own = NT == 1 || grp == 0 ? e_t[0] : e_t[NT - 1];                                  \
     if (S == 1 || S * (T) + grp < n_live)                                                        \
-      fwd_step<D>(CUR, NXT, oacc, qreg, m_run, l_run,                                            \
+      fwd_step<D>(CUR, NXT, oacc, qreg, sm,                                                      \
                   smem + C::K_OFF + ((((T) + 1) & 1) * S + grp) * C::K_BYTES, vs_,               \
                   (const int*)(vs_ + C::V_BYTES),                                                \
                   entry_wave_class(e_own, wrow) != T_UNMASKED ? entry_mask_mode(e_own) : 0, w);  \
@@ -519,16 +530,16 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
           for (int rq = 0; rq < 4; ++rq)
             *(f32x4*)(part + (db * 4 + rq) * 256) =
                 f32x4{oacc[db][rq * 4], oacc[db][rq * 4 + 1], oacc[db][rq * 4 + 2], oacc[db][rq * 4 + 3]};
-        part_ml[0] = m_run;
-        part_ml[64] = l_run;
+        part_ml[0] = sm.reference();
+        part_ml[64] = sm.l;
       }
       barrier_nofence();
       if (grp == 1) return;
-      const float m_1 = part_ml[0], m_new = fmaxf(m_run, m_1);
-      const float a_0 = m_run == -INFINITY ? 0.f : fast_exp2(m_run - m_new);
+      const float m_0 = sm.reference(), m_1 = part_ml[0], m_new = fmaxf(m_0, m_1);
+      const float a_0 = m_0 == -INFINITY ? 0.f : fast_exp2(m_0 - m_new);
       const float a_1 = m_1 == -INFINITY ? 0.f : fast_exp2(m_1 - m_new);
-      l_run = l_run * a_0 + part_ml[64] * a_1;
-      m_run = m_new;
+      sm.l = sm.l * a_0 + part_ml[64] * a_1;
+      sm.neg_ref = -m_new;
 #pragma unroll
       for (int db = 0; db < NDB; ++db)
 #pragma unroll
@@ -538,7 +549,7 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
           for (int e = 0; e < 4; ++e) oacc[db][rq * 4 + e] = oacc[db][rq * 4 + e] * a_0 + o[e] * a_1;
         }
     }
-    const float lt = l_run + partner32(l_run);
+    const float lt = sm.l + partner32(sm.l);
     const float inv = lt > 0.f ? 1.f / lt : 0.f;
     const int row = qw0 + c;
     // every wave is past its last tile and nothing is in flight into the K / V stages (the barrier that
@@ -556,7 +567,7 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
         RSt::put(stage, c, g, db, rq, o4);
       }
     RSt::flush(stage, op + (size_t)qw0 * o_rs, o_rs, lane, RAGGED ? min(32, Nr - qw0) : 32);
-    if ((!RAGGED || row < Nr) && g == 0) lp[row] = lt > 0.f ? (m_run + fast_log2(lt)) * kLn2 : -INFINITY;
+    if ((!RAGGED || row < Nr) && g == 0) lp[row] = lt > 0.f ? (fast_log2(lt) - sm.neg_ref) * kLn2 : -INFINITY;
   }
 }
 
