@@ -149,22 +149,25 @@ __device__ __forceinline__ u32x4 ldg16(const void* p) { return *reinterpret_cast
 
 // LDS layout of a [rows][D] bf16 tile, shared by all tile loops.
 //
-// LDS serves 64 banks x 4 B per clock; a 128-bit read is issued 16 lanes per
-// clock and the 64-bit transpose read 32 lanes per clock.  A tile is read in
-// two ways: as MFMA operand rows (16 consecutive rows, one 16-byte chunk each
-// per clock) and through the transpose read (4 consecutive rows x 64 bytes per
-// clock).  A tile is groups of 16 rows, a group is panels of 64 bytes of each of its rows (1 KB: what one
+// LDS serves 64 banks x 4 B per clock: 16 lanes of a 128-bit read -- 0-3, 12-15 and 20-27, then 4-11, 16-19 and
+// 28-31, then the same of the upper half, as the conflict counter shows -- and 32 lanes of the 64-bit transpose read.
+// A tile is groups of 16 rows, a group is panels of 64 bytes of each of its rows (1 KB: what one
 // instruction of the direct global->LDS copy writes), and the four 16-byte chunks of a row's part of a panel are
-// XORed with bits 2 and 3 of the row: 16 consecutive rows hit 16 different 16-byte slots of the 256-byte bank
-// line (first pattern), and 4 consecutive rows of a panel are one bank line (second pattern): both reads are
-// conflict-free.
+// XORed with 0, 2, 3 or 1, a value to every four rows.  All reads are conflict-free:
+//  - operand rows of the 32x32x16 product (32 rows, lanes 0-31 one chunk): 16 lanes have rows of all four values;
+//  - operand rows of the 16x16x32 product (16 rows, lanes 16-31 the chunk behind that of lanes 0-15): rows 0-3 and 12-15 of
+//    one chunk meet rows 4-11 of its neighbour (chunk ^ 1), four different slots because 0, 1 and 2 ^ 1, 3 ^ 1 differ.  With 0, 2, 1, 3
+//    they met in pairs, 4 clocks a read, 40 % of the dQ loop's LDS cycles at d = 128;
+//  - transpose reads: 4 rows x 64 bytes of a panel are one bank line, 8 rows x 32 bytes two halves of different bit 1.
+// dQ, prefix 4096 of 32768, 16 heads, d = 128: LDS cycles 1378e6 -> 831e6, of them conflicts 548e6 -> 1.6e6 (the results'
+// staging), time unchanged (5074 -> 5076 us: power); d = 64, 1024 units of 1024 to 16384 tokens, 0.4 to 1.5 % faster.
 // off(row + 16*m, col) == off(row, col) + 16*m*RS, and a panel further on is 1 KB further on, so callers precompute
 // the lane-dependent part once and nearly all of a tile's reads differ from it by an instruction's immediate offset.
 template <int D>
 struct TileLayout {
   static constexpr int RS = D * 2;       // bytes per row
   static constexpr int PANELS = D / 32;  // of 64 bytes per row
-  static __device__ __forceinline__ int swz(int row) { return ((row >> 1) & 2) | ((row >> 3) & 1); }
+  static __device__ __forceinline__ int swz(int row) { return ((row >> 1 ^ row >> 2) & 2) | ((row >> 3) & 1); }
   static __device__ __forceinline__ int off(int row, int byte_col) {
     return (row >> 4) * (16 * RS) + (byte_col >> 6) * 1024 + (row & 15) * 64 +
            (((((byte_col >> 4) & 3) ^ swz(row)) << 4) | (byte_col & 15));
