@@ -523,8 +523,8 @@ __device__ __forceinline__ constexpr int dkdv_vec_off(int r, bool d_part) {
 // The element mask of a lane's key is two row intervals: a 32-row block's are formed as a word with a bit per row
 // (interval_rows) beside the first block's score MFMAs, which no other vector work rides along with, and an element's bit,
 // spread over a word, is ANDed to its P.  Two instructions per element and 42 per tile, where comparing the row with both
-// intervals and selecting took six: a partially masked tile has 530 instead of 619 instructions (417 instead of 506 at
-// d = 64; 422 and 308 without mask).  Training step, both sides: eleven documents in 8192 tokens, 64 slices, d = 128 1050 ->
+// intervals and selecting took six: a partially masked tile had 530 instead of 619 instructions (417 instead of 506 at
+// d = 64; 422 and 308 without mask; now 504 and 402, 398 and 297 without, branches counted).  Training step, both sides: eleven documents in 8192 tokens, 64 slices, d = 128 1050 ->
 // 1030 us, five in 1000, 32 slices 86.7 -> 81.5; window 1024, N = 32768 1458 -> 1443.
 __device__ __forceinline__ void dkdv_stage_a(const f32x16& s, const f32x16& dp, float (&t)[16], float (&u)[16],
                                              const f32x4 (&l4)[4], int e0, int cnt, float sc) {
@@ -887,7 +887,7 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
   // fetches made for them are never used, and every entry costs the same number of copies.
   // S = 2: t counts steps of two tiles, of which this wave's group takes one.
   // A step's list entries are read without a bound and its stages follow from the last step's: 394 instead of 407 instructions
-  // a tile at d = 128, dK/dV prefix 32768 6775 -> 6703 us, documents at 131072 4225 -> 4173, answers 16384 1190 -> 1175.
+  // a tile at d = 128 (branches not counted), dK/dV prefix 32768 6775 -> 6703 us, documents at 131072 4225 -> 4173, answers 16384 1190 -> 1175.
 #define FM_TILE_LOOP(T0, T1, MASK)                                                                     \
   for (int t = (T0); t < (T1); ++t) {                                                                  \
     const int v_next = list[S * (t + 1) + grp];                                                        \
