@@ -1,6 +1,6 @@
 """The order of direct units: every unit is taken by exactly one workgroup of the launch, the workgroups beyond take none, an
-XCD (workgroup number modulo 8) works on the run of slices of its class, each XCD of a slice gets its share of the blocks, and
-nothing but rounding makes the grid larger than the unit count."""
+XCD (workgroup number modulo 8) works on the run of slices of its class, a slice's blocks all go to one XCD (as many slices to each)
+or in equal shares to the class, each XCD gets its share of all units and of a causal mask's work, and nothing but rounding makes the grid larger than the unit count."""
 import os
 import shutil
 import subprocess
@@ -17,13 +17,14 @@ PROGRAM = r"""
 
 int main() {
   long long checked = 0;
-  for (int slices : {1, 2, 3, 4, 5, 6, 7, 8, 9, 12, 16, 20, 24, 32, 40, 64, 100})
+  for (int slices : {1, 2, 3, 4, 5, 6, 7, 8, 9, 12, 16, 20, 24, 25, 32, 40, 64, 75, 100, 125, 127, 150, 175, 250, 252, 255})
     for (int group : {1, 2, 3, 4, 8})
-      for (int blocks : {1, 2, 3, 7, 8, 9, 16, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 1024}) {
+      for (int blocks : {1, 2, 3, 4, 5, 6, 7, 8, 9, 16, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 1024}) {
         const FmDirectOrder o = fm_direct_order(slices, blocks);
         const int grid = fm_direct_grid(o, group, blocks), classes = 1 << o.classes;
         std::vector<int> taken(slices * group * blocks);
         std::vector<std::vector<int>> share(8, std::vector<int>(slices));   // blocks of a slice that an XCD works on
+        std::vector<long long> units(8), work(8);   // of an XCD; a causal mask's block 0 is the longest
         for (int x = 0; x < grid; ++x, ++checked) {
           const FmDirectUnit u = fm_direct_unit(o, x, group, blocks);
           if (u.block < 0) continue;
@@ -34,21 +35,43 @@ int main() {
           }
           ++taken[(u.slice * group + u.member) * blocks + u.block];
           ++share[x % 8][u.slice];
+          ++units[x % 8];
+          work[x % 8] += blocks - u.block;
         }
         for (int n : taken)
           if (n != 1) {
             std::printf("%d %d %d: a unit is taken %d times\n", slices, group, blocks, n);
             return 1;
           }
+        std::vector<int> alone(8);   // slices that an XCD has to itself
         for (int s = 0; s < slices; ++s)
-          for (int a = 0; a < 8; ++a)
-            for (int b = 0; b < 8; ++b)
-              if (a % classes == s / o.own && b % classes == s / o.own &&
-                  share[a][s] - share[b][s] > group << o.chunk) {
-                std::printf("%d %d %d: slice %d is shared %d : %d\n", slices, group, blocks, s, share[a][s], share[b][s]);
-                return 1;
-              }
-        if (grid >= slices * group * (blocks + (1 << (o.sharing + o.chunk)))) {
+          if (8 / classes * o.whole > s % o.own) {
+            for (int a = 0; a < 8; ++a) alone[a] += share[a][s] == group * blocks;
+          } else {
+            for (int a = 0; a < 8; ++a)
+              for (int b = 0; b < 8; ++b)
+                if (a % classes == s / o.own && b % classes == s / o.own &&
+                    share[a][s] - share[b][s] > group << o.chunk) {
+                  std::printf("%d %d %d: slice %d is shared %d : %d\n", slices, group, blocks, s, share[a][s], share[b][s]);
+                  return 1;
+                }
+          }
+        for (int a = 0; a < 8; ++a)
+          if (alone[a] != (o.whole > 0 ? o.whole : 0)) {
+            std::printf("%d %d %d: XCD %d has %d slices to itself\n", slices, group, blocks, a, alone[a]);
+            return 1;
+          }
+        // An XCD takes chunks: at most one of the longest more than its even share, and slices end with a chunk that is not
+        // full, which costs the work of the shortest.
+        const long long chunk = group << o.chunk, all = 1ll * slices * group * blocks;
+        const long long pads = o.chunk ? 1ll * slices * group * ((1 << o.chunk) - 1) / 8 : 0;
+        for (int x = 0; x < 8; ++x)
+          if (8 * units[x] > all + 8 * (chunk + pads) || 8 * work[x] > all * (blocks + 1) / 2 + 8 * (chunk * blocks + pads)) {
+            std::printf("%d %d %d: XCD %d has %lld of %lld units, work %lld\n", slices, group, blocks, x, units[x], all, work[x]);
+            return 1;
+          }
+        // empty workgroups: those of the last turns
+        if (grid >= (o.whole < 0 ? all + slices * (chunk << o.sharing) : all + 8 * chunk)) {
           std::printf("%d %d %d: grid %d\n", slices, group, blocks, grid);
           return 1;
         }
