@@ -57,10 +57,10 @@ __device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
     bh = rec[0] / t_r;
     i_blk = rec[0] - bh * t_r;
   } else {
-    const int group = GEN ? a.H / a.Hk : 1;
-    const FmDirectUnit u = fm_direct_unit(a.order, (int)blockIdx.x, group, t_r);
+    args_at_once(a.order, a.q, a.lts, a.lte, a.uts, a.ute, a.N, a.Np, a.H);
+    const FmDirectUnit u = fm_direct_unit<GEN>(a.order, (int)blockIdx.x);
     if (u.block < 0) return;
-    bh = u.slice * group + u.member;
+    bh = GEN ? u.slice * (int)a.order.group.n + u.member : u.slice;
     i_blk = t_r - 1 - u.block;
   }
   const int tid = threadIdx.x, lane = tid & 63;
@@ -834,7 +834,8 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
   if (!DIRECT) {
     rec = queue_take(a.queue_dkdv, qwords + 8);
   } else {
-    direct = fm_direct_unit(a.order, (int)blockIdx.x, 1, (a.N + C::BC - 1) / C::BC);
+    args_at_once(a.order, a.k, a.lts, a.lte, a.uts, a.ute, a.N, a.Np, a.H);
+    direct = fm_direct_unit<false>(a.order, (int)blockIdx.x);
     rec[0] = direct.block;
     rec[2] = (a.N + QT - 1) / QT;   // every row block may be live
   }
@@ -1191,8 +1192,8 @@ static hipError_t launch_dq_s(const FmBwdArgs& a, hipStream_t stream) {
   FmBwdArgs args = a;
   args.queue_dq = fm_queue_for_launch(a.queue_dq, FM_DQ_PER_CU);
   const int blocks = (a.N + C::BR - 1) / C::BR;
-  args.order = fm_direct_order(a.B * a.Hk, blocks);
-  const int grid = U == FM_QUEUED ? fm_launch_grid(args.queue_dq) : fm_direct_grid(args.order, a.H / a.Hk, blocks);
+  if (U != FM_QUEUED) args.order = fm_direct_order(a.B * a.Hk, a.H / a.Hk, blocks, a.B * a.H * blocks <= fm_compute_units());
+  const int grid = U == FM_QUEUED ? fm_launch_grid(args.queue_dq) : fm_direct_grid(args.order);
   hipLaunchKernelGGL(L::kernel(), dim3(grid), dim3(C::THREADS), C::LDS_BYTES, stream, args);
   return hipGetLastError();
 }
@@ -1245,8 +1246,8 @@ static hipError_t launch_dkdv_s(const FmBwdArgs& a, hipStream_t stream) {
   FmBwdArgs args = a;
   args.queue_dkdv = fm_queue_for_launch(a.queue_dkdv, C::PER_CU);
   const int blocks = (a.N + C::BC - 1) / C::BC;
-  args.order = fm_direct_order(a.B * a.Hk, blocks);
-  const int grid = U != FM_QUEUED   ? fm_direct_grid(args.order, 1, blocks)
+  if (U != FM_QUEUED) args.order = fm_direct_order(a.B * a.Hk, 1, blocks, a.B * a.Hk * blocks <= fm_compute_units());
+  const int grid = U != FM_QUEUED   ? fm_direct_grid(args.order)
                    : C::PERSISTENT ? fm_persistent_grid(args.queue_dkdv)
                                    : fm_launch_grid(args.queue_dkdv);
   hipLaunchKernelGGL(L::kernel(), dim3(grid), dim3(256), C::LDS_BYTES, stream, args);

@@ -5,26 +5,30 @@
 
 // Workgroup x runs on XCD x % 8, and each XCD has an L2 of its own.  The slices (batch row and K/V head; `group` query heads of
 // it take turns) are dealt to m classes of XCDs in contiguous runs, m = the largest power of two up to 8 that divides their
-// count, so that a slice is worked on by at most 8 / m XCDs and the bounds of its batch row are read by as few.  An XCD takes its
-// slices' blocks in step, in the order 0, 1, 2, ...: what is longest in masks with a causal side comes first for all of them
-// (the callers count row blocks from the last).
-//  - Slices of at least four blocks to each XCD of their class are shared by all of it: its XCDs take chunks of up to eight
-//    neighbouring blocks in turn, back and forth, so that they get equal shares of a length that falls from block to block;
-//    neighbours have much of their tiles in common, a window's nearly all.  Where the turns do not come out even, each slice
-//    begins one XCD further on than the one before, so that what is over does not go to the same XCDs for all of them.
-//  - Shorter ones would leave XCDs without a block, and every XCD would fetch every slice: each XCD has as many of them to
-//    itself as there are for all, and the fewer than 8 / m left over are shared block by block, ahead of the others.
-// An XCD then has at most one block (chunk) of a group more than its even share, whatever the counts.  With all slices shared
-// and begun at the same XCD, the XCDs past the last block had nothing: one XCD all 255 units of as many slices of one block.
-// Forward / backward in us, causal, all begun at one XCD -> now:
-//   d = 128  255 slices, N = 128  70.5 / 177 -> 11.3 / 30;  three rows of 25, N = 512  31.8 / 93 -> 16.4 / 46
-//   d = 64   255 slices, N = 128  23.3 / 55 -> 7.2 / 17;    three rows of 25, N = 512  19.4 / 52 -> 11.8 / 29
-// With short slices shared block by block, too, 85 of 384 tokens took 1.16 / 1.08 and 75 of 1024 1.10 / 1.05 times as long
-// (d = 128); with those of 16 and more blocks whole, 20 of 4000 (d = 64) 1.06 / 1.03.
+// count, so that a slice is worked on by at most 8 / m XCDs and the bounds of its batch row are read by as few.  Every XCD of a
+// class gets as many units, to one: where units are about as many as compute units, an XCD with one too many takes twice as long.
+// An XCD takes its slices' blocks in step, in the order 0, 1, 2, ...: what is longest in masks with a causal side comes first
+// for all of them (the callers count row blocks from the last).
+//  - Turns, for slices of at least four blocks to each XCD of their class: its XCDs take chunks of up to eight neighbouring
+//    blocks in turn, back and forth, so that they get equal shares of a length that falls from block to block; neighbours
+//    have much of their tiles in common, a window's nearly all.  With an odd number of turns each slice begins one XCD further
+//    on than the one before.  The blocks after the last whole turn go round one by one, slice after slice.
+//  - Whole, for shorter slices, of which XCDs would be left without a block or every XCD would fetch every one: each XCD has
+//    as many of them to itself as there are for all, and the fewer than 8 / m others go round one by one, ahead of those.
+//  - Runs, where each compute unit has one unit at most, so that no order matters, and turns would bring several slices to
+//    every XCD of a class: each has a contiguous run of units.
+// Forward / backward in us, causal (3 slices: window 256), all slices in turns that begin at the same XCD -> now:
+//   255 slices, N = 128          d = 128  70.5 / 177 -> 11.2 / 30   d = 64  23.3 / 55 -> 7.2 / 17    one XCD had all 255 units
+//   three rows of 25, N = 512    d = 128  31.8 / 93 -> 16.4 / 46    d = 64  19.4 / 52 -> 11.8 / 29   four XCDs had none
+//   3 slices, N = 5376           d = 128  21.4 / 48 -> 13.1 / 30                                  an XCD had 36 units for 32 compute units
+//   7 slices, N = 1920           d = 128  25.1 / 62 -> 24.3 / 59                                  every XCD fetched every slice
+// Against turns, runs take 1 % longer where a class has a single slice (1 of 8192 tokens, 4 of 1000), and with two units to
+// a compute unit 1.2 times as long (12 of 2048, d = 64).  With short slices in turns, too, 85 of 384 tokens took 1.16 /
+// 1.08 and 75 of 1024 1.10 / 1.05 times as long (d = 128); with those of 16 and more blocks whole, 20 of 4000 (d = 64) 1.06 / 1.03.
 //
-// Before, an XCD had one contiguous run of units, slice after slice: of few heads one XCD had all the long units of a causal mask
+// Before turns, an XCD had one contiguous run of units, slice after slice: of few heads one XCD had all the long units of a causal mask
 // and another all the short ones; in several rounds, units started in the order of the slices; and where two workgroups share a
-// compute unit, they were equally long.  Loop times in us, before -> now (fwd / dQ / dK,dV):
+// compute unit, they were equally long.  Loop times in us, runs -> turns (fwd / dQ / dK,dV):
 //   d = 128  2 heads, N = 16384   causal 240 -> 211 / 304 -> 280 / 377 -> 246, documents of 700 tokens 64 -> 63 / 76 -> 75 / 79 -> 64
 //            3 heads, N = 8192    causal 112 -> 108 / 147 / 158 -> 111;  16 heads, N = 2048 (one round, a unit to a compute unit) as before
 //            32 heads on 8 K/V heads, two rows of 2048, shared questions   dK/dV 122 -> 112
@@ -32,59 +36,97 @@
 //            2 heads, N = 16384   causal 165 -> 133 / 194 -> 161 / 218 -> 162;  4 heads, N = 8192, documents 40 -> 41 / 46 -> 47 / 37 -> 36
 // Windows of 256 keep their times within 2 to 3 %.  With the blocks of a slice dealt to its XCDs one by one, windows took up to 8 %
 // longer (each tile came to every L2) and the three heads' documents 46 instead of 55 us of dK/dV.
-struct FmDirectOrder {
-  int own;                              // slices of a class
-  int classes, sharing, chunk;          // m, XCDs of a class, blocks taken together: powers of two, as their logarithms
-  int whole;                            // short slices: those that an XCD has to itself; -1: its class shares all
-  int turns;                            // of an XCD, a chunk each: at every slice, or of short ones at those shared together
-  int turned;                           // whether a slice begins one XCD further on than the one before
+
+// x / n for 0 <= x < 2^31 by a product (Granlund and Montgomery, "Division by Invariant Integers using Multiplication"): the
+// divisors are the launch's, and a division takes a workgroup some 30 instructions of its prologue, one behind the other.
+struct FmDivisor {
+  unsigned n, factor;
+  int shift;
 };
-FM_HOST_DEVICE inline FmDirectOrder fm_direct_order(int slices, int blocks) {
+FM_HOST_DEVICE inline FmDivisor fm_divisor(int n) {
+  const int shift = n > 1 ? 63 - __builtin_clz(n - 1) : 31;   // 31 and the logarithm of n, rounded up
+  return FmDivisor{(unsigned)n, (unsigned)((1ull << shift) / (unsigned)n + 1), shift};
+}
+FM_HOST_DEVICE inline int fm_div(int x, const FmDivisor& d) { return (int)((unsigned long long)(unsigned)x * d.factor >> d.shift); }
+
+enum FmDirectDeal { FM_DEAL_RUNS, FM_DEAL_WHOLE, FM_DEAL_TURNS };
+// What a workgroup needs to know is worked out by the host: its way from its number to its unit is a chain of scalar
+// instructions in front of everything else.
+struct FmDirectOrder {
+  FmDirectDeal deal;
+  int own, blocks;               // slices of a class, blocks of a slice
+  int classes, sharing, chunk;   // m, XCDs of a class, blocks taken together: powers of two, as their logarithms
+  int share;                     // workgroups of an XCD; of them, [odd_from, odd_to) take units one by one:
+  int odd_from, odd_to;          // of the slices from odd_slice on, the blocks from odd_block on
+  int odd_slice, odd_block;
+  int turned;                    // (turns) whether a slice begins one XCD further on than the one before
+  FmDivisor odd, step, group;    // slices of these units (runs: units of a slice); slices in step otherwise; query heads of a slice
+};
+// at_once: no more units than compute units.
+FM_HOST_DEVICE inline FmDirectOrder fm_direct_order(int slices, int group, int blocks, bool at_once) {
   constexpr int kLogXcds = 3, kLogTurns = 2, kLogChunk = 3;
-  FmDirectOrder o = {slices, 0, kLogXcds, 0, -1, 0, 0};
-  for (; o.classes < kLogXcds && o.own % 2 == 0; o.own /= 2, --o.sharing) ++o.classes;
-  int chunks;
-  if (o.sharing == 0 || blocks >> (kLogTurns + o.sharing) == 0) {
-    o.whole = o.own >> o.sharing;
-    chunks = blocks * (o.own & ((1 << o.sharing) - 1));
+  FmDirectOrder o = {};
+  o.own = slices;
+  o.blocks = blocks;
+  for (o.sharing = kLogXcds; o.classes < kLogXcds && o.own % 2 == 0; o.own /= 2, --o.sharing) ++o.classes;
+  const int last = (1 << o.sharing) - 1;
+  int odd = o.own, step = o.own;
+  o.share = o.odd_to = (o.own * group * blocks + last) >> o.sharing;
+  if (at_once && o.sharing && o.own > 1) {
+    o.deal = FM_DEAL_RUNS;
+    odd = group * blocks;
+  } else if (o.sharing == 0 || blocks >> (kLogTurns + o.sharing) == 0) {
+    o.deal = FM_DEAL_WHOLE;
+    odd = o.own & last;
+    step = o.own >> o.sharing;
+    o.odd_to -= step * group * blocks;
+    o.odd_slice = o.own - odd;
   } else {
+    o.deal = FM_DEAL_TURNS;
     while (o.chunk < kLogChunk && blocks >> (o.chunk + 1 + kLogTurns + o.sharing)) ++o.chunk;
-    chunks = (blocks + (1 << o.chunk) - 1) >> o.chunk;
-    o.turned = blocks % (2 << (o.sharing + o.chunk)) != 0;
+    const int turns = blocks >> (o.sharing + o.chunk);
+    o.turned = turns & 1;
+    o.odd_block = turns << (o.sharing + o.chunk);
+    o.odd_from = o.own * group * (turns << o.chunk);
   }
-  o.turns = (chunks + (1 << o.sharing) - 1) >> o.sharing;
+  o.odd = fm_divisor(odd ? odd : 1);
+  o.step = fm_divisor(step ? step : 1);
+  o.group = fm_divisor(group);
   return o;
 }
 // Workgroups of the launch.
-FM_HOST_DEVICE inline int fm_direct_grid(const FmDirectOrder& o, int group, int blocks) {
-  return 8 * group * (o.whole < 0 ? o.own * (o.turns << o.chunk) : o.turns + o.whole * blocks);
-}
-// The slice, member of its group and block that workgroup x takes; block = -1: none.
+FM_HOST_DEVICE inline int fm_direct_grid(const FmDirectOrder& o) { return 8 * o.share; }
+// The slice, member of its group and block that workgroup x takes; block = -1: none.  GROUPED = false: groups of one.
 struct FmDirectUnit {
   int slice, member, block;
 };
-FM_HOST_DEVICE inline FmDirectUnit fm_direct_unit(const FmDirectOrder& o, int x, int group, int blocks) {
-  const int xcd = x & 7, p = xcd >> o.classes, last = (1 << o.sharing) - 1;
-  int at = x >> 3, slice, member, block;   // at: which of the XCD's workgroups, slice: of the class
-  const int ahead = o.whole < 0 ? 0 : o.turns * group;
-  if (at < ahead) {   // short slices that the class shares: block 0 of all, block 1, ..., the XCDs in turn
-    const int turn = group == 1 ? at : at / group, n = o.own & last, pass = n == 1 ? turn : turn / n;
-    const int k = (turn << o.sharing) + (pass & 1 ? last - p : p);
-    member = at - turn * group;
-    block = n == 1 ? k : k / n;
-    slice = (o.whole << o.sharing) + k - block * n;
-  } else {
-    at -= ahead;
-    const int n = o.whole < 0 ? o.own : o.whole, step = n == 1 ? at : at / n, i = group == 1 ? step : step / group;
-    slice = at - step * n;
-    member = step - i * group;
-    block = i;
-    if (o.whole < 0) {
-      const int turn = i >> o.chunk, mine = (p + (o.turned ? slice : 0)) & last;
-      block = (((turn << o.sharing) + (turn & 1 ? last - mine : mine)) << o.chunk) + (i & ((1 << o.chunk) - 1));
-    } else {
-      slice += p * n;
+template <bool GROUPED>
+FM_HOST_DEVICE inline FmDirectUnit fm_direct_unit(const FmDirectOrder& o, int x) {
+  const int xcd = x & 7, p = xcd >> o.classes, at = x >> 3;   // at: which of the XCD's workgroups
+  const int first = (xcd & ((1 << o.classes) - 1)) * o.own, group = GROUPED ? (int)o.group.n : 1;
+  int slice, i;   // slice of the class; block * group + member
+  if (at >= o.odd_from && at < o.odd_to) {
+    if (o.deal == FM_DEAL_RUNS) {
+      const int unit = p * o.share + at;
+      slice = fm_div(unit, o.odd);
+      i = slice < o.own ? unit - slice * (int)o.odd.n : group * o.blocks;
+    } else {   // a unit to each XCD in turn: every slice's next block, then the block after it
+      const int k = ((at - o.odd_from) << o.sharing) + p;
+      i = fm_div(k, o.odd);
+      slice = o.odd_slice + k - i * (int)o.odd.n;
+      i += o.odd_block * group;
     }
+  } else if (o.deal == FM_DEAL_WHOLE) {
+    i = fm_div(at - o.odd_to, o.step);
+    slice = at - o.odd_to + (p - i) * (int)o.step.n;
+  } else {
+    i = fm_div(at, o.step);
+    slice = at - i * o.own;
+    const int last = (1 << o.sharing) - 1, j = GROUPED ? fm_div(i, o.group) : i;
+    const int turn = j >> o.chunk, mine = (p + (o.turned ? slice : 0)) & last;
+    const int block = (((turn << o.sharing) + (turn & 1 ? last - mine : mine)) << o.chunk) + (j & ((1 << o.chunk) - 1));
+    return FmDirectUnit{first + slice, i - j * group, block};
   }
-  return FmDirectUnit{(xcd & ((1 << o.classes) - 1)) * o.own + slice, member, block < blocks ? block : -1};
+  const int block = GROUPED ? fm_div(i, o.group) : i;
+  return FmDirectUnit{first + slice, i - block * group, block < o.blocks ? block : -1};
 }

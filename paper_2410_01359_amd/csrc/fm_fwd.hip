@@ -306,10 +306,10 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
     bh = rec[0] / t_r;
     i_blk = rec[0] - bh * t_r;
   } else {
-    const int group = GEN ? a.H / a.Hk : 1;
-    const FmDirectUnit u = fm_direct_unit(a.order, (int)blockIdx.x, group, t_r);
+    args_at_once(a.order, a.q, a.lts, a.lte, a.uts, a.ute, a.N, a.Np, a.H);
+    const FmDirectUnit u = fm_direct_unit<GEN>(a.order, (int)blockIdx.x);
     if (u.block < 0) return;
-    bh = u.slice * group + u.member;
+    bh = GEN ? u.slice * (int)a.order.group.n + u.member : u.slice;
     i_blk = t_r - 1 - u.block;
   }
   const int tid = threadIdx.x, lane = tid & 63;
@@ -612,8 +612,8 @@ static hipError_t launch_fwd_s(const FmFwdArgs& a, hipStream_t stream) {
   FmFwdArgs args = a;
   args.queue = fm_queue_for_launch(a.queue, FwdCfg<D>::PER_CU);
   const int blocks = (a.N + C::BR - 1) / C::BR;
-  args.order = fm_direct_order(a.B * a.Hk, blocks);
-  const int grid = U == FM_QUEUED ? fm_launch_grid(args.queue) : fm_direct_grid(args.order, a.H / a.Hk, blocks);
+  if (U != FM_QUEUED) args.order = fm_direct_order(a.B * a.Hk, a.H / a.Hk, blocks, a.B * a.H * blocks <= fm_compute_units());
+  const int grid = U == FM_QUEUED ? fm_launch_grid(args.queue) : fm_direct_grid(args.order);
   hipLaunchKernelGGL(L::kernel(), dim3(grid), dim3(C::THREADS), C::LDS_BYTES, stream, args);
   return hipGetLastError();
 }

@@ -1,6 +1,7 @@
 """The order of direct units: every unit is taken by exactly one workgroup of the launch, the workgroups beyond take none, an
 XCD (workgroup number modulo 8) works on the run of slices of its class, a slice's blocks all go to one XCD (as many slices to each)
-or in equal shares to the class, each XCD gets its share of all units and of a causal mask's work, and nothing but rounding makes the grid larger than the unit count."""
+or in equal shares to the class, each XCD gets its share of all units, rounded up, and of a causal mask's work, and the launch
+holds no more workgroups than that."""
 import os
 import shutil
 import subprocess
@@ -17,16 +18,24 @@ PROGRAM = r"""
 
 int main() {
   long long checked = 0;
+  for (int n = 1; n < 5000; ++n)
+    for (long long x : {0ll, 1ll, n - 1ll, 1ll * n, n + 1ll, 1000ll * n - 1, 1000ll * n, 0x7fffffffll / n * n - 1, 0x7fffffffll / n * n, 0x7fffffffll})
+      if (const FmDivisor d = fm_divisor(n); fm_div((int)x, d) != x / n) {
+        std::printf("%lld / %d is not %d\n", x, n, fm_div((int)x, d));
+        return 1;
+      }
   for (int slices : {1, 2, 3, 4, 5, 6, 7, 8, 9, 12, 16, 20, 24, 25, 32, 40, 64, 75, 100, 125, 127, 150, 175, 250, 252, 255})
-    for (int group : {1, 2, 3, 4, 8})
-      for (int blocks : {1, 2, 3, 4, 5, 6, 7, 8, 9, 16, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, 1024}) {
-        const FmDirectOrder o = fm_direct_order(slices, blocks);
-        const int grid = fm_direct_grid(o, group, blocks), classes = 1 << o.classes;
+    for (int group : {1, 2, 3, 4, 5, 8})
+      for (int blocks : {1, 2, 3, 4, 5, 6, 7, 8, 9, 16, 31, 32, 33, 63, 64, 65, 84, 127, 128, 129, 255, 256, 257, 1024})
+      for (bool at_once : {false, true}) {
+        const FmDirectOrder o = fm_direct_order(slices, group, blocks, at_once);
+        const int grid = fm_direct_grid(o), classes = 1 << o.classes;
+        const int whole = o.deal == FM_DEAL_WHOLE ? o.own * classes / 8 : 0;   // slices that an XCD has to itself
         std::vector<int> taken(slices * group * blocks);
         std::vector<std::vector<int>> share(8, std::vector<int>(slices));   // blocks of a slice that an XCD works on
         std::vector<long long> units(8), work(8);   // of an XCD; a causal mask's block 0 is the longest
         for (int x = 0; x < grid; ++x, ++checked) {
-          const FmDirectUnit u = fm_direct_unit(o, x, group, blocks);
+          const FmDirectUnit u = group == 1 ? fm_direct_unit<false>(o, x) : fm_direct_unit<true>(o, x);
           if (u.block < 0) continue;
           if (u.slice < 0 || u.slice >= slices || u.member < 0 || u.member >= group || u.block >= blocks ||
               u.slice / o.own != x % 8 % classes) {
@@ -43,9 +52,11 @@ int main() {
             std::printf("%d %d %d: a unit is taken %d times\n", slices, group, blocks, n);
             return 1;
           }
-        std::vector<int> alone(8);   // slices that an XCD has to itself
+        std::vector<int> alone(8);
         for (int s = 0; s < slices; ++s)
-          if (8 / classes * o.whole > s % o.own) {
+          if (o.deal == FM_DEAL_RUNS) {
+            ;
+          } else if (8 / classes * whole > s % o.own) {
             for (int a = 0; a < 8; ++a) alone[a] += share[a][s] == group * blocks;
           } else {
             for (int a = 0; a < 8; ++a)
@@ -57,21 +68,27 @@ int main() {
                 }
           }
         for (int a = 0; a < 8; ++a)
-          if (alone[a] != (o.whole > 0 ? o.whole : 0)) {
+          if (alone[a] != whole) {
             std::printf("%d %d %d: XCD %d has %d slices to itself\n", slices, group, blocks, a, alone[a]);
             return 1;
           }
-        // An XCD takes chunks: at most one of the longest more than its even share, and slices end with a chunk that is not
-        // full, which costs the work of the shortest.
-        const long long chunk = group << o.chunk, all = 1ll * slices * group * blocks;
-        const long long pads = o.chunk ? 1ll * slices * group * ((1 << o.chunk) - 1) / 8 : 0;
+        if (o.deal == FM_DEAL_RUNS)
+          for (int a = 0; a < 8; ++a) {   // a run of the class's units: of at most one slice more than the even share, rounded up
+            int touched = 0;
+            for (int s = 0; s < slices; ++s) touched += share[a][s] > 0;
+            if (!at_once || touched > (o.own * classes + 7) / 8 + 1) {
+              std::printf("%d %d %d: XCD %d works on %d slices\n", slices, group, blocks, a, touched);
+              return 1;
+            }
+          }
+        // An XCD has no unit more than its even share, and of the work a chunk of the longest more at most.
+        const long long all = 1ll * slices * group * blocks, even = (all + 7) / 8;
         for (int x = 0; x < 8; ++x)
-          if (8 * units[x] > all + 8 * (chunk + pads) || 8 * work[x] > all * (blocks + 1) / 2 + 8 * (chunk * blocks + pads)) {
+          if (units[x] > even || (o.deal != FM_DEAL_RUNS && 8 * work[x] > all * (blocks + 1) / 2 + 8ll * (group << o.chunk) * blocks)) {
             std::printf("%d %d %d: XCD %d has %lld of %lld units, work %lld\n", slices, group, blocks, x, units[x], all, work[x]);
             return 1;
           }
-        // empty workgroups: those of the last turns
-        if (grid >= (o.whole < 0 ? all + slices * (chunk << o.sharing) : all + 8 * chunk)) {
+        if (grid != 8 * even) {
           std::printf("%d %d %d: grid %d\n", slices, group, blocks, grid);
           return 1;
         }

@@ -56,3 +56,13 @@ def test_cuts_strided_grouped(H, Hk, N, d):
     uts[:], ute[:] = 0, np.maximum(ute, 3)                 # rows 0..2 see nothing
     w.vectors = [(lts, lte, uts, ute)]
     _heads_alike(w, H, Hk, True, f"H={H}/{Hk} N={N} d={d}")
+
+
+# How fm_direct_order.h deals the units, with groups of query heads and without, odd slices to two, four and eight XCDs: runs
+# (12 on 3, 12 on 6 and 42 on 14 at d = 128), whole slices and units one by one (36 on 9; 42 on 14 at d = 64), turns that begin
+# one XCD further on and a block after the last turn (20 alone and 12 on 6 at d = 64).
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,Hk,N", [(12, 3, 1100), (42, 14, 640), (36, 9, 1000), (12, 6, 2100), (20, 20, 1300)])
+def test_deals(H, Hk, N, d):
+    w = workloads.small_workload("document", N, seed=H + N, B=1, H=1, d=d)
+    _heads_alike(w, H, Hk, H != Hk, f"H={H}/{Hk} N={N} d={d}")
