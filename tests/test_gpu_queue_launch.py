@@ -34,6 +34,21 @@ def test_every_head_alike(H, N, d):
         check_bwd(bf16_to_np(got[0, 0]), ref, name, f"H={H} N={N} d={d}")
 
 
+# Some of the sizes above take direct units; these reach the queues, with a few units more than a loop runs at once (two or
+# three workgroups to a compute unit in the row-parallel loops, two for the keys at d = 64) and one, three or five slices more than
+# fill rounds of eight queues.
+Q, D = fm.FM_CUT_QUEUED, fm.FM_CUT_DIRECT
+PAST_ONE_ROUND = [(17, 4096, 128, (Q, Q, Q)), (19, 3500, 128, (Q, Q, Q)), (13, 5250, 128, (Q, Q, Q)), (25, 4096, 64, (Q, Q, Q)),
+                  (27, 3650, 64, (Q, Q, Q)), (17, 4224, 64, (D, Q, Q))]
+
+
+@pytest.mark.parametrize("H,N,d,cuts", PAST_ONE_ROUND, ids=[f"{H}x{N}-d{d}" for H, N, d, _ in PAST_ONE_ROUND])
+def test_every_head_alike_past_one_round(H, N, d, cuts):
+    passes = (fm.FM_PASS_FWD, fm.FM_PASS_BWD_DQ, fm.FM_PASS_BWD_DKDV)
+    assert tuple(fm.flashmask_work_cut(p, 1, H, H, N, d, compute_units=256) for p in passes) == cuts
+    test_every_head_alike(H, N, d)
+
+
 @pytest.mark.parametrize("B,H,N", [(1, 64, 1024), (1, 7, 640), (3, 5, 384), (2, 12, 1152), (1, 1, 128)])
 def test_units_lie_within_the_tickets(B, H, N):
     """No queue is longer than the launch's ticket count: whole rounds of slices, then a half, a quarter and an eighth
