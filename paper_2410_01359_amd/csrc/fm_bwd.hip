@@ -597,11 +597,10 @@ __device__ __forceinline__ constexpr int dkdv_kk(int y) {
 }
 
 // Per-lane LDS addresses of a list entry's stage: the stage's address plus the lane-dependent part of
-// the three read patterns (row reads; transpose reads of rows 0-7 and 8-15 of a 16-row group).  A
-// step's column offset is XORed into the sum -- stage addresses are multiples of 256 bytes, so the sum
-// keeps the lane part's low byte -- which costs one instruction per read and no register that lives
-// across tiles; XORing into the lane part first would either keep every (pattern, column) pair in a
-// register for the whole loop or take two instructions per read.
+// the three read patterns (row reads; transpose reads of rows 0-7 and 8-15 of a 16-row group).  Further columns,
+// rows and the dO tile are immediate offsets, but for every second column group of the row reads, 32 bytes further
+// on, which is an XOR (TileLayout::add_col): stage addresses are multiples of 256 bytes, so the sum keeps the lane
+// part's low byte.
 struct DkdvBases {
   unsigned a, t0, t1;
 };
@@ -718,10 +717,10 @@ __device__ __forceinline__ void dkdv_tile(unsigned qs, const DkdvAhead<S>& ah,
           dvacc[db] = mfma32(op[x % RD], pa[qb][h], dvacc[db]);
       } else if (u & 1) {
         // dsa[qb][h] / pa[qb][h] were converted several steps ago (the vector work of a block ends before the
-        // block's dV, dK steps begin), so no idle instruction is needed in front of their first reader
-        mfma32_acc(dkacc[db], op[x % RD], dsa[qb][h], false);
+        // block's dV, dK steps begin), which is the distance that mfma32_acc asks for
+        mfma32_acc(dkacc[db], op[x % RD], dsa[qb][h]);
       } else {
-        mfma32_acc(dvacc[db], op[x % RD], pa[qb][h], false);
+        mfma32_acc(dvacc[db], op[x % RD], pa[qb][h]);
       }
     }
     // --- the workgroup step(s) and the copies behind it
@@ -802,7 +801,7 @@ __device__ __forceinline__ void dkdv_tile(unsigned qs, const DkdvAhead<S>& ah,
             }
             if (D == 128) {
               // here and not just in front of the MFMAs that read them, where ragged lengths' branches let the compiler
-              // sink the conversions to: mfma32_acc's idle instruction is left out there
+              // sink the conversions to: closer than mfma32_acc allows
               settle(pa[qb][hh]);
               settle(dsa[qb][hh]);
             }

@@ -84,24 +84,19 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
 __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
-// The same product accumulated in place in accumulation registers (AGPRs).  For accumulators that
+// mfma32's product (32x32x16) accumulated in place in accumulation registers (AGPRs).  For accumulators that
 // live through a whole tile loop and are touched by nothing but their own MFMAs: the compiler picks
 // one register file for all of a kernel's MFMA results, and keeping these in the vector file leaves the
 // loop's vector work half the registers.  The compiler does not look into the asm, so the wait states
 // an MFMA needs are the caller's business:
-//  - a vector instruction that writes an A/B source must be two wait states ahead of the MFMA: pass
-//    fresh = true (a constant once the caller's step loop is unrolled) for the first MFMA that reads
-//    a source just produced by vector instructions (it puts an idle instruction of two cycles in
-//    front); sources loaded from LDS only need the wait the compiler already inserts for the asm's
-//    operands;
+//  - a vector instruction that writes an A/B source must be two wait states ahead of the MFMA: the caller
+//    converts its sources several steps ahead; sources loaded from LDS only need the wait the compiler already
+//    inserts for the asm's operands;
 //  - in-place accumulation with one opcode needs none between dependent MFMAs;
 //  - a reader of `acc` other than this function must be kept clear of the last MFMA (mfma_acc_drain).
-__device__ __forceinline__ void mfma32_acc(f32x16& acc, bf16x8 a, bf16x8 b, bool fresh) {
+__device__ __forceinline__ void mfma32_acc(f32x16& acc, bf16x8 a, bf16x8 b) {
   const i32x4 ai = __builtin_bit_cast(i32x4, a), bi = __builtin_bit_cast(i32x4, b);
-  if (fresh)
-    asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(ai), "v"(bi));
-  else
-    asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(ai), "v"(bi));
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(ai), "v"(bi));
 }
 // After the last mfma32_acc of a loop nest, in the same block of straight-line code (volatile asm
 // statements keep their order): 48 idle cycles, the depth of the matrix pipe for this instruction
