@@ -96,11 +96,11 @@ PassSpace pass_space(int B, int H, int N, int block_r, int block_c, bool row_uni
 }
 
 // How the loops cut their work on `cus` compute units.
-FmUnits fwd_units(int B, int H, int N, int d, int cus) {
-  return fm_row_units((long long)B * H * (padded_len(N) / FM_FWD_BR), fm_fwd_per_cu(d), d, padded_len(N), cus);
+FmUnits fwd_units(int B, int H, int Hk, int N, int d, int cus) {
+  return fm_row_units((long long)B * H * (padded_len(N) / FM_FWD_BR), H / Hk, fm_fwd_per_cu(d), d, N, cus);
 }
-FmUnits dq_units(int B, int H, int N, int d, int cus) {
-  return fm_row_units((long long)B * H * (padded_len(N) / FM_DQ_BR), FM_DQ_PER_CU, d, padded_len(N), cus);
+FmUnits dq_units(int B, int H, int Hk, int N, int d, int cus) {
+  return fm_row_units((long long)B * H * (padded_len(N) / FM_DQ_BR), H / Hk, FM_DQ_PER_CU, d, N, cus);
 }
 FmUnits dkdv_units(int B, int H, int Hk, int N, int d, int cus) {
   return fm_key_units((long long)B * Hk * (padded_len(N) / FM_DKDV_BC), H / Hk, d, N, cus);
@@ -174,8 +174,8 @@ int flashmask_work_cut(int pass, int B, int H, int H_kv, int N, int d, int compu
   if (H_kv <= 0 || H % H_kv != 0) return FM_ERR_SHAPE;
   const int cus = compute_units > 0 ? compute_units : fm_compute_units();
   switch (pass) {
-    case FM_PASS_FWD: *cut = fwd_units(B, H, N, d, cus); return FM_OK;
-    case FM_PASS_BWD_DQ: *cut = dq_units(B, H, N, d, cus); return FM_OK;
+    case FM_PASS_FWD: *cut = fwd_units(B, H, H_kv, N, d, cus); return FM_OK;
+    case FM_PASS_BWD_DQ: *cut = dq_units(B, H, H_kv, N, d, cus); return FM_OK;
     case FM_PASS_BWD_DKDV: *cut = dkdv_units(B, H, H_kv, N, d, cus); return FM_OK;
     default: return FM_ERR_ARG;
   }
@@ -187,8 +187,8 @@ int flashmask_setup_launches(int pass, int B, int H, int H_kv, int N, int d, int
   if (H_kv <= 0 || H % H_kv != 0) return FM_ERR_SHAPE;
   if (pass != FM_PASS_FWD && pass != FM_PASS_BWD) return FM_ERR_ARG;
   const int cus = compute_units > 0 ? compute_units : fm_compute_units();
-  const int queued = pass == FM_PASS_FWD ? fwd_units(B, H, N, d, cus) == FM_QUEUED
-                                         : (dq_units(B, H, N, d, cus) == FM_QUEUED) + (dkdv_units(B, H, H_kv, N, d, cus) == FM_QUEUED);
+  const int queued = pass == FM_PASS_FWD ? fwd_units(B, H, H_kv, N, d, cus) == FM_QUEUED
+                                         : (dq_units(B, H, H_kv, N, d, cus) == FM_QUEUED) + (dkdv_units(B, H, H_kv, N, d, cus) == FM_QUEUED);
   *launches = queued ? fm_setup_launches(queued, B, H_kv, padded_len(N), cus) : 0;
   return FM_OK;
 }
@@ -246,7 +246,7 @@ static int fwd_impl(const void* q, const void* k, const void* v, const int32_t* 
   int* range = (int*)(ws + sp.range);
   int* order = (int*)(ws + sp.order);
   FmFwdArgs a;
-  a.units = fwd_units(B, H, N, d, fm_compute_units());
+  a.units = fwd_units(B, H, Hk, N, d, fm_compute_units());
   if (a.units == FM_QUEUED) {
     e = fm_launch_setup(lts, lte, uts, ute, B, H, Hk, N, Np, FmSetup{FM_FWD_BR, FM_FWD_BC, minmax, work, range, order, FM_PADS_MASKED},
                         false, stream);
@@ -378,7 +378,7 @@ static int bwd_impl(const void* q, const void* k, const void* v, const void* out
                      (int*)(ws + sq.order), FM_PADS_MASKED};
   const FmSetup cols{FM_DKDV_BR, FM_DKDV_BC, (int*)(ws + skv.minmax), (int*)(ws + skv.work), (int*)(ws + skv.range),
                      (int*)(ws + skv.order), FM_PADS_NONE};
-  a.units_dq = dq_units(B, H, N, d, fm_compute_units());
+  a.units_dq = dq_units(B, H, Hk, N, d, fm_compute_units());
   a.units_dkdv = dkdv_units(B, H, Hk, N, d, fm_compute_units());
   const bool queue_dq = a.units_dq == FM_QUEUED, queue_dkdv = a.units_dkdv == FM_QUEUED;
   if (queue_dq && queue_dkdv) {

@@ -128,7 +128,8 @@ inline bool fm_in_step(long long units, int d, int N, long long cus) { return un
 //            512 units, N = 8192   halved 112 / 47 / 63 / 33, queued 116 / 59 / 73 / 21; N = 16384 causal 267, queued 219
 // (all with a contiguous run of units to an XCD; in step the direct ones are faster, see fm_direct_order.h)
 // Forward units at d = 64 that all run at once, three to a compute unit, are direct up to N = 8192: direct / queued over the six masks
-// 768 units, N = 8192 0.82, N = 8115 0.92 (window 1.24), 528 units, N = 4099 0.99.  Below 512 units the halved cut stays ahead (320 units,
+// 768 units, N = 8192 0.82, N = 8115 0.92 (window 1.24), 528 units, N = 4099 0.99; ragged with grouped heads up to 5120 0.95 to 1.03
+// (six sizes, mean 0.99), beyond 1.00 to 1.10 (nine, 1.05): queued.  Below 512 units the halved cut stays ahead (320 units,
 // N = 4096, direct / halved 1.20, 384 units, N = 2048 1.07).
 // At long sequences, forward alone with its setup, direct | queued, causal, prefix, documents of 700 tokens, eight documents,
 // window 256, shared questions (geometric mean of the ratios):
@@ -146,7 +147,8 @@ inline bool fm_in_step(long long units, int d, int N, long long cus) { return un
 //            512 units, N = 8115   halved 125 124 57 74 44 71 | 120 120 54 103 26 71   (1.06)
 // Windows lose at these lengths, ragged ones most, and at d = 64 ragged documents much shorter than the sequence.  The line
 // carries no N and is one for all lengths: windows apart, the ragged mean does not cross either (0.92 and 0.96 in the last two).
-inline FmUnits fm_row_units(long long units, int per_cu, int d, int N, long long cus) {
+inline FmUnits fm_row_units(long long units, int group, int per_cu, int d, int n, long long cus) {
+  const int N = (n + 127) / 128 * 128;
   if (d == 128) {
     if (2 * units <= cus) return FM_DIRECT_HALVED;
     if (units <= cus) return FM_DIRECT_PAIRED;
@@ -154,7 +156,8 @@ inline FmUnits fm_row_units(long long units, int per_cu, int d, int N, long long
   }
   if (units <= cus) return FM_DIRECT_HALVED;
   if (units <= 2 * cus && N > 1024) return N <= 8192 ? FM_DIRECT_HALVED : FM_QUEUED;
-  return fm_in_step(units, d, N, cus) || (units <= per_cu * cus && N <= 8192) || fm_short_direct(units, d, N, cus) ? FM_DIRECT : FM_QUEUED;
+  const int at_once_to = n != N && group > 1 ? 5120 : 8192;
+  return fm_in_step(units, d, N, cus) || (units <= per_cu * cus && N <= at_once_to) || fm_short_direct(units, d, N, cus) ? FM_DIRECT : FM_QUEUED;
 }
 // The same for the dK/dV loop over units of 128 keys of `group` query heads each (a chain `group` times as long; lists
 // are built from the unit's own keys' bounds at any N).  Masks as above:
