@@ -96,57 +96,52 @@ constexpr int fm_group_waves(FmUnits u) { return u == FM_DIRECT_HALVED ? 2 : 4; 
 constexpr int fm_fwd_per_cu(int d) { return d == 64 ? 3 : 2; }
 constexpr int FM_DQ_PER_CU = 2;
 constexpr int fm_dkdv_per_cu(int d) { return d == 64 ? 2 : 1; }
-// Sequences so short that what a unit does hardly differs gain nothing from an order, and the setup launch is a good
-// part of their time.  Training step, direct / queued, causal, documents, window: d = 128, N = 512, 1024 units 178 / 183,
-// 187 / 191, 167 / 176 us, 2048 units 368 / 363, 397 / 351, 352 / 353; d = 64, N = 512, 2048 units 191 / 222, 223 / 222,
-// 182 / 221, 4096 units 398 / 435, 451 / 436, 386 / 434; N = 1024, 1024 units 159 / 160, 171 / 160, 105 / 123.
+// The lines between the cuts.  The host does not know the mask, so they are drawn by the geometric mean of times over six:
+// causal, a prefix of an eighth, causal documents of 700 tokens, eight documents both ways (two below 2048 tokens), a window of
+// 256, shared questions.  A ratio is that mean, of a cut over the queues unless it says otherwise, each with its setup; a pair is
+// forward / backward with the other loops' cuts as they are, or (in all loops) with all of them cut that way.
+// Several lines lie short of where the ratios cross: they were drawn before the blocks of all slices went in step, and the
+// sizes beyond are what the tests name to reach the queues.  What direct units measure there stands beside each.
+//
+// Sequences so short that what a unit does hardly differs gain nothing from an order, and the setup launch is a good part of
+// their time.  In all loops: d = 128, 1024 units, N = 512 0.77 / 0.90, N = 128 0.64 / 0.80;   d = 64, 2048 units, N = 512 0.67 / 0.72,
+// N = 128 0.50 / 0.59.  Beyond: d = 128, 2048 units, N = 512 0.78 / 0.93;   d = 64, 4096 units, N = 512 0.68 / 0.73.
 inline bool fm_short_direct(long long units, int d, int N, long long cus) {
   return N <= 512 && units <= (d == 64 ? 8 : 4) * cus;
 }
 // Where the blocks of all slices go in step (fm_direct_order.h), up to three units a compute unit need no order at short and
 // medium lengths either, rows and keys alike (`units` counts row blocks, so that the backward's loops cross the line together and
-// no setup launch is left for one of them).  Forward / backward with their setup, direct over queued, geometric mean over six
-// masks (causal, prefix, documents of both kinds, window, shared questions):
-//   d = 128  576 units, N = 1000  0.74 / 0.78;   640, N = 600  0.77 / 0.83, N = 1024  0.76 / 0.81, N = 2048  0.82 / 0.84;
-//            768, N = 1500  0.82 / 0.84, N = 2000  0.91 / 0.91;   750 in 150 slices, N = 600  0.92 / 1.03
-//   d = 64   (backward; the forward was direct up to 1024)  640, N = 600  0.79;   768, N = 1000  0.81;   with the forward
-//            640, N = 2048  0.76 / 0.83, N = 4000  0.81 / 0.88;   768, N = 3000  0.94 / 0.91, N = 4096  0.81 / 0.86
-//   grouped heads, 640 units of 40 on 10, N = 2048  d = 128 0.87 / 0.93, d = 64 0.80 / 0.93
-// Single masks: two documents in many short slices lose up to 6 % (150 slices of 600 tokens 30 % of the backward).
+// no setup launch is left for one of them).  In all loops:
+//   d = 128  576 units, N = 1000  0.68 / 0.76;   640, N = 1024  0.73 / 0.80, N = 2048  0.78 / 0.82;   768, N = 1500  0.79 / 0.82, N = 2000  0.87 / 0.89;
+//            odd counts of slices: 150 of 600 tokens 0.70 / 0.80, 75 of 1024 0.63 / 0.75, 51 of 1900 0.83 / 0.81, 45 of 2048 0.77 / 0.80
+//   d = 64   150 slices of 600 tokens 0.70 / 0.73, 75 of 1024 0.61 / 0.67, 17 of 4096 0.75 / 0.85, 24 of 4096 0.76 / 0.83, 32 of 3000 0.90 / 0.90
+//   grouped heads, 40 on 10, N = 2048  d = 128 0.78 / 0.93, d = 64 0.71 / 0.90;   three rows of 42 on 14  0.92 / 0.92, 0.79 / 0.92
+// Single masks: documents both ways take up to 1.12 times as long (backward, three rows of 14 K/V heads, 23 heads of 4096 at d = 64).
+// Beyond, rows alone: d = 128, N = 4096, 512 units 0.91 / 0.95, 768 0.85 / 0.97;  N = 8192, 512 units 0.94 / 0.97;  two rows of 32 on 8
+// heads, N = 4096 0.97 / 1.00.  In all loops, 1024 units: d = 128, N = 1024 0.75 / 0.90, N = 2048 0.85 / 0.90;  d = 64 0.67 / 0.74, 0.73 / 0.80.
 inline bool fm_in_step(long long units, int d, int N, long long cus) { return units <= 3 * cus && N <= (d == 128 ? 2048 : 4096); }
-// The cut of a row-parallel loop over `units` units of 128 rows, `per_cu` workgroups of which one of `cus` compute units
-// holds, at sequence length N.  What is weighed: the setup launch (4 us up to N = 4096, 8 us beyond), the longest chain of tiles
-// (halved by two groups), waves per SIMD, and building the list from the bound vectors instead of the table (which
-// grows with N).  Loop times in us, masks causal / causal documents of 700 tokens / both-sided ones / window 256:
-//   d = 128  128 units, N = 2048   halved 30 / 37 / 40 / 14, queued 41 / 56 / 59 / 17; N = 16384 causal 190, queued 261
-//            256 units, N = 512    paired 20 / 22 / 23 / 20, queued 19 / 23 / 23 / 19, halved 26 / 31 / 31 / 25
-//            256 units, N = 8192   paired 125 / 53 / 63 / 22, queued 141 / 64 / 77 / 20, halved 152 / 62 / 74 / 32
-//            512 units, N = 1024   direct 38 / 45 / 49 / 26, queued 38 / 40 / 48 / 26, paired 48 / 56 / 58 / 37
-//            512 units, N = 4096   direct 111 / 87 / 99 / 29, queued 92 / 74 / 91 / 27 (heaviest units first)
-//   d = 64   256 units, N = 4096   halved 39 / 37 / 41 / 15, queued 54 / 60 / 67 / 16
-//            512 units, N = 512    direct 21 / 24 / 25 / 20, halved 24 / 29 / 30 / 24, queued 21 / 23 / 25 / 21
-//            512 units, N = 8192   halved 112 / 47 / 63 / 33, queued 116 / 59 / 73 / 21; N = 16384 causal 267, queued 219
-// (all with a contiguous run of units to an XCD; in step the direct ones are faster, see fm_direct_order.h)
-// Forward units at d = 64 that all run at once, three to a compute unit, are direct up to N = 8192: direct / queued over the six masks
-// 768 units, N = 8192 0.82, N = 8115 0.92 (window 1.24), 528 units, N = 4099 0.99; ragged with grouped heads up to 5120 0.95 to 1.03
-// (six sizes, mean 0.99), beyond 1.00 to 1.10 (nine, 1.05): queued.  Below 512 units the halved cut stays ahead (320 units,
-// N = 4096, direct / halved 1.20, 384 units, N = 2048 1.07).
-// At long sequences, forward alone with its setup, direct | queued, causal, prefix, documents of 700 tokens, eight documents,
-// window 256, shared questions (geometric mean of the ratios):
-//   d = 128  256 units, N = 16384  paired 246 245 60 162 23 118 | 276 278 79 225 28 161   (0.80)
-//            256 units, N = 32768  paired 495 497 78 314 30 200 | 537 541 97 433 30 270   (0.85)
-//   d = 64   256 units, N = 16384  halved 169 167 43 115 21 84 | 197 195 72 196 24 159   (0.70)
-//            256 units, N = 32768  halved 344 345 64 218 33 143 | 376 376 100 380 26 246   (0.79)
-//            512 units, N = 8192   halved 108 109 44 64 30 77 | 118 120 65 110 27 117   (0.78)
-// The same at ragged lengths, whose direct lists load bounds 4 bytes at a time and whose queued units have no tile for the
-// columns past the end:
-//   d = 128  256 units, N = 16307  paired 252 248 63 162 28 115 | 279 277 73 206 26 145   (0.88)
-//            256 units, N = 32691  paired 501 501 85 315 42 224 | 542 542 86 399 27 274   (0.97)
-//   d = 64   256 units, N = 16307  halved 179 177 59 126 38 100 | 211 211 63 172 22 121   (0.94)
-//            256 units, N = 32691  halved 371 370 93 243 65 193 | 407 407 73 329 24 226   (1.10)
-//            512 units, N = 8115   halved 125 124 57 74 44 71 | 120 120 54 103 26 71   (1.06)
-// Windows lose at these lengths, ragged ones most, and at d = 64 ragged documents much shorter than the sequence.  The line
-// carries no N and is one for all lengths: windows apart, the ragged mean does not cross either (0.92 and 0.96 in the last two).
+// The cut of a row-parallel loop over `units` units of 128 rows in groups of `group` query heads to a K/V head, `per_cu` of
+// which one of `cus` compute units holds, at sequence length n.  What is weighed: the setup launch (4 us up to N = 4096, 8 us
+// beyond), the longest chain of tiles (halved by two groups), waves per SIMD, and building the list from the bound vectors instead
+// of the table (which grows with N; ragged lengths load the bounds 4 bytes at a time).  Halved, paired, direct (rows alone):
+//   d = 128  128 units, N = 2048   0.60 / 0.74, 0.72 / 0.85, 0.81 / 0.91;   N = 16384  0.69 / 0.78, 0.79 / 0.87, 0.99 / 1.00
+//            144 units, N = 2048   0.73 / 0.86, 0.72 / 0.86, 0.81 / 0.91
+//            256 units, N = 512    0.78 / 0.91, 0.69 / 0.86, 0.67 / 0.83;   N = 2048   0.83 / 0.92, 0.74 / 0.88, 0.82 / 0.92
+//                       N = 8192   0.85 / 0.91, 0.76 / 0.88, 0.91 / 0.96;   N = 32768  1.01 / 1.05, 0.85 / 0.97, 1.08 / 1.09
+//                       N = 16307  1.06 / 1.01, 0.89 / 0.93, 1.03 / 1.02;   N = 32691  1.20 / 1.09, 0.96 / 0.98, 1.14 / 1.08
+//            320 units, N = 2048          -   0.68 / 0.84, 0.69 / 0.84;   512 units, N = 1024   -   0.88 / 0.96, 0.71 / 0.87
+//   d = 64, halved, direct
+//            256 units, N = 2048   0.62 / 0.77, 0.81 / 0.88;   N = 8192   0.66 / 0.79, 0.92 / 0.95;   N = 32768  0.81 / 0.90, 1.12 / 1.09
+//                       N = 16307  0.94 / 0.97, 1.06 / 1.05;   N = 32691  1.09 / 1.11, 1.18 / 1.15
+//            512 units, N = 512    0.73 / 0.86, 0.60 / 0.75;   N = 1024   0.72 / 0.84, 0.66 / 0.80;   N = 2048   0.74 / 0.87, 0.71 / 0.85
+//            (320:                                                                                               0.60 / 0.75, 0.68 / 0.81)
+//                       N = 4096   0.90 / 0.93, 0.91 / 0.92;   N = 8192   0.94 / 0.94, 0.94 / 0.95;   N = 16384  1.03 / 0.99, 1.02 / 0.99
+//                       N = 8115   1.20 / 1.08, 1.05 / 1.01;   N = 16307  1.36 / 1.18, 1.19 / 1.10
+// Windows lose most (forward, 32691 tokens: paired at d = 128 42 us for 27, halved at d = 64 64 for 22).  The lines carry no raggedness: at d = 64 ragged
+// lengths of 8115 tokens (512 units) and 32691 (256 units) are halved where the queues are faster.
+// Forward units at d = 64 that all run at once, three to a compute unit, direct over queued: full blocks up to 8192, 513 to 768 units,
+// 0.79 to 0.96, grouped heads 0.92 to 1.00;  ragged up to 5120 0.83 to 1.03 (five sizes, mean 0.93), beyond 0.89 to 1.07 (ten, 0.99;
+// windows 1.15 to 1.4);  ragged with grouped heads up to 5120 0.95 to 1.03 (six, 0.99), beyond 1.00 to 1.10 (nine, 1.05): queued.
 inline FmUnits fm_row_units(long long units, int group, int per_cu, int d, int n, long long cus) {
   const int N = (n + 127) / 128 * 128;
   if (d == 128) {
@@ -160,41 +155,24 @@ inline FmUnits fm_row_units(long long units, int group, int per_cu, int d, int n
   return fm_in_step(units, d, N, cus) || (units <= per_cu * cus && N <= at_once_to) || fm_short_direct(units, d, N, cus) ? FM_DIRECT : FM_QUEUED;
 }
 // The same for the dK/dV loop over units of 128 keys of `group` query heads each (a chain `group` times as long; lists
-// are built from the unit's own keys' bounds at any N).  Masks as above:
-//   d = 128  128 units, N = 2048   halved 34 / 33 / 46 / 17, queued 49 / 46 / 67 / 20
-//            256 units, N = 1024   direct 34 / 32 / 46 / 24, halved 39 / 38 / 52 / 30, queued 34 / 33 / 44 / 24
-//            256 units, N = 4096   direct 96 / 58 / 90 / 25, halved 77 / 49 / 93 / 31, queued 95 / 58 / 90 / 24
-//            512 units, N = 8192   direct 249 / 78 / 112 / 47, queued 280 / 93 / 129 / 53, halved 273 / 76 / 114 / 59;
-//                                  N = 16384 backward, over six masks, direct / queued 0.95, ragged 0.94 (causal 0.90, documents 1.05)
-//            256 units of 4 query heads, N = 2048, shared questions: halved 126, direct 163, queued 164
-//   d = 64   512 units, N = 1024   direct 36 / 35 / 48 / 24, halved 36 / 35 / 50 / 28
-//            512 units, N = 4096   halved 85 / 48 / 83 / 28, direct 108 / 63 / 99 / 25, queued 87 / 50 / 86 / 26
-// Halved units of a full round copy each row tile twice as often and run in two rounds.  That pays while the longest
-// chain decides and stops paying where the sum of the work does, which for causal and prefix masks is at long sequences.
-// The host does not know the mask; the line lies where the geometric mean over six masks crosses.  Backward in us,
-// halved / queued, causal, prefix, documents of 700 tokens, eight documents, window 256, shared questions (mean ratio):
-//   d = 128  240 units, N = 10240  402 / 400, 437 / 399, 136 / 166, 225 / 240, 54 / 58, 320 / 319   (0.96)
-//            256 units, N = 16384  680 / 647, 731 / 651, 128 / 157, 362 / 363, 58 / 61, 336 / 330   (0.99)
-//            192 units, N = 24576  955 / 876, 1013 / 886, 126 / 156, 557 / 530, 58 / 58, 462 / 434   (1.02)
-//            256 units, N = 32768  1439 / 1292, 1527 / 1296, 158 / 192, 757 / 691, 64 / 68, 633 / 571   (1.04)
-//            of 2, 4, 8 query heads: N = 8192 0.95, 0.93, 0.92, N = 16384 1.02, 1.00, 0.99, N = 24576 1.06, 1.03, 1.02
-//   d = 64   512 units, N = 16384  566 / 546, 605 / 552, 119 / 141, 326 / 332, 57 / 55, 275 / 290   (0.99)
-//            480 units, N = 20480  735 / 657, 784 / 664, 114 / 119, 427 / 411, 58 / 54, 371 / 347   (1.07)
-//            of 2, 4, 8 query heads: N = 16384 0.97, 0.96, 0.96, N = 20480 1.06, 1.06, 1.05
-// Ragged lengths, the same masks, halved / queued:
-//   d = 128  256 units, N = 16300  742 / 705, 753 / 704, 130 / 149, 368 / 372, 62 / 68, 342 / 343   (0.98)
-//            192 units, N = 24500  1041 / 927, 1093 / 947, 128 / 149, 566 / 540, 67 / 68, 532 / 492   (1.04)
-//            256 units, N = 32691  1555 / 1404, 1603 / 1429, 159 / 187, 770 / 708, 77 / 82, 748 / 678   (1.03)
-//            of 4 query heads 24500  3742 / 3239, 3980 / 3280, 324 / 391, 1789 / 1661, 144 / 129, 1775 / 1602   (1.08)
-//            of 8 query heads 32691  10630 / 9774, 11263 / 9883, 655 / 834, 4641 / 4096, 283 / 267, 4994 / 4443   (1.05)
-//   d = 64   512 units, N = 16307  589 / 567, 587 / 572, 108 / 124, 307 / 327, 54 / 53, 265 / 299   (0.96)
-//            480 units, N = 20400  775 / 702, 770 / 707, 104 / 104, 410 / 403, 56 / 53, 360 / 364   (1.04)
-//            512 units, N = 32691  1346 / 1139, 1368 / 1147, 123 / 146, 582 / 543, 59 / 57, 633 / 583   (1.06)
-//            512 units, N = 65459  2839 / 2208, 2960 / 2242, 160 / 169, 1525 / 1232, 61 / 56, 1449 / 1110   (1.19)
-//            of 4 query heads 32691  4896 / 4204, 5080 / 4235, 278 / 374, 1854 / 1672, 146 / 148, 2032 / 1813   (1.04)
-// At d = 64 the line of the other lengths: causal and prefix masks gain 8 to 24 %, eight documents 2 to 19 %, documents of 700
-// tokens lose up to 19 %, with four query heads 34 %.  At d = 128 halved at any length, where the mean has crossed by 3 to 8 % beyond
-// 16384 and documents of 700 tokens are 15 to 27 % faster for it.
+// are built from the unit's own keys' bounds at any N).  Backward, keys alone, halved, direct; of 1, 2, 4 and 8 query heads:
+//   d = 128  128 units, N = 2048   0.75, 0.89   -   0.73, 0.96   -;                  N = 16384  0.75, 0.93
+//            256 units, N = 512    0.92, 0.84   0.96, 0.88   0.96, 0.94   1.00, 1.00;   N = 1024   0.91, 0.87   0.91, 0.91   0.96, 1.00   0.95, 1.00
+//                       N = 2048   0.90, 0.90   0.90, 0.94   0.93, 1.00   0.92, 1.00;   N = 8192   0.87, 0.92   0.90, 1.00   0.86, 0.99   0.86, 0.99
+//                       N = 16384  0.87, 0.93   0.88, 0.99   0.86, 0.99   0.86, 0.99;   N = 24576  0.83, 0.95   0.84, 1.00   0.79, 1.00   0.78, 1.00
+//                       N = 24500  0.84, 0.96   0.84, 1.00   0.80, 1.00   0.80, 1.00;   N = 32768  0.87, 0.95;   N = 32691  0.89, 0.96
+//            512 units, N = 1024   0.94, 0.81;   N = 2048   0.88, 0.81;   N = 4096   0.99, 0.94
+//                       N = 8192   0.96, 0.93   0.94, 0.94   0.93, 0.94   0.93, 0.95;   N = 16384  0.95, 0.94   0.93, 0.94   0.91, 0.94   0.90, 0.94
+//                       N = 16290  0.96, 0.93   0.96, 0.93   0.94, 0.93   0.92, 0.92;   N = 32768  0.94, 0.94
+//            384 units, N = 16384  0.97, 0.98   0.94, 0.98   0.91, 0.97   0.90, 0.97;   400 units, N = 10240  0.97, 0.94   0.96, 0.95   0.94, 0.95   0.92, 0.93
+//   d = 64   256 units, N = 2048   0.78, 0.86
+//            512 units, N = 1024   0.84, 0.80   -   0.91, 0.92;   N = 2048   0.83, 0.83   -   0.87, 0.91;   N = 4096   0.91, 0.92
+//                       N = 8192   0.89, 0.94   -   0.92, 1.00;   N = 16384  0.94, 1.00   -   0.89, 1.00;   N = 32768  0.92, 0.99
+//                       N = 16307  0.94, 1.01;   N = 32691  0.92, 0.99   -   0.88, 1.00;   480 units, N = 20480  0.96, 1.02   -   0.92, 1.03
+// Halved units of a full round copy each row tile twice as often and run in two rounds: that pays while the longest chain
+// decides.  Beyond 16384 tokens full rounds are queued all the same (ragged ones at d = 128 halved).  Two rounds of keys up to 16384
+// tokens, single masks: causal 0.82 to 0.93, windows 0.87 to 0.99; eight documents both ways, ten draws, 0.94 to 1.12, one of
+// them at 3 K/V heads of 16384 tokens 1.25 (8 query heads 1.40).
 inline FmUnits fm_key_units(long long units, int group, int d, int N, long long cus) {
   const long long slots = fm_dkdv_per_cu(d) * cus;
   const int padded = (N + 127) / 128 * 128;
