@@ -378,8 +378,9 @@ static int bwd_impl(const void* q, const void* k, const void* v, const void* out
                      (int*)(ws + sq.order), FM_PADS_MASKED};
   const FmSetup cols{FM_DKDV_BR, FM_DKDV_BC, (int*)(ws + skv.minmax), (int*)(ws + skv.work), (int*)(ws + skv.range),
                      (int*)(ws + skv.order), FM_PADS_NONE};
-  a.units_dq = dq_units(B, H, Hk, N, d, fm_compute_units());
-  a.units_dkdv = dkdv_units(B, H, Hk, N, d, fm_compute_units());
+  const int cus = fm_compute_units();
+  a.units_dq = dq_units(B, H, Hk, N, d, cus);
+  a.units_dkdv = dkdv_units(B, H, Hk, N, d, cus);
   const bool queue_dq = a.units_dq == FM_QUEUED, queue_dkdv = a.units_dkdv == FM_QUEUED;
   if (queue_dq && queue_dkdv) {
     e = fm_launch_bwd_setup(lts, lte, uts, ute, B, H, Hk, N, Np, rows, cols, stream);

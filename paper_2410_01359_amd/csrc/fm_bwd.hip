@@ -1189,9 +1189,9 @@ static hipError_t launch_dq_s(const FmBwdArgs& a, hipStream_t stream) {
   using L = DqLaunch<D, RAGGED, GEN, U>;
   using C = typename L::C;
   FmBwdArgs args = a;
-  args.queue_dq = fm_queue_for_launch(a.queue_dq, FM_DQ_PER_CU);
   const int blocks = (a.N + C::BR - 1) / C::BR;
-  if (U != FM_QUEUED) args.order = fm_direct_order(a.B * a.Hk, a.H / a.Hk, blocks, a.B * a.H * blocks <= fm_compute_units());
+  if (U == FM_QUEUED) args.queue_dq = fm_queue_for_launch(a.queue_dq, FM_DQ_PER_CU);
+  else args.order = fm_direct_order(a.B * a.Hk, a.H / a.Hk, blocks, a.B * a.H * blocks <= fm_compute_units());
   const int grid = U == FM_QUEUED ? fm_launch_grid(args.queue_dq) : fm_direct_grid(args.order);
   hipLaunchKernelGGL(L::kernel(), dim3(grid), dim3(C::THREADS), C::LDS_BYTES, stream, args);
   return hipGetLastError();
@@ -1243,9 +1243,9 @@ static hipError_t launch_dkdv_s(const FmBwdArgs& a, hipStream_t stream) {
   using L = DkdvLaunch<D, RAGGED, GEN, U>;
   using C = typename L::C;
   FmBwdArgs args = a;
-  args.queue_dkdv = fm_queue_for_launch(a.queue_dkdv, C::PER_CU);
   const int blocks = (a.N + C::BC - 1) / C::BC;
-  if (U != FM_QUEUED) args.order = fm_direct_order(a.B * a.Hk, 1, blocks, a.B * a.Hk * blocks <= fm_compute_units());
+  if (U == FM_QUEUED) args.queue_dkdv = fm_queue_for_launch(a.queue_dkdv, C::PER_CU);
+  else args.order = fm_direct_order(a.B * a.Hk, 1, blocks, a.B * a.Hk * blocks <= fm_compute_units());
   const int grid = U != FM_QUEUED   ? fm_direct_grid(args.order)
                    : C::PERSISTENT ? fm_persistent_grid(args.queue_dkdv)
                                    : fm_launch_grid(args.queue_dkdv);

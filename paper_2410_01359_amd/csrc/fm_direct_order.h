@@ -44,7 +44,8 @@ struct FmDivisor {
   int shift;
 };
 FM_HOST_DEVICE inline FmDivisor fm_divisor(int n) {
-  const int shift = n > 1 ? 63 - __builtin_clz(n - 1) : 31;   // 31 and the logarithm of n, rounded up
+  if (n == 1) return FmDivisor{1, (1u << 31) + 1, 31};
+  const int shift = 63 - __builtin_clz(n - 1);   // 31 and the logarithm of n, rounded up
   return FmDivisor{(unsigned)n, (unsigned)((1ull << shift) / (unsigned)n + 1), shift};
 }
 FM_HOST_DEVICE inline int fm_div(int x, const FmDivisor& d) { return (int)((unsigned long long)(unsigned)x * d.factor >> d.shift); }

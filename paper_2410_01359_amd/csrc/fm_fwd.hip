@@ -610,9 +610,9 @@ static hipError_t launch_fwd_s(const FmFwdArgs& a, hipStream_t stream) {
   using L = FwdLaunch<D, RAGGED, GEN, U>;
   using C = typename L::C;
   FmFwdArgs args = a;
-  args.queue = fm_queue_for_launch(a.queue, FwdCfg<D>::PER_CU);
   const int blocks = (a.N + C::BR - 1) / C::BR;
-  if (U != FM_QUEUED) args.order = fm_direct_order(a.B * a.Hk, a.H / a.Hk, blocks, a.B * a.H * blocks <= fm_compute_units());
+  if (U == FM_QUEUED) args.queue = fm_queue_for_launch(a.queue, FwdCfg<D>::PER_CU);
+  else args.order = fm_direct_order(a.B * a.Hk, a.H / a.Hk, blocks, a.B * a.H * blocks <= fm_compute_units());
   const int grid = U == FM_QUEUED ? fm_launch_grid(args.queue) : fm_direct_grid(args.order);
   hipLaunchKernelGGL(L::kernel(), dim3(grid), dim3(C::THREADS), C::LDS_BYTES, stream, args);
   return hipGetLastError();
