@@ -499,7 +499,7 @@ __device__ __forceinline__ int entry_mask_mode(int entry) {
 // results meet in LDS at the end, which halves the longest chain of tiles.
 //
 // The order of the units is fm_direct_order.h's; row blocks count from the last there, key blocks from the first.
-//
+
 // The arguments that a direct unit's first requests depend on, read together: left where the compiler puts them, behind what
 // tells whether they are needed, they are two or three round trips in a row.  Forward / backward, together over two in a row:
 // 2 slices of 512 tokens, d = 64 0.98 / 0.98, 8 of 333 0.98 / 0.98, 8 of 1920 0.99 / 0.99.
@@ -509,6 +509,7 @@ __device__ __forceinline__ void args_at_once(const FmDirectOrder& o, const T* ro
   asm volatile("" ::"s"(o.deal), "s"(o.step.factor), "s"(o.group.factor), "s"(rows), "s"(lts), "s"(lte), "s"(uts), "s"(ute), "s"(n),
                "s"(np), "s"(h));
 }
+
 // build_live_key_blocks for key blocks of 64 columns straight from the bound vectors (vec: a batch row's LTS, LTE,
 // UTS, UTE; n columns).  Sixteen lanes take a block, four columns each, so a pass of four waves covers 1024
 // columns; where the columns go beyond that, two passes have their loads in flight together (forward over a window of
