@@ -506,8 +506,8 @@ __device__ __forceinline__ int entry_mask_mode(int entry) {
 template <class T>
 __device__ __forceinline__ void args_at_once(const FmDirectOrder& o, const T* rows, const int* lts, const int* lte, const int* uts,
                                              const int* ute, int n, int np, int h) {
-  asm volatile("" ::"s"(o.deal), "s"(o.step.factor), "s"(o.group.factor), "s"(rows), "s"(lts), "s"(lte), "s"(uts), "s"(ute), "s"(n),
-               "s"(np), "s"(h));
+  asm volatile("" ::"s"(o.deal), "s"(o.odd.shift), "s"(o.step.n), "s"(o.step.factor), "s"(o.step.shift), "s"(o.group.factor),
+               "s"(o.all.factor), "s"(o.all.shift), "s"(rows), "s"(lts), "s"(lte), "s"(uts), "s"(ute), "s"(n), "s"(np), "s"(h));
 }
 
 // build_live_key_blocks for key blocks of 64 columns straight from the bound vectors (vec: a batch row's LTS, LTE,

@@ -14,7 +14,8 @@
 //    have much of their tiles in common, a window's nearly all.  With an odd number of turns each slice begins one XCD further
 //    on than the one before.  The blocks after the last whole turn go round one by one, slice after slice.
 //  - Whole, for shorter slices, of which XCDs would be left without a block or every XCD would fetch every one: each XCD has
-//    as many of them to itself as there are for all, and the fewer than 8 / m others go round one by one, ahead of those.
+//    as many of them to itself as there are for all, and the blocks of the fewer than 8 / m others go round one by one, spread
+//    evenly among those, so that the longest of both come first.
 //  - Runs, where each compute unit has one unit at most, so that no order matters, and turns would bring several slices to
 //    every XCD of a class: each has a contiguous run of units.
 // Forward / backward in us, causal (3 slices: window 256), all slices in turns that begin at the same XCD -> now:
@@ -25,6 +26,8 @@
 // Against turns, runs take 1 % longer where a class has a single slice (1 of 8192 tokens, 4 of 1000), and with two units to
 // a compute unit 1.2 times as long (12 of 2048, d = 64).  With short slices in turns, too, 85 of 384 tokens took 1.16 /
 // 1.08 and 75 of 1024 1.10 / 1.05 times as long (d = 128); with those of 16 and more blocks whole, 20 of 4000 (d = 64) 1.06 / 1.03.
+// With the blocks of the others ahead of the whole slices instead of among them, three rows of 10 heads on 5 took 1.04 / 1.03 (1792
+// tokens, d = 128) and 1.08 / 1.05 (967, d = 64), 75 of 1024 0.96 / 0.97 times as long; behind them 1.1 to 1.2 throughout.
 //
 // Before turns, an XCD had one contiguous run of units, slice after slice: of few heads one XCD had all the long units of a causal mask
 // and another all the short ones; in several rounds, units started in the order of the slices; and where two workgroups share a
@@ -57,11 +60,11 @@ struct FmDirectOrder {
   FmDirectDeal deal;
   int own, blocks;               // slices of a class, blocks of a slice
   int classes, sharing, chunk;   // m, XCDs of a class, blocks taken together: powers of two, as their logarithms
-  int share;                     // workgroups of an XCD; of them, [odd_from, odd_to) take units one by one:
-  int odd_from, odd_to;          // of the slices from odd_slice on, the blocks from odd_block on
-  int odd_slice, odd_block;
+  int share, odd_units;          // workgroups of an XCD; of them, those that take units one by one: of the slices
+  int odd_slice, odd_block;      // from odd_slice on, the blocks from odd_block on
   int turned;                    // (turns) whether a slice begins one XCD further on than the one before
   FmDivisor odd, step, group;    // slices of these units (runs: units of a slice); slices in step otherwise; query heads of a slice
+  FmDivisor all;                 // share
 };
 // at_once: no more units than compute units.
 FM_HOST_DEVICE inline FmDirectOrder fm_direct_order(int slices, int group, int blocks, bool at_once) {
@@ -72,7 +75,7 @@ FM_HOST_DEVICE inline FmDirectOrder fm_direct_order(int slices, int group, int b
   for (o.sharing = kLogXcds; o.classes < kLogXcds && o.own % 2 == 0; o.own /= 2, --o.sharing) ++o.classes;
   const int last = (1 << o.sharing) - 1;
   int odd = o.own, step = o.own;
-  o.share = o.odd_to = (o.own * group * blocks + last) >> o.sharing;
+  o.share = (o.own * group * blocks + last) >> o.sharing;
   if (at_once && o.sharing && o.own > 1) {
     o.deal = FM_DEAL_RUNS;
     odd = group * blocks;
@@ -80,7 +83,7 @@ FM_HOST_DEVICE inline FmDirectOrder fm_direct_order(int slices, int group, int b
     o.deal = FM_DEAL_WHOLE;
     odd = o.own & last;
     step = o.own >> o.sharing;
-    o.odd_to -= step * group * blocks;
+    o.odd_units = o.share - step * group * blocks;
     o.odd_slice = o.own - odd;
   } else {
     o.deal = FM_DEAL_TURNS;
@@ -88,11 +91,12 @@ FM_HOST_DEVICE inline FmDirectOrder fm_direct_order(int slices, int group, int b
     const int turns = blocks >> (o.sharing + o.chunk);
     o.turned = turns & 1;
     o.odd_block = turns << (o.sharing + o.chunk);
-    o.odd_from = o.own * group * (turns << o.chunk);
+    o.odd_units = o.share - o.own * group * (turns << o.chunk);
   }
   o.odd = fm_divisor(odd ? odd : 1);
   o.step = fm_divisor(step ? step : 1);
   o.group = fm_divisor(group);
+  o.all = fm_divisor(o.share);
   return o;
 }
 // Workgroups of the launch.
@@ -106,27 +110,32 @@ FM_HOST_DEVICE inline FmDirectUnit fm_direct_unit(const FmDirectOrder& o, int x)
   const int xcd = x & 7, p = xcd >> o.classes, at = x >> 3;   // at: which of the XCD's workgroups
   const int first = (xcd & ((1 << o.classes) - 1)) * o.own, group = GROUPED ? (int)o.group.n : 1;
   int slice, i;   // slice of the class; block * group + member
-  if (at >= o.odd_from && at < o.odd_to) {
-    if (o.deal == FM_DEAL_RUNS) {
-      const int unit = p * o.share + at;
-      slice = fm_div(unit, o.odd);
-      i = slice < o.own ? unit - slice * (int)o.odd.n : group * o.blocks;
-    } else {   // a unit to each XCD in turn: every slice's next block, then the block after it
-      const int k = ((at - o.odd_from) << o.sharing) + p;
+  if (o.deal == FM_DEAL_RUNS) {
+    const int unit = p * o.share + at;
+    slice = fm_div(unit, o.odd);
+    i = slice < o.own ? unit - slice * (int)o.odd.n : group * o.blocks;
+  } else {
+    // which of the units one by one, or of the others: those come last (turns), or evenly among them (short slices, so that
+    // at * odd_units stays below 2^31)
+    const bool turns = o.deal == FM_DEAL_TURNS;
+    const int odd_before = turns ? at - (o.share - o.odd_units) : fm_div(at * o.odd_units, o.all);
+    const bool odd = turns ? odd_before >= 0 : fm_div((at + 1) * o.odd_units, o.all) != odd_before;
+    if (odd) {   // a unit to each XCD in turn: every slice's next block, then the block after it
+      const int k = (odd_before << o.sharing) + p;
       i = fm_div(k, o.odd);
       slice = o.odd_slice + k - i * (int)o.odd.n;
       i += o.odd_block * group;
+    } else if (!turns) {
+      i = fm_div(at - odd_before, o.step);
+      slice = at - odd_before + (p - i) * (int)o.step.n;
+    } else {
+      i = fm_div(at, o.step);
+      slice = at - i * o.own;
+      const int last = (1 << o.sharing) - 1, j = GROUPED ? fm_div(i, o.group) : i;
+      const int turn = j >> o.chunk, mine = (p + (o.turned ? slice : 0)) & last;
+      const int block = (((turn << o.sharing) + (turn & 1 ? last - mine : mine)) << o.chunk) + (j & ((1 << o.chunk) - 1));
+      return FmDirectUnit{first + slice, i - j * group, block};
     }
-  } else if (o.deal == FM_DEAL_WHOLE) {
-    i = fm_div(at - o.odd_to, o.step);
-    slice = at - o.odd_to + (p - i) * (int)o.step.n;
-  } else {
-    i = fm_div(at, o.step);
-    slice = at - i * o.own;
-    const int last = (1 << o.sharing) - 1, j = GROUPED ? fm_div(i, o.group) : i;
-    const int turn = j >> o.chunk, mine = (p + (o.turned ? slice : 0)) & last;
-    const int block = (((turn << o.sharing) + (turn & 1 ? last - mine : mine)) << o.chunk) + (j & ((1 << o.chunk) - 1));
-    return FmDirectUnit{first + slice, i - j * group, block};
   }
   const int block = GROUPED ? fm_div(i, o.group) : i;
   return FmDirectUnit{first + slice, i - block * group, block < o.blocks ? block : -1};
