@@ -42,7 +42,7 @@ struct DqCfg {
 
 // RAGGED: see the forward kernel -- loops at the padded length, clamped tile copies, guarded stores.
 template <int D, bool RAGGED, bool GEN, int S, int WR, bool DIRECT>
-__device__ __forceinline__ void dq_body(const FmBwdArgs& a) {
+__device__ __forceinline__ void dq_body(const FmBwdKernelArgs<GEN>& a) {
   using C = DqCfg<D, S, WR, DIRECT>;
   constexpr int NTC = WR == 4 ? 1 : S;    // tiles per step that a wave takes part in copying (see the forward)
   constexpr int KT = C::KT, NKB = KT / 32, NDB = D / 16, NKK = D / 32;
@@ -820,7 +820,7 @@ __device__ __forceinline__ void dkdv_tile(unsigned qs, const DkdvAhead<S>& ah,
 // walks the query heads that share it one after the other (same list of live row blocks: the
 // mask does not depend on the head), accumulating dK and dV over all of them.
 template <int D, bool RAGGED, bool GEN, int S, bool DIRECT>
-__device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
+__device__ __forceinline__ void dkdv_body(const FmBwdKernelArgs<GEN>& a) {
   using C = DkdvCfg<D, S>;
   constexpr int QT = C::QT, NDB = D / 32, NKK = D / 16;
   static_assert(QT == 64, "the tile loop is written for two 32-row blocks per tile");
@@ -1139,32 +1139,32 @@ __device__ __forceinline__ void dkdv_body(const FmBwdArgs& a) {
 }
 
 template <int D, bool RAGGED, bool GEN>
-__global__ __launch_bounds__(256, FM_DQ_PER_CU) void dq_kernel(FmBwdArgs a) {
+__global__ __launch_bounds__(256, FM_DQ_PER_CU) void dq_kernel(FmBwdKernelArgs<GEN> a) {
   dq_body<D, RAGGED, GEN, 1, 4, false>(a);
 }
 template <int D, bool RAGGED, bool GEN>
-__global__ __launch_bounds__(256, fm_dkdv_per_cu(D)) void dkdv_kernel(FmBwdArgs a) {
+__global__ __launch_bounds__(256, fm_dkdv_per_cu(D)) void dkdv_kernel(FmBwdKernelArgs<GEN> a) {
   dkdv_body<D, RAGGED, GEN, 1, false>(a);
 }
 // Direct units.  LDS for two tiles per step leaves one workgroup per compute unit at d = 128, two at d = 64.
 template <int D, bool RAGGED, bool GEN>
-__global__ __launch_bounds__(256, FM_DQ_PER_CU) void single_dq_kernel(FmBwdArgs a) {
+__global__ __launch_bounds__(256, FM_DQ_PER_CU) void single_dq_kernel(FmBwdKernelArgs<GEN> a) {
   dq_body<D, RAGGED, GEN, 1, 4, true>(a);
 }
 template <int D, bool RAGGED, bool GEN>
-__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void direct_dq_kernel(FmBwdArgs a) {
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void direct_dq_kernel(FmBwdKernelArgs<GEN> a) {
   dq_body<D, RAGGED, GEN, 2, 2, true>(a);
 }
 template <int D, bool RAGGED, bool GEN>
-__global__ __launch_bounds__(512, 1) void wide_dq_kernel(FmBwdArgs a) {
+__global__ __launch_bounds__(512, 1) void wide_dq_kernel(FmBwdKernelArgs<GEN> a) {
   dq_body<D, RAGGED, GEN, 2, 4, true>(a);
 }
 template <int D, bool RAGGED, bool GEN>
-__global__ __launch_bounds__(256, fm_dkdv_per_cu(D)) void single_dkdv_kernel(FmBwdArgs a) {
+__global__ __launch_bounds__(256, fm_dkdv_per_cu(D)) void single_dkdv_kernel(FmBwdKernelArgs<GEN> a) {
   dkdv_body<D, RAGGED, GEN, 1, true>(a);
 }
 template <int D, bool RAGGED, bool GEN>
-__global__ __launch_bounds__(256, fm_dkdv_per_cu(D)) void direct_dkdv_kernel(FmBwdArgs a) {
+__global__ __launch_bounds__(256, fm_dkdv_per_cu(D)) void direct_dkdv_kernel(FmBwdKernelArgs<GEN> a) {
   dkdv_body<D, RAGGED, GEN, 2, true>(a);
 }
 
@@ -1188,7 +1188,7 @@ template <int D, bool RAGGED, bool GEN, FmUnits U>
 static hipError_t launch_dq_s(const FmBwdArgs& a, hipStream_t stream) {
   using L = DqLaunch<D, RAGGED, GEN, U>;
   using C = typename L::C;
-  FmBwdArgs args = a;
+  auto args = fm_kernel_args<GEN>(a);
   const int blocks = (a.N + C::BR - 1) / C::BR;
   if (U == FM_QUEUED) args.queue_dq = fm_queue_for_launch(a.queue_dq, FM_DQ_PER_CU);
   else args.order = fm_direct_order(a.B * a.Hk, a.H / a.Hk, blocks, a.B * a.H * blocks <= fm_compute_units());
@@ -1242,7 +1242,7 @@ template <int D, bool RAGGED, bool GEN, FmUnits U>
 static hipError_t launch_dkdv_s(const FmBwdArgs& a, hipStream_t stream) {
   using L = DkdvLaunch<D, RAGGED, GEN, U>;
   using C = typename L::C;
-  FmBwdArgs args = a;
+  auto args = fm_kernel_args<GEN>(a);
   const int blocks = (a.N + C::BC - 1) / C::BC;
   if (U == FM_QUEUED) args.queue_dkdv = fm_queue_for_launch(a.queue_dkdv, C::PER_CU);
   else args.order = fm_direct_order(a.B * a.Hk, 1, blocks, a.B * a.Hk * blocks <= fm_compute_units());

@@ -289,7 +289,7 @@ __device__ __forceinline__ void fwd_step(f32x16 (&cur)[2], f32x16 (&nxt)[2], f32
 // GEN: tensors with caller-given strides and fewer K/V heads than query heads (see FmFwdArgs).
 // DIRECT: direct units (see fm_common.h), else queued ones.
 template <int D, bool RAGGED, bool GEN, int S, int WR, bool DIRECT>
-__device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
+__device__ __forceinline__ void fwd_body(const FmFwdKernelArgs<GEN>& a) {
   using C = FwdCfg<D, S, WR>;
   // Four waves copy a tile, 16 of its 64 rows each: a group of four its own tiles, a group of two every tile
   // together with the other group.
@@ -572,20 +572,20 @@ __device__ __forceinline__ void fwd_body(const FmFwdArgs& a) {
 }
 
 template <int D, bool RAGGED, bool GEN>
-__global__ __launch_bounds__(256, FwdCfg<D>::PER_CU) void fwd_kernel(FmFwdArgs a) {
+__global__ __launch_bounds__(256, FwdCfg<D>::PER_CU) void fwd_kernel(FmFwdKernelArgs<GEN> a) {
   fwd_body<D, RAGGED, GEN, 1, 4, false>(a);
 }
 // Direct units.  LDS for two tiles per step leaves one workgroup per compute unit at d = 128, two at d = 64.
 template <int D, bool RAGGED, bool GEN>
-__global__ __launch_bounds__(256, FwdCfg<D>::PER_CU) void single_fwd_kernel(FmFwdArgs a) {
+__global__ __launch_bounds__(256, FwdCfg<D>::PER_CU) void single_fwd_kernel(FmFwdKernelArgs<GEN> a) {
   fwd_body<D, RAGGED, GEN, 1, 4, true>(a);
 }
 template <int D, bool RAGGED, bool GEN>
-__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void direct_fwd_kernel(FmFwdArgs a) {
+__global__ __launch_bounds__(256, D == 64 ? 2 : 1) void direct_fwd_kernel(FmFwdKernelArgs<GEN> a) {
   fwd_body<D, RAGGED, GEN, 2, 2, true>(a);
 }
 template <int D, bool RAGGED, bool GEN>
-__global__ __launch_bounds__(512, 1) void wide_fwd_kernel(FmFwdArgs a) {
+__global__ __launch_bounds__(512, 1) void wide_fwd_kernel(FmFwdKernelArgs<GEN> a) {
   fwd_body<D, RAGGED, GEN, 2, 4, true>(a);
 }
 
@@ -609,7 +609,7 @@ template <int D, bool RAGGED, bool GEN, FmUnits U>
 static hipError_t launch_fwd_s(const FmFwdArgs& a, hipStream_t stream) {
   using L = FwdLaunch<D, RAGGED, GEN, U>;
   using C = typename L::C;
-  FmFwdArgs args = a;
+  auto args = fm_kernel_args<GEN>(a);
   const int blocks = (a.N + C::BR - 1) / C::BR;
   if (U == FM_QUEUED) args.queue = fm_queue_for_launch(a.queue, FwdCfg<D>::PER_CU);
   else args.order = fm_direct_order(a.B * a.Hk, a.H / a.Hk, blocks, a.B * a.H * blocks <= fm_compute_units());
